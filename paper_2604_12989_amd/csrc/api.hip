@@ -3,8 +3,6 @@
 #include "common.hpp"
 
 namespace ddt {
-size_t attn_ws_upper(int batch, int T, int Hq, int Hkv, int D);
-
 Profiler &profiler()
 {
     static Profiler p;
@@ -57,7 +55,7 @@ extern "C" size_t ddtree_workspace_bytes(int batch, int B, int V, int N, int Hq,
     TopkPlan tp = topk_plan(batch, B, V, K);
     if (!tp.ok) return 0;
     size_t need = tp.bytes;
-    const size_t a = attn_ws_upper(batch, T, Hq, Hkv, D);
+    const size_t a = attn_scratch_upper(batch, T, Hq, Hkv, D);
     if (a > need) need = a;
     const size_t c = accept_plan(batch, T, V).bytes;
     if (c > need) need = c;
@@ -71,7 +69,7 @@ extern "C" size_t ddtree_verify_attn_workspace_bytes(int batch, int T, int Hq, i
     if (batch < 1 || batch > DDTREE_MAX_BATCH || T < 1 || T > DDTREE_MAX_N + 1 || Hq < 1 || Hkv < 1 ||
         Hq % Hkv != 0 || D < 8 || D > 256 || D % 8 != 0 || sum_L < 0)
         return 0;
-    return attn_plan(batch, T, Hq, Hkv, D, sum_L, dtype).bytes;
+    return attn_scratch_bytes(batch, T, Hq, Hkv, D, dtype, sum_L);
 }
 
 extern "C" int ddtree_profile_enable(unsigned kernel_mask, int capacity)

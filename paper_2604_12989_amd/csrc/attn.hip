@@ -2,8 +2,9 @@
 // attends to the whole cached context and, inside the tree, only to the root, its ancestors and
 // itself (the ancestor bitmask).
 //
-// Two device paths behind ddtree_verify_attn:
+// Three device paths behind ddtree_verify_attn:
 //   * attn_mfma_kernel   bf16, head_dim 128: flash-style kernel on the gfx950 matrix cores.
+//   * attn_wave_kernel   (attn_wave.hip) bf16, head_dim 128 with little work, and head_dim 64.
 //   * attn_generic_kernel  any supported shape and fp32: one workgroup per (node, head) on the
 //                        vector ALUs; used for the small fp32 configuration and odd shapes.
 //
@@ -27,17 +28,10 @@
 // The ancestor mask touches only the tree tiles (the last ceil(T/64) tiles): one 64-bit word per
 // (row, tile), bit test per score.  Cache tiles carry no mask work at all.
 #include <algorithm>
-#include <vector>
 
-#include "common.hpp"
+#include "attn_common.hpp"
 
 namespace ddt {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
-typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 
 // Eight waves of 32 query rows, two waves per SIMD with 256 registers each, so that one wave's
 // waits (LDS, matrix results, barrier) are filled by the other; everything fits the 256
@@ -47,9 +41,6 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 // (measured slower, in the kernel and in a micro-benchmark of the loop alone).
 constexpr int kWaves = 8;
 constexpr int kAttnThreads = 64 * kWaves;
-constexpr int kKT = 64;        // keys per tile
-constexpr int kHD = 128;       // head dim of the MFMA path
-constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kAttnStages = 4;  // a power of two: the stage of tile i is i & 3
 constexpr int kKRowBytes = 272;                  // K tile row in LDS: 256 B + 16 B pad (17 chunks)
 constexpr int kVRowBytes = 256;                  // V tile row in LDS: no pad, 64-byte blocks swizzled by the row
@@ -65,193 +56,10 @@ constexpr int kMaskStageBytes = kWaves * 32 * 8;
 constexpr int kAttnLdsBytes = 256 + kRingBytes + kMaskStages * kMaskStageBytes;  // 256: the ring starts on a 256-byte boundary
 static_assert(kAttnLdsBytes <= 160 * 1024, "fits the LDS of a compute unit");
 
-struct AttnArgs {
+struct AttnGenericArgs {
     int32_t kv_start[DDTREE_MAX_BATCH];  // first cache row of each sequence
     int32_t kv_len[DDTREE_MAX_BATCH];    // its number of cache rows
-    // matrix-core kernel only: the sequences longest cache first -- entry p = {sequence, its
-    // first cache row, its number of cache rows, 0}, one 16-byte scalar load -- and the first work
-    // item of each of the 8 XCDs' runs (run x = work items xcd_start[x] .. xcd_start[x + 1] - 1)
-    int32_t by_length[DDTREE_MAX_BATCH][4];
-    int32_t xcd_start[9];
-    // Reciprocals for the divisions of the work-item decode, ceil(2^32 / d): x / d = mulhi(x, magic)
-    // whenever x * d < 2^32.  0 where d = 1 or where the host could not guarantee that bound (the
-    // kernel then divides).
-    int32_t group_size;                  // G = Hq / Hkv
-    uint32_t g_magic;                    // d = G, x = a row index
-    uint32_t per_grp_magic;              // d = work items per (sequence, kv head), x = a work item
-    uint32_t main_tiles_magic;           // d = whole row tiles, x = a work item within its group
-    uint32_t hkv_magic;                  // d = Hkv, x = a group
-    uint32_t splits_magic[2];            // d = key ranges of a whole / of the tail tile, x = key tiles * range + d - 1
 };
-
-__host__ __device__ __forceinline__ uint32_t magic_of(uint64_t d, uint64_t x_max)
-{
-    return (d >= 2 && x_max * d < 0x100000000ull) ? (uint32_t)((0x100000000ull + d - 1) / d) : 0u;
-}
-__host__ __device__ __forceinline__ int div_by(int x, int d, uint32_t magic)
-{
-    return magic != 0u ? (int)(((uint64_t)(uint32_t)x * magic) >> 32) : (d == 1 ? x : x / d);
-}
-
-// Shapes of the matrix-core kernel.  (The bound on the KV heads keeps the pitch between cache
-// rows below 2^24 bytes, which the kernel's 24-bit address multiplies rely on.)
-static bool mfma_shape(int dtype, int D, int Hkv) { return dtype == DDTREE_DTYPE_BF16 && D == kHD && Hkv <= 32768; }
-
-AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, long long sum_L, int dtype)
-{
-    AttnPlan p{};
-    p.splits = 1;
-    if (!mfma_shape(dtype, D, Hkv)) return p;  // generic path needs no scratch
-    const int G = Hq / Hkv;
-    const long long M = (long long)T * G;
-    const int nblk = (int)((M + 31) / 32);
-    p.n_tiles = (nblk + 7) / 8;
-    p.blk_base = nblk / p.n_tiles;
-    p.blk_extra = nblk % p.n_tiles;
-    const long long tiles = (sum_L / batch + T) / kKT;  // key tiles per sequence, roughly
-    const long long base = (long long)batch * Hkv * p.n_tiles;  // workgroups per split
-    // One workgroup per compute unit and launch round: base * S workgroups take
-    // ceil(base * S / 256) rounds of 1/S of the key range each.  Take the S that minimises that
-    // time, charged 2 % per split for the partials it writes and the merge reads, with at least
-    // 4 key tiles per split.
-    int best_s = 1;
-    double best_cost = 1e30;
-    for (int S = 1; S <= 32; ++S) {
-        if (S > 1 && (long long)S * 4 > tiles) break;
-        const long long rounds = (base * S + 255) / 256;
-        const double cost = (double)rounds / S * (1.0 + 0.02 * (S - 1));
-        if (cost < best_cost - 1e-12) {
-            best_cost = cost;
-            best_s = S;
-        }
-    }
-    p.splits = best_s;
-    p.part_splits = best_s;
-    // Uneven form: when the blocks are a few more than whole tiles of 8 (T = 257 with four heads per
-    // KV head: 33 blocks), even tiling leaves a fifth of the wave slots idle at no gain in time (a
-    // tile is as slow as its busiest SIMD).  Whole tiles plus one small tail tile, the tail cut
-    // into fewer key ranges because it runs about twice as fast per key tile, fills the 256 compute
-    // units with shorter key ranges.  Taken when everything fits one round and the model says so.
-    const int full = nblk / 8, rem = nblk % 8;
-    if (full >= 1 && rem >= 1 && rem <= 4 && tiles >= 1) {
-        const double c_tail = 0.6;  // a key tile of the small tail tile against one of a whole tile (measured)
-        best_cost *= 0.97;  // (with key ranges the uneven form goes through partials: it has to pay for them)
-        const long long base_m = (long long)batch * Hkv * full, base_t = (long long)batch * Hkv;
-        for (int Sm = 1; Sm <= 32; ++Sm) {
-            if (Sm > 1 && (long long)Sm * 4 > tiles) break;
-            for (int St = 1; St <= 32; ++St) {
-                if (St > 1 && (long long)St * 4 > tiles) break;
-                if (base_m * Sm + base_t * St > 256) break;
-                const double t_m = (double)((tiles + Sm - 1) / Sm), t_t = c_tail * (double)((tiles + St - 1) / St);
-                const int smax = Sm > St ? Sm : St;
-                const double cost = (t_m > t_t ? t_m : t_t) / (double)(tiles > 0 ? tiles : 1) * (1.0 + 0.02 * (smax - 1));
-                if (cost < best_cost - 1e-12) {
-                    best_cost = cost;
-                    p.n_tiles = full + 1;
-                    p.blk_base = 8;
-                    p.blk_extra = rem;  // (read as: blocks of the tail tile)
-                    p.splits = Sm;
-                    p.tail_splits = St;
-                    p.part_splits = smax;
-                }
-            }
-        }
-    }
-    size_t off = 0;
-    if (p.part_splits > 1) {
-        const size_t rows = (size_t)batch * T * Hq;  // indexed by global row
-        p.part_off = off;
-        off = align_up(off + (size_t)p.part_splits * rows * D * 2, 256);  // fp16 partials
-        p.lse_off = off;
-        off = align_up(off + (size_t)p.part_splits * rows * 8, 256);      // (log2-sum-exp, scale) per row
-    }
-    p.bytes = off;
-    return p;
-}
-
-// Upper bound of attn_plan(...).bytes over all sum_L.  In the even form the key ranges only shrink
-// in number with shorter caches; in the uneven form the rounding of key tiles per range moves the
-// optimum around, so the bound there is what one round of workgroups allows at all.
-size_t attn_ws_upper(int batch, int T, int Hq, int Hkv, int D)
-{
-    AttnPlan p = attn_plan(batch, T, Hq, Hkv, D, (long long)1 << 40, DDTREE_DTYPE_BF16);
-    int cap = p.part_splits;
-    const int G = Hq / Hkv;
-    const int nblk = (int)(((long long)T * G + 31) / 32);
-    const int full = nblk / 8, rem = nblk % 8;
-    const long long base_m = (long long)batch * Hkv * full, base_t = (long long)batch * Hkv;
-    bool uneven_possible = false;
-    if (full >= 1 && rem >= 1 && rem <= 4 && base_m + base_t <= 256) {
-        uneven_possible = true;  // (it stores partials even with a single key range)
-        long long sm = (256 - base_t) / base_m;
-        if (sm > 32) sm = 32;
-        if ((int)sm > cap) cap = (int)sm;
-    }
-    if (cap <= 1 && !uneven_possible) return p.bytes;
-    const size_t rows = (size_t)batch * T * Hq;
-    size_t off = align_up((size_t)cap * rows * D * 2, 256);
-    off = align_up(off + (size_t)cap * rows * 8, 256);
-    return off > p.bytes ? off : p.bytes;
-}
-
-__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) { return (a & 0xFFFFu) | (b << 16); }
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) { return (a >> 16) | (b & 0xFFFF0000u); }
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-// two floats -> packed bf16 pair (round to nearest even), one v_cvt_pk_bf16_f32
-__device__ __forceinline__ uint32_t f2bf_pair(float lo, float hi)
-{
-    const floatx2 f = {lo, hi};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(f, bf16x2));
-}
-
-// two floats -> packed fp16 pair (round to nearest even)
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ uint32_t f2h_pair(float lo, float hi)
-{
-    const f16x2 h = {(_Float16)lo, (_Float16)hi};
-    return __builtin_bit_cast(uint32_t, h);
-}
-
-// Compile-time loop: f(IC<B>{}), ..., f(IC<E-1>{}); the index is a constant expression inside f,
-// as the immediate operands of the asm helpers below require.
-template <int N>
-struct IC {
-    static constexpr int value = N;
-};
-template <int B, int E, class F>
-__device__ __forceinline__ void static_for(F &&f)
-{
-    if constexpr (B < E) {
-        f(IC<B>{});
-        static_for<B + 1, E>(f);
-    }
-}
-
-// Reads of the K/V tiles are written as asm.  The tiles are filled by LDS-DMA
-// (global_load_lds); the compiler cannot tell which stage a given LDS read touches and would
-// wait for every outstanding tile load before each read, serialising prefetch and compute.  With
-// asm reads the waits are placed by hand: s_waitcnt vmcnt(0) + barrier once per tile for the
-// DMA, lds_wait_*() below for the reads (LDS reads return in order, so "at most N outstanding"
-// identifies exactly which of them have landed).
-// The destination of a read is tied to its previous value ("+v"): the read lands in the register
-// of the operand it replaces and cannot be scheduled above the matrix instruction that still
-// reads that operand.
-template <int OFF>
-__device__ __forceinline__ void lds_rd128(u32x4 &v, uint32_t addr)
-{
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF) : "memory");
-}
-// LDS transpose read (ds_read_b64_tr_b16).  Within each group of 16 lanes, lane 4*j + r points
-// at four consecutive 16-bit elements; afterwards lane i of the group holds, for j = 0..3, element
-// i % 4 of what lane 4*j + i / 4 pointed at.  With lane 4*j + r pointing at V[key_j][d0 + 4*r ..],
-// lane i receives V[key_0..3][d0 + i]: a column of the row-major V tile, which is what the A
-// operand (V^T) of the second product needs.
-template <int OFF>
-__device__ __forceinline__ void lds_rdtr(u32x2 &v, uint32_t addr)
-{
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "+v"(v) : "v"(addr), "n"(OFF) : "memory");
-}
 // Wait for every outstanding LDS read of the wave; the operands tie the wait to the registers it
 // protects so that their uses cannot be scheduled above it.
 __device__ __forceinline__ void lds_wait_all(u32x4 (&k)[8], u32x2 (&v)[2][4][2])
@@ -272,20 +80,12 @@ __device__ __forceinline__ void lds_wait_all(u32x4 (&k)[8], u32x2 (&v)[2][4][2])
 // than that and the workgroup redoes its key range with the true row maxima as references.
 constexpr float kSumLimit = 0x1p72f;
 
-template <int N>
-__device__ __forceinline__ void vm_wait()
-{
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
                       const uint16_t *__restrict__ v_cache, const uint16_t *__restrict__ k_tree,
                       const uint16_t *__restrict__ v_tree, const uint64_t *__restrict__ mask,
-                      AttnArgs args, int batch_n, int T, int Hq, int Hkv, float scale_log2e, int n_tiles_m,
-                      int blk_base, int blk_extra, int main_splits, int tail_splits, int part_splits,
-                      uint16_t *__restrict__ out,
-                      uint16_t *__restrict__ part, float2 *__restrict__ lse)
+                      AttnMainArgs args, int T, int Hq, int Hkv, float scale_log2e,
+                      uint16_t *__restrict__ out, uint16_t *__restrict__ part, float2 *__restrict__ lse)
 {
     // LDS: kAttnStages stages of {K tile, V tile}, filled by direct global->LDS loads.  One wave
     // instruction writes 64 x 16 B contiguously, but every lane may fetch any 16-byte chunk, so
@@ -309,45 +109,17 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     // and V rows share an L2, and those rows leave HBM once.  The host cuts the runs so that
     // each holds an eighth of the keys to visit (sequences of a ragged batch differ in length)
     // and lists the sequences longest first, so that an XCD's long work items start early.
-    // The work items of a group are its main tiles, row tile fastest within a key range, then (in
-    // the uneven form) the key ranges of its tail tile.
-    const int main_tiles = tail_splits > 0 ? n_tiles_m - 1 : n_tiles_m;
-    const int per_grp = main_tiles * main_splits + tail_splits;
-    const int xcd = (int)blockIdx.x & 7;
-    const int wid = args.xcd_start[xcd] + ((int)blockIdx.x >> 3);
-    if (wid >= args.xcd_start[xcd + 1]) return;
-    // (the divisions of this decode are multiplications by the host's reciprocals: a division by a
-    // run-time value is some thirty instructions, and all of this sits before the first tile request)
-    const int grp = div_by(wid, per_grp, args.per_grp_magic);  // (sequence, kv head) pair
-    const int wg = wid - grp * per_grp;
-    const bool tail = wg >= main_tiles * main_splits;
-    const int wg_split = div_by(wg, main_tiles, args.main_tiles_magic);
-    const int mt = tail ? main_tiles : wg - wg_split * main_tiles;
-    const int split = tail ? wg - main_tiles * main_splits : wg_split;
-    const int splits = tail ? tail_splits : main_splits;  // key ranges of this tile
-    const int grp_seq = div_by(grp, Hkv, args.hkv_magic);
-    const int hk = grp - grp_seq * Hkv;
-    const int seq = args.by_length[grp_seq][0];
+    const int wid = args.xcd_start[(int)blockIdx.x & 7] + ((int)blockIdx.x >> 3);
+    if (wid >= args.xcd_start[((int)blockIdx.x & 7) + 1]) return;
+    const AttnMainItem item = attn_main_item(args, wid, T);
+    const int seq = item.seq, hk = item.hk, split = item.split, splits = item.splits;
+    const int part_splits = item.ranges > 1 ? item.ranges : 0, first_slot = item.first_slot;
+    const int L0 = item.kv_start, L = item.kv_len;
     const int G = args.group_size;
     const int W = (T + 63) >> 6;
-    const int M = T * G;
-    const int L0 = args.by_length[grp_seq][1];
-    const int L = args.by_length[grp_seq][2];
-    // this tile's blocks of 32 rows: wave w owns block w of the tile
-    const int first_blk = tail_splits > 0 ? mt * 8 : mt * blk_base + min(mt, blk_extra);
-    const int n_blk = tail_splits > 0 ? (tail ? blk_extra : 8) : blk_base + (mt < blk_extra ? 1 : 0);
-    const int m0 = first_blk * 32;
-    const int m_end = min(M, (first_blk + n_blk) * 32);
-    const int last_node = min(T - 1, div_by(m_end - 1, G, args.g_magic));
-    const int n_cache_tiles = (L + kKT - 1) / kKT;
-    const int n_tree_tiles = last_node / kKT + 1;
-    const int nt = n_cache_tiles + n_tree_tiles;
-    // key ranges rounded up, so that a surplus tile goes to the early ranges: the last range holds
-    // the tree tiles, which carry the mask work on top
-    // (nt < 2^25 key tiles and at most 32 key ranges: 32-bit arithmetic is exact)
-    const uint32_t s_magic = args.splits_magic[tail ? 1 : 0];
-    const int t_begin = div_by(nt * split + splits - 1, splits, s_magic);
-    const int t_end = div_by(nt * (split + 1) + splits - 1, splits, s_magic);
+    const int m0 = item.m0, m_end = item.m_end;  // this tile's rows: wave w owns block w of 32
+    const int n_cache_tiles = item.n_cache_tiles;
+    const int t_begin = item.t_begin, t_end = item.t_end;
     const bool wave_active = m0 + wave * 32 < m_end;
 
     // Nothing derived from the lane's row is kept through the key loop: the masked steps, the
@@ -786,7 +558,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     asm volatile("" : "+v"(e_tid));
     const int e_lane = e_tid & 63, e_l32 = e_tid & 31, e_half = (e_tid >> 5) & 1, e_wave = e_tid >> 6;
     unsigned char *stg = smem + e_wave * (32 * kEpiRow);
-    const size_t n_rows = (size_t)batch_n * T * Hq;
+    const size_t rows_seq = (size_t)T * Hq;
     {
         int e_row, e_node;
         bool e_valid;
@@ -822,15 +594,17 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
             }
         if (part_splits != 0 && e_valid && e_half == 0) {
             // log2-sum-exp and scale of this key range, indexed by global row
-            const size_t ridx = (size_t)((seq * T + e_node) * Hq + hk * G + (e_row - e_node * G));
-            lse[(size_t)split * n_rows + ridx] =
+            // (the slot's row)
+            const size_t ridx = (size_t)(first_slot + split) * rows_seq + (size_t)(e_node * Hq + hk * G + (e_row - e_node * G));
+            lse[ridx] =
                 make_float2(inv > 0.0f ? m_ref + __builtin_amdgcn_logf(l_tot) : -INFINITY, rs);
             // key ranges this tile does not have (the other kind of tile has more): empty
             if (split == 0)
-                for (int sx = splits; sx < part_splits; ++sx) lse[(size_t)sx * n_rows + ridx] = make_float2(-INFINITY, 1.0f);
+                for (int sx = splits; sx < part_splits; ++sx) lse[ridx + (size_t)sx * rows_seq] = make_float2(-INFINITY, 1.0f);
         }
     }
-    uint16_t *dst_base = part_splits == 0 ? out : part + (size_t)split * n_rows * kHD;
+    uint16_t *dst_base = part_splits == 0 ? out + seq * rows_seq * kHD
+                                          : part + (size_t)(first_slot + split) * rows_seq * kHD;
     const int chunk = e_lane & 15;
     int r = m0 + e_wave * 32 + (e_lane >> 4);  // rows lane >> 4, + 4, + 8, ... of the block
     int node = div_by(r, G, args.g_magic), g = r - node * G;
@@ -838,7 +612,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     for (int rr = 0; rr < 8; ++rr) {
         if (r < m_end) {
             const uint4 v = *reinterpret_cast<const uint4 *>(stg + (rr * 4 + (e_lane >> 4)) * kEpiRow + chunk * 16);
-            const size_t rg = (size_t)(seq * T + node) * Hq + hk * G + g;
+            const size_t rg = (size_t)node * Hq + hk * G + g;
             *reinterpret_cast<uint4 *>(dst_base + rg * kHD + chunk * 8) = v;
         }
         r += 4;
@@ -857,18 +631,24 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
 // together: 8 for up to 8 key ranges, 16 beyond (small budgets on long caches).
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
-template <int kMergeBatch>
+struct AttnMergeArgs {
+    int32_t range[DDTREE_MAX_BATCH][2];  // first slot and key ranges of each sequence
+};
+template <int D, int kMergeBatch>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t *__restrict__ part_all,
-                                                         const float2 *__restrict__ lse_all, size_t n_rows,
-                                                         int splits, uint16_t *__restrict__ out)
+                                                         const float2 *__restrict__ lse_all, AttnMergeArgs args,
+                                                         int rows_seq, uint16_t *__restrict__ out)
 {
-    const size_t gid = (size_t)blockIdx.x * 256 + threadIdx.x;
-    const size_t row = gid >> 4;
-    const int dg = (int)(gid & 15);
-    if (row >= n_rows) return;
-    const uint16_t *part = part_all + row * kHD + dg * 8;
-    const float2 *lse = lse_all + row;
-    const size_t pstride = n_rows * kHD;
+    constexpr int CH = D / 8;
+    const int seq = blockIdx.y, splits = args.range[seq][1];
+    const int gid = (int)blockIdx.x * 256 + (int)threadIdx.x;
+    const int row = gid / CH, dg = gid % CH;
+    if (row >= rows_seq || splits == 1) return;  // (an uncut key range is already in `out`)
+    const size_t first = (size_t)args.range[seq][0] * rows_seq + row;
+    const uint16_t *part = part_all + first * D + dg * 8;
+    const float2 *lse = lse_all + first;
+    const size_t n_rows = rows_seq, pstride = n_rows * D;
+    out += ((size_t)seq * rows_seq + row) * D + dg * 8;
 
     // one pass: the weights are taken against the largest lse seen so far and what has been
     // summed is rescaled when a batch brings a larger one
@@ -913,7 +693,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t *__restr
     val.y = f2bf_pair(acc[2] * inv, acc[3] * inv);
     val.z = f2bf_pair(acc[4] * inv, acc[5] * inv);
     val.w = f2bf_pair(acc[6] * inv, acc[7] * inv);
-    *reinterpret_cast<uint4 *>(out + row * kHD + dg * 8) = val;
+    *reinterpret_cast<uint4 *>(out) = val;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -954,7 +734,7 @@ template <typename TIO>
 __global__ __launch_bounds__(kGenThreads) void attn_generic_kernel(
     const TIO *__restrict__ q, const TIO *__restrict__ k_cache, const TIO *__restrict__ v_cache,
     const TIO *__restrict__ k_tree, const TIO *__restrict__ v_tree,
-    const uint64_t *__restrict__ mask, AttnArgs args, int T, int Hq, int Hkv, int D, float scale,
+    const uint64_t *__restrict__ mask, AttnGenericArgs args, int T, int Hq, int Hkv, int D, float scale,
     TIO *__restrict__ out)
 {
     __shared__ float s_q[256];
@@ -1067,73 +847,6 @@ __global__ __launch_bounds__(kGenThreads) void attn_generic_kernel(
 
 }  // namespace ddt
 
-// The launch tables of the matrix-core kernel for a plan: reciprocals for the work-item decode, the
-// sequences by length, the cut of the work items into the 8 XCDs' runs.  *grid_x = workgroups to
-// launch.  False if the launch would exceed 2^28 work items.
-static bool attn_fill_args(ddt::AttnArgs &args, const ddt::AttnPlan &p, const int32_t *kv_start,
-                           const int32_t *kv_len, int batch, int T, int Hkv, long long *grid_x)
-{
-    using namespace ddt;
-    const int main_tiles = p.tail_splits > 0 ? p.n_tiles - 1 : p.n_tiles;
-    // Work items in launch order: sequences longest first, then kv head, then the items of
-    // the group.  An item visits about (L + T) / splits keys; the 8 runs are cut where the
-    // running sum of that passes each eighth of the total.
-    const long long per_seq = (long long)Hkv * (main_tiles * p.splits + p.tail_splits);
-    const long long total = per_seq * batch;
-    if (total > (1ll << 28)) return false;
-    {
-        long long max_len = 0;
-        for (int i = 0; i < batch; ++i) max_len = std::max<long long>(max_len, kv_len[i]);
-        const uint64_t per_grp = (uint64_t)(main_tiles * p.splits + p.tail_splits);
-        const uint64_t nt_max = (uint64_t)((max_len + kKT - 1) / kKT + (T + kKT - 1) / kKT);
-        args.per_grp_magic = magic_of(per_grp, (uint64_t)total);
-        args.main_tiles_magic = magic_of((uint64_t)main_tiles, per_grp);
-        args.hkv_magic = magic_of((uint64_t)Hkv, (uint64_t)batch * Hkv);
-        args.splits_magic[0] = magic_of((uint64_t)p.splits, nt_max * p.splits + p.splits);
-        args.splits_magic[1] = magic_of((uint64_t)p.tail_splits, nt_max * p.tail_splits + p.tail_splits);
-    }
-    int32_t order[DDTREE_MAX_BATCH];
-    for (int i = 0; i < batch; ++i) order[i] = i;
-    std::stable_sort(order, order + batch, [&](int32_t a, int32_t b) { return kv_len[a] > kv_len[b]; });
-    for (int i = 0; i < batch; ++i) {
-        args.by_length[i][0] = order[i];
-        args.by_length[i][1] = kv_start[order[i]];
-        args.by_length[i][2] = kv_len[order[i]];
-        args.by_length[i][3] = 0;
-    }
-    long long work_total = 0;
-    for (int i = 0; i < batch; ++i) work_total += per_seq * ((long long)kv_len[i] + T);
-    {
-        long long done = 0, first = 0;  // work and items before sequence position `pos`
-        int pos = 0, x = 1;
-        args.xcd_start[0] = 0;
-        while (x < 8) {
-            const long long target = (work_total * x + 7) / 8;
-            const int sq = order[pos];
-            const long long w = (long long)kv_len[sq] + T;
-            if (pos < batch - 1 && done + per_seq * w < target) {
-                done += per_seq * w;
-                first += per_seq;
-                ++pos;
-                continue;
-            }
-            long long k = (target - done + w - 1) / w;  // items of this sequence before the cut
-            if (k < 0) k = 0;
-            if (k > per_seq) k = per_seq;
-            args.xcd_start[x++] = (int32_t)(first + k);
-        }
-        args.xcd_start[8] = (int32_t)total;
-    }
-    long long run_max = 0;
-    for (int x = 0; x < 8; ++x) {
-        if (args.xcd_start[x + 1] < args.xcd_start[x]) args.xcd_start[x + 1] = args.xcd_start[x];
-        const long long run = args.xcd_start[x + 1] - args.xcd_start[x];
-        if (run > run_max) run_max = run;
-    }
-    *grid_x = run_max * 8;
-    return true;
-}
-
 static int verify_attn_impl(const void *q, const void *k_cache, const void *v_cache, const void *k_tree,
                             const void *v_tree, const uint64_t *ancestor_mask, const int32_t *kv_start,
                             const int32_t *kv_len, int batch, int T, int Hq, int Hkv, int D,
@@ -1151,54 +864,79 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
         return DDTREE_ERR_ARG;
     if (dtype != DDTREE_DTYPE_BF16 && dtype != DDTREE_DTYPE_FP32) return DDTREE_ERR_ARG;
     if (!(softmax_scale > 0.0f) || !(softmax_scale < 1e30f)) return DDTREE_ERR_ARG;
-    AttnArgs args{};
-    {
-        const uint32_t G = (uint32_t)(Hq / Hkv);
-        args.group_size = (int32_t)G;
-        args.g_magic = magic_of(G, (uint64_t)T * G);
-        args.per_grp_magic = args.main_tiles_magic = args.hkv_magic = args.splits_magic[0] = args.splits_magic[1] = 0u;
-    }
     long long sum_L = 0;
+    int longest = 0;
     for (int s = 0; s < batch; ++s) {
         if (kv_start[s] < 0 || kv_len[s] < 0 || (long long)kv_start[s] + kv_len[s] > 0x7FFFFFFFll)
             return DDTREE_ERR_ARG;
-        args.kv_start[s] = kv_start[s];
-        args.kv_len[s] = kv_len[s];
         sum_L += kv_len[s];
+        longest = std::max(longest, kv_len[s]);
     }
     if (sum_L > 0 && (!k_cache || !v_cache)) return DDTREE_ERR_ARG;
     hipStream_t st = as_stream(stream);
 
-    if (mfma_shape(dtype, D, Hkv)) {
-        AttnPlan p = attn_plan(batch, T, Hq, Hkv, D, sum_L, dtype);
+    if (attn_mfma_shape(dtype, D, Hkv)) {
+        const bool ws_usable = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
+        const size_t slot_bytes = (size_t)T * Hq * (D * 2 + 8);
+        const long long room = ws_usable && workspace_bytes > 512 ? (long long)((workspace_bytes - 512) / slot_bytes) : 0;
+        // (a long key range that few workgroups share is not walked uncut because a workspace is missing)
+        if (D == kHD && room < 2LL * batch && longest + T >= 8 * kKT && (long long)batch * Hkv * ((T * (Hq / Hkv) + 255) / 256) <= 128)
+            return DDTREE_ERR_WORKSPACE;
+        const AttnPlan p = attn_plan(batch, T, Hq, Hkv, D, kv_len, room);
         if (!ws_ok(workspace, workspace_bytes, p.bytes)) return DDTREE_ERR_WORKSPACE;
         char *wsb = static_cast<char *>(workspace);
         uint16_t *part = reinterpret_cast<uint16_t *>(wsb + p.part_off);
         float2 *lse = reinterpret_cast<float2 *>(wsb + p.lse_off);
-        static std::atomic<bool> lds_allowed{false};
-        if (!allow_dynamic_lds(reinterpret_cast<const void *>(attn_mfma_kernel), kAttnLdsBytes, lds_allowed))
-            return DDTREE_ERR_HIP;
-        long long gx = 0;
-        if (!attn_fill_args(args, p, kv_start, kv_len, batch, T, Hkv, &gx)) return DDTREE_ERR_ARG;
-        const int part_splits = p.part_splits > 1 ? p.part_splits : 0;
-        DDT_LAUNCH(DDTREE_KERNEL_ATTN, st, attn_mfma_kernel, dim3((unsigned)gx), dim3(kAttnThreads),
-                   kAttnLdsBytes, st, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
-                   static_cast<const uint16_t *>(v_cache), static_cast<const uint16_t *>(k_tree),
-                   static_cast<const uint16_t *>(v_tree), ancestor_mask, args, batch, T, Hq, Hkv,
-                   softmax_scale * kLog2e, p.n_tiles, p.blk_base, p.blk_extra, p.splits, p.tail_splits, part_splits,
-                   static_cast<uint16_t *>(out), part, lse);
-        if (part_splits > 0) {
-            const size_t n_rows = (size_t)batch * T * Hq;
-            if (part_splits <= 8)
-                DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, attn_merge_kernel<8>,
-                           dim3((unsigned)((n_rows * 16 + 255) / 256)), dim3(256), 0, st, part, lse, n_rows,
-                           part_splits, static_cast<uint16_t *>(out));
-            else
-                DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, attn_merge_kernel<16>,
-                           dim3((unsigned)((n_rows * 16 + 255) / 256)), dim3(256), 0, st, part, lse, n_rows,
-                           part_splits, static_cast<uint16_t *>(out));
+        AttnMergeArgs merge;
+        int most = 1;
+        for (int i = 0; i < batch; ++i) {
+            merge.range[i][0] = p.seq[i].first_slot;
+            merge.range[i][1] = p.seq[i].ranges;
+            most = std::max(most, p.seq[i].ranges);
+        }
+        if (p.row_blocks > 0) {
+            AttnWaveArgs args;
+            if (!attn_wave_args(args, p, kv_start, kv_len, batch, T, Hq, Hkv)) return DDTREE_ERR_ARG;
+            args.q = static_cast<const uint16_t *>(q);
+            args.k_cache = static_cast<const uint16_t *>(k_cache);
+            args.v_cache = static_cast<const uint16_t *>(v_cache);
+            args.k_tree = static_cast<const uint16_t *>(k_tree);
+            args.v_tree = static_cast<const uint16_t *>(v_tree);
+            args.mask = ancestor_mask;
+            args.out = static_cast<uint16_t *>(out);
+            args.part = part;
+            args.lse = lse;
+            args.T = T;
+            args.Hq = Hq;
+            args.Hkv = Hkv;
+            args.scale_log2e = softmax_scale * kLog2e;
+            if (!attn_wave_launch(args, D, p.row_blocks, st)) return DDTREE_ERR_HIP;
+        } else {
+            AttnMainArgs args;
+            if (!attn_main_args(args, p, kv_start, kv_len, batch, T, Hq, Hkv)) return DDTREE_ERR_ARG;
+            static std::atomic<bool> lds_allowed{false};
+            if (!allow_dynamic_lds(reinterpret_cast<const void *>(attn_mfma_kernel), kAttnLdsBytes, lds_allowed))
+                return DDTREE_ERR_HIP;
+            DDT_LAUNCH(DDTREE_KERNEL_ATTN, st, attn_mfma_kernel, dim3((unsigned)args.grid), dim3(kAttnThreads),
+                       kAttnLdsBytes, st, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
+                       static_cast<const uint16_t *>(v_cache), static_cast<const uint16_t *>(k_tree),
+                       static_cast<const uint16_t *>(v_tree), ancestor_mask, args, T, Hq, Hkv,
+                       softmax_scale * kLog2e, static_cast<uint16_t *>(out), part, lse);
+        }
+        if (most > 1) {
+            const int rows_seq = T * Hq;
+            const dim3 grid((unsigned)((rows_seq * (D / 8) + 255) / 256), (unsigned)batch);
+            auto *kernel = D == kHD ? (most <= 8 ? attn_merge_kernel<kHD, 8> : attn_merge_kernel<kHD, 16>)
+                                    : (most <= 8 ? attn_merge_kernel<64, 8> : attn_merge_kernel<64, 16>);
+            DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, kernel, grid, dim3(256), 0, st, part, lse, merge, rows_seq,
+                       static_cast<uint16_t *>(out));
         }
         return launch_status();
+    }
+    AttnGenericArgs args{};
+    for (int s = 0; s < batch; ++s) {
+        args.kv_start[s] = kv_start[s];
+        args.kv_len[s] = kv_len[s];
     }
     if (dtype == DDTREE_DTYPE_FP32)
         DDT_LAUNCH(DDTREE_KERNEL_ATTN_GENERIC, st, attn_generic_kernel<float>, dim3(Hq, T, batch), dim3(kGenThreads), 0, st,
@@ -1244,135 +982,3 @@ extern "C" int ddtree_verify_attn_spans(const void *q, const void *k_cache, cons
                             Hq, Hkv, D, softmax_scale, dtype, out, workspace, workspace_bytes, stream);
 }
 
-// ------------------------------------------------------------------------------------------
-// Host-side self-check of the matrix-core kernel's launch arithmetic (no GPU involved): for a
-// list of shapes, the plan, the XCD runs and the reciprocals are built as for a launch, every
-// workgroup index of the grid is decoded the way the kernel decodes it, and the result is held
-// against plain division and against what the decomposition promises: every (sequence, KV head,
-// row tile, key range) exactly once, the row blocks of a group's tiles a partition of its rows,
-// the key ranges of a tile a partition of its key tiles in order.
-// Returns 0, or 100 * (index of the failing shape + 1) + the number of the failed check.
-// ------------------------------------------------------------------------------------------
-namespace ddt {
-int attn_selftest_host()
-{
-    struct Shape {
-        int batch, T, Hq, Hkv;
-        int32_t len[4];
-    };
-    static const Shape shapes[] = {
-        {1, 257, 32, 8, {8192}},        {1, 513, 32, 8, {32768}},       {1, 65, 32, 8, {2048}},
-        {4, 129, 64, 8, {1533, 7527, 4000, 1024}},                      {1, 1025, 8, 2, {1500}},
-        {3, 33, 16, 2, {130, 0, 517}},  {1, 17, 4, 1, {128}},           {2, 40, 12, 1, {1000, 3}},
-        {1, 2, 1, 1, {0}},              {4, 1024, 8, 8, {100, 0, 64, 7}}, {1, 75, 16, 4, {3000}},
-        {1, 300, 6, 2, {9000}},         {2, 273, 32, 8, {5000, 4999}},  {1, 1025, 128, 1, {200000}},
-    };
-    // exhaustive check of the reciprocal division itself on small divisors
-    for (uint32_t d = 2; d <= 64; ++d) {
-        const uint64_t x_max = 0xFFFFFFFFull / d;
-        const uint32_t m = magic_of(d, x_max);
-        if (m == 0u) return 1;
-        for (uint64_t x = 0; x <= x_max; x += (x < 70000 ? 1 : 9973))
-            if (div_by((int)(x & 0x7FFFFFFF), (int)d, m) != (int)((x & 0x7FFFFFFF) / d)) return 2;
-        if (magic_of(d, x_max + 1) != 0u && (x_max + 1) * d >= 0x100000000ull) return 3;
-    }
-    int si = 0;
-    for (const Shape &sh : shapes) {
-        ++si;
-        const int batch = sh.batch, T = sh.T, Hq = sh.Hq, Hkv = sh.Hkv, G = Hq / Hkv;
-        int32_t kv_start[4], kv_len[4];
-        long long sum_L = 0;
-        for (int i = 0; i < batch; ++i) {
-            kv_start[i] = (int32_t)sum_L;
-            kv_len[i] = sh.len[i];
-            sum_L += sh.len[i];
-        }
-        const AttnPlan p = attn_plan(batch, T, Hq, Hkv, kHD, sum_L, DDTREE_DTYPE_BF16);
-        AttnArgs args{};
-        args.group_size = G;
-        args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
-        long long gx = 0;
-        if (!attn_fill_args(args, p, kv_start, kv_len, batch, T, Hkv, &gx)) return 100 * si + 1;
-        const int main_tiles = p.tail_splits > 0 ? p.n_tiles - 1 : p.n_tiles;
-        const int per_grp = main_tiles * p.splits + p.tail_splits;
-        const long long total = (long long)batch * Hkv * per_grp;
-        if (args.xcd_start[0] != 0 || args.xcd_start[8] != total) return 100 * si + 2;
-        for (int x = 0; x < 8; ++x)
-            if (args.xcd_start[x + 1] < args.xcd_start[x]) return 100 * si + 3;
-        const int M = T * G, W = (T + 63) >> 6;
-        (void)W;
-        std::vector<int> seen((size_t)total, 0);
-        // per (group, tile): the next key tile expected, and the rows covered
-        std::vector<int> next_t((size_t)batch * Hkv * p.n_tiles, 0), rows((size_t)batch * Hkv, 0);
-        std::vector<int> by_split((size_t)total, -1);
-        for (long long b = 0; b < gx; ++b) {
-            const int xcd = (int)(b & 7);
-            const int wid = args.xcd_start[xcd] + (int)(b >> 3);
-            if (wid >= args.xcd_start[xcd + 1]) continue;
-            if (wid < 0 || wid >= total) return 100 * si + 4;
-            // the kernel's decode
-            const int grp = div_by(wid, per_grp, args.per_grp_magic);
-            const int wg = wid - grp * per_grp;
-            const bool tail = wg >= main_tiles * p.splits;
-            const int wg_split = div_by(wg, main_tiles, args.main_tiles_magic);
-            const int mt = tail ? main_tiles : wg - wg_split * main_tiles;
-            const int split = tail ? wg - main_tiles * p.splits : wg_split;
-            const int splits = tail ? p.tail_splits : p.splits;
-            const int grp_seq = div_by(grp, Hkv, args.hkv_magic);
-            const int hk = grp - grp_seq * Hkv;
-            const int seq = args.by_length[grp_seq][0];
-            const int L = args.by_length[grp_seq][2];
-            const int first_blk = p.tail_splits > 0 ? mt * 8 : mt * p.blk_base + std::min(mt, p.blk_extra);
-            const int n_blk = p.tail_splits > 0 ? (tail ? p.blk_extra : 8) : p.blk_base + (mt < p.blk_extra ? 1 : 0);
-            const int m0 = first_blk * 32, m_end = std::min(M, (first_blk + n_blk) * 32);
-            const int last_node = std::min(T - 1, div_by(m_end - 1, G, args.g_magic));
-            const int nt = (L + kKT - 1) / kKT + last_node / kKT + 1;
-            const uint32_t s_magic = args.splits_magic[tail ? 1 : 0];
-            const int t_begin = div_by(nt * split + splits - 1, splits, s_magic);
-            const int t_end = div_by(nt * (split + 1) + splits - 1, splits, s_magic);
-            // against plain division
-            if (grp != wid / per_grp || wg_split != wg / main_tiles || grp_seq != grp / Hkv) return 100 * si + 5;
-            if (last_node != std::min(T - 1, (m_end - 1) / G)) return 100 * si + 6;
-            if (t_begin != (int)(((long long)nt * split + splits - 1) / splits) ||
-                t_end != (int)(((long long)nt * (split + 1) + splits - 1) / splits))
-                return 100 * si + 7;
-            // against the decomposition
-            if (grp < 0 || grp >= batch * Hkv || hk < 0 || hk >= Hkv || seq < 0 || seq >= batch || L != kv_len[seq] ||
-                args.by_length[grp_seq][1] != kv_start[seq])
-                return 100 * si + 8;
-            if (mt < 0 || mt >= p.n_tiles || split < 0 || split >= splits || m0 >= m_end || m0 >= M) return 100 * si + 9;
-            if (t_begin < 0 || t_end > nt || t_begin > t_end) return 100 * si + 10;
-            if (seen[(size_t)wid]++) return 100 * si + 11;
-            by_split[(size_t)wid] = t_begin;
-            if (split == 0) rows[(size_t)grp] += m_end - m0;
-            // the key ranges of a tile, taken in the order of their work items (split ascending
-            // within a tile for main tiles: item = split * main_tiles + mt; tail: consecutive)
-            (void)next_t;
-        }
-        for (long long w = 0; w < total; ++w)
-            if (seen[(size_t)w] != 1) return 100 * si + 12;
-        for (int g = 0; g < batch * Hkv; ++g)
-            if (rows[(size_t)g] != M) return 100 * si + 13;
-        // key ranges: for every (group, tile) the ranges 0 .. splits-1 follow each other from 0 to nt
-        for (int g = 0; g < batch * Hkv; ++g)
-            for (int tile = 0; tile < p.n_tiles; ++tile) {
-                const bool tail = p.tail_splits > 0 && tile == main_tiles;
-                const int splits = tail ? p.tail_splits : p.splits;
-                int expect = 0;
-                for (int sp = 0; sp < splits; ++sp) {
-                    const long long wid = (long long)g * per_grp + (tail ? main_tiles * p.splits + sp : sp * main_tiles + tile);
-                    if (by_split[(size_t)wid] != expect) return 100 * si + 14;
-                    // end of this range = begin of the next (or nt for the last), recomputed exactly
-                    const int seq = args.by_length[g / Hkv][0];
-                    const int first_blk = p.tail_splits > 0 ? tile * 8 : tile * p.blk_base + std::min(tile, p.blk_extra);
-                    const int n_blk = p.tail_splits > 0 ? (tail ? p.blk_extra : 8) : p.blk_base + (tile < p.blk_extra ? 1 : 0);
-                    const int m_end = std::min(M, (first_blk + n_blk) * 32);
-                    const int nt = (kv_len[seq] + kKT - 1) / kKT + std::min(T - 1, (m_end - 1) / G) / kKT + 1;
-                    expect = (int)(((long long)nt * (sp + 1) + splits - 1) / splits);
-                    if (sp == splits - 1 && expect != nt) return 100 * si + 15;
-                }
-            }
-    }
-    return 0;
-}
-}  // namespace ddt

@@ -1,0 +1,433 @@
+// How a call of the attention is cut into workgroups: which of the two matrix-core kernels, how many
+// key ranges each sequence's rows are cut into, the launch tables the kernels decode, and the host-side
+// self-check that holds this arithmetic against plain division and exact coverage.  Host code only.
+#include <algorithm>
+#include <vector>
+
+#include "attn_common.hpp"
+
+namespace ddt {
+
+// Shapes of the matrix-core kernels.  (The bound on the KV heads keeps the pitch between cache
+// rows below 2^24 bytes, which the kernels' 24-bit address multiplies rely on.)
+bool attn_mfma_shape(int dtype, int D, int Hkv)
+{
+    return dtype == DDTREE_DTYPE_BF16 && (D == kHD || D == 64) && Hkv <= 32768;
+}
+
+// Scratch of `slots` partial results: fp16 rows, then (log2-sum-exp, scale) per row.
+static void plan_scratch(AttnPlan &p, int T, int Hq, int D, long long slots)
+{
+    p.slots = slots;
+    p.part_off = p.lse_off = p.bytes = 0;
+    if (slots == 0) return;
+    const size_t rows = (size_t)slots * T * Hq;
+    p.lse_off = align_up(rows * D * 2, 256);
+    p.bytes = align_up(p.lse_off + rows * 8, 256);
+}
+
+static inline int up(int a, int b) { return (a + b - 1) / b; }
+
+// Partial results a plan may leave: what about two rounds of workgroups on 256 compute units make.
+static long long wave_slot_cap(int batch, int T, int Hq, int Hkv, int row_blocks)
+{
+    const long long M = (long long)T * (Hq / Hkv);
+    return std::max<long long>(batch, 512 / (Hkv * ((M + 32 * row_blocks - 1) / (32 * row_blocks))));
+}
+static long long main_slot_cap(int batch, int T, int Hq, int Hkv)
+{
+    const long long M = (long long)T * (Hq / Hkv);
+    return batch + 640 / (Hkv * ((M + 255) / 256));
+}
+
+// Time (us) of the merge of `slots` partial results: a launch, and reading them.  (Measured: 4.0 us for
+// 3 x 65 x 32 rows of 128, 4.7 for 7 x 257 x 32, 22 for 32 x 129 x 64.)
+static double merge_us(long long slots, int T, int Hq, int D) { return 4.0 + (double)slots * T * Hq * D * 2 / 6.0e6; }
+
+// Workgroups of a few sizes, longest first: `count` of `cost` us each.
+struct Sized {
+    double cost;
+    long long count;
+};
+// Their time on 256 compute units, one at a time on each: what all of them make together and half of
+// the longest, and no less than k times the k-th round's longest.
+static double rounds_us(const Sized *w, int n)
+{
+    long long items = 0;
+    double sum = 0.0, t = 0.0;
+    for (int i = 0; i < n; ++i) {
+        for (long long k = (items + 255) / 256; k * 256 < items + w[i].count; ++k) t = std::max(t, (double)(k + 1) * w[i].cost);
+        items += w[i].count;
+        sum += w[i].cost * w[i].count;
+    }
+    return items <= 256 ? t : std::max(t, sum / 256 + 0.5 * w[0].cost);
+}
+
+static void longest_first(int32_t *order, const int32_t *kv_len, int batch)
+{
+    for (int i = 0; i < batch; ++i) order[i] = i;
+    std::stable_sort(order, order + batch, [&](int32_t a, int32_t b) { return kv_len[a] > kv_len[b]; });
+}
+
+// attn_wave_kernel: every sequence's key range in pieces of about the same length, so that the pieces
+// of a ragged batch end together.
+static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, int row_blocks, long long slot_room)
+{
+    AttnPlan p{};
+    const int M = T * (Hq / Hkv);
+    p.row_blocks = row_blocks;
+    p.groups = up(M, 32 * row_blocks);
+    p.rows_per_group = up(M, p.groups);
+    const long long cap = std::min(slot_room, wave_slot_cap(batch, T, Hq, Hkv, row_blocks));
+    const int tree = up(T, kSK);
+    int32_t order[DDTREE_MAX_BATCH];
+    longest_first(order, kv_len, batch);
+    long long sub_tiles = 0;
+    for (int i = 0; i < batch; ++i) sub_tiles += up(kv_len[i], kSK) + tree;
+    const int nt_max = up(kv_len[order[0]], kSK) + tree;
+    Sized sized[DDTREE_MAX_BATCH];
+    // Measured (us): a workgroup's fixed cost (launch, first requests, combining the waves' results), a
+    // step of its eight waves (32 keys each), the rates at which the L2s and HBM serve all of them.
+    const double fix = 7.0, step = D == 64 ? (row_blocks == 1 ? 0.62 : 1.17) : 1.2;
+    const double l2_us = (double)sub_tiles * Hkv * p.groups * (kSK * 4.0 * D) / 20.0e6;
+    const double hbm_us = (double)sub_tiles * Hkv * (kSK * 4.0 * D) / 3.5e6;
+    int best_c = nt_max;
+    p.cost = 1e30;
+    for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= nt_max && (long long)s * nt_max < (1ll << 30))); ++s) {
+        const int c = up(nt_max, s);
+        long long slots = 0;
+        for (int i = 0; i < batch; ++i) {
+            const int nt = up(kv_len[order[i]], kSK) + tree, si = up(nt, c);
+            slots += si;
+            sized[i] = Sized{fix + step * up(up(nt, si), 8), (long long)si * Hkv * p.groups};
+        }
+        if (s > 1 && slots > cap) break;
+        double cost = rounds_us(sized, batch);
+        cost = std::max(cost, 5.0 + std::max(l2_us, hbm_us)) + (s > 1 ? merge_us(slots, T, Hq, D) : 0.0);
+        if (cost < p.cost) p.cost = cost, best_c = c;
+    }
+    int first = 0;
+    bool cut = false;
+    for (int i = 0; i < batch; ++i) {
+        const int si = up(up(kv_len[i], kSK) + tree, best_c);
+        p.seq[i] = AttnSeqPlan{si, 0, si, first};
+        first += si;
+        cut = cut || si > 1;
+    }
+    p.items = (long long)first * Hkv * p.groups;
+    plan_scratch(p, T, Hq, D, cut ? first : 0);
+    return p;
+}
+
+// attn_mfma_kernel.  Even form: row tiles of the same height.  Uneven form, where the blocks of 32 rows are
+// a few more than whole tiles of 8 (T = 257 with four heads per KV head: 33 blocks): whole tiles plus one
+// small tail tile with key ranges of its own.
+static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_len, long long slot_room)
+{
+    const int nblk = up(T * (Hq / Hkv), 32), full = nblk / 8, rem = nblk % 8;
+    const int tree = up(T, kKT);
+    int32_t order[DDTREE_MAX_BATCH];
+    longest_first(order, kv_len, batch);
+    const int nt_max = up(kv_len[order[0]], kKT) + tree;
+    Sized sized[DDTREE_MAX_BATCH];
+    long long key_tiles = 0;
+    for (int i = 0; i < batch; ++i) key_tiles += up(kv_len[i], kKT) + tree;
+    const double hbm_us = (double)key_tiles * Hkv * (kKT * 4.0 * kHD) / 5.0e6;
+    // Measured (us): a workgroup's fixed cost, a key tile, and a key tile of a tail tile against that.
+    const double fix = 11.0, tile = 1.52, c_tail = 0.6;
+    const long long cap = std::min(slot_room, main_slot_cap(batch, T, Hq, Hkv));
+    AttnPlan best{};
+    best.cost = 1e30;
+    int best_c = nt_max, best_ct = 0;
+    for (int uneven = 0; uneven < 2; ++uneven) {
+        if (uneven && !(full >= 1 && rem >= 1 && rem <= 4)) break;
+        const int tiles = uneven ? full : up(nblk, 8);
+        for (int s = 1; s <= 32 && (s == 1 || s * 2 <= nt_max); ++s) {
+            const int c = up(nt_max, s);
+            if (s > 1 && up(nt_max, s - 1) == c) continue;
+            // tail ranges: as long as a whole tile's, a little longer or a little shorter
+            const int t0 = uneven ? std::max(1, (int)(c_tail * nt_max / c)) : 0;
+            for (int t = t0; t <= (uneven ? std::min(t0 + 1, 32) : 0); ++t) {
+                const int ct = uneven ? up(nt_max, t) : 0;
+                long long items = 0, slots = 0;
+                for (int i = 0; i < batch; ++i) {
+                    const int nt = up(kv_len[order[i]], kKT) + tree, si = up(nt, c), ti = uneven ? up(nt, ct) : 0;
+                    items += tiles * si + ti;
+                    slots += std::max(si, ti);
+                    sized[i] = Sized{fix + tile * std::max((double)up(nt, si), ti ? c_tail * up(nt, ti) : 0.0),
+                                     (long long)(tiles * si + ti) * Hkv};
+                }
+                const bool cut = s > 1 || t > 1;
+                if (cut && slots > cap) break;
+                const double cost = std::max(rounds_us(sized, batch), hbm_us) + (cut ? merge_us(slots, T, Hq, kHD) : 0.0);
+                if (cost < best.cost) {
+                    best.cost = cost;
+                    best.uneven = uneven != 0;
+                    best_c = c, best_ct = ct;
+                    best.items = items * Hkv;
+                }
+            }
+        }
+    }
+    best.n_tiles = best.uneven ? full + 1 : up(nblk, 8);
+    best.blk_base = best.uneven ? 8 : nblk / best.n_tiles;
+    best.blk_extra = best.uneven ? rem : nblk % best.n_tiles;
+    int first = 0;
+    bool cut = false;
+    for (int i = 0; i < batch; ++i) {
+        const int nt = up(kv_len[i], kKT) + tree, si = up(nt, best_c), ti = best.uneven ? up(nt, best_ct) : 0;
+        best.seq[i] = AttnSeqPlan{si, ti, std::max(si, ti), first};
+        first += best.seq[i].ranges;
+        cut = cut || best.seq[i].ranges > 1;
+    }
+    plan_scratch(best, T, Hq, kHD, cut ? first : 0);
+    return best;
+}
+
+// The cheaper of the two by the estimates above.  Both measured where they meet (32 query and 8 KV heads
+// of 128, one sequence; waves of their own / shared tiles, us): 129 nodes x 4096 keys 26.8 / 26.9,
+// 401 x 600 21.8 / 25.7, 257 x 8192 102 / 51, 17 x 8192 17.5 / 20.7.  Heads of 64: 32-row groups against 64-row
+// groups at 257 x 4096 36.9 / 28.5 (two rounds of workgroups against one), at 65 x 2047 11.5 / 13.0.
+AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long slot_room)
+{
+    const AttnPlan w = plan_wave(batch, T, Hq, Hkv, D, kv_len, 1, slot_room);
+    const AttnPlan m = D == kHD ? plan_main(batch, T, Hq, Hkv, kv_len, slot_room)
+                                : plan_wave(batch, T, Hq, Hkv, D, kv_len, 2, slot_room);
+    return w.cost <= m.cost ? w : m;
+}
+
+size_t attn_scratch_upper(int batch, int T, int Hq, int Hkv, int D)
+{
+    if (!attn_mfma_shape(DDTREE_DTYPE_BF16, D, Hkv)) return 0;
+    long long slots = std::max(wave_slot_cap(batch, T, Hq, Hkv, 1), wave_slot_cap(batch, T, Hq, Hkv, 2));
+    if (D == kHD) slots = std::max(slots, main_slot_cap(batch, T, Hq, Hkv));
+    AttnPlan p{};
+    plan_scratch(p, T, Hq, D, slots);
+    return p.bytes;
+}
+
+// The lengths of the sequences are not known here: no key range is shorter than two key tiles, and a
+// single sequence takes what the plan for its length takes.
+size_t attn_scratch_bytes(int batch, int T, int Hq, int Hkv, int D, int dtype, long long sum_L)
+{
+    if (!attn_mfma_shape(dtype, D, Hkv)) return 0;
+    if (batch == 1 && sum_L <= 0x7FFFFFFF) {
+        const int32_t len = (int32_t)sum_L;
+        return attn_plan(1, T, Hq, Hkv, D, &len, 1ll << 40).bytes;
+    }
+    long long slots = std::max(wave_slot_cap(batch, T, Hq, Hkv, 1), wave_slot_cap(batch, T, Hq, Hkv, 2));
+    if (D == kHD) slots = std::max(slots, main_slot_cap(batch, T, Hq, Hkv));
+    slots = std::min(slots, batch + (sum_L + (T + 128LL) * batch) / (2 * kKT));
+    AttnPlan p{};
+    plan_scratch(p, T, Hq, D, slots);
+    return p.bytes;
+}
+
+// False if the launch would exceed 2^28 work items.
+bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_start, const int32_t *kv_len, int batch,
+                    int T, int Hq, int Hkv)
+{
+    if (p.items > (1ll << 28)) return false;
+    const int G = Hq / Hkv;
+    args.T = T, args.Hq = Hq, args.Hkv = Hkv, args.batch = batch;
+    args.items = (int32_t)p.items;
+    args.groups = p.groups;
+    args.rows_per_group = p.rows_per_group;
+    args.group_size = G;
+    // One round: an eighth of the items per XCD, consecutive ones, which read the same keys.  More: the row
+    // groups of one key range go to one XCD, the key ranges to the XCDs in turn, so that each has its
+    // share of the long sequences.
+    args.run = p.items <= 256 ? (int32_t)((p.items + 7) / 8) : p.groups;
+    const int per_pass = 8 * args.run;
+    args.grid = (int32_t)((p.items + per_pass - 1) / per_pass * per_pass);
+    args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
+    args.groups_magic = magic_of((uint64_t)p.groups, (uint64_t)p.items);
+    args.hkv_magic = magic_of((uint64_t)Hkv, (uint64_t)p.items);
+    args.run_magic = magic_of((uint64_t)args.run, (uint64_t)args.grid);
+    int32_t order[DDTREE_MAX_BATCH];
+    longest_first(order, kv_len, batch);
+    int unit = 0;
+    for (int i = 0; i < batch; ++i) {
+        const int s = order[i];
+        args.seq[i] = AttnWaveSeq{s, kv_start[s], kv_len[s], unit, p.seq[s].splits, p.seq[s].first_slot, p.seq[s].ranges,
+                                  magic_of((uint64_t)p.seq[s].splits, (uint64_t)(up(kv_len[s], kSK) + up(T, kSK)) * p.seq[s].splits)};
+        unit += p.seq[s].splits * Hkv;
+    }
+    return true;
+}
+
+// False if the launch would exceed 2^28 work items.
+bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_start, const int32_t *kv_len, int batch,
+                    int T, int Hq, int Hkv)
+{
+    const int G = Hq / Hkv, main_tiles = p.n_tiles - (p.uneven ? 1 : 0);
+    args.batch = batch, args.n_tiles = p.n_tiles, args.blk_base = p.blk_base, args.blk_extra = p.blk_extra;
+    args.uneven = p.uneven ? 1 : 0;
+    args.group_size = G;
+    args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
+    int32_t order[DDTREE_MAX_BATCH];
+    longest_first(order, kv_len, batch);
+    long long total = 0, per_head_max = 1;
+    double work = 0.0;
+    for (int i = 0; i < batch; ++i) {
+        const int s = order[i];
+        const AttnSeqPlan &q = p.seq[s];
+        const long long per_head = (long long)main_tiles * q.splits + q.tail_splits;
+        const uint64_t nt = (uint64_t)(up(kv_len[s], kKT) + up(T, kKT));
+        args.seq[i] = AttnMainSeq{s, kv_start[s], kv_len[s], (int32_t)total, q.splits, q.tail_splits, q.first_slot, q.ranges,
+                                  magic_of((uint64_t)per_head, (uint64_t)per_head * Hkv),
+                                  magic_of((uint64_t)q.splits, nt * q.splits + q.splits),
+                                  magic_of((uint64_t)q.tail_splits, nt * q.tail_splits + q.tail_splits), 0u};
+        total += per_head * Hkv;
+        if (total > (1ll << 28)) return false;
+        per_head_max = std::max(per_head_max, per_head);
+        work += (double)nt * per_head / std::max(1, q.splits) * Hkv;
+    }
+    args.main_tiles_magic = magic_of((uint64_t)main_tiles, (uint64_t)per_head_max);
+    // Consecutive work items run on the same XCD: the row tiles that read the same K and V rows share an
+    // L2, and those rows leave HBM once.  In one round each XCD has an eighth of the items, at most one
+    // per compute unit; otherwise an eighth of the key tiles to visit.
+    args.xcd_start[0] = 0;
+    if (total <= 256) {
+        const int run = (int)((total + 7) / 8);
+        for (int x = 1; x <= 8; ++x) args.xcd_start[x] = (int32_t)std::min<long long>(total, (long long)run * x);
+    } else {
+        double done = 0.0;
+        int x = 1;
+        for (int i = 0; i < batch; ++i) {
+            const AttnSeqPlan &q = p.seq[order[i]];
+            const long long per_seq = ((long long)main_tiles * q.splits + q.tail_splits) * Hkv;
+            const double each = (double)(up(kv_len[order[i]], kKT) + up(T, kKT)) / std::max(1, q.splits);
+            for (; x < 8 && work * x / 8 < done + each * per_seq; ++x)
+                args.xcd_start[x] = args.seq[i].first_item + (int32_t)std::min<long long>(per_seq, (long long)((work * x / 8 - done) / each + 0.5));
+            done += each * per_seq;
+        }
+        for (; x < 8; ++x) args.xcd_start[x] = (int32_t)total;
+        args.xcd_start[8] = (int32_t)total;
+    }
+    int run_max = 0;
+    for (int x = 0; x < 8; ++x) {
+        args.xcd_start[x + 1] = std::max(args.xcd_start[x + 1], args.xcd_start[x]);
+        run_max = std::max(run_max, args.xcd_start[x + 1] - args.xcd_start[x]);
+    }
+    args.grid = run_max * 8;
+    return true;
+}
+
+// ------------------------------------------------------------------------------------------
+// Host-side self-check (no GPU involved): for a list of shapes the plan and the launch tables of both
+// kernels are built as for a launch, every workgroup index of the grid is decoded the way the kernel
+// decodes it, and the work items are held against what the decomposition promises: every
+// (sequence, KV head, query row) meets every key tile exactly once, in consecutive key ranges, and each
+// of its key ranges has a partial result of its own within the scratch.
+// Returns 0, or 100 * (index of the failing shape + 1) + the number of the failed check.
+// ------------------------------------------------------------------------------------------
+namespace {
+struct Shape {
+    int batch, T, Hq, Hkv, D;
+    int32_t len[4];
+};
+struct Item {
+    int seq, hk, r0, r1, t0, t1, split, ranges, slot, keys_per_tile, nt;
+};
+}  // namespace
+
+static int check_items(const Shape &sh, const AttnPlan &p, const std::vector<Item> &items, long long expected)
+{
+    const int M = sh.T * (sh.Hq / sh.Hkv);
+    if ((long long)items.size() != expected) return 4;
+    // per (sequence, head, row): the key ranges it has met
+    std::vector<std::vector<const Item *>> met((size_t)sh.batch * sh.Hkv * M);
+    for (const Item &w : items) {
+        if (w.seq < 0 || w.seq >= sh.batch || w.hk < 0 || w.hk >= sh.Hkv || w.r0 < 0 || w.r0 >= w.r1 || w.r1 > M) return 5;
+        if (w.t0 < 0 || w.t0 > w.t1 || w.t1 > w.nt || w.split < 0 || w.split >= w.ranges) return 6;
+        if (w.ranges > 1 && (w.slot < 0 || w.slot >= p.slots)) return 7;
+        for (int r = w.r0; r < w.r1; ++r) met[((size_t)w.seq * sh.Hkv + w.hk) * M + r].push_back(&w);
+    }
+    for (size_t i = 0; i < met.size(); ++i) {
+        auto &v = met[i];
+        const int r = (int)(i % M), node = r / (sh.Hq / sh.Hkv);
+        std::sort(v.begin(), v.end(), [](const Item *a, const Item *b) { return a->split < b->split; });
+        int next = 0;
+        for (size_t j = 0; j < v.size(); ++j) {
+            if (v[j]->split != (int)j || v[j]->t0 != next) return 8;
+            next = v[j]->t1;
+        }
+        if (v.empty() || next != v[0]->nt) return 9;
+        // the row's own tree key is among the tiles
+        const int kt = v[0]->keys_per_tile, need = (sh.len[v[0]->seq] + kt - 1) / kt + node / kt + 1;
+        if (v[0]->nt < need) return 10;
+    }
+    // the slots of two sequences do not overlap
+    for (int a = 0; a < sh.batch; ++a)
+        for (int b = 0; b < sh.batch; ++b)
+            if (a != b && p.slots > 0 && p.seq[a].first_slot < p.seq[b].first_slot + p.seq[b].ranges &&
+                p.seq[b].first_slot < p.seq[a].first_slot + p.seq[a].ranges)
+                return 11;
+    return 0;
+}
+
+int attn_selftest_host()
+{
+    static const Shape shapes[] = {
+        {1, 257, 32, 8, 128, {8192}},        {1, 513, 32, 8, 128, {32768}},       {1, 65, 32, 8, 128, {2048}},
+        {4, 129, 64, 8, 128, {1533, 7527, 4000, 1024}},                           {1, 1025, 8, 2, 128, {1500}},
+        {3, 33, 16, 2, 128, {130, 0, 517}},  {1, 17, 4, 1, 128, {128}},           {2, 40, 12, 1, 128, {1000, 3}},
+        {1, 2, 1, 1, 128, {0}},              {4, 1024, 8, 8, 128, {100, 0, 64, 7}}, {1, 75, 16, 4, 128, {3000}},
+        {1, 300, 6, 2, 128, {9000}},         {2, 273, 32, 8, 128, {5000, 4999}},  {1, 1025, 128, 1, 128, {200000}},
+        {1, 65, 16, 4, 64, {2047}},          {3, 257, 32, 8, 64, {4096, 31, 33}}, {1, 2, 1, 1, 64, {0}},
+        {4, 101, 24, 8, 128, {37, 3001, 900, 1700}},
+    };
+    // exhaustive check of the reciprocal division itself on small divisors
+    for (uint32_t d = 2; d <= 64; ++d) {
+        const uint64_t x_max = 0xFFFFFFFFull / d;
+        const uint32_t m = magic_of(d, x_max);
+        if (m == 0u) return 1;
+        for (uint64_t x = 0; x <= x_max; x += (x < 70000 ? 1 : 9973))
+            if (div_by((int)(x & 0x7FFFFFFF), (int)d, m) != (int)((x & 0x7FFFFFFF) / d)) return 2;
+        if (magic_of(d, x_max + 1) != 0u && (x_max + 1) * d >= 0x100000000ull) return 3;
+    }
+    int si = 0;
+    for (const Shape &sh : shapes) {
+        ++si;
+        int32_t kv_start[4], sum = 0;
+        for (int i = 0; i < sh.batch; ++i) {
+            kv_start[i] = sum;
+            sum += sh.len[i];
+        }
+        for (int kind = 0; kind < 3; ++kind)             // waves with keys of their own, 32 and 64 rows; shared key tiles
+            for (long long room : {1ll << 40, 0ll}) {    // with scratch and without
+                if ((kind == 1 && sh.D != 64) || (kind == 2 && sh.D != kHD)) continue;
+                const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len, room)
+                                             : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len, kind + 1, room);
+                if (p.slots > room || p.bytes > attn_scratch_upper(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D)) return 100 * si + 1;
+                std::vector<Item> items;
+                if (kind == 2) {
+                    AttnMainArgs args;
+                    if (!attn_main_args(args, p, kv_start, sh.len, sh.batch, sh.T, sh.Hq, sh.Hkv)) return 100 * si + 2;
+                    for (int b = 0; b < args.grid; ++b) {
+                        const int wid = args.xcd_start[b & 7] + (b >> 3);
+                        if (wid >= args.xcd_start[(b & 7) + 1]) continue;
+                        const AttnMainItem w = attn_main_item(args, wid, sh.T);
+                        if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits > w.ranges) return 100 * si + 3;
+                        items.push_back({w.seq, w.hk, w.m0, w.m_end, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, kKT,
+                                         w.n_cache_tiles + (w.m_end - 1) / (sh.Hq / sh.Hkv) / kKT + 1});
+                    }
+                } else {
+                    AttnWaveArgs args;
+                    if (!attn_wave_args(args, p, kv_start, sh.len, sh.batch, sh.T, sh.Hq, sh.Hkv)) return 100 * si + 2;
+                    for (int b = 0; b < args.grid; ++b) {
+                        AttnWaveItem w;
+                        if (!attn_wave_item(args, b, w)) continue;
+                        if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits != w.ranges) return 100 * si + 3;
+                        items.push_back({w.seq, w.hk, w.r0, w.r1, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, kSK,
+                                         w.n_cache + (w.r1 - 1) / (sh.Hq / sh.Hkv) / kSK + 1});
+                    }
+                }
+                if (const int rc = check_items(sh, p, items, p.items)) return 100 * si + rc;
+            }
+    }
+    return 0;
+}
+
+}  // namespace ddt

@@ -52,21 +52,10 @@ constexpr int kTopkChunkMax = 12288;      // keys held in LDS by one chunk workg
 constexpr int kTopkMergeMaxCand = 14336;  // u64 candidates held in LDS by the merge workgroup
 TopkPlan topk_plan(int batch, int B, int V, int K);
 
-// ---- layout of the attention scratch ----
-struct AttnPlan {
-    // The query rows of one (sequence, kv head) pair, in blocks of 32, are dealt as evenly as
-    // possible to n_tiles row tiles of at most 8 blocks: tile i holds blk_base + (i < blk_extra)
-    // blocks.  The key range of every tile is cut into `splits` parts; partial results exist
-    // only when splits > 1.
-    int n_tiles, blk_base, blk_extra, splits;
-    // Uneven form (tail_splits > 0): the first n_tiles - 1 tiles hold 8 blocks and `splits` key
-    // ranges each; the last tile holds the few blocks left over (at most one wave per SIMD, so
-    // it runs about twice as fast per key tile) and `tail_splits` key ranges.  Partials are laid
-    // out for part_splits = max(splits, tail_splits) ranges.
-    int tail_splits, part_splits;
-    size_t part_off, lse_off, bytes;
-};
-AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, long long sum_L, int dtype);
+// ---- attention scratch (bytes): what ddtree_verify_attn may use for a shape and total cache length,
+//      and for any cache length ----
+size_t attn_scratch_bytes(int batch, int T, int Hq, int Hkv, int D, int dtype, long long sum_L);
+size_t attn_scratch_upper(int batch, int T, int Hq, int Hkv, int D);
 
 // ---- layout of the accept scratch ----
 struct AcceptPlan {

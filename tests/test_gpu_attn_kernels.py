@@ -1,0 +1,99 @@
+"""The two matrix-core attention kernels at the sizes where their tiling can go wrong: single rows and
+keys, edges of the 32-row and 64-row groups and of the 32-key sub-tiles, more waves than sub-tiles,
+key ranges cut differently for every sequence of a batch, scores that keep outgrowing the softmax
+reference.  Against the oracle, with the bound of the other bf16 attention tests (1e-2)."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+import ddtree_inputs as di  # noqa: E402
+import oracle  # noqa: E402
+
+if torch.cuda.is_available():
+    import paper_2604_12989_amd as dd  # noqa: E402
+    from tests import gpu_util as gu  # noqa: E402
+
+
+@pytest.fixture(scope="module", autouse=True)
+def _need_gpu():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU tests selected but no GPU is visible")
+
+
+def _tree_mask(rng, T, n=None):
+    n = T - 1 if n is None else n
+    par = np.full(T, -1, np.int32)
+    for i in range(1, n + 1):
+        par[i] = i - 1 if rng.random() < 0.5 else rng.integers(0, i)
+    return oracle.ancestor_mask(par, n, T=T)
+
+
+def _check(seed, Ts, Ls, Hq, Hkv, D, n_pairs=40, edit=None, n_nodes=None):
+    """A ragged batch of equal T against the oracle on sampled (node, head) pairs, the corners among them."""
+    rng = np.random.default_rng(seed)
+    T, batch = Ts, len(Ls)
+    off = np.concatenate([[0], np.cumsum(Ls)]).astype(np.int32)
+    parts = [di.attn_tensors(seed + b, T, Ls[b], Hq, Hkv, D, "bf16") for b in range(batch)]
+    masks = [_tree_mask(rng, T, n_nodes) for _ in range(batch)]
+    if edit is not None:
+        for p in parts:
+            edit(*p)
+    got = gu.gpu_attn(*(np.concatenate([p[i] for p in parts]) for i in range(5)), np.stack(masks), off, batch, T, "bf16")
+    worst = 0.0
+    for b in range(batch):
+        pairs = np.stack([rng.integers(0, T, n_pairs), rng.integers(0, Hq, n_pairs)], axis=1).astype(np.int32)
+        pairs[:4] = [[0, 0], [T - 1, Hq - 1], [0, Hq - 1], [T - 1, 0]]
+        ref = oracle.verify_attn(*parts[b], masks[b], pairs=pairs)
+        worst = max(worst, gu.attn_err(got[b][pairs[:, 0], pairs[:, 1]], ref))
+    assert worst < 1e-2, worst
+
+
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("T,L,Hq,Hkv", [
+    (1, 0, 1, 1), (1, 1, 2, 2), (2, 31, 1, 1), (8, 32, 4, 1), (33, 33, 1, 1), (11, 255, 3, 1), (32, 256, 2, 1),
+    (65, 257, 1, 1), (63, 7, 8, 8), (64, 900, 7, 1), (66, 31, 5, 5), (17, 4000, 4, 1), (97, 1025, 4, 2)])
+def test_few_rows_edges(T, L, Hq, Hkv, D):
+    _check(100 + T, T, [L], Hq, Hkv, D)
+
+
+@pytest.mark.parametrize("T,Ls,Hq,Hkv,D", [
+    (257, [4096], 32, 8, 64), (129, [3000, 0, 65, 1700], 32, 8, 64), (1025, [700], 8, 2, 64),   # 64-row groups
+    (273, [5000], 32, 8, 128), (129, [5000, 100, 2600], 32, 8, 128), (257, [9000, 64], 16, 4, 128),  # shared key tiles
+    (33, [900, 0, 31, 2500, 64], 12, 4, 128), (20, [40] * 9, 8, 8, 64)])
+def test_ragged_batches_with_key_ranges_of_their_own(T, Ls, Hq, Hkv, D):
+    _check(300 + T, T, Ls, Hq, Hkv, D, n_pairs=24)
+
+
+@pytest.mark.parametrize("T,L,Hq,Hkv,D", [(40, 1500, 8, 2, 64), (40, 1500, 8, 2, 128), (257, 4096, 32, 8, 64), (273, 5000, 32, 8, 128)])
+def test_scores_that_keep_outgrowing_the_reference(T, L, Hq, Hkv, D):
+    # from key 200 on, keys point along a query with a factor that grows to 8: scores up to about 90, so a
+    # row's maximum moves again and again by more than the slack of its reference
+    def edit(q, kc, vc, kt, vt):
+        G = Hq // Hkv
+        for j in range(200, L, 3):
+            f = 8.0 * (j - 200) / (L - 200)
+            for hk in range(Hkv):
+                kc[j, hk] = di.round_to_bf16((f * q[j % T, hk * G + j % G]).astype(np.float32))
+    _check(500 + T, T, [L], Hq, Hkv, D, edit=edit)
+
+
+def test_padding_rows_are_zero_in_every_kernel():
+    for T, L, Hq, Hkv, D in ((80, 50, 4, 2, 64), (80, 50, 4, 2, 128), (300, 6000, 32, 8, 128), (257, 4096, 32, 8, 64)):
+        rng = np.random.default_rng(T)
+        q, kc, vc, kt, vt = di.attn_tensors(T, T, L, Hq, Hkv, D, "bf16")
+        got = gu.gpu_attn(q, kc, vc, kt, vt, _tree_mask(rng, T, 40)[None], [0, L], 1, T, "bf16")[0]
+        assert not got[41:].any() and np.isfinite(got).all() and np.abs(got[:41]).min(axis=(1, 2)).max() > 0.0
+
+
+def test_heads_of_64_need_no_scratch():
+    """Without a workspace no key range is cut; the result is that of the cut one up to rounding."""
+    T, L, Hq, Hkv, D = 65, 3000, 8, 2, 64
+    rng = np.random.default_rng(9)
+    q, kc, vc, kt, vt = (gu.bf16_dev(a) for a in di.attn_tensors(9, T, L, Hq, Hkv, D, "bf16"))
+    mask = gu.to_dev(_tree_mask(rng, T).view(np.int64)[None])
+    args = (q, kc, vc, kt, vt, mask, [0, L], 1, T, Hq, Hkv, D, 0.125, dd.DTYPE_BF16)
+    a = dd.verify_attn(*args, None)
+    b = dd.verify_attn(*args, dd.Workspace(1, 4, 100, T - 1, Hq, Hkv, D, L))
+    assert (a.float() - b.float()).abs().max().item() < 1e-2
