@@ -128,8 +128,8 @@ extern "C" int ddtree_selftest_host(void)
 {
     using namespace ddt;
     if (const int rc = attn_selftest_host()) return rc;
-    // top-K: chunks tile the row, stay within what a chunk workgroup holds, and their candidates
-    // fit the merge workgroup; a plan that cannot be made says so
+    // top-K: chunks tile the row and stay within what a chunk workgroup holds; the scratch holds what
+    // the kernels index
     const int Vs[] = {1, 2, 7, 64, 1000, 1024, 4096, 12288, 12289, 20000, 50001, 100000, 151936, 172032, 200003, 344064, 688128, 1000000};
     const int Ks[] = {1, 2, 16, 64, 255, 256, 257, 512, 1024};
     const int rows_[] = {1, 2, 3, 8, 16, 17, 64, 127, 128, 1024};
@@ -138,28 +138,15 @@ extern "C" int ddtree_selftest_host(void)
             for (int rows : rows_) {
                 if (K > V) continue;
                 const TopkPlan p = topk_plan(1, rows, V, K);
-                if (!p.ok) {
-                    // only where the candidates of a row cannot fit the merge workgroup
-                    const long long c_min = (V + kTopkChunkMax - 1) / kTopkChunkMax;
-                    const long long len = ((V + c_min - 1) / c_min + 3) / 4 * 4;
-                    if (c_min * (K < len ? K : len) <= kTopkMergeMaxCand) return 10001;
-                    continue;
-                }
-                if (p.row_kernel) {
-                    if (rows < kTopkRowKernelMinRows) return 10002;
-                    continue;
-                }
-                if (rows >= kTopkRowKernelMinRows) return 10003;
+                if (!p.ok) return 10001;
                 if (p.chunk_len % 4 != 0 || p.chunk_len < 1 || p.chunk_len > kTopkChunkMax) return 10004;
                 if ((long long)(p.chunks - 1) * p.chunk_len >= V || (long long)p.chunks * p.chunk_len < V) return 10005;
-                if (p.kc != (K < p.chunk_len ? K : p.chunk_len)) return 10006;
-                if ((long long)p.chunks * p.kc > kTopkMergeMaxCand) return 10007;
-                // K candidates exist: the first chunk is whole unless it is the only one
-                const int first_len = p.chunks > 1 ? p.chunk_len : V;
-                if (p.kc < K && p.kc != p.chunk_len) return 10008;
-                if (p.kc == K && first_len < K) return 10009;
-                if (p.stat_off < (size_t)rows * p.chunks * p.kc * 8 || p.bytes < p.stat_off + (size_t)rows * p.chunks * 16) return 10010;
-                if ((p.stat_off & 255u) || (p.bytes & 255u)) return 10011;
+                if (p.group < 1 || p.group > 8 || (p.group & (p.group - 1)) || p.maxima * p.group != 512) return 10006;
+                if (p.hot_rank < 1 || p.hot_rank > 64 || p.hot_cap < 0 || (p.hot_cap & (p.hot_cap - 1))) return 10007;
+                const size_t per = (size_t)rows * p.chunks;
+                if (p.stat_off < per * p.maxima * 4 || p.hot_off < p.stat_off + per * 24 || p.bytes < p.hot_off + per * p.hot_cap * 8)
+                    return 10010;
+                if ((p.stat_off & 255u) || (p.hot_off & 255u) || (p.bytes & 255u)) return 10011;
             }
     // accept: segments tile the row in multiples of four, scratch holds one partial per segment
     for (int V : Vs)

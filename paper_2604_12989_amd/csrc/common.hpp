@@ -42,14 +42,14 @@ inline bool ws_ok(const void *ws, size_t have, size_t need)
 struct TopkPlan {
     int chunks;     // chunks per logits row
     int chunk_len;  // elements per chunk (multiple of 4), last chunk may be shorter
-    int kc;         // candidates kept per chunk = min(K, chunk_len)
-    size_t cand_off, stat_off, bytes;
+    int group;      // threads per group maximum
+    int maxima;     // group maxima per chunk
+    int hot_rank;   // which of a chunk's 64 maxima is its hot bound
+    int hot_cap;    // room of a chunk's hot list (a power of two, or 0)
+    size_t max_off, stat_off, hot_off, bytes;
     bool ok;
-    bool row_kernel;  // many rows: one workgroup scans a whole row, no chunks and no scratch
 };
-constexpr int kTopkRowKernelMinRows = 128;
-constexpr int kTopkChunkMax = 12288;      // keys held in LDS by one chunk workgroup
-constexpr int kTopkMergeMaxCand = 14336;  // u64 candidates held in LDS by the merge workgroup
+constexpr int kTopkChunkMax = 6144;  // elements held in registers by one chunk workgroup
 TopkPlan topk_plan(int batch, int B, int V, int K);
 
 // ---- attention scratch (bytes): what ddtree_verify_attn may use for a shape and total cache length,

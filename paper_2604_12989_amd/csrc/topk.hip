@@ -2,17 +2,30 @@
 // ordering q_i^(1) >= q_i^(2) >= ... of each position's distribution; Lemma 1: K ranks suffice).
 //
 // Two kernels.
-//   chunk kernel  one workgroup per (row, vocabulary chunk): the chunk is read once from HBM
-//                 (coalesced 16-byte loads) into LDS as order-preserving integer keys; the
-//                 workgroup reduces max and sum-of-exp (fp64) for the row's log-sum-exp and
-//                 selects the chunk's exact top-kc by a multi-level radix select held in LDS.
-//   merge kernel  one workgroup per row: merges the chunk statistics into the fp64
-//                 log-sum-exp, selects the row's top-K among chunks*kc candidates, ranks them
-//                 (key descending, token id ascending) and writes tokens and log-probabilities.
+//   chunk kernel   one workgroup per (row, vocabulary chunk): reads the chunk once, into registers, and
+//                  leaves its maximum, its sum of exponentials (fp64), the maxima of its groups of
+//                  adjacent threads, and its "hot" elements, about twice as many as it is likely to
+//                  contribute to the row's top K.  It orders nothing.
+//   finish kernel  one workgroup per row: the K-th largest of the row's group maxima is a lower bound on
+//                  the row's K-th largest element (the maxima are K distinct elements) and a tight
+//                  one, about 1.1 K elements reach it.  Those are all hot unless a chunk's hot bound
+//                  turns out to lie above it: that chunk is read again.  They are ranked exactly (key
+//                  descending, token id ascending) and written with their log-probabilities.
+// A row of one chunk is finished by its chunk workgroup; rows whose candidates do not fit on chip (heavy
+// ties) take a radix select over the row.
 //
 // Every candidate is the 64-bit composite (key << 32) | ~token_id, so all composites of a row
 // are distinct and "larger composite" is exactly "larger logit, or equal logit and smaller id".
-#include <type_traits>
+//
+// What bounds it: latencies (two launches, two first touches of memory), and in the chunk kernel the fp64
+// exponentials; at 256 rows the chunk kernel reads 3.4 TB/s, four workgroups of 512 threads on a compute
+// unit each waiting for memory or computing.  Before, every chunk ranked its exact top K (three barriers
+// and per-slot code worth 3.2 us) for a merge that looked at a sixteenth of them, in workgroups of 1024
+// threads that fill a compute unit alone, and 128 rows or more took one workgroup per row.
+// Measured (both kernels back to back, V = 151936, before -> now): 16 rows K = 256 16.4 -> 14.0 us, K = 1024
+// 20.0 -> 16.2; 32 rows K = 128 23.8 -> 17.6; 112 rows 53.9 -> 29.6; 256 rows 66 -> 54; 8 rows of 1024 12.0 -> 7.3.
+#include <algorithm>
+#include <cmath>
 
 #include "common.hpp"
 
@@ -20,46 +33,53 @@ namespace ddt {
 
 constexpr int kListCap = 1024;  // a radix bin this small is finished by rank counting
 constexpr int kHistBins = 4096;
+constexpr int kChunkThreads = 512;
+constexpr int kChunkWaves = kChunkThreads / 64;
+constexpr int kVecPerThread = kTopkChunkMax / 4 / kChunkThreads;
+constexpr int kSlots = 4 * kVecPerThread + 2;  // float4 body + one head and one tail element
+static_assert(kVecPerThread * 4 * kChunkThreads == kTopkChunkMax, "chunk must tile the workgroup");
+constexpr int kRankCap = 4096;   // candidates of a row held on chip
+constexpr int kBuckets = 1024;
+
+struct ChunkStat {
+    double sum;        // sum of exp(x - max) over everything but one instance of the maximum
+    float max, low;    // largest element, smallest (finite) group maximum
+    float hot;         // hot bound: the elements that reach it are in the hot list (+inf: there is no list, or they did not fit)
+    int32_t pad;
+};
 
 TopkPlan topk_plan(int batch, int B, int V, int K)
 {
     TopkPlan p{};
-    p.ok = false;
     if (batch < 1 || B < 1 || V < 1 || K < 1 || K > V) return p;
-    long long rows = (long long)batch * B;
-    if (rows >= kTopkRowKernelMinRows) {  // one workgroup per row, no scratch
-        p.row_kernel = true;
-        p.chunks = 1;
-        p.chunk_len = V;
-        p.kc = K;
-        p.cand_off = p.stat_off = 0;
-        p.bytes = 256;
-        p.ok = true;
-        return p;
-    }
-    int c_min = (V + kTopkChunkMax - 1) / kTopkChunkMax;
-    int want = (int)((256 + rows - 1) / rows);
-    int c_cap = V / 1024 > 0 ? V / 1024 : 1;  // keep chunks at least 1024 long
-    int C = want < c_cap ? want : c_cap;
-    if (C < c_min) C = c_min;
-    for (;;) {
-        int len = (V + C - 1) / C;
-        len = (len + 3) / 4 * 4;
-        int real_c = (V + len - 1) / len;
-        int kc = K < len ? K : len;
-        if ((long long)real_c * kc <= kTopkMergeMaxCand) {
-            p.chunks = real_c;
-            p.chunk_len = len;
-            p.kc = kc;
-            break;
-        }
-        if (C == c_min) return p;
-        --C;
-    }
-    p.cand_off = 0;
-    size_t cand_bytes = (size_t)rows * p.chunks * p.kc * sizeof(uint64_t);
-    p.stat_off = align_up(cand_bytes, 256);
-    p.bytes = align_up(p.stat_off + (size_t)rows * p.chunks * 16, 256);
+    const long long rows = (long long)batch * B;
+    // two workgroups per compute unit, chunks of at least 1024 elements, at most one chunk per lane of a wave
+    const int c_min = (V + kTopkChunkMax - 1) / kTopkChunkMax;
+    const int want = (int)std::min<long long>({(512 + rows - 1) / rows, std::max(1, V / 1024), 64});
+    // A row that one workgroup holds is finished by it: one launch (8 rows of 3000, K = 200: 8.4 us, with two
+    // chunks 11.8) -- unless its 512 maxima are too few to bound K (16 rows of 4000, K = 1024: 16.0 us, with
+    // three chunks 12.4).
+    const bool one = c_min == 1 && 3LL * K / 2 <= kChunkThreads;
+    const int want_c = one ? 1 : std::max(c_min, want);
+    int len = (V + want_c - 1) / want_c;
+    len = (len + 3) / 4 * 4;
+    p.chunk_len = len;
+    p.chunks = (V + len - 1) / len;
+    // threads per group: as many as leave half as many maxima again as ranks are wanted
+    p.group = 8;
+    while (p.group > 1 && (long long)p.chunks * std::min(kChunkThreads, len / 4) / p.group < 3LL * K / 2) p.group >>= 1;
+    p.maxima = kChunkThreads / p.group;
+    // Hot bound: the hot_rank-th largest of the chunk's 64 (fewer in a short chunk) maxima of 8 threads.
+    // With c elements wanted, evenly spread over g groups, a share 1 - exp(-c / g) of the groups has one.
+    const double share = (double)K / p.chunks, c = 2.2 * share + 12.0;
+    const int g = std::max(1, std::min(64, len / 32));
+    p.hot_rank = (int)(g * (1.0 - std::exp(-c / g)));
+    if (p.hot_rank < 1) p.hot_rank = 1;
+    p.hot_cap = c <= 40.0 ? 64 : c <= 90.0 ? 128 : c <= 200.0 ? 256 : c <= 420.0 ? 512 : 0;  // (0: most elements would be hot)
+    p.max_off = 0;
+    p.stat_off = align_up((size_t)rows * p.chunks * p.maxima * sizeof(float), 256);
+    p.hot_off = align_up(p.stat_off + (size_t)rows * p.chunks * sizeof(ChunkStat), 256);
+    p.bytes = align_up(p.hot_off + (size_t)rows * p.chunks * p.hot_cap * sizeof(uint64_t), 256);
     p.ok = true;
     return p;
 }
@@ -192,108 +212,14 @@ __device__ void block_rank_emit(const uint64_t *list, int m, Emit emit)
     }
 }
 
-constexpr int kCandCap = 2048;  // elements placed in LDS for exact ranking
-constexpr int kBuckets = 1024;
-
-struct BucketScratch {
-    uint32_t *cnt;     // [kBuckets]
-    int *start;        // [kBuckets + 1]
-    uint64_t *sorted;  // [kCandCap]
-    int *s_wave;       // [NT/64]
-    int *s_misc;       // [8]
-};
-
-// Exact descending ranks, for ranks < want, of the workgroup's elements whose value lies in
-// [lo, hi].  Each thread brings NS values in registers (-inf = empty slot; values below lo are
-// ignored) and comp(i), the composite of slot i, evaluated only for the few elements that are
-// placed.  Bit i of `active` (uniform over the wave) tells whether slot i can be non-empty
-// anywhere in the wave, so that a wave skips the code of slots it does not use.
-// The value range is cut into kBuckets equal buckets, bucket 0 the highest: an element's rank
-// is the population of the buckets above its own plus the number of larger elements inside its
-// bucket, which is found by placing the buckets that can reach rank < want side by side in LDS.
-// Returns false, having emitted nothing, if those buckets hold more than kCandCap elements
-// (heavy ties); *total_out = number of elements considered.
-template <int NT, int NS, class Comp, class Emit>
-__device__ bool block_bucket_rank(const float (&x)[NS], Comp comp, uint32_t active, float lo, float hi,
-                                  int want, BucketScratch s, int *total_out, Emit emit)
-{
-    static_assert(NT == kBuckets, "one bucket per thread");
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    s.cnt[tid] = 0;
-    if (tid == 0) {
-        s.s_misc[0] = -1;
-        s.s_misc[1] = kBuckets - 1;
-        s.start[kBuckets] = 0;  // read (and ignored) by slots that hold no element
-    }
-    __syncthreads();
-    const float inv = (float)kBuckets / fmaxf(hi - lo, 1e-30f);
-    // monotone in the value: float subtraction, scaling and truncation all preserve order
-    auto bucket_of = [&](float v) { return min((int)((hi - v) * inv), kBuckets - 1); };
-    // the counting atomics go out back to back: the positions they return are not needed
-    // before the scan below
-    int bkt[NS];
-    uint32_t pos[NS];
-#pragma unroll
-    for (int i = 0; i < NS; ++i) {
-        bkt[i] = kBuckets;
-        pos[i] = 0;
-        if ((active >> i) & 1u) {
-            if (x[i] >= lo) {
-                bkt[i] = bucket_of(x[i]);
-                pos[i] = atomicAdd(&s.cnt[bkt[i]], 1u);
-            }
-        }
-    }
-    __syncthreads();
-    // exclusive scan of the bucket populations, bucket 0 (highest values) first
-    const int mine = (int)s.cnt[tid];
-    const int incl = wave_scan_inclusive_i32(mine);
-    if (lane == 63) s.s_wave[wave] = incl;
-    __syncthreads();
-    int base = 0, total = 0;
-#pragma unroll
-    for (int w = 0; w < NT / 64; ++w) {
-        const int v = s.s_wave[w];
-        base += w < wave ? v : 0;
-        total += v;
-    }
-    const int start = base + incl - mine;
-    s.start[tid] = start;
-    if (start < want && start + mine >= want) {  // the last bucket that can hold a rank < want
-        s.s_misc[0] = start + mine;
-        s.s_misc[1] = tid;
-    }
-    __syncthreads();
-    const int placed = s.s_misc[0] < 0 ? total : s.s_misc[0];
-    const int b_last = s.s_misc[1];
-    *total_out = total;
-    if (placed > kCandCap) return false;
-    // place the elements of buckets 0..b_last side by side, bucket by bucket
-#pragma unroll
-    for (int i = 0; i < NS; ++i)
-        if ((active >> i) & 1u) {
-            const int st = s.start[bkt[i]];
-            if (bkt[i] <= b_last) s.sorted[st + (int)pos[i]] = comp(i);
-        }
-    __syncthreads();
-    // one thread per placed element: count the larger members of its bucket
-    for (int e = tid; e < placed; e += NT) {
-        const uint64_t ce = s.sorted[e];
-        const int b = bucket_of(key_float((uint32_t)(ce >> 32)));
-        const int bs = s.start[b], nb = (int)s.cnt[b];
-        int g = 0;
-        for (int j = 0; j < nb; ++j) g += s.sorted[bs + j] > ce ? 1 : 0;
-        if (bs + g < want) emit(bs + g, ce);
-    }
-    return true;
-}
 
 // exp(y) for y <= 0 in fp64 to a relative error below 4e-11: y = (64 n + j) ln2/64 + r with
 // |r| <= ln2/128, so exp(y) = 2^n * 2^(j/64) * exp(r); 2^(j/64) comes from a 64-entry table and
 // exp(r) from its Taylor polynomial of degree 3 (remainder r^4/24 < 3.6e-11; the reduction by one
 // fp64 multiple of ln2/64 is off by less than 6e-14).  The row's log-sum-exp needs its sum to some
 // 1e-8 for a log-probability that is right to the last fp32 bit; every fp64 instruction here is
-// paid 9.7 million times a step.  Returns 0 below the fp64 range.
+// paid 9.7 million times a step.  64 n + j is read off the low bits of y * 64/ln2 + 1.5 * 2^52.
+// 0 far below the fp64 range.
 __device__ const double kExp2Table[64] = {
     0x1.0000000000000p+0, 0x1.02c9a3e778061p+0, 0x1.059b0d3158574p+0, 0x1.0874518759bc8p+0,
     0x1.0b5586cf9890fp+0, 0x1.0e3ec32d3d1a2p+0, 0x1.11301d0125b51p+0, 0x1.1429aaea92de0p+0,
@@ -313,96 +239,326 @@ __device__ const double kExp2Table[64] = {
     0x1.ea4afa2a490dap+0, 0x1.efa1bee615a27p+0, 0x1.f50765b6e4540p+0, 0x1.fa7c1819e90d8p+0};
 __device__ __forceinline__ double exp_nonpositive(double y, const double *s_tab)
 {
-    const double k = rint(y * 92.33248261689366);              // 64 / ln 2
-    const double r = fma(k, -0x1.62e42fefa39efp-7, y);         // ln2/64
-    const int ki = (int)k;
+    y = fmax(y, -800.0);
+    const double t = fma(y, 92.33248261689366, 0x1.8p52);      // 64 / ln 2
+    const double r = fma(t - 0x1.8p52, -0x1.62e42fefa39efp-7, y);  // ln2/64
+    const int ki = __double2loint(t);
     double p = fma(r, 1.0 / 6.0, 0.5);
     p = fma(r, p, 1.0);
     p = fma(r, p, 1.0);
-    const double v = ldexp(s_tab[ki & 63] * p, ki >> 6);
-    return y > -708.0 ? v : 0.0;
+    return ldexp(s_tab[ki & 63] * p, ki >> 6);
+}
+
+// ------------------------------------------------------------------------------------------
+// A row's top K from what its chunks left.  NT threads.
+// ------------------------------------------------------------------------------------------
+struct FinishLds {
+    uint64_t list[kRankCap];    // the candidates
+    uint64_t sorted[kRankCap];  // bucket by bucket
+    uint32_t cnt[kBuckets];
+    int start[kBuckets + 1];
+    int wave[17];
+    int misc[8];
+    uint64_t thr;
+    double exc;                 // log1p(sum over everything but the first maximum), i.e. lse - max
+    int n_list;
+};
+struct FinishArgs {
+    int V, K, chunks, chunk_len, maxima, hot_cap;
+};
+
+template <int NT>
+__device__ void finish_row(const float *p, const FinishArgs a, const float *maxima, const ChunkStat *stat, const uint64_t *hot,
+                           FinishLds &L, int32_t *tok, float *lp)
+{
+    constexpr int NW = NT / 64, PRE = 4;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int n_max = a.chunks * a.maxima, n_hot = a.chunks * a.hot_cap, K = a.K;
+    const int cap_shift = a.hot_cap ? 31 - __builtin_clz(a.hot_cap) : 0;
+    // Everything the common case reads, requested together.  Every wave holds the statistics of all chunks,
+    // one per lane (of the first 64; beyond, they are read as needed), so that what follows from them
+    // needs no barrier.
+    ChunkStat st;
+    st.max = st.low = -INFINITY;
+    st.hot = -INFINITY;
+    st.sum = 0.0;
+    if (lane < a.chunks) st = stat[lane];
+    float g[PRE];
+    uint64_t h[PRE];
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) g[u] = tid + u * NT < n_max ? maxima[tid + u * NT] : -INFINITY;
+#pragma unroll
+    for (int u = 0; u < PRE; ++u) h[u] = tid + u * NT < n_hot ? hot[tid + u * NT] : 0ull;
+    for (int i = tid; i < kBuckets; i += NT) L.cnt[i] = 0u;
+    if (tid == 0) {
+        L.n_list = 0;
+        L.misc[0] = kBuckets;
+        L.misc[7] = 0;
+    }
+    __syncthreads();
+    // ---- the K-th largest group maximum, to the resolution of kBuckets equal buckets over the range of
+    //      the maxima, bucket 0 the highest.  (Float subtraction, scaling and truncation are monotone: an
+    //      element above another never lands in a later bucket.) ----
+    float vmax = st.max;
+    uint32_t vlow = st.low > -INFINITY ? float_key(st.low) : ~0u;
+    for (int c = lane + 64; c < a.chunks; c += 64) {
+        vmax = fmaxf(vmax, stat[c].max);
+        if (stat[c].low > -INFINITY) vlow = min(vlow, float_key(stat[c].low));
+    }
+    const float hi = wave_max_f32(vmax);
+    vlow = wave_min_u32(vlow);
+    const float lo = vlow == ~0u ? hi : key_float(vlow);
+    const float inv = (float)kBuckets / fmaxf(hi - lo, 1e-30f);
+    auto bucket_of = [&](float v) { return (int)fminf((hi - v) * inv, (float)(kBuckets - 1)); };
+#pragma unroll
+    for (int u = 0; u < PRE; ++u)
+        if (g[u] > -INFINITY) atomicAdd(&L.cnt[bucket_of(g[u])], 1u);
+    for (int i = tid + PRE * NT; i < n_max; i += NT) {
+        const float v = maxima[i];
+        if (v > -INFINITY) atomicAdd(&L.cnt[bucket_of(v)], 1u);
+    }
+    __syncthreads();
+    const double mx = (double)hi;
+    // log-sum-exp from the chunk statistics (fp64, fixed order), by one whole wave.  The chunk sums leave one
+    // instance of their own maximum out; the first chunk that holds the row's maximum stays that way,
+    // every other gets its instance back.
+    auto log_sum_exp = [&]() {
+        bool owned = false;
+        double part = 0.0;
+        for (int c0 = 0; c0 < a.chunks; c0 += 64) {
+            const ChunkStat t = c0 == 0 ? st : (c0 + lane < a.chunks ? stat[c0 + lane] : ChunkStat{0.0, -INFINITY, -INFINITY, 0.0f, 0});
+            const uint64_t top = __builtin_amdgcn_ballot_w64(c0 + lane < a.chunks && t.max == hi);
+            const bool owner = !owned && top != 0ull && lane == __builtin_ctzll(top);
+            owned = owned || top != 0ull;
+            if (c0 + lane < a.chunks) part += (t.sum + (owner ? 0.0 : 1.0)) * exp((double)t.max - mx);
+        }
+        part = wave_sum_f64_lane63(part);
+        if (lane == 63) L.exc = log1p(part);
+    };
+    // cumulative populations, highest bucket first; the counters are left empty
+    constexpr int PB = kBuckets / NT;
+    auto scan = [&](int want, bool starts) {  // (all threads)
+        int mine = 0, c[PB];
+#pragma unroll
+        for (int j = 0; j < PB; ++j) {
+            c[j] = (int)L.cnt[tid * PB + j];
+            mine += c[j];
+        }
+        const int incl = wave_scan_inclusive_i32(mine);
+        if (lane == 63) L.wave[wave] = incl;
+        __syncthreads();
+        int before = incl - mine;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) before += w < wave ? L.wave[w] : 0;
+#pragma unroll
+        for (int j = 0; j < PB; ++j) {
+            if (starts) L.start[tid * PB + j] = before;
+            else L.cnt[tid * PB + j] = 0u;
+            if (before < want && before + c[j] >= want) L.misc[0] = tid * PB + j;
+            before += c[j];
+        }
+        __syncthreads();
+    };
+    scan(K, false);
+    const bool whole = a.hot_cap == 0 || L.misc[0] == kBuckets;  // the row is read again, all of it
+    if (L.misc[0] == kBuckets) {  // fewer maxima than ranks: the same over all elements
+        for (int i0 = 0; i0 < a.V; i0 += PRE * NT) {
+            float x[PRE];
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) x[u] = i0 + u * NT + tid < a.V ? p[i0 + u * NT + tid] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (i0 + u * NT + tid < a.V) atomicAdd(&L.cnt[bucket_of(x[u])], 1u);
+        }
+        __syncthreads();
+        scan(K, false);
+    }
+    const int last = L.misc[0];  // elements of buckets 0 .. last are candidates, at least K of them
+    auto composite = [&](float x, int i) -> uint64_t {
+        return ((uint64_t)float_key(x) << 32) | (uint64_t)(uint32_t)(~(uint32_t)i);
+    };
+    auto emit = [&](int rank, uint64_t cc) {
+        tok[rank] = (int32_t)(~(uint32_t)cc);
+        lp[rank] = (float)(((double)key_float((uint32_t)(cc >> 32)) - mx) - L.exc);
+    };
+    // a chunk whose hot list may lack candidates: its bound falls among their buckets
+    auto lacks = [&](float bound) { return !(bucket_of(bound) > last) || bound == INFINITY; };
+    const uint64_t lacking = __builtin_amdgcn_ballot_w64(lane < a.chunks && lacks(st.hot));  // of the first 64
+    auto reserve = [&](int n) -> int {  // n list places for this thread (one atomic per wave)
+        const int incl = wave_scan_inclusive_i32(n);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (total == 0) return 0;
+        int base = 0;
+        if (lane == 63) base = atomicAdd(&L.n_list, total);
+        return __builtin_amdgcn_readlane(base, 63) + incl - n;
+    };
+    if (!whole)
+        for (int b0 = 0; b0 < n_hot; b0 += PRE * NT) {  // (uniform)
+            if (b0 > 0) {
+#pragma unroll
+                for (int u = 0; u < PRE; ++u) h[u] = b0 + tid + u * NT < n_hot ? hot[b0 + tid + u * NT] : 0ull;
+            }
+            bool take[PRE];
+            int n = 0;
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) {
+                const int i = b0 + tid + u * NT, c = i >> cap_shift;
+                take[u] = h[u] != 0ull && bucket_of(key_float((uint32_t)(h[u] >> 32))) <= last &&
+                          !(c < 64 ? (bool)((lacking >> c) & 1ull) : lacks(stat[c].hot));
+                n += take[u] ? 1 : 0;
+            }
+            int at = reserve(n);
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (take[u]) {
+                    if (at < kRankCap) L.list[at] = h[u];
+                    ++at;
+                }
+        }
+    auto rescan = [&](int begin, int end) {  // (uniform over the workgroup)
+        for (int i0 = begin; i0 < end; i0 += PRE * NT) {
+            float x[PRE];
+            bool take[PRE];
+            int n = 0;
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) x[u] = i0 + u * NT + tid < end ? p[i0 + u * NT + tid] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < PRE; ++u) {
+                take[u] = i0 + u * NT + tid < end && bucket_of(x[u]) <= last;
+                n += take[u] ? 1 : 0;
+            }
+            int at = reserve(n);
+#pragma unroll
+            for (int u = 0; u < PRE; ++u)
+                if (take[u]) {
+                    if (at < kRankCap) L.list[at] = composite(x[u], i0 + u * NT + tid);
+                    ++at;
+                }
+        }
+    };
+    if (whole) rescan(0, a.V);
+    for (int c0 = 0; c0 < a.chunks && !whole; c0 += 64) {
+        uint64_t todo = c0 == 0 ? lacking : __builtin_amdgcn_ballot_w64(c0 + lane < a.chunks && lacks(stat[min(c0 + lane, a.chunks - 1)].hot));
+        for (; todo != 0ull; todo &= todo - 1ull) {
+            const int begin = (c0 + __builtin_ctzll(todo)) * a.chunk_len;
+            rescan(begin, min(begin + a.chunk_len, a.V));
+        }
+    }
+    __syncthreads();
+    const int m = L.n_list;
+    if (m > kRankCap) {
+        // heavy ties: exact radix select over the row
+        if (wave == NW - 1) log_sum_exp();
+        SelectScratch sc{reinterpret_cast<uint32_t *>(L.sorted), L.sorted + kHistBins / 2, L.wave, L.misc, &L.thr};
+        auto get = [&](int i) -> uint64_t { return composite(p[i], i); };
+        const uint64_t thr = block_select_threshold<NT>(get, a.V, K, sc);
+        for (int i = tid; i < a.V; i += NT) {
+            const uint64_t cc = get(i);
+            if (cc >= thr) {
+                const int at = atomicAdd(&L.misc[7], 1);  // exactly K
+                if (at < kRankCap) L.list[at] = cc;
+            }
+        }
+        __syncthreads();
+        block_rank_emit<NT>(L.list, K, emit);
+        return;
+    }
+    if (m <= NT / 8) {
+        // all pairs: the threads of a wave share the element they compare with (a broadcast read), and
+        // each element's comparisons are dealt to NT / E threads
+        int E = 64;
+        while (E < m) E <<= 1;
+        const int parts = NT / E, e = tid & (E - 1), part_no = tid / E;
+        const uint64_t mine = e < m ? L.list[e] : 0ull;
+        const int j1 = min(m, (part_no + 1) * ((m + parts - 1) / parts));
+        int above = 0;
+        for (int j = part_no * ((m + parts - 1) / parts); j < j1; ++j) above += L.list[j] > mine ? 1 : 0;
+        if (e < m && above) atomicAdd(&L.cnt[e], (uint32_t)above);
+        if (wave == NW - 1) log_sum_exp();  // (this wave has the fewest candidates)
+        __syncthreads();
+        if (tid < m && (int)L.cnt[tid] < K) emit((int)L.cnt[tid], mine);
+        return;
+    }
+    // by buckets over the candidates' own range: a candidate's rank is the population of the buckets above
+    // its own plus the larger members of its bucket
+    const float span = (float)(last + 1) / inv;
+    const float inv2 = (float)kBuckets / fmaxf(span, 1e-30f);
+    auto bucket2 = [&](uint64_t cc) { return (int)fminf((hi - key_float((uint32_t)(cc >> 32))) * inv2, (float)(kBuckets - 1)); };
+    constexpr int PER = kRankCap / NT;
+    uint64_t mine[PER];
+    int bkt[PER], pos[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int i = tid + u * NT;
+        bkt[u] = pos[u] = 0;
+        mine[u] = 0ull;
+        if (i < m) {
+            mine[u] = L.list[i];
+            bkt[u] = bucket2(mine[u]);
+            pos[u] = (int)atomicAdd(&L.cnt[bkt[u]], 1u);
+        }
+    }
+    if (wave == NW - 1) log_sum_exp();
+    __syncthreads();
+    scan(0, true);
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (tid + u * NT < m) L.sorted[L.start[bkt[u]] + pos[u]] = mine[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        if (tid + u * NT >= m) break;
+        const int bs = L.start[bkt[u]], nb = (int)L.cnt[bkt[u]];
+        if (bs >= K) continue;
+        int above = bs;
+        for (int j = 0; j < nb; ++j) above += L.sorted[bs + j] > mine[u] ? 1 : 0;
+        if (above < K) emit(above, mine[u]);
+    }
 }
 
 // ------------------------------------------------------------------------------------------
 // Chunk kernel
 // ------------------------------------------------------------------------------------------
-constexpr int kChunkThreads = 1024;
-constexpr int kChunkWaves = kChunkThreads / 64;
-constexpr int kVecPerThread = kTopkChunkMax / 4 / kChunkThreads;
-constexpr int kSlots = 4 * kVecPerThread + 2;  // float4 body + one head and one tail element
-static_assert(kVecPerThread * 4 * kChunkThreads == kTopkChunkMax, "chunk must tile the workgroup");
-
-// Largest value of each group of `group` adjacent lanes (a power of two), then the smallest of
-// the wave's group maxima.  Valid in lane 63.
-__device__ __forceinline__ uint32_t wave_min_of_group_max(uint32_t v, int group)
+template <bool FINISH>
+__global__ __launch_bounds__(kChunkThreads, 4) void topk_chunk_kernel(
+    const float *__restrict__ logits, const FinishArgs a, int group, int hot_rank, float *maxima, ChunkStat *stat,
+    uint64_t *hot, int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
 {
-    auto step = [&](uint32_t o, int d) { v = d < group ? max(v, o) : min(v, o); };
-    step(dpp_u<0xB1>(v), 1);
-    step(dpp_u<0x4E>(v), 2);
-    step(dpp_u<0x141>(v), 4);
-    step(dpp_u<0x140>(v), 8);
-    step(dpp_u<0x142, 0xA>(v), 16);
-    step(dpp_u<0x143, 0xC>(v), 32);
-    return v;
-}
-
-// The chunk stays in registers (at most 14 elements per thread).  A lower bound t on the
-// chunk's kc-th largest value comes almost free: cut every wave into g >= kc / waves groups of
-// adjacent lanes, take each group's largest value, and let t be the smallest of all group
-// maxima; the waves * g >= kc maxima are distinct elements that reach t.  Elements >= t (about
-// one in seven for kc = 256) are ranked exactly by block_bucket_rank and the top kc written in
-// descending order.  Chunks it cannot handle (heavy ties, or kc so large that the bound passes
-// most of the chunk) take the radix select over keys staged in LDS.
-__global__ __launch_bounds__(kChunkThreads) void topk_chunk_kernel(
-    const float *__restrict__ logits, int V, int chunk_len, int kc, int chunks,
-    uint64_t *__restrict__ cand, double *__restrict__ stat)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    uint32_t *s_key = reinterpret_cast<uint32_t *>(smem);  // [chunk_len], fallback only
-    uint32_t *hist = s_key + chunk_len;                    // [kHistBins], fallback only
-    __shared__ __align__(16) uint64_t s_list[kCandCap];
-    __shared__ uint32_t s_cnt[kBuckets];
-    __shared__ int s_start[kBuckets + 1];
-    __shared__ int s_wave[kChunkWaves + 1];
-    __shared__ int s_misc[8];
-    __shared__ uint64_t s_thr;
-    __shared__ float s_fmax[kChunkWaves];
-    __shared__ uint32_t s_bound[kChunkWaves];
-    __shared__ float s_fmin[kChunkWaves];
+    __shared__ float s_fmax[kChunkWaves], s_group[64];
+    __shared__ uint32_t s_low[kChunkWaves];
     __shared__ double s_dsum[kChunkWaves];
-    __shared__ int s_neq[kChunkWaves];
+    __shared__ int s_neq[kChunkWaves], s_count;
     __shared__ double s_exp2[64];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = blockIdx.x;
     const size_t row = (size_t)blockIdx.z * gridDim.y + blockIdx.y;
-    const int start = c * chunk_len;
-    const int n = min(chunk_len, V - start);
-    const float *p = logits + row * (size_t)V + start;
+    const int start = c * a.chunk_len;
+    const int n = min(a.chunk_len, a.V - start);
+    const float *p = logits + row * (size_t)a.V + start;
 
     // ---- load: scalar head up to 16-byte alignment, float4 body, scalar tail; all of a
-    //      thread's loads are in flight together ----
+    //      thread's loads are in flight together.  Empty slots hold -inf: no effect on a maximum, an
+    //      exp term of 0 ----
     int head = (int)((4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
     if (head > n) head = n;
     const int nvec = (n - head) >> 2;
     const int tail0 = head + 4 * nvec;
     const float4 *pv = reinterpret_cast<const float4 *>(p + head);
-    // empty slots hold -inf: no effect on the max, an exp term of 0, and below every bound lo
-    // that block_bucket_rank is given (chunks with real -inf elements take the radix select)
-    const float kEmpty = -INFINITY;
     float x[kSlots];
 #pragma unroll
     for (int u = 0; u < kVecPerThread; ++u) {
         const int j = tid + u * kChunkThreads;
-        const float4 v = j < nvec ? pv[j] : make_float4(kEmpty, kEmpty, kEmpty, kEmpty);
+        const float4 v = j < nvec ? pv[j] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
         x[4 * u + 0] = v.x;
         x[4 * u + 1] = v.y;
         x[4 * u + 2] = v.z;
         x[4 * u + 3] = v.w;
     }
-    x[kSlots - 2] = tid < head ? p[tid] : kEmpty;
-    x[kSlots - 1] = tid < n - tail0 ? p[tail0 + tid] : kEmpty;
+    x[kSlots - 2] = tid < head ? p[tid] : -INFINITY;
+    x[kSlots - 1] = tid < n - tail0 ? p[tail0 + tid] : -INFINITY;
     if (tid < 64) s_exp2[tid] = kExp2Table[tid];
+    if (tid == 0) s_count = 0;
     // element index of slot s within the chunk, -1 if the slot is empty
     auto slot_index = [&](int s) -> int {
         if (s < 4 * kVecPerThread) {
@@ -412,543 +568,149 @@ __global__ __launch_bounds__(kChunkThreads) void topk_chunk_kernel(
         if (s == kSlots - 2) return tid < head ? tid : -1;
         return tid < n - tail0 ? tail0 + tid : -1;
     };
-    // slots that hold an element in at least one lane of this wave (uniform)
+    // loads that hold an element in at least one lane of this wave (uniform)
     const int wave_base = __builtin_amdgcn_readfirstlane(tid & ~63);
-    uint32_t active = 0;
+    int loads = 0;
 #pragma unroll
-    for (int u = 0; u < kVecPerThread; ++u)
-        if (wave_base + u * kChunkThreads < nvec) active |= 0xFu << (4 * u);
-    if (wave_base < head) active |= 1u << (kSlots - 2);
-    if (wave_base < n - tail0) active |= 1u << (kSlots - 1);
+    for (int u = 0; u < kVecPerThread; ++u) loads += wave_base + u * kChunkThreads < nvec ? 1 : 0;
+    const bool edges = wave_base == 0 && (head > 0 || n > tail0);
 
-    // ---- chunk max, chunk min and the bound t.  Every element is ranked (t = chunk min) when
-    //      the chunk is small, or when a group has no element at all and the bound is void ----
-    const bool take_all = n <= kCandCap;
-    const bool void_bound = nvec < kChunkThreads;  // some thread holds no element
-    float tmax = -INFINITY, tmin = INFINITY;
+    // ---- maxima of the threads, of groups of `group` of them, and of groups of eight ----
+    float tmax = fmaxf(x[kSlots - 2], x[kSlots - 1]);
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s)
-        if ((active >> s) & 1u) tmax = fmaxf(tmax, x[s]);
-    if (take_all || void_bound) {
-#pragma unroll
-        for (int s = 0; s < kSlots; ++s)
-            if (((active >> s) & 1u) && slot_index(s) >= 0) tmin = fminf(tmin, x[s]);
-    }
-    const bool any = tid < nvec || tid < head || tid < n - tail0;
-    const float wmax = wave_max_f32(tmax);
-    int group = 64;  // lanes per group: the largest power of two with waves * (64 / group) >= kc
-    while (group > 1 && kChunkWaves * (64 / group) < kc) group >>= 1;
-    const uint32_t bound = wave_min_of_group_max(any ? float_key(tmax) : 0u, group);
-    const float wmin = -wave_max_f32(-tmin);
+    for (int s = 0; s < 4 * kVecPerThread; ++s) tmax = fmaxf(tmax, x[s]);
+    float g = tmax;
+    const float g1 = g;
+    g = fmaxf(g, dpp_f<0xB1>(g, g));
+    const float g2 = g;
+    g = fmaxf(g, dpp_f<0x4E>(g, g));
+    const float g4 = g;
+    g = fmaxf(g, dpp_f<0x141>(g, g));
+    const float mine = group == 8 ? g : group == 4 ? g4 : group == 2 ? g2 : g1;
+    if ((lane & (group - 1)) == 0) maxima[((row * a.chunks + c) * kChunkThreads + tid) / group] = mine;
+    if ((lane & 7) == 0) s_group[tid >> 3] = g;
+    const float wmax = wave_max_f32(g);
+    const uint32_t low = wave_min_u32(mine > -INFINITY ? float_key(mine) : ~0u);
     if (lane == 63) {
         s_fmax[wave] = wmax;
-        s_fmin[wave] = wmin;
-        s_bound[wave] = bound;
+        s_low[wave] = low;
     }
     __syncthreads();
-    float cmax = s_fmax[0], cmin = s_fmin[0];
-    uint32_t t = s_bound[0];
+    float cmax = s_fmax[0];
 #pragma unroll
-    for (int w = 1; w < kChunkWaves; ++w) {
-        cmax = fmaxf(cmax, s_fmax[w]);
-        cmin = fminf(cmin, s_fmin[w]);
-        t = min(t, s_bound[w]);
+    for (int w = 1; w < kChunkWaves; ++w) cmax = fmaxf(cmax, s_fmax[w]);
+
+    // ---- the hot bound: a value that hot_rank of the 64 maxima of eight threads reach and few more, found
+    //      by bisection (each wave for itself: no barrier); then the hot elements, in no order ----
+    uint64_t *const out = hot + (row * a.chunks + c) * (size_t)a.hot_cap;
+    float bound = -INFINITY;
+    if (a.hot_cap > 0) {
+        const float v = s_group[lane];
+        float up = cmax;
+        bound = -wave_max_f32(v > -INFINITY ? -v : -INFINITY);
+        if (__builtin_popcountll(__builtin_amdgcn_ballot_w64(v > -INFINITY)) < hot_rank) bound = -INFINITY;
+        for (int i = 0; i < 9; ++i) {
+            const float mid = 0.5f * (bound + up);
+            const bool enough = __builtin_popcountll(__builtin_amdgcn_ballot_w64(v >= mid)) >= hot_rank;
+            bound = enough ? mid : bound;
+            up = enough ? up : mid;
+        }
     }
-    const float lo = (take_all || void_bound) ? cmin : key_float(t);
+    if (bound > -INFINITY) {
+        int cnt = 0;
+#pragma unroll
+        for (int s = 0; s < kSlots; ++s) cnt += x[s] >= bound ? 1 : 0;
+        const int incl = wave_scan_inclusive_i32(cnt), total = __builtin_amdgcn_readlane(incl, 63);
+        if (total > 0) {
+            int base = 0;
+            if (lane == 63) base = atomicAdd(&s_count, total);
+            int at = __builtin_amdgcn_readlane(base, 63) + incl - cnt;
+            if (cnt > 0) {
+#pragma unroll
+                for (int s = 0; s < kSlots; ++s)
+                    if (x[s] >= bound) {
+                        if (at < a.hot_cap)
+                            out[at] = ((uint64_t)float_key(x[s]) << 32) | (uint64_t)(uint32_t)(~(uint32_t)(start + slot_index(s)));
+                        ++at;
+                    }
+            }
+        }
+    }
 
     // ---- sum of exp(x - cmax) in fp64, fixed reduction order, one instance of the maximum left
     //      out: the row's log-sum-exp is formed as max + log1p(sum over everything else), which
     //      stays accurate when one token holds nearly all the probability (its log-probability
     //      is -log1p(tiny), and a sum that starts at 1 would have rounded the tiny part away).
-    //      Elements equal to the maximum are counted, not added.
-    //      (The four elements of a 16-byte load go through the exponential side by side, in one
-    //      basic block: taken one slot at a time behind a test of its own, each exponential is a
-    //      chain of dependent fp64 instructions and an LDS read with nothing to overlap it.)
+    //      Elements equal to the maximum are counted, not added; most waves hold none.
+    //      (The elements of a load go through the exponential side by side, in one basic block:
+    //      one at a time each is a chain of dependent fp64 instructions and an LDS read.) ----
     double acc = 0.0;
     int neq = 0;
-    static_assert(kVecPerThread == 3, "the grouping below is written for three loads per thread");
-    auto exp_slots = [&](auto First, auto Count) {
-        constexpr int s0 = decltype(First)::value, cnt = decltype(Count)::value;
-        double e[cnt];
+    const bool has_max = __builtin_amdgcn_ballot_w64(tmax == cmax) != 0ull;
+    auto exp_load = [&](int s0, int cnt) __attribute__((always_inline)) {
+        double e[8];
 #pragma unroll
         for (int j = 0; j < cnt; ++j) e[j] = exp_nonpositive((double)x[s0 + j] - (double)cmax, s_exp2);
+        if (has_max) {
 #pragma unroll
-        for (int j = 0; j < cnt; ++j) {
-            const bool eq = x[s0 + j] == cmax;
-            neq += eq ? 1 : 0;
-            acc += eq ? 0.0 : e[j];
+            for (int j = 0; j < cnt; ++j) {
+                const bool eq = x[s0 + j] == cmax;
+                neq += eq ? 1 : 0;
+                e[j] = eq ? 0.0 : e[j];
+            }
         }
+#pragma unroll
+        for (int j = 0; j < cnt; ++j) acc += e[j];
     };
-    // (the four slots of a load are active together; the first two loads of a wave mostly both are)
-    if ((active & 0xFFu) == 0xFFu) {
-        exp_slots(std::integral_constant<int, 0>{}, std::integral_constant<int, 8>{});
-    } else {
-        if (active & 0x1u) exp_slots(std::integral_constant<int, 0>{}, std::integral_constant<int, 4>{});
-        if (active & 0x10u) exp_slots(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{});
-    }
-    if (active & 0x100u) exp_slots(std::integral_constant<int, 8>{}, std::integral_constant<int, 4>{});
-#pragma unroll
-    for (int s = 4 * kVecPerThread; s < kSlots; ++s)
-        if ((active >> s) & 1u) {
-            const bool eq = x[s] == cmax;
-            neq += eq ? 1 : 0;
-            const double e = exp_nonpositive((double)x[s] - (double)cmax, s_exp2);
-            acc += eq ? 0.0 : e;
-        }
+    static_assert(kVecPerThread == 3, "the grouping below is written for three loads per thread");
+    if (loads >= 2) exp_load(0, 8);
+    else if (loads == 1) exp_load(0, 4);
+    if (loads == 3) exp_load(8, 4);
+    if (edges) exp_load(4 * kVecPerThread, 2);
     acc = wave_sum_f64_lane63(acc);
     neq = wave_scan_inclusive_i32(neq);
     if (lane == 63) {
         s_dsum[wave] = acc;
         s_neq[wave] = neq;
     }
-
-    // ---- rank the elements that reach t ----
-    const uint32_t base_id = (uint32_t)start;
-    auto composite = [&](uint32_t key, int i) -> uint64_t {
-        return ((uint64_t)key << 32) | (uint64_t)(uint32_t)(~(base_id + (uint32_t)i));
-    };
-    auto comp = [&](int s) { return composite(float_key(x[s]), slot_index(s)); };
-    uint64_t *out = cand + (row * chunks + c) * (size_t)kc;
-    auto emit = [&](int rank, uint64_t cc) { out[rank] = cc; };
-    BucketScratch bs{s_cnt, s_start, s_list, s_wave, s_misc};
-    int m = 0;
-    const bool done = lo > -INFINITY &&
-                      block_bucket_rank<kChunkThreads, kSlots>(x, comp, active, lo, cmax, kc, bs, &m, emit);
     __syncthreads();
+    const int hot_count = s_count;
+    if (tid >= hot_count && tid < a.hot_cap) out[tid] = 0ull;  // (no candidate)
     if (tid == 0) {
         double S = s_dsum[0];
         int n_max = s_neq[0];
+        uint32_t lowest = s_low[0];
         for (int w = 1; w < kChunkWaves; ++w) {
             S += s_dsum[w];
             n_max += s_neq[w];
+            lowest = min(lowest, s_low[w]);
         }
-        double *st = stat + (row * chunks + c) * 2;
-        st[0] = (double)cmax;
-        st[1] = S + (double)(n_max - 1);  // everything but one instance of the chunk maximum
+        ChunkStat r;
+        r.sum = S + (double)(n_max - 1);  // everything but one instance of the chunk maximum
+        r.max = cmax;
+        r.low = lowest == ~0u ? -INFINITY : key_float(lowest);
+        r.hot = bound > -INFINITY && hot_count <= a.hot_cap ? bound : INFINITY;
+        r.pad = 0;
+        stat[row * a.chunks + c] = r;
     }
-    if (!done) {
-        // exact radix select over the whole chunk, then all-pairs ranking of the kc selected
-#pragma unroll
-        for (int s = 0; s < kSlots; ++s) {
-            const int i = slot_index(s);
-            if (i >= 0) s_key[i] = float_key(x[s]);
-        }
-        if (tid == 0) s_misc[7] = 0;
-        __syncthreads();
-        auto get = [&](int i) -> uint64_t { return composite(s_key[i], i); };
-        if (n <= kc) {
-            // a ragged last chunk no longer than kc (it holds real -inf entries, or it would have
-            // been ranked above): every element is a candidate; n <= kc <= kCandCap
-            for (int i = tid; i < n; i += kChunkThreads) s_list[i] = get(i);
-            __syncthreads();
-            block_rank_emit<kChunkThreads>(s_list, n, emit);
-            m = n;
-        } else {
-            SelectScratch sc{hist, s_list, s_wave, s_misc, &s_thr};
-            const uint64_t thr = block_select_threshold<kChunkThreads>(get, n, kc, sc);
-            for (int i = tid; i < n; i += kChunkThreads) {
-                const uint64_t cc = get(i);
-                if (cc >= thr) s_list[atomicAdd(&s_misc[7], 1)] = cc;  // exactly kc <= kCandCap
-            }
-            __syncthreads();
-            block_rank_emit<kChunkThreads>(s_list, kc, emit);
-            m = kc;
-        }
+    if constexpr (FINISH) {
+        __shared__ __align__(16) FinishLds L;
+        __syncthreads();  // (what this workgroup wrote, it reads back)
+        finish_row<kChunkThreads>(p, a, maxima + row * a.maxima, stat + row, hot + row * (size_t)a.hot_cap, L,
+                                  topk_tok + row * (size_t)a.K, topk_lp + row * (size_t)a.K);
     }
-    for (int i = m + tid; i < kc; i += kChunkThreads) out[i] = 0ull;  // chunk shorter than kc
 }
 
-// ------------------------------------------------------------------------------------------
-// Merge kernel
-// ------------------------------------------------------------------------------------------
-constexpr int kMergeThreads = 1024;
-constexpr int kMergeWaves = kMergeThreads / 64;
-constexpr int kMergeLoads = (kTopkMergeMaxCand + kMergeThreads - 1) / kMergeThreads;
-// The kernel is built for 4, 8 and kMergeLoads candidates per thread and the host takes the
-// smallest that holds the row's chunks * kc candidates (config 3: 4096 = 4 per thread): the
-// per-slot code of the ranking is issued by all sixteen waves whether a slot holds anything or not.
-
-// Every chunk's list arrives sorted, so the q-th entry of each (q = ceil(K / chunks)) bounds
-// the row's K-th largest from below: T = the smallest of them is reached by at least
-// chunks * q >= K candidates.  Only candidates >= T (a little more than K) are ranked.
-template <int NS>
-__global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
-    const uint64_t *__restrict__ cand, const double *__restrict__ stat, int K, int kc, int chunks,
-    int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
+constexpr int kFinishThreads = 1024;
+__global__ __launch_bounds__(kFinishThreads) void topk_finish_kernel(
+    const float *__restrict__ logits, const FinishArgs a, const float *__restrict__ maxima,
+    const ChunkStat *__restrict__ stat, const uint64_t *__restrict__ hot, int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
-    const int n = chunks * kc;
-    uint64_t *s_cand = reinterpret_cast<uint64_t *>(smem);        // [n], fallback only
-    uint32_t *hist = reinterpret_cast<uint32_t *>(s_cand + n);    // [kHistBins], fallback only
-    __shared__ __align__(16) uint64_t s_list[kCandCap];
-    __shared__ uint32_t s_cnt[kBuckets];
-    __shared__ int s_start[kBuckets + 1];
-    __shared__ int s_wave[kMergeWaves + 1];
-    __shared__ int s_misc[8];
-    __shared__ uint64_t s_thr;
-    __shared__ unsigned long long s_T, s_top;
-    __shared__ uint32_t s_mkey;
-    __shared__ double s_part[kMergeWaves];
-    __shared__ double s_lse;  // log1p(sum over everything but the first maximum): lse - max
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ __align__(16) FinishLds L;
     const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-    const uint64_t *in = cand + row * (size_t)n;
-    const double *st = stat + row * (size_t)chunks * 2;
-    if (tid == 0) {
-        s_T = ~0ull;
-        s_top = 0ull;
-        s_mkey = 0u;
-        s_misc[7] = 0;
-    }
-    // candidates of the row (at most kTopkMergeMaxCand): loads issued back to back
-    const int wave_base = __builtin_amdgcn_readfirstlane(tid & ~63);
-    uint32_t active = 0;
-    uint64_t cv[NS];
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int i = tid + u * kMergeThreads;
-        cv[u] = i < n ? in[i] : 0ull;
-        if (wave_base + u * kMergeThreads < n) active |= 1u << u;
-    }
-    float xv[NS];  // candidate values, -inf where there is none
-#pragma unroll
-    for (int u = 0; u < NS; ++u)
-        xv[u] = cv[u] != 0ull ? key_float((uint32_t)(cv[u] >> 32)) : -INFINITY;
-    // per-chunk entries: statistics, first (largest) and q-th candidate
-    const int q = (K + chunks - 1) / chunks;
-    uint64_t c_q = ~0ull, c_top = 0ull;
-    double c_max = 0.0, c_sum = 0.0;
-    if (tid < chunks) {
-        c_q = in[(size_t)tid * kc + q - 1];
-        c_top = in[(size_t)tid * kc];
-        c_max = st[2 * tid];
-        c_sum = st[2 * tid + 1];
-    }
-    __syncthreads();
-    if (tid < chunks) {
-        atomicMax(&s_mkey, float_key((float)c_max));
-        atomicMin(&s_T, (unsigned long long)c_q);
-        atomicMax(&s_top, (unsigned long long)c_top);
-    }
-    for (int c = tid + kMergeThreads; c < chunks; c += kMergeThreads) {
-        atomicMax(&s_mkey, float_key((float)st[2 * c]));
-        atomicMin(&s_T, (unsigned long long)in[(size_t)c * kc + q - 1]);
-        atomicMax(&s_top, (unsigned long long)in[(size_t)c * kc]);
-    }
-    __syncthreads();
-    // ---- log-sum-exp of the row from the chunk statistics (fp64, fixed order) ----
-    // The chunk sums leave one instance of their own maximum out; the chunk that holds the row's
-    // first maximum (its top candidate is the row's top candidate) stays that way, every other
-    // chunk gets its instance back: the total is the sum over everything but the row's first
-    // maximum, and the log-sum-exp is mx + log1p(total).
-    const double mx = (double)key_float(s_mkey);
-    double part = tid < chunks ? (c_sum + (c_top == s_top ? 0.0 : 1.0)) * exp(c_max - mx) : 0.0;
-    for (int c = tid + kMergeThreads; c < chunks; c += kMergeThreads)
-        part += (st[2 * c + 1] + (in[(size_t)c * kc] == s_top ? 0.0 : 1.0)) * exp(st[2 * c] - mx);
-    part = wave_sum_f64_lane63(part);
-    // T == 0 (a chunk shorter than q): every candidate counts, which the radix select handles
-    const float lo = s_T >> 32 ? key_float((uint32_t)(s_T >> 32)) : -INFINITY;
-    const float hi = key_float((uint32_t)(s_top >> 32));
-    // s_lse is read by emit() only after the barriers of the ranking
-    if (chunks <= 64) {
-        if (tid == 63) s_lse = log1p(part);
-    } else {
-        if (lane == 63) s_part[wave] = part;
-        __syncthreads();
-        if (tid == kMergeThreads - 1) {
-            double S = s_part[0];
-            for (int w = 1; w < kMergeWaves; ++w) S += s_part[w];
-            s_lse = log1p(S);
-        }
-    }
-    // ---- rank the candidates that reach T ----
-    auto emit = [&](int rank, uint64_t cc) {
-        topk_tok[row * (size_t)K + rank] = (int32_t)(~(uint32_t)cc);
-        topk_lp[row * (size_t)K + rank] = (float)(((double)key_float((uint32_t)(cc >> 32)) - mx) - s_lse);
-    };
-    BucketScratch bs{s_cnt, s_start, s_list, s_wave, s_misc};
-    int m;
-    if (lo > -INFINITY && block_bucket_rank<kMergeThreads, NS>(
-                              xv, [&](int u) { return cv[u]; }, active, lo, hi, K, bs, &m, emit))
-        return;
-    __syncthreads();  // s_lse is complete
-    // heavy ties: exact radix select over all candidates staged in LDS
-#pragma unroll
-    for (int u = 0; u < NS; ++u) {
-        const int i = tid + u * kMergeThreads;
-        if (i < n) s_cand[i] = cv[u];
-    }
-    __syncthreads();
-    auto get = [&](int i) -> uint64_t { return s_cand[i]; };
-    SelectScratch sc{hist, s_list, s_wave, s_misc, &s_thr};
-    // zero padding entries are smaller than every candidate, and K <= the number of real ones
-    const uint64_t thr = n > K ? block_select_threshold<kMergeThreads>(get, n, K, sc) : 1ull;
-    for (int i = tid; i < n; i += kMergeThreads) {
-        const uint64_t cc = s_cand[i];
-        if (cc >= thr && cc != 0ull) s_list[atomicAdd(&s_misc[7], 1)] = cc;  // exactly K
-    }
-    __syncthreads();
-    block_rank_emit<kMergeThreads>(s_list, K, emit);
-}
-
-
-// ------------------------------------------------------------------------------------------
-// Row kernel: with a row for every compute unit (many sequences per call) one workgroup scans a
-// whole row, the chunk / merge pair and its scratch are not needed, and the scan is bound by HBM
-// and the fp64 exponentials instead of by the latency chain of a single chunk.
-//   pass 1  every thread streams its share of the row keeping a running maximum, the fp64 sum of
-//           exp(x - maximum) over the entries that differ from it and the count of those equal to
-//           it (a new maximum rescales sum + count); the workgroup merges these into the row
-//           maximum and the sum over everything but one instance of it.  The smallest of the
-//           maxima of groups of adjacent threads bounds the K-th largest entry from below.
-//   pass 2  the row is read again (it is still in the last-level cache), entries that reach the
-//           bound go to a list in LDS, a radix select over the list finds the K-th largest, and
-//           the K selected are ranked all-pairs.
-// A list that overflows (heavy ties, a void bound) falls back to the radix select over the row.
-// ------------------------------------------------------------------------------------------
-constexpr int kRowThreads = 1024;
-constexpr int kRowWaves = kRowThreads / 64;
-constexpr int kRowCap = 8192;  // candidates held in LDS
-constexpr int kRowBatch = 4;   // 16-byte loads in flight per thread
-constexpr size_t kRowLdsBytes = (size_t)kRowCap * 8 + (size_t)kListCap * 8 + (size_t)kHistBins * 4;
-
-template <int N>
-__device__ __forceinline__ void row_absorb(const float (&x)[N], float &tmax, double &S, int &neq,
-                                           const double *s_exp2)
-{
-    float bmax = x[0];
-#pragma unroll
-    for (int i = 1; i < N; ++i) bmax = fmaxf(bmax, x[i]);
-    if (bmax > tmax) {
-        // what was summed against the old maximum, its own instances included, moves to the new one
-        S = tmax > -INFINITY ? (S + (double)neq) * exp_nonpositive((double)tmax - (double)bmax, s_exp2) : 0.0;
-        neq = 0;
-        tmax = bmax;
-    }
-    if (tmax > -INFINITY) {
-#pragma unroll
-        for (int i = 0; i < N; ++i) {
-            const bool eq = x[i] == tmax;
-            const double e = exp_nonpositive((double)x[i] - (double)tmax, s_exp2);
-            neq += eq ? 1 : 0;
-            S += eq ? 0.0 : e;
-        }
-    }
-}
-
-__global__ __launch_bounds__(kRowThreads) void topk_row_kernel(const float *__restrict__ logits, int V, int K,
-                                                               int32_t *__restrict__ topk_tok,
-                                                               float *__restrict__ topk_lp)
-{
-    extern __shared__ __align__(16) unsigned char smem[];
-    uint64_t *s_list = reinterpret_cast<uint64_t *>(smem);       // [kRowCap]
-    uint64_t *s_sel = s_list + kRowCap;                          // [kListCap] >= K
-    uint32_t *s_hist = reinterpret_cast<uint32_t *>(s_sel + kListCap);  // [kHistBins]
-    __shared__ int s_wave[kRowWaves + 1];
-    __shared__ int s_misc[8];
-    __shared__ uint64_t s_thr;
-    __shared__ float s_fmax[kRowWaves];
-    __shared__ uint32_t s_bound[kRowWaves];
-    __shared__ double s_dsum[kRowWaves];
-    __shared__ double s_exp2[64];
-    __shared__ double s_exc;
-    __shared__ int s_owner, s_cnt;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const size_t row = blockIdx.x;
-    const float *p = logits + row * (size_t)V;
-    int head = (int)((4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
-    if (head > V) head = V;
-    const int nvec = (V - head) >> 2;
-    const int tail0 = head + 4 * nvec;
-    const float4 *pv = reinterpret_cast<const float4 *>(p + head);
-    const bool edge = tid < head || tid < V - tail0;  // this thread holds a head or tail element
-    if (tid < 64) s_exp2[tid] = kExp2Table[tid];
-    if (tid == 0) {
-        s_owner = kRowThreads;
-        s_cnt = 0;
-    }
-    __syncthreads();
-
-    const bool any = tid < nvec || edge;
-    const bool take_all = V <= kRowCap || nvec < kRowThreads;  // some thread may hold no element
-    int group = 64;  // lanes per group: the largest power of two with waves * (64 / group) >= K
-    while (group > 1 && kRowWaves * (64 / group) < K) group >>= 1;
-    // Lower bound on the row's K-th largest entry from what the threads have seen so far: the
-    // smallest of the maxima of groups of adjacent threads (waves * 64 / group >= K distinct
-    // entries reach it).  It only grows as the scan proceeds.
-    float tmax = -INFINITY;
-    auto bound_now = [&]() -> float {
-        const uint32_t bound = wave_min_of_group_max(any ? float_key(tmax) : 0u, group);
-        if (lane == 63) s_bound[wave] = bound;
-        __syncthreads();
-        uint32_t t = s_bound[0];
-#pragma unroll
-        for (int w = 1; w < kRowWaves; ++w) t = min(t, s_bound[w]);
-        __syncthreads();
-        return key_float(t);
-    };
-    float lo = -INFINITY;  // entries >= lo go to the list
-    auto composite = [&](float x, int i) -> uint64_t {
-        return ((uint64_t)float_key(x) << 32) | (uint64_t)(uint32_t)(~(uint32_t)i);
-    };
-    auto push = [&](bool on, float x, int i) {
-        const bool take = on && x >= lo;
-        const uint64_t bal = __ballot(take);
-        if (bal == 0) return;  // uniform over the wave
-        const int n_take = __popcll(bal);
-        int base = 0;
-        if (lane == __builtin_ctzll(bal)) base = atomicAdd(&s_cnt, n_take);
-        base = __shfl(base, __builtin_ctzll(bal), 64);
-        const int pos = base + __popcll(bal & ((1ull << lane) - 1ull));
-        if (take && pos < kRowCap) s_list[pos] = composite(x, i);
-    };
-    // the same for the sixteen entries of a batch with one list reservation per wave
-    auto push_batch = [&](const float (&x)[4 * kRowBatch], int base) {
-        int n = 0;
-#pragma unroll
-        for (int u = 0; u < kRowBatch; ++u) {
-            const bool on = base + u * kRowThreads + tid < nvec;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) n += (on && x[4 * u + e] >= lo) ? 1 : 0;
-        }
-        const int incl = wave_scan_inclusive_i32(n);
-        const int total = __builtin_amdgcn_readlane(incl, 63);
-        if (total == 0) return;  // uniform over the wave
-        int first = 0;
-        if (lane == 63) first = atomicAdd(&s_cnt, total);
-        int pos = __builtin_amdgcn_readlane(first, 63) + incl - n;
-#pragma unroll
-        for (int u = 0; u < kRowBatch; ++u) {
-            const int j = base + u * kRowThreads + tid;
-            const bool on = j < nvec;
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (on && x[4 * u + e] >= lo) {
-                    if (pos < kRowCap) s_list[pos] = composite(x[4 * u + e], head + 4 * j + e);
-                    ++pos;
-                }
-        }
-    };
-    auto push_edges = [&]() {  // head and tail elements live in the first lanes of wave 0
-        if (wave == 0) {
-            push(tid < head, tid < head ? p[tid] : 0.0f, tid);
-            push(tid < V - tail0, tid < V - tail0 ? p[tail0 + tid] : 0.0f, tail0 + tid);
-        }
-    };
-
-    // ---- the scan: running maximum, sum and count per thread; entries that reach the bound of
-    //      the moment (refreshed after 1, 2 and 4 batches) are appended to the list, a superset
-    //      of what the final bound admits ----
-    double S = 0.0;
-    int neq = 0;
-    int batch_no = 0;
-    // the loads of the next batch are requested before the exponentials of this one
-    auto load_batch = [&](int base, float4 (&v)[kRowBatch]) {
-#pragma unroll
-        for (int u = 0; u < kRowBatch; ++u) {
-            const int j = base + u * kRowThreads + tid;
-            v[u] = j < nvec ? pv[j] : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        }
-    };
-    float4 nxt[kRowBatch];
-    load_batch(0, nxt);
-    for (int base = 0; base < nvec; base += kRowBatch * kRowThreads, ++batch_no) {
-        float x[4 * kRowBatch];
-#pragma unroll
-        for (int u = 0; u < kRowBatch; ++u) {
-            x[4 * u + 0] = nxt[u].x;
-            x[4 * u + 1] = nxt[u].y;
-            x[4 * u + 2] = nxt[u].z;
-            x[4 * u + 3] = nxt[u].w;
-        }
-        load_batch(base + kRowBatch * kRowThreads, nxt);  // past the end: nothing is read
-        row_absorb(x, tmax, S, neq, s_exp2);
-        if (!take_all && (batch_no == 0 || batch_no == 1 || batch_no == 3)) lo = bound_now();
-        push_batch(x, base);
-    }
-    if (edge) {
-        const float x[2] = {tid < head ? p[tid] : -INFINITY, tid < V - tail0 ? p[tail0 + tid] : -INFINITY};
-        row_absorb(x, tmax, S, neq, s_exp2);
-    }
-    push_edges();
-
-    // ---- row maximum and the sum over everything but one instance of it ----
-    const float wmax = wave_max_f32(tmax);
-    if (lane == 63) s_fmax[wave] = wmax;
-    __syncthreads();
-    float m = s_fmax[0];
-#pragma unroll
-    for (int w = 1; w < kRowWaves; ++w) m = fmaxf(m, s_fmax[w]);
-    if (any && tmax == m) atomicMin(&s_owner, tid);  // one thread gives up one instance of the maximum
-    __syncthreads();
-    double c = 0.0;
-    if (tmax > -INFINITY)
-        c = (S + (double)(neq - (tid == s_owner ? 1 : 0))) * exp_nonpositive((double)tmax - (double)m, s_exp2);
-    c = wave_sum_f64_lane63(c);
-    if (lane == 63) s_dsum[wave] = c;
-    __syncthreads();
-    if (tid == 0) {
-        double S1 = s_dsum[0];
-        for (int w = 1; w < kRowWaves; ++w) S1 += s_dsum[w];
-        s_exc = log1p(S1);  // read by emit() after later barriers
-    }
-
-    // ---- a list that overflowed is filled again with the final bound, from the row in cache ----
-    if (s_cnt > kRowCap && !take_all) {
-        lo = bound_now();  // also orders the reads of s_cnt above before its reset
-        if (tid == 0) s_cnt = 0;
-        __syncthreads();
-        for (int base = 0; base < nvec; base += kRowBatch * kRowThreads) {
-            float4 v[kRowBatch];
-            load_batch(base, v);
-            float x[4 * kRowBatch];
-#pragma unroll
-            for (int u = 0; u < kRowBatch; ++u) {
-                x[4 * u + 0] = v[u].x;
-                x[4 * u + 1] = v[u].y;
-                x[4 * u + 2] = v[u].z;
-                x[4 * u + 3] = v[u].w;
-            }
-            push_batch(x, base);
-        }
-        push_edges();
-    }
-    if (tid == 0) s_misc[7] = 0;
-    __syncthreads();
-    const int cnt = s_cnt;  // at least K: the bound is reached by K entries, or everything was taken
-
-    // ---- the K largest of the list (or, on overflow, of the row), then their exact order ----
-    SelectScratch sc{s_hist, s_sel, s_wave, s_misc, &s_thr};
-    if (cnt <= kRowCap) {
-        auto get = [&](int i) -> uint64_t { return s_list[i]; };
-        const uint64_t thr = cnt > K ? block_select_threshold<kRowThreads>(get, cnt, K, sc) : 0ull;
-        for (int i = tid; i < cnt; i += kRowThreads) {
-            const uint64_t cc = s_list[i];
-            if (cc >= thr) {
-                const int pos = atomicAdd(&s_misc[7], 1);
-                if (pos < kListCap) s_sel[pos] = cc;  // exactly K
-            }
-        }
-    } else {
-        auto get = [&](int i) -> uint64_t { return composite(p[i], i); };
-        const uint64_t thr = block_select_threshold<kRowThreads>(get, V, K, sc);
-        for (int i = tid; i < V; i += kRowThreads) {
-            const uint64_t cc = get(i);
-            if (cc >= thr) {
-                const int pos = atomicAdd(&s_misc[7], 1);
-                if (pos < kListCap) s_sel[pos] = cc;  // exactly K
-            }
-        }
-    }
-    __syncthreads();
-    auto emit = [&](int rank, uint64_t cc) {
-        topk_tok[row * (size_t)K + rank] = (int32_t)(~(uint32_t)cc);
-        topk_lp[row * (size_t)K + rank] =
-            (float)(((double)key_float((uint32_t)(cc >> 32)) - (double)m) - s_exc);
-    };
-    block_rank_emit<kRowThreads>(s_sel, K, emit);
+    finish_row<kFinishThreads>(logits + row * (size_t)a.V, a, maxima + row * (size_t)a.chunks * a.maxima,
+                               stat + row * (size_t)a.chunks, hot + row * (size_t)a.chunks * a.hot_cap, L,
+                               topk_tok + row * (size_t)a.K, topk_lp + row * (size_t)a.K);
 }
 }  // namespace ddt
 
@@ -960,44 +722,23 @@ extern "C" int ddtree_topk(const float *logits, int batch, int B, int V, int K, 
     if (batch < 1 || batch > DDTREE_MAX_BATCH || B < 1 || B > DDTREE_MAX_B || V < 1 || K < 1 ||
         K > V || K > DDTREE_MAX_N)
         return DDTREE_ERR_ARG;
-    TopkPlan p = topk_plan(batch, B, V, K);
+    const TopkPlan p = topk_plan(batch, B, V, K);
     if (!p.ok) return DDTREE_ERR_ARG;
     if (!ws_ok(workspace, workspace_bytes, p.bytes)) return DDTREE_ERR_WORKSPACE;
-    uint64_t *cand = reinterpret_cast<uint64_t *>(static_cast<char *>(workspace) + p.cand_off);
-    double *stat = reinterpret_cast<double *>(static_cast<char *>(workspace) + p.stat_off);
-
+    char *ws = static_cast<char *>(workspace);
+    float *maxima = reinterpret_cast<float *>(ws + p.max_off);
+    ChunkStat *stat = reinterpret_cast<ChunkStat *>(ws + p.stat_off);
+    uint64_t *hot = reinterpret_cast<uint64_t *>(ws + p.hot_off);
+    const FinishArgs a{V, K, p.chunks, p.chunk_len, p.maxima, p.hot_cap};
     hipStream_t st = as_stream(stream);
-    if (p.row_kernel) {
-        static std::atomic<bool> row_lds_allowed{false};
-        if (!allow_dynamic_lds(reinterpret_cast<const void *>(topk_row_kernel), kRowLdsBytes, row_lds_allowed))
-            return DDTREE_ERR_HIP;
-        DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_row_kernel, dim3(batch * B), dim3(kRowThreads), kRowLdsBytes,
-                   st, logits, V, K, topk_tok, topk_lp);
+    if (p.chunks == 1) {
+        DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_chunk_kernel<true>, dim3(1, B, batch), dim3(kChunkThreads), 0, st, logits, a,
+                   p.group, p.hot_rank, maxima, stat, hot, topk_tok, topk_lp);
         return launch_status();
     }
-    static std::atomic<bool> chunk_lds_allowed{false}, merge_lds_allowed[3] = {{false}, {false}, {false}};
-    const size_t lds_chunk = (size_t)p.chunk_len * 4 + kHistBins * 4;
-    const size_t lds_merge = (size_t)p.chunks * p.kc * 8 + kHistBins * 4;
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(topk_chunk_kernel), kTopkChunkMax * 4 + kHistBins * 4,
-                           chunk_lds_allowed) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(topk_merge_kernel<4>), kTopkMergeMaxCand * 8 + kHistBins * 4,
-                           merge_lds_allowed[0]) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(topk_merge_kernel<8>), kTopkMergeMaxCand * 8 + kHistBins * 4,
-                           merge_lds_allowed[1]) ||
-        !allow_dynamic_lds(reinterpret_cast<const void *>(topk_merge_kernel<kMergeLoads>),
-                           kTopkMergeMaxCand * 8 + kHistBins * 4, merge_lds_allowed[2]))
-        return DDTREE_ERR_HIP;
-    DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_chunk_kernel, dim3(p.chunks, B, batch), dim3(kChunkThreads), lds_chunk, st,
-                       logits, V, p.chunk_len, p.kc, p.chunks, cand, stat);
-    const long long per_thread = ((long long)p.chunks * p.kc + kMergeThreads - 1) / kMergeThreads;
-    if (per_thread <= 4)
-        DDT_LAUNCH(DDTREE_KERNEL_TOPK_MERGE, st, topk_merge_kernel<4>, dim3(B, batch), dim3(kMergeThreads), lds_merge,
-                   st, cand, stat, K, p.kc, p.chunks, topk_tok, topk_lp);
-    else if (per_thread <= 8)
-        DDT_LAUNCH(DDTREE_KERNEL_TOPK_MERGE, st, topk_merge_kernel<8>, dim3(B, batch), dim3(kMergeThreads), lds_merge,
-                   st, cand, stat, K, p.kc, p.chunks, topk_tok, topk_lp);
-    else
-        DDT_LAUNCH(DDTREE_KERNEL_TOPK_MERGE, st, topk_merge_kernel<kMergeLoads>, dim3(B, batch), dim3(kMergeThreads),
-                   lds_merge, st, cand, stat, K, p.kc, p.chunks, topk_tok, topk_lp);
+    DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_chunk_kernel<false>, dim3(p.chunks, B, batch), dim3(kChunkThreads), 0, st, logits,
+               a, p.group, p.hot_rank, maxima, stat, hot, topk_tok, topk_lp);
+    DDT_LAUNCH(DDTREE_KERNEL_TOPK_MERGE, st, topk_finish_kernel, dim3(B, batch), dim3(kFinishThreads), 0, st, logits, a, maxima,
+               stat, hot, topk_tok, topk_lp);
     return launch_status();
 }
