@@ -194,7 +194,7 @@ int ddtree_accept(const float *target_logits, int batch, int T, int V, const int
  * (256 KiB) on every GPU the library runs on, held until the process ends.  The call allocates and
  * frees nothing.  Arguments and results as in ddtree_accept, without the workspace.
  *   - Shapes whose partials exceed the array return DDTREE_ERR_WORKSPACE and launch nothing:
- *     batch * T * segments * 8 bytes must fit, segments = min(ceil(3072 / (batch * T)), max(1, V / 8192))
+ *     batch * T * segments * 8 bytes must fit, segments = min(ceil(3072 / (batch * T)), max(1, V / 4096))
  *     (the headline shape, 257 rows of 151936 logits, takes 24 KB; 16 sequences of 129 rows 33 KB;
  *     the largest call the other entry points accept, 64 sequences of 1025 rows, 525 KB, is refused).
  *   - All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different

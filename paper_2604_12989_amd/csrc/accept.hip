@@ -10,22 +10,22 @@
 //                  chose.  The accepted nodes form the single path the sequential walk of the
 //                  paper visits, and the deepest one yields the bonus token.
 //   compact kernel copies the accepted tree rows of K and V behind the cache.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ddt {
 
 constexpr int kArgmaxThreads = 256;
-constexpr int kWalkThreads = 256;
 
-AcceptPlan accept_plan(int batch, int T, int V, bool sampled)
+AcceptPlan accept_plan(int batch, int T, int V)
 {
     AcceptPlan p{};
     long long rows = (long long)batch * T;
-    // about 3000 workgroups stream closest to the HBM rate; the sampled scan prunes key evaluations
-    // against the best key a wave has found so far, which longer segments serve better
-    const int target = sampled ? 1024 : 3072;
-    int S = (int)((target + rows - 1) / rows);
-    int s_cap = V / 8192 > 0 ? V / 8192 : 1;  // keep segments at least 8192 long
+    // About 3000 workgroups stream closest to the HBM rate; a segment of 4096 elements is four 16-byte loads
+    // a thread (65 rows of 151936: 8.5 us, with at least 8192 elements 9.1; 404 rows of 50021: 13.8 and 14.7).
+    int S = (int)((3072 + rows - 1) / rows);
+    int s_cap = V / 4096 > 0 ? V / 4096 : 1;
     if (S > s_cap) S = s_cap;
     if (S < 1) S = 1;
     int len = (V + S - 1) / S;
@@ -70,11 +70,9 @@ __device__ __forceinline__ uint32_t sample_mix(uint32_t x)
     x ^= x >> 16;
     return x;
 }
-template <bool SAMPLE>
-__device__ __forceinline__ float select_key(float logit, uint32_t id, uint32_t row_term, const SampleArgs &sa)
+// the key of one element from its hash
+__device__ __forceinline__ float sample_key(float logit, uint32_t h, const SampleArgs &sa)
 {
-    if (!SAMPLE) return logit;
-    const uint32_t h = sample_mix(sample_mix(id ^ sa.seed_lo) + row_term);
     // -ln u in fp32 without losing the draws that matter most (u close to 1 gives the largest
     // noise): for k < 2^23, u = (k + 0.5) / 2^24 is exact in fp32; otherwise w = 1 - u =
     // (2^24 - 1 - k + 0.5) / 2^24 is, and -ln(1 - w) is taken from its series when w is small
@@ -88,103 +86,10 @@ __device__ __forceinline__ float select_key(float logit, uint32_t id, uint32_t r
     return fmaf(logit, sa.inv_tau, g);
 }
 
-template <bool SAMPLE>
-__global__ __launch_bounds__(kArgmaxThreads) void accept_argmax_kernel(
-    const float *__restrict__ logits, int T, int V, int seg_len, int splits,
-    const int32_t *__restrict__ n_nodes, ArgPart *__restrict__ part, SampleArgs sa)
+// The workgroup's best (value, id), valid in thread 0.
+__device__ __forceinline__ void workgroup_best(float &bv, int &bi, float *s_v, int *s_i)
 {
-    __shared__ float s_v[kArgmaxThreads / 64];
-    __shared__ int s_i[kArgmaxThreads / 64];
     const int tid = threadIdx.x;
-    const int seg = blockIdx.x, i = blockIdx.y, seq = blockIdx.z;
-    if (i > n_nodes[seq]) return;  // padding row: never read, the walk ignores its partial
-    const size_t rowi = (size_t)seq * T + i;
-    const uint32_t row_term = 0x9E3779B9u * (uint32_t)rowi + sa.seed_hi;
-    const int start = seg * seg_len;
-    const int n = min(seg_len, V - start);
-    const float *p = logits + rowi * (size_t)V + start;
-
-    float bv = -INFINITY;
-    int bi = 0x7FFFFFFF;
-    int head = (int)((4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
-    if (head > n) head = n;
-    if (tid < head) {
-        bv = select_key<SAMPLE>(p[tid], (uint32_t)(start + tid), row_term, sa);
-        bi = start + tid;
-    }
-    const int nvec = (n - head) >> 2;
-    const float4 *pv = reinterpret_cast<const float4 *>(p + head);
-    // eight independent 16-byte loads in flight per thread and iteration: about 128 KB per compute
-    // unit, what it takes to cover the HBM latency at full bandwidth; the logits are read once,
-    // so the loads are marked non-temporal
-    constexpr int kInFlight = 8;
-    // Sampling: most elements are settled without their logarithms.  The noise is bounded from the
-    // hash alone, g = -ln(-ln u) <= -ln(1 - u) = ln(2^25 / w) with the odd integer
-    // w = 2^25 - 2k - 1, hence g <= ln2 * (clz(w) - 6); an element whose bound stays below a key
-    // this wave has already found (wb) cannot be the row's maximum, nor tie with it.
-    // The loop bound is uniform over the wave (its lanes leave the loop together): the wave
-    // maximum below reads lane 63, which must have taken part in every round.
-    float wb = -INFINITY;
-    for (int jb = tid & ~63; jb < nvec; jb += kInFlight * kArgmaxThreads) {
-        const int j0 = jb + (tid & 63);
-        float4 x[kInFlight];
-#pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-            const int j = j0 + u * kArgmaxThreads;
-            if (j < nvec) {
-                const float *q = reinterpret_cast<const float *>(pv + j);
-                x[u].x = __builtin_nontemporal_load(q);
-                x[u].y = __builtin_nontemporal_load(q + 1);
-                x[u].z = __builtin_nontemporal_load(q + 2);
-                x[u].w = __builtin_nontemporal_load(q + 3);
-            } else {
-                x[u] = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-            }
-        }
-        if (SAMPLE) wb = wave_max_f32(bv);
-#pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-            const int ia = start + head + 4 * (j0 + u * kArgmaxThreads);
-            if (SAMPLE) {
-                if (j0 + u * kArgmaxThreads >= nvec) continue;  // padding lanes draw no noise
-                const float xe[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-                bool need[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const uint32_t h = sample_mix(sample_mix((uint32_t)(ia + e) ^ sa.seed_lo) + row_term);
-                    const uint32_t w = 0x1FFFFFFu - ((h >> 8) << 1);
-                    const float g_max = 0.6931472f * (float)(__builtin_clz(w) - 6);
-                    // (the margin covers the rounding of the exact key, about 2e-6)
-                    need[e] = fmaf(xe[e], sa.inv_tau, g_max) + 2e-3f >= wb;
-                }
-                if (__ballot(need[0] || need[1] || need[2] || need[3]) != 0ull) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (need[e]) {
-                            const float ke = select_key<true>(xe[e], (uint32_t)(ia + e), row_term, sa);
-                            if (ke > bv) {
-                                bv = ke;
-                                bi = ia + e;
-                            }
-                        }
-                }
-                continue;
-            }
-            const float k0 = select_key<SAMPLE>(x[u].x, (uint32_t)ia, row_term, sa);
-            const float k1 = select_key<SAMPLE>(x[u].y, (uint32_t)ia + 1u, row_term, sa);
-            const float k2 = select_key<SAMPLE>(x[u].z, (uint32_t)ia + 2u, row_term, sa);
-            const float k3 = select_key<SAMPLE>(x[u].w, (uint32_t)ia + 3u, row_term, sa);
-            if (k0 > bv) { bv = k0; bi = ia; }
-            if (k1 > bv) { bv = k1; bi = ia + 1; }
-            if (k2 > bv) { bv = k2; bi = ia + 2; }
-            if (k3 > bv) { bv = k3; bi = ia + 3; }
-        }
-    }
-    const int tail0 = head + 4 * nvec;
-    if (tid < n - tail0) {
-        const float x = select_key<SAMPLE>(p[tail0 + tid], (uint32_t)(start + tail0 + tid), row_term, sa);
-        if (x > bv) { bv = x; bi = start + tail0 + tid; }
-    }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const float ov = __shfl_xor(bv, d, 64);
@@ -199,15 +104,184 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_argmax_kernel(
     if (tid == 0) {
 #pragma unroll
         for (int w = 1; w < kArgmaxThreads / 64; ++w) arg_update(bv, bi, s_v[w], s_i[w]);
-        ArgPart r;
-        r.val = bv;
-        r.idx = bi;
-        part[rowi * splits + seg] = r;
     }
 }
 
-__global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(
-    const ArgPart *__restrict__ part, int T, int splits, int B, const int32_t *__restrict__ tokens,
+__device__ __forceinline__ float4 load_streamed(const float4 *p)  // (read once: marked non-temporal)
+{
+    const float *q = reinterpret_cast<const float *>(p);
+    return make_float4(__builtin_nontemporal_load(q), __builtin_nontemporal_load(q + 1), __builtin_nontemporal_load(q + 2),
+                       __builtin_nontemporal_load(q + 3));
+}
+
+__global__ __launch_bounds__(kArgmaxThreads) void accept_argmax_kernel(
+    const float *__restrict__ logits, int T, int V, int seg_len, int splits,
+    const int32_t *__restrict__ n_nodes, ArgPart *__restrict__ part)
+{
+    __shared__ float s_v[kArgmaxThreads / 64];
+    __shared__ int s_i[kArgmaxThreads / 64];
+    const int tid = threadIdx.x;
+    const int seg = blockIdx.x, i = blockIdx.y, seq = blockIdx.z;
+    if (i > n_nodes[seq]) return;  // padding row: never read, the walk ignores its partial
+    const size_t rowi = (size_t)seq * T + i;
+    const int start = seg * seg_len;
+    const int n = min(seg_len, V - start);
+    const float *p = logits + rowi * (size_t)V + start;
+
+    float bv = -INFINITY;
+    int bi = 0x7FFFFFFF;
+    int head = (int)((4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
+    if (head > n) head = n;
+    if (tid < head) {
+        bv = p[tid];
+        bi = start + tid;
+    }
+    const int nvec = (n - head) >> 2;
+    const float4 *pv = reinterpret_cast<const float4 *>(p + head);
+    // eight independent 16-byte loads in flight per thread and iteration: about 128 KB per compute
+    // unit, what it takes to cover the HBM latency at full bandwidth
+    constexpr int kInFlight = 8;
+    for (int j0 = tid; j0 < nvec; j0 += kInFlight * kArgmaxThreads) {
+        float4 x[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int j = j0 + u * kArgmaxThreads;
+            x[u] = j < nvec ? load_streamed(pv + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        }
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int ia = start + head + 4 * (j0 + u * kArgmaxThreads);
+            if (x[u].x > bv) { bv = x[u].x; bi = ia; }
+            if (x[u].y > bv) { bv = x[u].y; bi = ia + 1; }
+            if (x[u].z > bv) { bv = x[u].z; bi = ia + 2; }
+            if (x[u].w > bv) { bv = x[u].w; bi = ia + 3; }
+        }
+    }
+    const int tail0 = head + 4 * nvec;
+    if (tid < n - tail0) {
+        const float x = p[tail0 + tid];
+        if (x > bv) { bv = x; bi = start + tail0 + tid; }
+    }
+    workgroup_best(bv, bi, s_v, s_i);
+    if (tid == 0) part[rowi * splits + seg] = ArgPart{bv, bi};
+}
+
+// The sampled scan, bound by the vector ALUs: the hash of an element is four 32-bit multiplies, a
+// quarter-rate instruction each, and its key two logarithms more.  Most elements are settled by their hash:
+// the noise is bounded by g = -ln(-ln u) <= -ln(1 - u), so an element can reach a key wb already found in the
+// row only if 1 - u <= exp(logit / tau - wb), a comparison of the hash with a threshold that is formed
+// once for the four elements of a load, from the largest of them, and then for the few that pass.  wb is
+// the best key of the whole workgroup (in LDS) and starts at a lower bound from the first load's hashes.
+// Measured (scan alone, tau = 0.8): 257 rows of 151936 47.3 -> 37.0 us, 258 rows (two trees) 48.9 -> 39.4, 17 rows 10.9 -> 7.6, 65 rows of 32003 9.0 -> 7.6; before,
+// every wave pruned against its own best with a bound a factor of two wide, and took its whole first round
+// of 32 elements a lane in full.  Four rows to a workgroup, sharing the half of the hash that does not
+// depend on the row, was slower than one (38 us against 36): fewer, longer-lived workgroups.  A greedy scan of
+// the same bytes takes 25 us.
+__global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
+    const float *__restrict__ logits, int T, int V, int seg_len, int splits,
+    const int32_t *__restrict__ n_nodes, ArgPart *__restrict__ part, SampleArgs sa)
+{
+    constexpr int kInFlight = 1;
+    __shared__ float s_v[kArgmaxThreads / 64];
+    __shared__ int s_i[kArgmaxThreads / 64];
+    __shared__ uint32_t s_best;  // a lower bound on the row's best key, order-preserving
+    const int tid = threadIdx.x;
+    const int seg = blockIdx.x, i = blockIdx.y, seq = blockIdx.z;
+    if (i > n_nodes[seq]) return;  // padding row: never read, the walk ignores its partial
+    const size_t rowi = (size_t)seq * T + i;
+    const uint32_t row_term = 0x9E3779B9u * (uint32_t)rowi + sa.seed_hi;
+    const int start = seg * seg_len;
+    const int n = min(seg_len, V - start);
+    const float *p = logits + rowi * (size_t)V + start;
+    int head = (int)((4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
+    if (head > n) head = n;
+    const int nvec = (n - head) >> 2, tail0 = head + 4 * nvec;
+    const float4 *pv = reinterpret_cast<const float4 *>(p + head);
+    auto hash = [&](int id) { return sample_mix(sample_mix((uint32_t)id ^ sa.seed_lo) + row_term); };
+
+    float4 x[kInFlight];
+    auto load = [&](int j0) {
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int j = j0 + u * kArgmaxThreads;
+            x[u] = j < nvec ? load_streamed(pv + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
+        }
+    };
+    load(tid);
+    if (tid == 0) s_best = 0u;
+    float bv = -INFINITY;
+    int bi = 0x7FFFFFFF;
+    // the scalar elements in front of and behind the 16-byte loads
+    if (tid < head) arg_update(bv, bi, sample_key(p[tid], hash(start + tid), sa), start + tid);
+    if (tid < n - tail0) arg_update(bv, bi, sample_key(p[tail0 + tid], hash(start + tail0 + tid), sa), start + tail0 + tid);
+    __syncthreads();
+    {
+        // for u >= 1/2, -ln u <= 2 ln 2 (1 - u), so g >= -ln(1.387 (1 - u))
+        const float xe[4] = {x[0].x, x[0].y, x[0].z, x[0].w};
+        float low = -INFINITY;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t h = hash(start + head + 4 * tid + e);
+            const float g = -0.693147f * (__builtin_amdgcn_logf((float)(~h) + 256.0f) - 32.0f) - 0.33f;
+            low = fmaxf(low, (h >> 31) ? fmaf(xe[e], sa.inv_tau, g) : -INFINITY);
+        }
+        low = wave_max_f32(low);
+        low -= fabsf(low) * 1e-6f;
+        if ((tid & 63) == 0 && low > -INFINITY) atomicMax(&s_best, float_key(low));
+    }
+    __syncthreads();
+    const float scale = sa.inv_tau * 1.44269504f;
+    // (the loop is uniform over a wave: the wave maximum below wants all its lanes in every round)
+    for (int jb = tid & ~63; jb < nvec; jb += kInFlight * kArgmaxThreads) {
+        const int j0 = jb + (tid & 63);
+        float4 c[kInFlight];
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) c[u] = x[u];
+        load(j0 + kInFlight * kArgmaxThreads);
+        // (another wave's key may or may not be there yet: any of them will do)
+        const uint32_t best = __hip_atomic_load(&s_best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        // With k = h >> 8, 2^32 (1 - u) = 2^32 - 256 k - 128 >= ~h - 127: only an element with
+        // ~h <= 2^32 exp(x / tau - wb) + 127 can matter.  (The margin covers the rounding of keys and threshold.)
+        const float wb = key_float(best) * 1.44269504f, bias = best ? 32.003f + (4e-7f * fabsf(wb) - wb) : INFINITY;
+        auto limit = [&](float v) {
+            const float t = __builtin_amdgcn_exp2f(fminf(fmaf(v, scale, bias), 32.0f));
+            return t < 4294960000.0f ? ~(uint32_t)(t + 129.0f) : 0u;
+        };
+#pragma unroll
+        for (int u = 0; u < kInFlight; ++u) {
+            const int j = j0 + u * kArgmaxThreads, ia = start + head + 4 * j;
+            uint32_t h[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = hash(ia + e);
+            const bool need = j < nvec && max(max(h[0], h[1]), max(h[2], h[3])) >=
+                                              limit(fmaxf(fmaxf(c[u].x, c[u].y), fmaxf(c[u].z, c[u].w)));
+            if (__builtin_amdgcn_ballot_w64(need) == 0ull) continue;
+            const float xe[4] = {c[u].x, c[u].y, c[u].z, c[u].w};
+            const float before = bv;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool this_one = need && h[e] >= limit(xe[e]);
+                if (__builtin_amdgcn_ballot_w64(this_one) == 0ull) continue;
+                const float k = sample_key(xe[e], h[e], sa);
+                if (this_one && k > bv) {
+                    bv = k;
+                    bi = ia + e;
+                }
+            }
+            if (__builtin_amdgcn_ballot_w64(bv > before) != 0ull) {
+                const float wmax = wave_max_f32(bv);
+                if ((tid & 63) == 0) atomicMax(&s_best, float_key(wmax));
+            }
+        }
+    }
+    workgroup_best(bv, bi, s_v, s_i);
+    if (tid == 0) part[rowi * splits + seg] = ArgPart{bv, bi};
+}
+
+// One workgroup per sequence, `lanes` (a power of two) per row.
+constexpr int kWalkMaxThreads = 1024;
+__global__ __launch_bounds__(kWalkMaxThreads) void accept_walk_kernel(
+    const ArgPart *__restrict__ part, int T, int splits, int lanes, int B, const int32_t *__restrict__ tokens,
     const int32_t *__restrict__ parent, const int32_t *__restrict__ depth,
     const int32_t *__restrict__ n_nodes, int32_t *__restrict__ path,
     int32_t *__restrict__ n_accepted, int32_t *__restrict__ bonus_token,
@@ -219,46 +293,43 @@ __global__ __launch_bounds__(kWalkThreads) void accept_walk_kernel(
     __shared__ int s_dep[DDTREE_MAX_N + 1];
     __shared__ int s_path[DDTREE_MAX_B + 1];
     __shared__ int s_len;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, threads = blockDim.x;
     const int seq = blockIdx.x;
     const int n = n_nodes[seq];
     const size_t base = (size_t)seq * T;
-    for (int i = tid; i < T; i += kWalkThreads) {
+    const int sub = tid & (lanes - 1), rows = threads / lanes;
+    constexpr int kPer = 8;  // partial results of a lane requested together
+    for (int i = tid / lanes; i - tid / lanes < T; i += rows) {  // (uniform: the lanes of a row stay together)
         // Everything a row needs is requested before the node count is looked at, so that its
-        // arrival and theirs overlap: the first eight partial results of the row (padding rows
-        // have none written: what is read there is never used), its token, parent and depth.
-        const ArgPart *pp = part + (base + i) * splits;
-        ArgPart a[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) a[u] = u < splits ? pp[u] : ArgPart{-INFINITY, -1};
-        const int tk = tokens[base + i], pr = parent[base + i], dp = depth[base + i];
-        const bool in_tree = i <= n;
-        int post = -1;
+        // arrival and theirs overlap: its partial results (padding rows have none written: what is
+        // read there is never used), its token, parent and depth.
+        const bool on = i < T;
+        const ArgPart *pp = part + (base + (on ? i : 0)) * splits;
         float bv = -INFINITY;
-        for (int s0 = 0; s0 < splits; s0 += 8) {
-            if (s0 > 0) {
+        int bi = 0x7FFFFFFF;
+        ArgPart a[kPer];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) a[u] = s0 + u < splits ? pp[s0 + u] : ArgPart{-INFINITY, -1};
-            }
+        for (int u = 0; u < kPer; ++u) a[u] = sub + u * lanes < splits ? pp[sub + u * lanes] : ArgPart{-INFINITY, 0x7FFFFFFF};
+        int tk = -1, pr = -1, dp = 0;
+        if (on && sub == 0) tk = tokens[base + i], pr = parent[base + i], dp = depth[base + i];
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
-                if (s0 + u < splits && (post < 0 || a[u].val > bv)) {
-                    // later segments hold higher ids: strict > keeps the first maximum
-                    bv = a[u].val;
-                    post = a[u].idx;
-                }
+        for (int u = 0; u < kPer; ++u) arg_update(bv, bi, a[u].val, a[u].idx);
+        for (int q = sub + kPer * lanes; q < splits; q += lanes) arg_update(bv, bi, pp[q].val, pp[q].idx);
+        for (int d = lanes >> 1; d >= 1; d >>= 1) arg_update(bv, bi, __shfl_xor(bv, d, 64), __shfl_xor(bi, d, 64));
+        if (on && sub == 0) {
+            const bool in_tree = i <= n;
+            const int post = in_tree ? bi : -1;
+            s_post[i] = post;
+            s_tok[i] = in_tree ? tk : -1;
+            s_par[i] = in_tree ? pr : -1;
+            s_dep[i] = dp;
+            if (posterior) posterior[base + i] = post;
         }
-        if (!in_tree) post = -1;
-        s_post[i] = post;
-        s_tok[i] = in_tree ? tk : -1;
-        s_par[i] = in_tree ? pr : -1;
-        s_dep[i] = dp;
-        if (posterior) posterior[base + i] = post;
     }
     if (tid <= B) s_path[tid] = tid == 0 ? 0 : -1;
     if (tid == 0) s_len = 0;
     __syncthreads();
-    for (int i = 1 + tid; i <= n; i += kWalkThreads) {
+    for (int i = 1 + tid; i <= n; i += threads) {
         bool ok = true;
         int j = i;
         while (j > 0 && ok) {
@@ -344,17 +415,21 @@ static int accept_impl(const float *target_logits, int batch, int T, int V, cons
     if (batch < 1 || batch > DDTREE_MAX_BATCH || T < 2 || T > DDTREE_MAX_N + 1 || V < 1 || B < 1 ||
         B > DDTREE_MAX_B)
         return DDTREE_ERR_ARG;
-    AcceptPlan p = accept_plan(batch, T, V, sample);
+    AcceptPlan p = accept_plan(batch, T, V);
     if (!ws_ok(workspace, workspace_bytes, p.bytes)) return DDTREE_ERR_WORKSPACE;
     ArgPart *part = reinterpret_cast<ArgPart *>(static_cast<char *>(workspace) + p.part_off);
     hipStream_t st = as_stream(stream);
     if (sample)
-        DDT_LAUNCH(DDTREE_KERNEL_ACCEPT_ARGMAX, st, accept_argmax_kernel<true>, dim3(p.splits, T, batch),
-                   dim3(kArgmaxThreads), 0, st, target_logits, T, V, p.seg_len, p.splits, n_nodes, part, sa);
+        DDT_LAUNCH(DDTREE_KERNEL_ACCEPT_ARGMAX, st, accept_sample_kernel, dim3(p.splits, T, batch), dim3(kArgmaxThreads), 0, st,
+                   target_logits, T, V, p.seg_len, p.splits, n_nodes, part, sa);
     else
-        DDT_LAUNCH(DDTREE_KERNEL_ACCEPT_ARGMAX, st, accept_argmax_kernel<false>, dim3(p.splits, T, batch),
-                   dim3(kArgmaxThreads), 0, st, target_logits, T, V, p.seg_len, p.splits, n_nodes, part, sa);
-    DDT_LAUNCH(DDTREE_KERNEL_ACCEPT_WALK, st, accept_walk_kernel, dim3(batch), dim3(kWalkThreads), 0, st, part, T, p.splits,
+        DDT_LAUNCH(DDTREE_KERNEL_ACCEPT_ARGMAX, st, accept_argmax_kernel, dim3(p.splits, T, batch), dim3(kArgmaxThreads), 0, st,
+                   target_logits, T, V, p.seg_len, p.splits, n_nodes, part);
+    // as many lanes per row as there are partial results, within one workgroup; every row at once (T = 1025: but one)
+    int lanes = 1;
+    while (lanes < 64 && lanes < p.splits && 2 * lanes * T <= kWalkMaxThreads) lanes *= 2;
+    const int threads = std::min(kWalkMaxThreads, std::max(64, (lanes * T + 63) / 64 * 64));
+    DDT_LAUNCH(DDTREE_KERNEL_ACCEPT_WALK, st, accept_walk_kernel, dim3(batch), dim3(threads), 0, st, part, T, p.splits, lanes,
                        B, tokens, parent, depth, n_nodes, path, n_accepted, bonus_token, posterior);
     return launch_status();
 }
@@ -382,7 +457,7 @@ extern "C" int ddtree_accept_noalloc(const float *target_logits, int batch, int 
         B > DDTREE_MAX_B)
         return DDTREE_ERR_ARG;
     // the partials of this shape must fit the static array (nothing here can grow it)
-    if (accept_plan(batch, T, V, false).bytes > kNoAllocScratchBytes) return DDTREE_ERR_WORKSPACE;
+    if (accept_plan(batch, T, V).bytes > kNoAllocScratchBytes) return DDTREE_ERR_WORKSPACE;
     void *ws = nullptr;
     const int rc = noalloc_scratch(&ws);
     if (rc != DDTREE_OK) return rc;

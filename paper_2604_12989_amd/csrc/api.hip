@@ -151,12 +151,11 @@ extern "C" int ddtree_selftest_host(void)
     // accept: segments tile the row in multiples of four, scratch holds one partial per segment
     for (int V : Vs)
         for (int T : {2, 17, 65, 257, 513, 1025})
-            for (int batch : {1, 16, 64})
-                for (int sampled = 0; sampled < 2; ++sampled) {
-                    const AcceptPlan p = accept_plan(batch, T, V, sampled != 0);
-                    if (p.seg_len % 4 != 0 || p.seg_len < 1 || p.splits < 1) return 10021;
-                    if ((long long)(p.splits - 1) * p.seg_len >= V || (long long)p.splits * p.seg_len < V) return 10022;
-                    if (p.bytes < (size_t)batch * T * p.splits * 8 || (p.bytes & 255u)) return 10023;
-                }
+            for (int batch : {1, 16, 64}) {
+                const AcceptPlan p = accept_plan(batch, T, V);
+                if (p.seg_len % 4 != 0 || p.seg_len < 1 || p.splits < 1) return 10021;
+                if ((long long)(p.splits - 1) * p.seg_len >= V || (long long)p.splits * p.seg_len < V) return 10022;
+                if (p.bytes < (size_t)batch * T * p.splits * 8 || (p.bytes & 255u)) return 10023;
+            }
     return 0;
 }

@@ -63,7 +63,7 @@ struct AcceptPlan {
     int seg_len; // elements per segment (multiple of 4)
     size_t part_off, bytes;
 };
-AcceptPlan accept_plan(int batch, int T, int V, bool sampled = false);  // the greedy plan needs the larger scratch
+AcceptPlan accept_plan(int batch, int T, int V);
 
 // ---- optional event timing around kernel launches (see ddtree_profile_enable) ----
 struct Profiler {
