@@ -29,7 +29,7 @@
 // (row, tile), bit test per score.  Cache tiles carry no mask work at all.
 #include <algorithm>
 
-#include "attn_common.hpp"
+#include "attn_wave_rows.hpp"
 
 namespace ddt {
 
@@ -80,6 +80,19 @@ __device__ __forceinline__ void lds_wait_all(u32x4 (&k)[8], u32x2 (&v)[2][4][2])
 // than that and the workgroup redoes its key range with the true row maxima as references.
 constexpr float kSumLimit = 0x1p72f;
 
+// What attn_wave_rows takes for a tail block.
+struct AttnTailArgs {
+    const uint16_t *q, *k_cache, *v_cache, *k_tree, *v_tree;
+    const uint64_t *mask;
+    uint16_t *out, *part;
+    float2 *lse;
+    int32_t T, Hq, Hkv, group_size;
+    uint32_t g_magic;
+    float scale_log2e;
+};
+static_assert(WaveShape<kHD, 1>::threads == kAttnThreads && WaveShape<kHD, 1>::lds_bytes <= kAttnLdsBytes,
+              "a tail block runs in a workgroup of this kernel");
+
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
                       const uint16_t *__restrict__ v_cache, const uint16_t *__restrict__ k_tree,
@@ -107,18 +120,31 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     // 8 runs of consecutive work items, run x being what XCD x executes, and consecutive
     // work items are the row tiles of one (group, key range): the row tiles that read the same K
     // and V rows share an L2, and those rows leave HBM once.  The host cuts the runs so that
-    // each holds an eighth of the keys to visit (sequences of a ragged batch differ in length)
+    // each holds an eighth of the work (sequences of a ragged batch differ in length)
     // and lists the sequences longest first, so that an XCD's long work items start early.
-    const int wid = args.xcd_start[(int)blockIdx.x & 7] + ((int)blockIdx.x >> 3);
-    if (wid >= args.xcd_start[((int)blockIdx.x & 7) + 1]) return;
-    const AttnMainItem item = attn_main_item(args, wid, T);
+    // The blocks of 32 rows left beside the whole tiles come last: eight waves that each walk keys of
+    // their own take a quarter of the time that a tile with one wave at work took (0.9 us per 64 keys and
+    // waiting for most of it), and fill what the whole tiles leave.  Measured (attention and merge, 32 query and 8
+    // KV heads): 1025 nodes x 8192 keys 194 -> 158 us (1024 nodes: 156); 16 sequences
+    // of 129 x 4355 243 -> 213 (128 nodes: 149; the tail blocks read the keys from HBM once more); dealt out
+    // between the whole tiles of their own keys instead 239: whole tiles then start late and end last.
+    AttnMainItem item;
+    if (!attn_main_item(args, (int)blockIdx.x, T, item)) return;
+    if (item.tail) {
+        const AttnTailArgs tail{q, k_cache, v_cache, k_tree, v_tree, mask, out, part, lse, T, Hq, Hkv,
+                                args.group_size, args.g_magic, scale_log2e};
+        const AttnWaveItem rows{item.seq, item.hk, 0, item.split, item.splits, item.ranges, item.first_slot, item.kv_start,
+                                item.kv_len, item.m0, item.m_end, item.n_cache, item.t_begin, item.t_end};
+        attn_wave_rows<kHD, 1>(tail, rows);
+        return;
+    }
     const int seq = item.seq, hk = item.hk, split = item.split, splits = item.splits;
     const int part_splits = item.ranges > 1 ? item.ranges : 0, first_slot = item.first_slot;
     const int L0 = item.kv_start, L = item.kv_len;
     const int G = args.group_size;
     const int W = (T + 63) >> 6;
     const int m0 = item.m0, m_end = item.m_end;  // this tile's rows: wave w owns block w of 32
-    const int n_cache_tiles = item.n_cache_tiles;
+    const int n_cache_tiles = item.n_cache;
     const int t_begin = item.t_begin, t_end = item.t_end;
     const bool wave_active = m0 + wave * 32 < m_end;
 

@@ -30,7 +30,7 @@ constexpr int kSK = 32;   // attn_wave_kernel: keys per sub-tile
 // ---- how a call is cut into workgroups, and the layout of its scratch (attn_plan.hip) ----
 struct AttnSeqPlan {
     int32_t splits;       // key ranges of a row group (attn_wave_kernel) or of a whole row tile
-    int32_t tail_splits;  // of the tail tile (attn_mfma_kernel, uneven form)
+    int32_t tail_splits;  // of a tail block (attn_mfma_kernel, uneven form)
     int32_t ranges;       // partial results of a row: the larger of the two; 1: none, the output is direct
     int32_t first_slot;   // the first of its partial results
 };
@@ -45,7 +45,7 @@ struct AttnPlan {
     int row_blocks, groups, rows_per_group;
     // attn_mfma_kernel: the query rows of one (sequence, kv head) pair, in blocks of 32.  Even form: dealt
     // as evenly as possible to n_tiles row tiles of at most 8 blocks, tile i holds blk_base +
-    // (i < blk_extra).  Uneven form: n_tiles - 1 tiles of 8 blocks and a tail tile of blk_extra.
+    // (i < blk_extra).  Uneven form: n_tiles tiles of 8 blocks and blk_extra tail blocks on their own.
     int n_tiles, blk_base, blk_extra;
     bool uneven;
 };
@@ -114,17 +114,19 @@ __host__ __device__ __forceinline__ bool attn_wave_item(const AttnWaveArgs &args
 
 // ---- attn_mfma_kernel ----
 struct AttnMainSeq {
-    int32_t seq, kv_start, kv_len, first_item;  // sequences longest first; their first work item
+    int32_t seq, kv_start, kv_len;       // sequences longest first
+    int32_t first_item, first_tail;      // their first work item among the whole tiles', among the tail blocks'
     int32_t splits, tail_splits, first_slot, ranges;
-    // reciprocals of the work items per kv head, of splits and of tail_splits
-    uint32_t per_head_magic, splits_magic, tail_magic, pad;
+    // reciprocals of the work items per kv head (whole tiles', tail blocks'), of splits and of tail_splits
+    uint32_t head_magic, tail_head_magic, splits_magic, tail_magic;
 };
 struct AttnMainArgs {
-    // work items xcd_start[x] .. xcd_start[x + 1] - 1 are what XCD x executes
-    int32_t xcd_start[9];
+    // XCD x executes the whole tiles' work items xcd_start[x] .. xcd_start[x + 1] - 1, then the tail
+    // blocks' tail_start[x] .. tail_start[x + 1] - 1
+    int32_t xcd_start[9], tail_start[9];
     int32_t batch, n_tiles, blk_base, blk_extra, uneven;
     int32_t group_size;                  // G = Hq / Hkv
-    uint32_t g_magic, main_tiles_magic;  // reciprocals of G and of the number of whole row tiles
+    uint32_t g_magic, tiles_magic, extra_magic;  // reciprocals of G, n_tiles and blk_extra
     int32_t grid;
     AttnMainSeq seq[DDTREE_MAX_BATCH];
 };
@@ -132,46 +134,51 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
                     int T, int Hq, int Hkv);
 
 struct AttnMainItem {
-    int seq, hk, tile, split, splits, ranges, first_slot, kv_start, kv_len;
-    int m0, m_end;                      // query rows
-    int n_cache_tiles, t_begin, t_end;  // cache tiles; the key tiles of the key range
+    int seq, hk, split, splits, ranges, first_slot, kv_start, kv_len;
+    bool tail;                    // a tail block: sub-tiles of kSK keys, otherwise tiles of kKT
+    int m0, m_end;                // query rows
+    int n_cache, t_begin, t_end;  // (sub-)tiles of the cache; those of the key range
 };
-// Work items: sequence by sequence, kv head by kv head, those of the whole row tiles (row tile fastest
-// within a key range), then the key ranges of the tail tile.
-__host__ __device__ __forceinline__ AttnMainItem attn_main_item(const AttnMainArgs &args, int wid, int T)
+// What workgroup `b` works on; false: nothing.  Work items of either kind: sequence by sequence, kv head by
+// kv head, key range by key range, row tile (tail block) fastest.
+__host__ __device__ __forceinline__ bool attn_main_item(const AttnMainArgs &args, int b, int T, AttnMainItem &w)
 {
-    AttnMainItem w;
+    const int x = b & 7, n_main = args.xcd_start[x + 1] - args.xcd_start[x];
+    int wid = b >> 3;
+    w.tail = wid >= n_main;
+    wid += w.tail ? args.tail_start[x] - n_main : args.xcd_start[x];
+    if (w.tail && wid >= args.tail_start[x + 1]) return false;
     int pos = 0;
 #pragma unroll
     for (int s = 32; s >= 1; s >>= 1)
-        if (pos + s < args.batch && args.seq[pos + s].first_item <= wid) pos += s;
+        if (pos + s < args.batch && (w.tail ? args.seq[pos + s].first_tail : args.seq[pos + s].first_item) <= wid) pos += s;
     const AttnMainSeq &e = args.seq[pos];
-    const int main_tiles = args.n_tiles - args.uneven;
-    const int per_head = main_tiles * e.splits + e.tail_splits;
-    const int local = wid - e.first_item;
-    w.hk = div_by(local, per_head, e.per_head_magic);
+    const int local = wid - (w.tail ? e.first_tail : e.first_item);
+    const int tiles = w.tail ? args.blk_extra : args.n_tiles;
+    const int per_head = tiles * (w.tail ? e.tail_splits : e.splits);
+    w.hk = div_by(local, per_head, w.tail ? e.tail_head_magic : e.head_magic);
     const int wg = local - w.hk * per_head;
-    const bool tail = wg >= main_tiles * e.splits;
-    const int wg_split = div_by(wg, main_tiles, args.main_tiles_magic);
-    w.tile = tail ? main_tiles : wg - wg_split * main_tiles;
-    w.split = tail ? wg - main_tiles * e.splits : wg_split;
-    w.splits = tail ? e.tail_splits : e.splits;
+    w.split = div_by(wg, tiles, w.tail ? args.extra_magic : args.tiles_magic);
+    const int tile = wg - w.split * tiles;
+    w.splits = w.tail ? e.tail_splits : e.splits;
     w.seq = e.seq, w.kv_start = e.kv_start, w.kv_len = e.kv_len, w.ranges = e.ranges, w.first_slot = e.first_slot;
     const int M = T * args.group_size;
-    const int first_blk = args.uneven ? w.tile * 8 : w.tile * args.blk_base + (w.tile < args.blk_extra ? w.tile : args.blk_extra);
-    const int n_blk = args.uneven ? (tail ? args.blk_extra : 8) : args.blk_base + (w.tile < args.blk_extra ? 1 : 0);
+    const int extra = args.uneven ? 0 : args.blk_extra;
+    const int first_blk = w.tail ? args.n_tiles * 8 + tile : tile * args.blk_base + (tile < extra ? tile : extra);
+    const int n_blk = w.tail ? 1 : args.blk_base + (tile < extra ? 1 : 0);
     w.m0 = first_blk * 32;
     w.m_end = (first_blk + n_blk) * 32 < M ? (first_blk + n_blk) * 32 : M;
     const int last_node = div_by(w.m_end - 1, args.group_size, args.g_magic);
-    w.n_cache_tiles = (w.kv_len + kKT - 1) / kKT;
-    const int nt = w.n_cache_tiles + last_node / kKT + 1;
+    const int keys = w.tail ? kSK : kKT;
+    w.n_cache = (int)(((unsigned)w.kv_len + keys - 1) / (unsigned)keys);
+    const int nt = w.n_cache + last_node / keys + 1;
     // key ranges rounded up, so that a surplus tile goes to the early ranges: the last range holds
     // the tree tiles, which carry the mask work on top
-    // (nt < 2^26 key tiles and at most 32 key ranges: 32-bit arithmetic is exact)
-    const uint32_t magic = tail ? e.tail_magic : e.splits_magic;
+    // (nt * splits < 2^30 wherever a key range is cut: 32-bit arithmetic is exact)
+    const uint32_t magic = w.tail ? e.tail_magic : e.splits_magic;
     w.t_begin = div_by(nt * w.split + w.splits - 1, w.splits, magic);
     w.t_end = div_by(nt * (w.split + 1) + w.splits - 1, w.splits, magic);
-    return w;
+    return true;
 }
 
 #if defined(__HIPCC__)

@@ -120,8 +120,8 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
 }
 
 // attn_mfma_kernel.  Even form: row tiles of the same height.  Uneven form, where the blocks of 32 rows are
-// a few more than whole tiles of 8 (T = 257 with four heads per KV head: 33 blocks): whole tiles plus one
-// small tail tile with key ranges of its own.
+// a few more than whole tiles of 8 (T = 257 with four heads per KV head: 33 blocks): whole tiles, and each
+// block left as a work item of its own with key ranges of its own (attn_wave_rows).
 static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_len, long long slot_room)
 {
     const int nblk = up(T * (Hq / Hkv), 32), full = nblk / 8, rem = nblk % 8;
@@ -129,12 +129,17 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
     int32_t order[DDTREE_MAX_BATCH];
     longest_first(order, kv_len, batch);
     const int nt_max = up(kv_len[order[0]], kKT) + tree;
+    const int sub_max = up(kv_len[order[0]], kSK) + up(T, kSK);
     Sized sized[DDTREE_MAX_BATCH];
     long long key_tiles = 0;
     for (int i = 0; i < batch; ++i) key_tiles += up(kv_len[i], kKT) + tree;
     const double hbm_us = (double)key_tiles * Hkv * (kKT * 4.0 * kHD) / 5.0e6;
-    // Measured (us): a workgroup's fixed cost, a key tile, and a key tile of a tail tile against that.
-    const double fix = 11.0, tile = 1.52, c_tail = 0.6;
+    // Measured (us): a workgroup's fixed cost and a key tile (below three quarters of the compute units at work,
+    // and with all of them, where the chip lowers its clock: 1.92 over 131 key tiles); for a tail block, and a
+    // step of eight sub-tiles beside them (1.2 alone, keys from the L2).  With 513 nodes x 32768 keys, four key
+    // ranges and the tail blocks in a second round (the sum of times says 246 us) took 340 where three and
+    // everything in one round take 307: the few workgroups of that second round wait for HBM.
+    const double fix = 11.0, tile_few = 1.52, tile_all = 1.9, tail_fix = 7.0, tail_step = 2.4;
     const long long cap = std::min(slot_room, main_slot_cap(batch, T, Hq, Hkv));
     AttnPlan best{};
     best.cost = 1e30;
@@ -145,37 +150,60 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
         for (int s = 1; s <= 32 && (s == 1 || s * 2 <= nt_max); ++s) {
             const int c = up(nt_max, s);
             if (s > 1 && up(nt_max, s - 1) == c) continue;
-            // tail ranges: as long as a whole tile's, a little longer or a little shorter
-            const int t0 = uneven ? std::max(1, (int)(c_tail * nt_max / c)) : 0;
-            for (int t = t0; t <= (uneven ? std::min(t0 + 1, 32) : 0); ++t) {
-                const int ct = uneven ? up(nt_max, t) : 0;
-                long long items = 0, slots = 0;
+            // ranges of a tail block: those that take as long as a whole tile's, and more of them in turn
+            const int t0 = uneven ? std::min(32, std::max(1, (int)(tail_step * up(sub_max, 8) / (fix - tail_fix + tile_few * c)))) : 0;
+            for (int t = t0; t <= std::min(8 * t0, 32); t *= 2) {
+                if (t > 1 && (long long)t * sub_max >= (1ll << 30)) break;
+                const int ct = uneven ? up(sub_max, t) : 0;
+                long long items = 0, tails = 0, slots = 0;
                 for (int i = 0; i < batch; ++i) {
-                    const int nt = up(kv_len[order[i]], kKT) + tree, si = up(nt, c), ti = uneven ? up(nt, ct) : 0;
-                    items += tiles * si + ti;
-                    slots += std::max(si, ti);
-                    sized[i] = Sized{fix + tile * std::max((double)up(nt, si), ti ? c_tail * up(nt, ti) : 0.0),
-                                     (long long)(tiles * si + ti) * Hkv};
+                    const int si = up(up(kv_len[order[i]], kKT) + tree, c);
+                    items += sized[i].count = (long long)tiles * si * Hkv;
+                    slots += si;
+                }
+                const double tile = tile_few + (tile_all - tile_few) * std::min(1.0, std::max(0.0, (items - 192) / 64.0));
+                double sum = 0.0, tail_longest = 0.0;
+                for (int i = 0; i < batch; ++i) {
+                    const int nt = up(kv_len[order[i]], kKT) + tree, si = up(nt, c);
+                    sized[i].cost = fix + tile * up(nt, si);
+                    sum += sized[i].cost * sized[i].count;
+                    if (!uneven) continue;
+                    const int sub = up(kv_len[order[i]], kSK) + up(T, kSK), ti = up(sub, ct);
+                    const double each = tail_fix + tail_step * up(up(sub, ti), 8);
+                    sum += each * rem * ti * Hkv;
+                    tail_longest = std::max(tail_longest, each);
+                    tails += (long long)rem * ti * Hkv;
+                    slots += std::max(0, ti - si);
                 }
                 const bool cut = s > 1 || t > 1;
                 if (cut && slots > cap) break;
-                const double cost = std::max(rounds_us(sized, batch), hbm_us) + (cut ? merge_us(slots, T, Hq, kHD) : 0.0);
+                // the whole tiles' items as if alone; the tail blocks' beside them, or where they end
+                double work = rounds_us(sized, batch);
+                if (items + tails <= 256)
+                    work = std::max(work, tail_longest);
+                else if (items <= 256)
+                    work += tails > 0 ? 1.5 * tail_longest * up((int)tails, 256) : 0.0;
+                else
+                    work = std::max(work, sum / 256 + 0.5 * tail_longest);
+                const double cost = std::max(work, hbm_us) + (cut ? merge_us(slots, T, Hq, kHD) : 0.0);
                 if (cost < best.cost) {
                     best.cost = cost;
                     best.uneven = uneven != 0;
                     best_c = c, best_ct = ct;
-                    best.items = items * Hkv;
+                    best.items = items + tails;
                 }
+                if (!uneven) break;
             }
         }
     }
-    best.n_tiles = best.uneven ? full + 1 : up(nblk, 8);
+    best.n_tiles = best.uneven ? full : up(nblk, 8);
     best.blk_base = best.uneven ? 8 : nblk / best.n_tiles;
     best.blk_extra = best.uneven ? rem : nblk % best.n_tiles;
     int first = 0;
     bool cut = false;
     for (int i = 0; i < batch; ++i) {
-        const int nt = up(kv_len[i], kKT) + tree, si = up(nt, best_c), ti = best.uneven ? up(nt, best_ct) : 0;
+        const int si = up(up(kv_len[i], kKT) + tree, best_c);
+        const int ti = best.uneven ? up(up(kv_len[i], kSK) + up(T, kSK), best_ct) : 0;
         best.seq[i] = AttnSeqPlan{si, ti, std::max(si, ti), first};
         first += best.seq[i].ranges;
         cut = cut || best.seq[i].ranges > 1;
@@ -260,56 +288,77 @@ bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_sta
 bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_start, const int32_t *kv_len, int batch,
                     int T, int Hq, int Hkv)
 {
-    const int G = Hq / Hkv, main_tiles = p.n_tiles - (p.uneven ? 1 : 0);
+    const int G = Hq / Hkv, tails = p.uneven ? p.blk_extra : 0;
     args.batch = batch, args.n_tiles = p.n_tiles, args.blk_base = p.blk_base, args.blk_extra = p.blk_extra;
     args.uneven = p.uneven ? 1 : 0;
     args.group_size = G;
     args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
     int32_t order[DDTREE_MAX_BATCH];
     longest_first(order, kv_len, batch);
-    long long total = 0, per_head_max = 1;
-    double work = 0.0;
+    long long total = 0, tail_total = 0, per_head_max = 1;
     for (int i = 0; i < batch; ++i) {
         const int s = order[i];
         const AttnSeqPlan &q = p.seq[s];
-        const long long per_head = (long long)main_tiles * q.splits + q.tail_splits;
-        const uint64_t nt = (uint64_t)(up(kv_len[s], kKT) + up(T, kKT));
-        args.seq[i] = AttnMainSeq{s, kv_start[s], kv_len[s], (int32_t)total, q.splits, q.tail_splits, q.first_slot, q.ranges,
+        const long long per_head = (long long)p.n_tiles * q.splits, per_tail = (long long)tails * q.tail_splits;
+        const uint64_t nt = (uint64_t)(up(kv_len[s], kKT) + up(T, kKT)), sub = (uint64_t)up(kv_len[s], kSK) + up(T, kSK);
+        args.seq[i] = AttnMainSeq{s, kv_start[s], kv_len[s], (int32_t)total, (int32_t)tail_total,
+                                  q.splits, q.tail_splits, q.first_slot, q.ranges,
                                   magic_of((uint64_t)per_head, (uint64_t)per_head * Hkv),
+                                  per_tail ? magic_of((uint64_t)per_tail, (uint64_t)per_tail * Hkv) : 0u,
                                   magic_of((uint64_t)q.splits, nt * q.splits + q.splits),
-                                  magic_of((uint64_t)q.tail_splits, nt * q.tail_splits + q.tail_splits), 0u};
+                                  per_tail ? magic_of((uint64_t)q.tail_splits, sub * q.tail_splits + q.tail_splits) : 0u};
         total += per_head * Hkv;
-        if (total > (1ll << 28)) return false;
-        per_head_max = std::max(per_head_max, per_head);
-        work += (double)nt * per_head / std::max(1, q.splits) * Hkv;
+        tail_total += per_tail * Hkv;
+        if (total + tail_total > (1ll << 28)) return false;
+        per_head_max = std::max(per_head_max, std::max(per_head, per_tail));
     }
-    args.main_tiles_magic = magic_of((uint64_t)main_tiles, (uint64_t)per_head_max);
+    args.tiles_magic = magic_of((uint64_t)p.n_tiles, (uint64_t)per_head_max);
+    args.extra_magic = tails ? magic_of((uint64_t)tails, (uint64_t)per_head_max) : 0u;
     // Consecutive work items run on the same XCD: the row tiles that read the same K and V rows share an
     // L2, and those rows leave HBM once.  In one round each XCD has an eighth of the items, at most one
-    // per compute unit; otherwise an eighth of the key tiles to visit.
-    args.xcd_start[0] = 0;
+    // per compute unit; otherwise an eighth of the work.
+    // The tail blocks' items: to compute units without a whole tile's where there are enough of those,
+    // otherwise an eighth of their work to each XCD.
+    args.xcd_start[0] = args.tail_start[0] = 0;
+    auto by_work = [&](int32_t *start, bool tail, long long all) {
+        // in key tiles (sub-tiles): those to visit, and seven for a workgroup's fixed cost
+        const int rows = tail ? tails : p.n_tiles, keys = tail ? kSK : kKT;
+        auto pieces = [&](int i) { return (long long)rows * (tail ? p.seq[order[i]].tail_splits : p.seq[order[i]].splits) * Hkv; };
+        auto cost = [&](int i) { return (double)(up(kv_len[order[i]], keys) + up(T, keys)) * rows * Hkv + 7.0 * pieces(i); };
+        double work = 0.0, done = 0.0;
+        for (int i = 0; i < batch; ++i) work += cost(i);
+        int x = 1;
+        for (int i = 0; i < batch; ++i) {
+            const double each = cost(i) / pieces(i);
+            for (; x < 8 && work * x / 8 < done + cost(i); ++x)
+                start[x] = (tail ? args.seq[i].first_tail : args.seq[i].first_item) +
+                           (int32_t)std::min<long long>(pieces(i), (long long)((work * x / 8 - done) / each + 0.5));
+            done += cost(i);
+        }
+        for (; x <= 8; ++x) start[x] = (int32_t)all;
+        start[8] = (int32_t)all;
+        for (x = 0; x < 8; ++x) start[x + 1] = std::max(start[x + 1], start[x]);
+    };
     if (total <= 256) {
         const int run = (int)((total + 7) / 8);
         for (int x = 1; x <= 8; ++x) args.xcd_start[x] = (int32_t)std::min<long long>(total, (long long)run * x);
     } else {
-        double done = 0.0;
-        int x = 1;
-        for (int i = 0; i < batch; ++i) {
-            const AttnSeqPlan &q = p.seq[order[i]];
-            const long long per_seq = ((long long)main_tiles * q.splits + q.tail_splits) * Hkv;
-            const double each = (double)(up(kv_len[order[i]], kKT) + up(T, kKT)) / std::max(1, q.splits);
-            for (; x < 8 && work * x / 8 < done + each * per_seq; ++x)
-                args.xcd_start[x] = args.seq[i].first_item + (int32_t)std::min<long long>(per_seq, (long long)((work * x / 8 - done) / each + 0.5));
-            done += each * per_seq;
+        by_work(args.xcd_start, false, total);
+    }
+    if (tail_total > 0 && total + tail_total > 256) {
+        by_work(args.tail_start, true, tail_total);
+    } else {
+        for (int x = 0; x < 8; ++x) {
+            int idle_behind = 0;  // compute units without an item on the XCDs that follow
+            for (int y = x + 1; y < 8; ++y) idle_behind += 32 - (args.xcd_start[y + 1] - args.xcd_start[y]);
+            const long long left = tail_total - args.tail_start[x];
+            const long long take = std::min<long long>(std::max((tail_total + 7) / 8, left - idle_behind), 32 - (args.xcd_start[x + 1] - args.xcd_start[x]));
+            args.tail_start[x + 1] = (int32_t)(args.tail_start[x] + std::min(left, take));
         }
-        for (; x < 8; ++x) args.xcd_start[x] = (int32_t)total;
-        args.xcd_start[8] = (int32_t)total;
     }
     int run_max = 0;
-    for (int x = 0; x < 8; ++x) {
-        args.xcd_start[x + 1] = std::max(args.xcd_start[x + 1], args.xcd_start[x]);
-        run_max = std::max(run_max, args.xcd_start[x + 1] - args.xcd_start[x]);
-    }
+    for (int x = 0; x < 8; ++x)
+        run_max = std::max(run_max, args.xcd_start[x + 1] - args.xcd_start[x] + args.tail_start[x + 1] - args.tail_start[x]);
     args.grid = run_max * 8;
     return true;
 }
@@ -405,13 +454,15 @@ int attn_selftest_host()
                 if (kind == 2) {
                     AttnMainArgs args;
                     if (!attn_main_args(args, p, kv_start, sh.len, sh.batch, sh.T, sh.Hq, sh.Hkv)) return 100 * si + 2;
+                    if (p.items <= 256 && args.grid > 256) return 100 * si + 3;  // one round stays one
                     for (int b = 0; b < args.grid; ++b) {
-                        const int wid = args.xcd_start[b & 7] + (b >> 3);
-                        if (wid >= args.xcd_start[(b & 7) + 1]) continue;
-                        const AttnMainItem w = attn_main_item(args, wid, sh.T);
+                        AttnMainItem w;
+                        if (!attn_main_item(args, b, sh.T, w)) continue;
                         if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits > w.ranges) return 100 * si + 3;
-                        items.push_back({w.seq, w.hk, w.m0, w.m_end, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, kKT,
-                                         w.n_cache_tiles + (w.m_end - 1) / (sh.Hq / sh.Hkv) / kKT + 1});
+                        const int keys = w.tail ? kSK : kKT;
+                        if (w.tail && w.m_end - w.m0 > 32) return 100 * si + 3;
+                        items.push_back({w.seq, w.hk, w.m0, w.m_end, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, keys,
+                                         w.n_cache + (w.m_end - 1) / (sh.Hq / sh.Hkv) / keys + 1});
                     }
                 } else {
                     AttnWaveArgs args;

@@ -30,7 +30,7 @@ def _tree_mask(rng, T, n=None):
     return oracle.ancestor_mask(par, n, T=T)
 
 
-def _check(seed, Ts, Ls, Hq, Hkv, D, n_pairs=40, edit=None, n_nodes=None):
+def _check(seed, Ts, Ls, Hq, Hkv, D, n_pairs=40, edit=None, n_nodes=None, also=()):
     """A ragged batch of equal T against the oracle on sampled (node, head) pairs, the corners among them."""
     rng = np.random.default_rng(seed)
     T, batch = Ts, len(Ls)
@@ -45,6 +45,7 @@ def _check(seed, Ts, Ls, Hq, Hkv, D, n_pairs=40, edit=None, n_nodes=None):
     for b in range(batch):
         pairs = np.stack([rng.integers(0, T, n_pairs), rng.integers(0, Hq, n_pairs)], axis=1).astype(np.int32)
         pairs[:4] = [[0, 0], [T - 1, Hq - 1], [0, Hq - 1], [T - 1, 0]]
+        pairs[4:4 + len(also)] = np.array(also, np.int32).reshape(-1, 2)
         ref = oracle.verify_attn(*parts[b], masks[b], pairs=pairs)
         worst = max(worst, gu.attn_err(got[b][pairs[:, 0], pairs[:, 1]], ref))
     assert worst < 1e-2, worst
@@ -64,6 +65,18 @@ def test_few_rows_edges(T, L, Hq, Hkv, D):
     (33, [900, 0, 31, 2500, 64], 12, 4, 128), (20, [40] * 9, 8, 8, 64)])
 def test_ragged_batches_with_key_ranges_of_their_own(T, Ls, Hq, Hkv, D):
     _check(300 + T, T, Ls, Hq, Hkv, D, n_pairs=24)
+
+
+@pytest.mark.parametrize("T,Ls,Hq,Hkv", [
+    (130, [4000], 32, 8), (257, [9000, 64], 16, 4),           # fewer key ranges than the whole tiles have
+    (1025, [700, 300], 16, 4), (1025, [8192], 32, 8),         # as many, and more
+    (96, [6000, 33], 32, 8), (265, [6000, 33], 32, 8), (101, [37, 3001, 900, 1700], 24, 8),  # several blocks
+    (257, [4096] * 5, 32, 8), (1025, [0, 0, 1], 32, 8)])      # uncut
+def test_blocks_left_beside_whole_row_tiles(T, Ls, Hq, Hkv):
+    """The last nodes' rows, which do not fill a tile of 256, take a path of their own."""
+    rng = np.random.default_rng(T)
+    last = [(T - 1 - i % min(T, 30), int(rng.integers(0, Hq))) for i in range(20)]
+    _check(700 + T, T, Ls, Hq, Hkv, 128, n_pairs=40, also=last)
 
 
 @pytest.mark.parametrize("T,L,Hq,Hkv,D", [(40, 1500, 8, 2, 64), (40, 1500, 8, 2, 128), (257, 4096, 32, 8, 64), (273, 5000, 32, 8, 128)])
