@@ -2,8 +2,8 @@
 // tree for the verifier (Section 4.4: token ids, depth as position id, ancestor-only mask).
 //
 // One workgroup per sequence; the pops are inherently serial (pop i+1 depends on the pushes of
-// pop i), so a single wavefront runs them and the other three wait at a barrier, then all
-// 256 threads write the outputs and the ancestor bitmask.
+// pop i), so a single wavefront runs them and the others wait at a barrier, then all
+// threads write the outputs and the ancestor bitmask.
 //
 // Frontier layout.  Algorithm 1's heap holds, at any time, exactly one candidate per node that
 // is already in the tree (root included): that node's next unused child rank.  Popping the
@@ -25,8 +25,6 @@
 #include <atomic>
 
 namespace ddt {
-
-constexpr int kBuildThreads = 256;
 
 __device__ __forceinline__ uint32_t pack_node(int parent, int rank, int depth)
 {
@@ -158,7 +156,8 @@ __device__ bool member_before(const float *m_score, const uint32_t *m_info, int 
     return da0 < db0;
 }
 
-// Exclusive prefix sum over the workgroup's kBuildThreads values; *total = their sum.
+// Exclusive prefix sum over the workgroup's NT values; *total = their sum.
+template <int NT>
 __device__ __forceinline__ int build_block_scan(int v, int *s_w, int *total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -167,7 +166,7 @@ __device__ __forceinline__ int build_block_scan(int v, int *s_w, int *total)
     __syncthreads();
     int base = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < kBuildThreads / 64; ++w) {
+    for (int w = 0; w < NT / 64; ++w) {
         const int x = s_w[w];
         base += w < wave ? x : 0;
         tot += x;
@@ -178,7 +177,8 @@ __device__ __forceinline__ int build_block_scan(int v, int *s_w, int *total)
 }
 
 // The same for two values at once; *a and *b are replaced by their exclusive prefixes.
-__device__ __forceinline__ void build_block_scan2(int *a, int *b, int (*s_w2)[kBuildThreads / 64],
+template <int NT>
+__device__ __forceinline__ void build_block_scan2(int *a, int *b, int (*s_w2)[NT / 64],
                                                   int *total_a, int *total_b)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -190,7 +190,7 @@ __device__ __forceinline__ void build_block_scan2(int *a, int *b, int (*s_w2)[kB
     __syncthreads();
     int base_a = 0, base_b = 0, ta = 0, tb = 0;
 #pragma unroll
-    for (int w = 0; w < kBuildThreads / 64; ++w) {
+    for (int w = 0; w < NT / 64; ++w) {
         const int xa = s_w2[0][w], xb = s_w2[1][w];
         base_a += w < wave ? xa : 0;
         base_b += w < wave ? xb : 0;
@@ -205,22 +205,23 @@ __device__ __forceinline__ void build_block_scan2(int *a, int *b, int (*s_w2)[kB
 }
 
 // Returns the number of nodes written to s_node / s_score (ids 1..n), or -1 after giving up.
+template <int NT>
 __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, LevelMem L,
                            uint32_t *s_node, float *s_score)
 {
-    static_assert(kBuildThreads == kLvBuckets, "one bucket per thread");
+    static_assert(NT >= kLvBuckets, "one bucket per thread");
     __shared__ __align__(16) int s_hist[kLvBuckets + 4];    // every prefix known so far, by bucket
     __shared__ __align__(16) int s_histc[kLvBuckets + 4];   // the candidates of the level; at the end: cursors
     __shared__ __align__(16) int s_histv[kLvBuckets + 4];   // the prefixes the level makes known
     __shared__ __align__(16) int s_pref[kLvBuckets + 4];    // exclusive prefix of s_histc, later of s_hist
     __shared__ int s_state[8];                // what the single-wave levels hand back to the workgroup
     __shared__ float s_cc[DDTREE_MAX_B + 1];  // scores of the top-1 chain's nodes
-    __shared__ int s_w[kBuildThreads / 64];
-    __shared__ int s_w2[2][kBuildThreads / 64];
+    __shared__ __align__(16) int s_w[NT / 64];
+    __shared__ __align__(16) int s_w2[2][NT / 64];
     __shared__ int s_M, s_fail, s_nbig, s_bstar, s_chain;
     __shared__ uint16_t s_big[kLvBigCap];
-    constexpr int NT = kBuildThreads;
     const int tid = threadIdx.x;
+    const bool has_bucket = NT == kLvBuckets || tid < kLvBuckets;
 
     if (tid == 0) {
         L.m_score[0] = 0.0f;
@@ -229,7 +230,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
         s_M = 1;
         s_fail = 0;
     }
-    s_hist[tid] = 0;
+    if (has_bucket) s_hist[tid] = 0;
     if (tid == 0) s_hist[kLvBuckets] = 0;
     const float hi = s_lp[0];
     // lower end of the bucket range: with K >= N the N-th rank of row 0 is a lower bound on the
@@ -489,7 +490,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                     }
                 }
                 int total;
-                const int off = Cn + build_block_scan(len, s_w, &total);
+                const int off = Cn + build_block_scan<NT>(len, s_w, &total);
                 if (chain_base + Cn + total > limit) return -1;  // (before anything of it is written)
                 if (len > 0) {
                     float v = S;
@@ -520,7 +521,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                     if (dp < B) c = max(0, count_children(s_lp + dp * Kp, S, cap, bstar) - 1);
                 }
                 int total;
-                const int off = H + build_block_scan(c, s_w, &total);
+                const int off = H + build_block_scan<NT>(c, s_w, &total);
                 if (head_base + H + total > limit) return -1;
                 // small families are written by their parent's thread, large ones are queued and
                 // written by the whole workgroup (s_nbig is 0 here: see the end of the round)
@@ -863,8 +864,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                     s_bstar = bstar;
                     s_chain = -1;
                 }
-                s_histc[tid] = 0;
-                s_histv[tid] = 0;
+                if (has_bucket) s_histc[tid] = s_histv[tid] = 0;
                 if (tid == 0) s_histc[kLvBuckets] = s_histv[kLvBuckets] = 0;
                 // 1. children at or above the cut, per parent, and where they go; small families
                 //    are written on the spot by their parent's thread, large ones are queued
@@ -883,7 +883,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                         }
                     }
                     int total;
-                    const int off = C + build_block_scan(c, s_w, &total);
+                    const int off = C + build_block_scan<NT>(c, s_w, &total);
                     if (i < n_par) {
                         L.p_c[i] = (uint16_t)(c | (cut ? 0x8000 : 0));
                         L.p_off[i] = (uint16_t)min(off, 0xFFFF);
@@ -925,9 +925,9 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                         if (newly_known(ls + i, r)) atomicAdd(&s_histv[bucket_of(S + row[r])], 1);
                 }
                 __syncthreads();
-                const int ha0 = s_hist[tid] + s_histv[tid];
+                const int ha0 = has_bucket ? s_hist[tid] + s_histv[tid] : 0;
                 int total0;
-                const int ex0 = build_block_scan(ha0, s_w, &total0);
+                const int ex0 = build_block_scan<NT>(ha0, s_w, &total0);
                 if (ex0 < N && ex0 + ha0 >= N) s_bstar = tid;
                 __syncthreads();
                 bstar = min(bstar, s_bstar);
@@ -960,13 +960,15 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                 }
             }
             __syncthreads();
-            const int hc = s_histc[tid];
-            const int ha = s_hist[tid] + s_histv[tid];
+            const int hc = has_bucket ? s_histc[tid] : 0;
+            const int ha = has_bucket ? s_hist[tid] + s_histv[tid] : 0;
             int total_a, total_c;
             int ex_a = ha, ex_c = hc;
-            build_block_scan2(&ex_a, &ex_c, s_w2, &total_a, &total_c);
-            s_pref[tid] = ex_c;
-            s_hist[tid] = ha;
+            build_block_scan2<NT>(&ex_a, &ex_c, s_w2, &total_a, &total_c);
+            if (has_bucket) {
+                s_pref[tid] = ex_c;
+                s_hist[tid] = ha;
+            }
             if (tid == 0) {
                 s_pref[kLvBuckets] = total_c;
                 s_hist[kLvBuckets] += s_histv[kLvBuckets];
@@ -1007,7 +1009,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
                     jl = L.m_jlo[m];
                 }
                 int tot;
-                const int dst = base + build_block_scan(keep ? 1 : 0, s_w, &tot);
+                const int dst = base + build_block_scan<NT>(keep ? 1 : 0, s_w, &tot);
                 if (keep) {  // dst <= m, and every entry up to this chunk's end has been read
                     remap[m] = (uint16_t)dst;
                     L.m_score[dst] = sc;
@@ -1067,8 +1069,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
     // ---- exact order of the members at or above the cut ----
     // (the members are counted per bucket afresh: the running histogram also holds prefixes that
     // were entered ahead of being found)
-    s_histv[tid] = 0;
-    s_histc[tid] = 0;
+    if (has_bucket) s_histv[tid] = s_histc[tid] = 0;
     if (tid == 0) s_histv[kLvBuckets] = s_histc[kLvBuckets] = 0;
     __syncthreads();
     for (int m = 1 + tid; m < M; m += NT) {
@@ -1076,11 +1077,11 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
         if (bk <= bstar) atomicAdd(&s_histv[bk], 1);
     }
     __syncthreads();
-    const int hb = tid <= bstar ? s_histv[tid] : 0;
+    const int hb = has_bucket && tid <= bstar ? s_histv[tid] : 0;
     if (tid == 0) s_bstar = bstar;
     int total_alive;
-    const int start = build_block_scan(hb, s_w, &total_alive);
-    s_pref[tid] = start;
+    const int start = build_block_scan<NT>(hb, s_w, &total_alive);
+    if (has_bucket) s_pref[tid] = start;
     if (tid == 0) s_pref[kLvBuckets] = total_alive;
     // The members are every prefix at or above the cut, so the N best of them are the tree: the
     // cut moves up to the bucket that holds the N-th best member, and whatever the construction
@@ -1141,8 +1142,88 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
     return min(N, total_alive);
 }
 
-template <int NSLOT>
-__global__ __launch_bounds__(kBuildThreads) void build_kernel(
+// The pops of a budget of at most 63 nodes, by one wave: entry e of the frontier in lane e, and with it the
+// record and score of node e, which leave for LDS at the end.  A pop is a chain of dependent instructions of a
+// wave that is alone on its SIMD, so what counts is how many there are; the log-probability that a popped
+// entry needs after its next one is looked up a pop ahead and taken over once the next pop's minimum is
+// known.  Returns the number of nodes.  Measured (kernel, rows peaked at 0.7): 16 nodes 9.7 -> 8.5 us, 32 nodes
+// 15.1 -> 13.4, of which 4 are launch, table and results.
+__device__ __forceinline__ int pops_of_one_slot(const float *s_lp, int Kp, int B, int N, uint32_t *s_node, float *s_score)
+{
+    constexpr uint32_t kEmpty = 0xFF800000u;
+    const int lane = threadIdx.x;
+    // lane d: the first two log-probabilities of row d, -inf past the last row
+    const float lp0 = lane < B ? s_lp[lane * Kp + 0] : -INFINITY;
+    const float lp1 = lane < B ? s_lp[lane * Kp + 1] : -INFINITY;
+    uint32_t cand = lane == 0 ? __float_as_uint(lp0) : kEmpty;
+    float nsc = 0.0f, nlp1 = lane == 0 ? lp1 : -INFINITY, ahead = 0.0f;
+    int meta = 0;  // (child rank << 8) | children's row
+    uint32_t node = pack_node(0, 0, 0);
+    int n = 0, prev = -1;  // prev: the entry popped last, which `ahead` belongs to
+    while (n < N) {
+        const uint32_t wmb = wave_min_u32(cand);
+        if (wmb == kEmpty) break;  // frontier empty: fewer than N prefixes exist
+        const unsigned long long bal = __ballot(cand == wmb);
+        nlp1 = lane == prev ? ahead : nlp1;
+        int wl = __ffsll((long long)bal) - 1;
+        const bool tie = (bal & (bal - 1)) != 0ull;
+        if (tie) {  // several candidates share the best score: the rank-tuple order decides
+            if (lane <= n) s_node[lane] = node;
+            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+            int bc = __builtin_amdgcn_readlane(meta, wl) >> 8;
+            for (unsigned long long mm = bal & (bal - 1); mm; mm &= mm - 1) {
+                const int l = __ffsll((long long)mm) - 1, c2 = __builtin_amdgcn_readlane(meta, l) >> 8;
+                if (tuple_before(s_node, l, c2, wl, bc)) {
+                    wl = l;
+                    bc = c2;
+                }
+            }
+            wl = __builtin_amdgcn_readfirstlane(wl);
+        }
+        const int M = __builtin_amdgcn_readlane(meta, wl);
+        const float NS = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nsc), wl));
+        float inc = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(nlp1), wl));
+        const int c = M >> 8, row = M & 0xFF, d = row + 1;
+        const float wm = __uint_as_float(wmb);
+        const float lp0d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lp0), d));
+        const float lp1d = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lp1), d));
+        const float *const rowp = s_lp + row * Kp;
+        const bool popped = lane == wl;
+        const int j = lane - (n + 1);  // entry n + 1 + j is the batch's j-th node
+        // sibling run: see the pops of any budget below
+        int J = 1;
+        float sc = wm;
+        if (wl == prev && !tie) {
+            const float others = __uint_as_float(wave_min_u32(popped ? kEmpty : cand));
+            const float bound = fmaxf(others, wm + lp0d);
+            const float mine = NS + rowp[min(c + lane, Kp - 1)];  // -inf past rank K-1
+            const unsigned long long okm = __ballot(lane == 0 || mine > bound);
+            J = ~okm == 0ull ? 64 : __ffsll((long long)~okm) - 1;
+            J = min(J, N - n);
+            if (J > 1) {
+                sc = __shfl(mine, j & 63, 64);
+                inc = rowp[min(c + J, Kp - 1)];
+            }
+        }
+        ahead = rowp[min(c + J + 1, Kp - 1)];  // -inf once c + J + 1 >= K
+        prev = wl;
+        const bool fresh = (unsigned)j < (unsigned)J;
+        cand = fresh ? __float_as_uint(sc + lp0d) : popped ? __float_as_uint(NS + inc) : cand;  // -inf once d == B
+        nsc = fresh ? sc : nsc;
+        nlp1 = fresh ? lp1d : nlp1;
+        meta = fresh ? d : popped ? M + (J << 8) : meta;
+        node = fresh ? pack_node(wl, c + j, d) : node;
+        n += J;
+    }
+    if (lane <= n) {
+        s_node[lane] = node;
+        s_score[lane] = nsc;
+    }
+    return n;
+}
+
+template <int NSLOT, int NT>
+__global__ __launch_bounds__(NT) void build_kernel(
     const int32_t *__restrict__ topk_tok, const float *__restrict__ topk_lp, int B, int K, int N,
     const int32_t *__restrict__ root_token, int32_t *__restrict__ tokens,
     int32_t *__restrict__ parent, int32_t *__restrict__ depth, int32_t *__restrict__ rank,
@@ -1175,26 +1256,26 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
     const int32_t *tk = topk_tok + (size_t)seq * B * K;
 
     // log-probabilities into LDS, rows padded with -inf.  The [B][K] table is contiguous: thread
-    // t takes the 16-byte pieces t, t + 256, ..., sixteen loads in flight at a time (one round trip
+    // t takes the 16-byte pieces t, t + NT, ..., sixteen loads in flight at a time (one round trip
     // to memory up to B K = 16384), and keeps (row, column) of its first element by stepping both.
     {
         const int n_el = B * K;
         // whole pieces of four, if this sequence's table starts on a 16-byte boundary (else, and
         // for the last one to three elements, the plain loop below)
         const int n_q = (reinterpret_cast<uintptr_t>(lp) & 15) == 0 ? n_el >> 2 : 0;
-        const int dq = (4 * kBuildThreads) / K, dr = (4 * kBuildThreads) % K;  // one step of 1024 elements
+        const int dq = (4 * NT) / K, dr = (4 * NT) % K;  // one step of 4 NT elements
         int d = (4 * tid) / K, k = (4 * tid) % K;
         const float4 *lp4 = reinterpret_cast<const float4 *>(lp);
-        for (int q0 = tid; q0 < n_q; q0 += 16 * kBuildThreads) {
+        for (int q0 = tid; q0 < n_q; q0 += 16 * NT) {
             float4 v[16];
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const int q = q0 + u * kBuildThreads;
+                const int q = q0 + u * NT;
                 v[u] = q < n_q ? lp4[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                if (q0 + u * kBuildThreads < n_q) {
+                if (q0 + u * NT < n_q) {
                     const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
                     int dd = d, kk = k;
 #pragma unroll
@@ -1214,8 +1295,8 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
                 }
             }
         }
-        for (int e = 4 * n_q + tid; e < n_el; e += kBuildThreads) s_lp[(e / K) * Kp + e % K] = lp[e];
-        for (int i = tid; i < 3 * B; i += kBuildThreads) s_lp[(i / 3) * Kp + K + i % 3] = -INFINITY;
+        for (int e = 4 * n_q + tid; e < n_el; e += NT) s_lp[(e / K) * Kp + e % K] = lp[e];
+        for (int i = tid; i < 3 * B; i += NT) s_lp[(i / 3) * Kp + K + i % 3] = -INFINITY;
     }
     if (tid == 0) {
         s_node[0] = pack_node(0, 0, 0);
@@ -1229,25 +1310,31 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
     // is recognised by the top-1 chain falling below the worst useful rank of row 0 within two
     // steps and by the best depth-1 node having fewer than four children above that rank.
     // Both constructions give the same tree; algo 1 / 2 force one of them.
+    // (Measured, rows peaked at 0.7, pops / levels: 32 nodes 13.4 / 14.5 us, 40 nodes 15.8 / 14.7, 64 nodes 32.6 / 15.3;
+    // flat rows 4.0 / 8.8 up to 63 nodes.)
     bool use_levels = capm > 0 && algo != DDTREE_BUILD_POPS;
-    if (use_levels && algo == DDTREE_BUILD_AUTO) {
-        const float worst = s_lp[min(K, N) - 1];
-        float chain = 0.0f;
-        int deep = 0;
-        for (int d = 0; d < B; ++d) {
-            chain += s_lp[d * Kp];
-            deep += chain >= worst ? 1 : 0;
+    if (use_levels && algo == DDTREE_BUILD_AUTO && N <= 256) {
+        use_levels = false;
+        if (N >= 36) {
+            const float worst = s_lp[min(K, N) - 1];
+            // (scores only fall along the chain: its third node speaks for the first two)
+            const bool deep = B >= 3 && (s_lp[0] + s_lp[Kp]) + s_lp[2 * Kp] >= worst;
+            const bool bushy = B >= 2 && s_lp[0] + s_lp[Kp + min(3, K - 1)] >= worst;
+            use_levels = deep || bushy;
         }
-        const bool bushy = B >= 2 && s_lp[0] + s_lp[Kp + min(3, K - 1)] >= worst;
-        use_levels = N > 256 || (N >= 48 && (deep >= 3 || bushy));
     }
     int level_n = -1;
     if (use_levels) {
-        level_n = level_build(s_lp, Kp, B, K, N, lv, s_node, s_score);
+        level_n = level_build<NT>(s_lp, Kp, B, K, N, lv, s_node, s_score);
         if (level_n < 0 && tid == 0) atomicAdd(&g_level_giveups, 1u);
     }
     if (level_n >= 0) {
         if (tid == 0) s_built = level_n;
+    } else if (NSLOT == 1) {
+        if (tid < kWave) {
+            const int n = pops_of_one_slot(s_lp, Kp, B, N, s_node, s_score);
+            if (tid == 0) s_built = n;
+        }
     } else if (tid < kWave) {
         const int lane = tid;
         // lane d holds the first two log-probabilities of row d (children of a node at depth
@@ -1406,9 +1493,9 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
 
     // Node ids are dealt so that T = 257 (a budget of 256 and the root) takes one pass: the last
     // thread also takes the root, whose row is trivial, before its own node.
-    for (int i0 = 1; i0 < T; i0 += kBuildThreads) {
+    for (int i0 = 1; i0 < T; i0 += NT) {
         const int i = i0 + tid;
-        if (i0 == 1 && tid == kBuildThreads - 1) {
+        if (i0 == 1 && tid == NT - 1) {
             const size_t o0 = (size_t)seq * T;
             tokens[o0] = root_token[seq];
             parent[o0] = -1;
@@ -1524,7 +1611,7 @@ static BuildLds build_lds_plan(int B, int K, int N, bool level)
 
 static std::atomic<int> g_build_algo{DDTREE_BUILD_AUTO};
 
-template <int NSLOT>
+template <int NSLOT, int NT>
 static int launch_build(const int32_t *topk_tok, const float *topk_lp, int batch, int B, int K, int N,
                         const int32_t *root_token, int32_t *tokens, int32_t *parent, int32_t *depth,
                         int32_t *rank, float *node_score, uint64_t *ancestor_mask, int32_t *n_nodes,
@@ -1533,9 +1620,9 @@ static int launch_build(const int32_t *topk_tok, const float *topk_lp, int batch
     const int algo = g_build_algo.load();
     const BuildLds lds = build_lds_plan(B, K, N, algo != DDTREE_BUILD_POPS);
     static std::atomic<bool> lds_allowed{false};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(build_kernel<NSLOT>), 150 * 1024, lds_allowed))
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(build_kernel<NSLOT, NT>), 150 * 1024, lds_allowed))
         return DDTREE_ERR_HIP;
-    DDT_LAUNCH(DDTREE_KERNEL_BUILD, st, build_kernel<NSLOT>, dim3(batch), dim3(kBuildThreads), lds.bytes,
+    DDT_LAUNCH(DDTREE_KERNEL_BUILD, st, (build_kernel<NSLOT, NT>), dim3(batch), dim3(NT), lds.bytes,
                        st, topk_tok, topk_lp, B, K, N, root_token, tokens, parent, depth, rank,
                        node_score, ancestor_mask, n_nodes, algo, lds.capm, lds.capp, lds.capc);
     return launch_status();
@@ -1577,14 +1664,17 @@ extern "C" int ddtree_build(const int32_t *topk_tok, const float *topk_lp, int b
     if (build_lds_bytes(B, K, N) > 150 * 1024) return DDTREE_ERR_ARG;
     hipStream_t st = as_stream(stream);
     const int slots = (N + 1 + 63) / 64;
-#define DDT_BUILD(S)                                                                              \
-    return launch_build<S>(topk_tok, topk_lp, batch, B, K, N, root_token, tokens, parent, depth, \
+    // Beyond 320 nodes the exact order, the masks and the generations have work for eight waves; below, barriers
+    // among more waves cost what they bring.  (256 / 512 / 1024 threads, us, rows peaked at 0.7: 256 nodes 19.7 / 18.9 /
+    // 21.4, at 0.3 26.4 / 27.6 / 31.0; 512 nodes 27.8 / 24.4 / 25.4; 1024 nodes 54.9 / 43.2 / 40.2, at 0.5 66.8 / 59.3 / 61.4.)
+#define DDT_BUILD(S, NT)                                                                          \
+    return launch_build<S, NT>(topk_tok, topk_lp, batch, B, K, N, root_token, tokens, parent, depth, \
                            rank, node_score, ancestor_mask, n_nodes, st)
-    if (slots <= 1) DDT_BUILD(1);
-    if (slots <= 2) DDT_BUILD(2);
-    if (slots <= 3) DDT_BUILD(3);
-    if (slots <= 5) DDT_BUILD(5);
-    if (slots <= 9) DDT_BUILD(9);
-    DDT_BUILD(17);
+    if (slots <= 1) DDT_BUILD(1, 256);
+    if (slots <= 2) DDT_BUILD(2, 256);
+    if (slots <= 3) DDT_BUILD(3, 256);
+    if (slots <= 5) DDT_BUILD(5, 256);
+    if (slots <= 9) DDT_BUILD(9, 512);
+    DDT_BUILD(17, 512);
 #undef DDT_BUILD
 }
