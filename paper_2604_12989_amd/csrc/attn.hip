@@ -179,7 +179,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     // ---- tile loads: a K tile is 17 and a V tile 16 DMA blocks of 1 KB of LDS; lane l of block b fills
     //      16-byte slot u = 64*b + l, i.e. row u / chunks_per_row, chunk position u % chunks_per_row.
     //      The blocks are dealt round-robin to the n_dma loading waves: all eight, or, in a workgroup
-    //      where at most two waves have query rows (the small tail tile), the six or seven waves
+    //      where at most two waves have query rows (few rows, long caches), the six or seven waves
     //      without any, so that the waves that compute issue no loads at all.  A loading wave
     //      issues 2 K + 2 V blocks per tile plus at most one more of each: 4, 5 or 6 loads, the
     //      same for whole and ragged tiles (see tiles_in_flight).  The per-lane source offsets

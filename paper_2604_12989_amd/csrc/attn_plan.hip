@@ -425,7 +425,7 @@ int attn_selftest_host()
         {1, 2, 1, 1, 128, {0}},              {4, 1024, 8, 8, 128, {100, 0, 64, 7}}, {1, 75, 16, 4, 128, {3000}},
         {1, 300, 6, 2, 128, {9000}},         {2, 273, 32, 8, 128, {5000, 4999}},  {1, 1025, 128, 1, 128, {200000}},
         {1, 65, 16, 4, 64, {2047}},          {3, 257, 32, 8, 64, {4096, 31, 33}}, {1, 2, 1, 1, 64, {0}},
-        {4, 101, 24, 8, 128, {37, 3001, 900, 1700}},
+        {4, 101, 24, 8, 128, {37, 3001, 900, 1700}}, {4, 1025, 40, 8, 128, {5000, 300, 9000, 700}},
     };
     // exhaustive check of the reciprocal division itself on small divisors
     for (uint32_t d = 2; d <= 64; ++d) {
