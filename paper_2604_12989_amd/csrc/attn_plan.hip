@@ -90,7 +90,7 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
     // step of its eight waves (32 keys each), the rates at which the L2s and HBM serve all of them.
     const double fix = 7.0, step = D == 64 ? (row_blocks == 1 ? 0.62 : 1.17) : 1.2;
     const double l2_us = (double)sub_tiles * Hkv * p.groups * (kSK * 4.0 * D) / 20.0e6;
-    const double hbm_us = (double)sub_tiles * Hkv * (kSK * 4.0 * D) / 3.5e6;
+    const double hbm_us = (double)sub_tiles * Hkv * (kSK * 4.0 * D) / 4.0e6;
     int best_c = nt_max;
     p.cost = 1e30;
     for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= nt_max && (long long)s * nt_max < (1ll << 30))); ++s) {
@@ -139,7 +139,9 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
     // step of eight sub-tiles beside them (1.2 alone, keys from the L2).  With 513 nodes x 32768 keys, four key
     // ranges and the tail blocks in a second round (the sum of times says 246 us) took 340 where three and
     // everything in one round take 307: the few workgroups of that second round wait for HBM.
-    const double fix = 11.0, tile_few = 1.52, tile_all = 1.9, tail_fix = 7.0, tail_step = 2.4;
+    // Workgroups of one or two blocks (few rows over long caches) spend less on a tile.
+    const bool low = nblk <= 2;
+    const double fix = 11.0, tile_few = low ? 0.95 : 1.52, tile_all = low ? 0.95 : 1.9, tail_fix = 7.0, tail_step = 2.4;
     const long long cap = std::min(slot_room, main_slot_cap(batch, T, Hq, Hkv));
     AttnPlan best{};
     best.cost = 1e30;
@@ -185,7 +187,7 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
                     work += tails > 0 ? 1.5 * tail_longest * up((int)tails, 256) : 0.0;
                 else
                     work = std::max(work, sum / 256 + 0.5 * tail_longest);
-                const double cost = std::max(work, hbm_us) + (cut ? merge_us(slots, T, Hq, kHD) : 0.0);
+                const double cost = std::max(work, fix + hbm_us) + (cut ? merge_us(slots, T, Hq, kHD) : 0.0);
                 if (cost < best.cost) {
                     best.cost = cost;
                     best.uneven = uneven != 0;
@@ -214,7 +216,8 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
 
 // The cheaper of the two by the estimates above.  Both measured where they meet (32 query and 8 KV heads
 // of 128, one sequence; waves of their own / shared tiles, us): 129 nodes x 4096 keys 26.8 / 26.9,
-// 401 x 600 21.8 / 25.7, 257 x 8192 102 / 51, 17 x 8192 17.5 / 20.7.  Heads of 64: 32-row groups against 64-row
+// 401 x 600 21.8 / 25.7, 257 x 8192 102 / 51, 17 x 8192 17.5 / 20.7; 16 sequences of 10 nodes over up to 26246 keys, 16 and
+// 4 heads, 145 / 103, four of 19 over up to 8468 31 / 36.  Heads of 64: 32-row groups against 64-row
 // groups at 257 x 4096 36.9 / 28.5 (two rounds of workgroups against one), at 65 x 2047 11.5 / 13.0.
 AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long slot_room)
 {

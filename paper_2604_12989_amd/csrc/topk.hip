@@ -75,7 +75,8 @@ TopkPlan topk_plan(int batch, int B, int V, int K)
     const int g = std::max(1, std::min(64, len / 32));
     p.hot_rank = (int)(g * (1.0 - std::exp(-c / g)));
     if (p.hot_rank < 1) p.hot_rank = 1;
-    p.hot_cap = c <= 40.0 ? 64 : c <= 90.0 ? 128 : c <= 200.0 ? 256 : c <= 420.0 ? 512 : 0;  // (0: most elements would be hot)
+    // (A tenth of a chunk is what the maxima of 32 elements can tell apart: beyond it the lists would lack some.)
+    p.hot_cap = c > 0.1 * len ? 0 : c <= 40.0 ? 64 : c <= 90.0 ? 128 : c <= 200.0 ? 256 : c <= 420.0 ? 512 : 0;  // (0: most elements would be hot)
     p.max_off = 0;
     p.stat_off = align_up((size_t)rows * p.chunks * p.maxima * sizeof(float), 256);
     p.hot_off = align_up(p.stat_off + (size_t)rows * p.chunks * sizeof(ChunkStat), 256);
