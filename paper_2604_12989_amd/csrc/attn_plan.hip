@@ -287,7 +287,7 @@ bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_sta
     return true;
 }
 
-// False if the launch would exceed 2^28 work items.
+// False if the launch would exceed 2^28 work items, or if the tables do not hold exactly the plan's items.
 bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_start, const int32_t *kv_len, int batch,
                     int T, int Hq, int Hkv)
 {
@@ -348,10 +348,12 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
     } else {
         by_work(args.xcd_start, false, total);
     }
-    if (tail_total > 0 && total + tail_total > 256) {
+    if (tail_total == 0) {
+        for (int x = 1; x <= 8; ++x) args.tail_start[x] = 0;
+    } else if (total + tail_total > 256) {
         by_work(args.tail_start, true, tail_total);
     } else {
-        for (int x = 0; x < 8; ++x) {
+        for (int x = 0; x < 8; ++x) {  // (at most 32 whole tiles' items on each XCD here)
             int idle_behind = 0;  // compute units without an item on the XCDs that follow
             for (int y = x + 1; y < 8; ++y) idle_behind += 32 - (args.xcd_start[y + 1] - args.xcd_start[y]);
             const long long left = tail_total - args.tail_start[x];
@@ -359,6 +361,10 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
             args.tail_start[x + 1] = (int32_t)(args.tail_start[x] + std::min(left, take));
         }
     }
+    // every work item has a workgroup, or the call is refused: nothing else would notice a missing one
+    bool whole = total + tail_total == p.items && args.xcd_start[8] == total && args.tail_start[8] == tail_total;
+    for (int x = 0; x < 8; ++x) whole = whole && args.xcd_start[x + 1] >= args.xcd_start[x] && args.tail_start[x + 1] >= args.tail_start[x];
+    if (!whole) return false;
     int run_max = 0;
     for (int x = 0; x < 8; ++x)
         run_max = std::max(run_max, args.xcd_start[x + 1] - args.xcd_start[x] + args.tail_start[x + 1] - args.tail_start[x]);
@@ -367,49 +373,55 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
 }
 
 // ------------------------------------------------------------------------------------------
-// Host-side self-check (no GPU involved): for a list of shapes the plan and the launch tables of both
-// kernels are built as for a launch, every workgroup index of the grid is decoded the way the kernel
-// decodes it, and the work items are held against what the decomposition promises: every
-// (sequence, KV head, query row) meets every key tile exactly once, in consecutive key ranges, and each
-// of its key ranges has a partial result of its own within the scratch.
-// Returns 0, or 100 * (index of the failing shape + 1) + the number of the failed check.
+// Host-side self-check (no GPU involved): for a list of shapes, and for a seeded sweep over batches, head
+// layouts, cache lengths and scratch at hand, the plan and the launch tables of both kernels are built as for a
+// launch, every workgroup index of the grid is decoded the way the kernel decodes it, and the work items
+// are held against what the decomposition promises: every (sequence, KV head, query row) meets every key
+// tile exactly once, in consecutive key ranges, and each of its key ranges has a partial result of its own
+// within the scratch.
+// Returns 0, or 100 * (index of the failing shape + 1) + the number of the failed check, the shapes of the sweep
+// counted from kSweepBase on.
 // ------------------------------------------------------------------------------------------
 namespace {
 struct Shape {
     int batch, T, Hq, Hkv, D;
-    int32_t len[4];
+    std::vector<int32_t> len;
 };
 struct Item {
     int seq, hk, r0, r1, t0, t1, split, ranges, slot, keys_per_tile, nt;
 };
+constexpr int kSweepBase = 10000, kSweepShapes = 600;
 }  // namespace
 
-static int check_items(const Shape &sh, const AttnPlan &p, const std::vector<Item> &items, long long expected)
+static int check_items(const Shape &sh, const AttnPlan &p, std::vector<Item> &items, long long expected)
 {
-    const int M = sh.T * (sh.Hq / sh.Hkv);
+    const int G = sh.Hq / sh.Hkv, M = sh.T * G;
     if ((long long)items.size() != expected) return 4;
-    // per (sequence, head, row): the key ranges it has met
-    std::vector<std::vector<const Item *>> met((size_t)sh.batch * sh.Hkv * M);
     for (const Item &w : items) {
         if (w.seq < 0 || w.seq >= sh.batch || w.hk < 0 || w.hk >= sh.Hkv || w.r0 < 0 || w.r0 >= w.r1 || w.r1 > M) return 5;
         if (w.t0 < 0 || w.t0 > w.t1 || w.t1 > w.nt || w.split < 0 || w.split >= w.ranges) return 6;
         if (w.ranges > 1 && (w.slot < 0 || w.slot >= p.slots)) return 7;
-        for (int r = w.r0; r < w.r1; ++r) met[((size_t)w.seq * sh.Hkv + w.hk) * M + r].push_back(&w);
+        // the last row's own tree key is among the tiles
+        if (w.nt < (sh.len[w.seq] + w.keys_per_tile - 1) / w.keys_per_tile + (w.r1 - 1) / G / w.keys_per_tile + 1) return 10;
     }
-    for (size_t i = 0; i < met.size(); ++i) {
-        auto &v = met[i];
-        const int r = (int)(i % M), node = r / (sh.Hq / sh.Hkv);
-        std::sort(v.begin(), v.end(), [](const Item *a, const Item *b) { return a->split < b->split; });
-        int next = 0;
-        for (size_t j = 0; j < v.size(); ++j) {
-            if (v[j]->split != (int)j || v[j]->t0 != next) return 8;
-            next = v[j]->t1;
+    // head by head: the row blocks follow each other from 0 to M, the key ranges of a block from 0 to nt
+    std::sort(items.begin(), items.end(), [](const Item &a, const Item &b) {
+        return a.seq != b.seq ? a.seq < b.seq : a.hk != b.hk ? a.hk < b.hk : a.r0 != b.r0 ? a.r0 < b.r0 : a.split < b.split;
+    });
+    size_t at = 0;
+    for (int head = 0; head < sh.batch * sh.Hkv; ++head)
+        for (int row = 0; row < M;) {
+            const Item *first = at < items.size() ? &items[at] : nullptr;
+            if (!first || first->seq != head / sh.Hkv || first->hk != head % sh.Hkv || first->r0 != row) return 8;
+            int next = 0, split = 0;
+            for (; at < items.size() && items[at].seq == first->seq && items[at].hk == first->hk && items[at].r0 == row; ++at, ++split) {
+                if (items[at].split != split || items[at].t0 != next || items[at].r1 != first->r1) return 8;
+                next = items[at].t1;
+            }
+            if (next != first->nt) return 9;
+            row = first->r1;
         }
-        if (v.empty() || next != v[0]->nt) return 9;
-        // the row's own tree key is among the tiles
-        const int kt = v[0]->keys_per_tile, need = (sh.len[v[0]->seq] + kt - 1) / kt + node / kt + 1;
-        if (v[0]->nt < need) return 10;
-    }
+    if (at != items.size()) return 9;
     // the slots of two sequences do not overlap
     for (int a = 0; a < sh.batch; ++a)
         for (int b = 0; b < sh.batch; ++b)
@@ -417,6 +429,46 @@ static int check_items(const Shape &sh, const AttnPlan &p, const std::vector<Ite
                 p.seq[b].first_slot < p.seq[a].first_slot + p.seq[a].ranges)
                 return 11;
     return 0;
+}
+
+// kind 0, 1: attn_wave_kernel with 32 and 64 rows; 2: attn_mfma_kernel
+static int check_plan(const Shape &sh, int kind, long long room)
+{
+    std::vector<int32_t> kv_start(sh.batch);
+    int32_t sum = 0;
+    for (int i = 0; i < sh.batch; ++i) {
+        kv_start[i] = sum;
+        sum += sh.len[i];
+    }
+    const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len.data(), room)
+                                 : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), kind + 1, room);
+    if (p.slots > room || p.bytes > attn_scratch_upper(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D)) return 1;
+    std::vector<Item> items;
+    if (kind == 2) {
+        AttnMainArgs args;
+        if (!attn_main_args(args, p, kv_start.data(), sh.len.data(), sh.batch, sh.T, sh.Hq, sh.Hkv)) return 2;
+        if (p.items <= 256 && args.grid > 256) return 3;  // one round stays one
+        for (int b = 0; b < args.grid; ++b) {
+            AttnMainItem w;
+            if (!attn_main_item(args, b, sh.T, w)) continue;
+            if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits > w.ranges) return 3;
+            const int keys = w.tail ? kSK : kKT;
+            if (w.tail && w.m_end - w.m0 > 32) return 3;
+            items.push_back({w.seq, w.hk, w.m0, w.m_end, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, keys,
+                             w.n_cache + (w.m_end - 1) / (sh.Hq / sh.Hkv) / keys + 1});
+        }
+    } else {
+        AttnWaveArgs args;
+        if (!attn_wave_args(args, p, kv_start.data(), sh.len.data(), sh.batch, sh.T, sh.Hq, sh.Hkv)) return 2;
+        for (int b = 0; b < args.grid; ++b) {
+            AttnWaveItem w;
+            if (!attn_wave_item(args, b, w)) continue;
+            if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits != w.ranges) return 3;
+            items.push_back({w.seq, w.hk, w.r0, w.r1, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, kSK,
+                             w.n_cache + (w.r1 - 1) / (sh.Hq / sh.Hkv) / kSK + 1});
+        }
+    }
+    return check_items(sh, p, items, p.items);
 }
 
 int attn_selftest_host()
@@ -429,6 +481,10 @@ int attn_selftest_host()
         {1, 300, 6, 2, 128, {9000}},         {2, 273, 32, 8, 128, {5000, 4999}},  {1, 1025, 128, 1, 128, {200000}},
         {1, 65, 16, 4, 64, {2047}},          {3, 257, 32, 8, 64, {4096, 31, 33}}, {1, 2, 1, 1, 64, {0}},
         {4, 101, 24, 8, 128, {37, 3001, 900, 1700}}, {4, 1025, 40, 8, 128, {5000, 300, 9000, 700}},
+        // row tiles of the same height in more than one round of workgroups
+        {16, 161, 32, 8, 128, std::vector<int32_t>(16, 4096)}, {8, 289, 32, 8, 128, std::vector<int32_t>(8, 1024)},
+        {4, 545, 32, 8, 128, std::vector<int32_t>(4, 4096)},   {2, 545, 32, 8, 128, {16384, 16384}},
+        {1, 321, 112, 16, 128, {5000}},                        {64, 41, 32, 8, 128, std::vector<int32_t>(64, 4096)},
     };
     // exhaustive check of the reciprocal division itself on small divisors
     for (uint32_t d = 2; d <= 64; ++d) {
@@ -442,44 +498,33 @@ int attn_selftest_host()
     int si = 0;
     for (const Shape &sh : shapes) {
         ++si;
-        int32_t kv_start[4], sum = 0;
-        for (int i = 0; i < sh.batch; ++i) {
-            kv_start[i] = sum;
-            sum += sh.len[i];
-        }
-        for (int kind = 0; kind < 3; ++kind)             // waves with keys of their own, 32 and 64 rows; shared key tiles
-            for (long long room : {1ll << 40, 0ll}) {    // with scratch and without
+        for (int kind = 0; kind < 3; ++kind)
+            for (long long room : {1ll << 40, 0ll}) {  // with scratch and without
                 if ((kind == 1 && sh.D != 64) || (kind == 2 && sh.D != kHD)) continue;
-                const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len, room)
-                                             : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len, kind + 1, room);
-                if (p.slots > room || p.bytes > attn_scratch_upper(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D)) return 100 * si + 1;
-                std::vector<Item> items;
-                if (kind == 2) {
-                    AttnMainArgs args;
-                    if (!attn_main_args(args, p, kv_start, sh.len, sh.batch, sh.T, sh.Hq, sh.Hkv)) return 100 * si + 2;
-                    if (p.items <= 256 && args.grid > 256) return 100 * si + 3;  // one round stays one
-                    for (int b = 0; b < args.grid; ++b) {
-                        AttnMainItem w;
-                        if (!attn_main_item(args, b, sh.T, w)) continue;
-                        if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits > w.ranges) return 100 * si + 3;
-                        const int keys = w.tail ? kSK : kKT;
-                        if (w.tail && w.m_end - w.m0 > 32) return 100 * si + 3;
-                        items.push_back({w.seq, w.hk, w.m0, w.m_end, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, keys,
-                                         w.n_cache + (w.m_end - 1) / (sh.Hq / sh.Hkv) / keys + 1});
-                    }
-                } else {
-                    AttnWaveArgs args;
-                    if (!attn_wave_args(args, p, kv_start, sh.len, sh.batch, sh.T, sh.Hq, sh.Hkv)) return 100 * si + 2;
-                    for (int b = 0; b < args.grid; ++b) {
-                        AttnWaveItem w;
-                        if (!attn_wave_item(args, b, w)) continue;
-                        if (w.kv_start != kv_start[w.seq] || w.kv_len != sh.len[w.seq] || w.splits != w.ranges) return 100 * si + 3;
-                        items.push_back({w.seq, w.hk, w.r0, w.r1, w.t_begin, w.t_end, w.split, w.ranges, w.first_slot + w.split, kSK,
-                                         w.n_cache + (w.r1 - 1) / (sh.Hq / sh.Hkv) / kSK + 1});
-                    }
-                }
-                if (const int rc = check_items(sh, p, items, p.items)) return 100 * si + rc;
+                if (const int rc = check_plan(sh, kind, room)) return 100 * si + rc;
             }
+    }
+    uint64_t seed = 1;
+    auto below = [&seed](uint64_t n) {  // splitmix64
+        uint64_t z = (seed += 0x9E3779B97F4A7C15ull);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        return (int)((z ^ (z >> 31)) % n);
+    };
+    for (si = kSweepBase; si < kSweepBase + kSweepShapes; ++si) {
+        Shape sh;
+        sh.batch = below(3) == 0 ? 1 : 1 + below(below(2) ? 8 : DDTREE_MAX_BATCH);
+        sh.T = 1 + below(below(2) ? 300 : DDTREE_MAX_N + 1);
+        sh.Hkv = 1 + below(16);
+        sh.Hq = sh.Hkv * (1 + below(below(2) ? 4 : 16));
+        sh.D = below(4) == 0 ? 64 : kHD;
+        const int longest = 1 << below(16), ragged = below(2);
+        for (int i = 0; i < sh.batch; ++i) sh.len.push_back(ragged ? below(longest + 1) : longest);
+        const long long room = below(3) == 0 ? below(4 * sh.batch) : 1ll << 40;
+        for (int kind = 0; kind < 3; ++kind) {
+            if ((kind == 1 && sh.D != 64) || (kind == 2 && sh.D != kHD)) continue;
+            if (const int rc = check_plan(sh, kind, room)) return 100 * si + rc;
+        }
     }
     return 0;
 }

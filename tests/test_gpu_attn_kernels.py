@@ -79,6 +79,12 @@ def test_blocks_left_beside_whole_row_tiles(T, Ls, Hq, Hkv):
     _check(700 + T, T, Ls, Hq, Hkv, 128, n_pairs=40, also=last)
 
 
+@pytest.mark.parametrize("T,Ls", [(161, [700] * 16), (161, [900, 30] + [700] * 14), (300, [1024] * 8), (545, [4096] * 4)])
+def test_whole_row_tiles_in_several_rounds_of_workgroups(T, Ls):
+    """More work items than compute units and no block left beside the tiles: every one is run."""
+    _check(900 + T, T, Ls, 32, 8, 128, n_pairs=32)
+
+
 @pytest.mark.parametrize("T,L,Hq,Hkv,D", [(40, 1500, 8, 2, 64), (40, 1500, 8, 2, 128), (257, 4096, 32, 8, 64), (273, 5000, 32, 8, 128)])
 def test_scores_that_keep_outgrowing_the_reference(T, L, Hq, Hkv, D):
     # from key 200 on, keys point along a query with a factor that grows to 8: scores up to about 90, so a
