@@ -70,9 +70,10 @@ size_t ddtree_workspace_bytes(int batch, int B, int V, int N, int Hq, int Hkv, i
                               int max_sum_L);
 
 /*
- * Scratch that one ddtree_verify_attn call uses for exactly this shape and total cache length
- * sum_L (0 for the shapes that take no scratch).  Never more than ddtree_workspace_bytes for the
- * same shape and any cache length.  Pure host arithmetic.
+ * Scratch that a ddtree_verify_attn call of this shape and total cache length sum_L uses: exactly for
+ * one sequence, at most for several, whose lengths are not known here (0 for the shapes that take no
+ * scratch).  A workspace of this size gives the same result as any larger one.  Never more than
+ * ddtree_workspace_bytes for the same shape and any cache length.  Pure host arithmetic.
  */
 size_t ddtree_verify_attn_workspace_bytes(int batch, int T, int Hq, int Hkv, int D, int dtype,
                                           long long sum_L);
@@ -144,7 +145,10 @@ int ddtree_build(const int32_t *topk_tok, const float *topk_lp, int batch, int B
  *   out        [device] [batch*T, Hq, D], same dtype as q
  * Requires Hq % Hkv == 0, D a multiple of 8 and <= 256, T <= DDTREE_MAX_N + 1,
  * batch <= DDTREE_MAX_BATCH.  bf16 with D = 128 or 64 (and Hkv <= 32768) runs on the matrix cores.
- * With D = 64 the workspace may be missing or small: key ranges are then cut less, or not at all.
+ * A workspace that is missing or too small for the key ranges that the call would be cut into makes them
+ * fewer, or one; only with D = 128, at least 512 keys a sequence on average and at most 128 (sequence, KV
+ * head, 256 query rows) triples is it an error (DDTREE_ERR_WORKSPACE) if it holds less than two partial
+ * results a sequence where the call would use them.
  */
 int ddtree_verify_attn(const void *q, const void *k_cache, const void *v_cache,
                        const void *k_tree, const void *v_tree, const uint64_t *ancestor_mask,

@@ -891,23 +891,18 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
     if (dtype != DDTREE_DTYPE_BF16 && dtype != DDTREE_DTYPE_FP32) return DDTREE_ERR_ARG;
     if (!(softmax_scale > 0.0f) || !(softmax_scale < 1e30f)) return DDTREE_ERR_ARG;
     long long sum_L = 0;
-    int longest = 0;
     for (int s = 0; s < batch; ++s) {
         if (kv_start[s] < 0 || kv_len[s] < 0 || (long long)kv_start[s] + kv_len[s] > 0x7FFFFFFFll)
             return DDTREE_ERR_ARG;
         sum_L += kv_len[s];
-        longest = std::max(longest, kv_len[s]);
     }
     if (sum_L > 0 && (!k_cache || !v_cache)) return DDTREE_ERR_ARG;
     hipStream_t st = as_stream(stream);
 
     if (attn_mfma_shape(dtype, D, Hkv)) {
         const bool ws_usable = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
-        const size_t slot_bytes = (size_t)T * Hq * (D * 2 + 8);
-        const long long room = ws_usable && workspace_bytes > 512 ? (long long)((workspace_bytes - 512) / slot_bytes) : 0;
-        // (a long key range that few workgroups share is not walked uncut because a workspace is missing)
-        if (D == kHD && room < 2LL * batch && longest + T >= 8 * kKT && (long long)batch * Hkv * ((T * (Hq / Hkv) + 255) / 256) <= 128)
-            return DDTREE_ERR_WORKSPACE;
+        const long long room = ws_usable ? attn_slot_room(T, Hq, D, workspace_bytes) : 0;
+        if (attn_lacks_scratch(batch, T, Hq, Hkv, D, kv_len, sum_L, room)) return DDTREE_ERR_WORKSPACE;
         const AttnPlan p = attn_plan(batch, T, Hq, Hkv, D, kv_len, room);
         if (!ws_ok(workspace, workspace_bytes, p.bytes)) return DDTREE_ERR_WORKSPACE;
         char *wsb = static_cast<char *>(workspace);

@@ -52,6 +52,8 @@ struct AttnPlan {
 bool attn_mfma_shape(int dtype, int D, int Hkv);
 // slot_room: partial results that the scratch at hand has room for.
 AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long slot_room);
+long long attn_slot_room(int T, int Hq, int D, size_t bytes);
+bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long sum_L, long long slot_room);
 
 // ---- attn_wave_kernel ----
 struct AttnWaveSeq {

@@ -26,6 +26,15 @@ static void plan_scratch(AttnPlan &p, int T, int Hq, int D, long long slots)
     p.bytes = align_up(p.lse_off + rows * 8, 256);
 }
 
+// Partial results that `bytes` of scratch have room for: the most that plan_scratch lays out in them.
+long long attn_slot_room(int T, int Hq, int D, size_t bytes)
+{
+    long long slots = (long long)(bytes / ((size_t)T * Hq * (D * 2 + 8)));
+    AttnPlan p{};
+    plan_scratch(p, T, Hq, D, slots);
+    return p.bytes <= bytes ? slots : slots - 1;  // (each array is padded to 256 bytes)
+}
+
 static inline int up(int a, int b) { return (a + b - 1) / b; }
 
 // Partial results a plan may leave: what about two rounds of workgroups on 256 compute units make.
@@ -225,6 +234,15 @@ AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_l
     const AttnPlan m = D == kHD ? plan_main(batch, T, Hq, Hkv, kv_len, slot_room)
                                 : plan_wave(batch, T, Hq, Hkv, D, kv_len, 2, slot_room);
     return w.cost <= m.cost ? w : m;
+}
+
+// A long key range that few workgroups share is not walked uncut because a workspace is missing: such a call
+// is refused, unless its plan takes no scratch in any case.
+bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long sum_L, long long slot_room)
+{
+    const long long tiles = (long long)batch * Hkv * (((long long)T * (Hq / Hkv) + 255) / 256);
+    if (D != kHD || slot_room >= 2LL * batch || tiles > 128 || (sum_L / batch + T) / kKT < 8) return false;
+    return attn_plan(batch, T, Hq, Hkv, D, kv_len, 1ll << 40).slots > slot_room;
 }
 
 size_t attn_scratch_upper(int batch, int T, int Hq, int Hkv, int D)
@@ -440,6 +458,16 @@ static int check_plan(const Shape &sh, int kind, long long room)
         kv_start[i] = sum;
         sum += sh.len[i];
     }
+    // the scratch that the library says a call uses is enough for the plan that unlimited scratch gives
+    {
+        const AttnPlan free = attn_plan(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), 1ll << 40);
+        const size_t said = attn_scratch_bytes(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, DDTREE_DTYPE_BF16, sum);
+        const long long has = attn_slot_room(sh.T, sh.Hq, sh.D, said);
+        if (free.bytes > said || has < free.slots || (sh.batch == 1 && (free.bytes != said || has != free.slots))) return 12;
+        const AttnPlan again = attn_plan(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), has);
+        if (again.bytes != free.bytes || again.items != free.items || again.cost != free.cost) return 13;
+        if (attn_lacks_scratch(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), sum, has)) return 14;
+    }
     const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len.data(), room)
                                  : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), kind + 1, room);
     if (p.slots > room || p.bytes > attn_scratch_upper(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D)) return 1;
@@ -518,7 +546,7 @@ int attn_selftest_host()
         sh.Hkv = 1 + below(16);
         sh.Hq = sh.Hkv * (1 + below(below(2) ? 4 : 16));
         sh.D = below(4) == 0 ? 64 : kHD;
-        const int longest = 1 << below(16), ragged = below(2);
+        const int longest = 1 << below(17), ragged = below(2);
         for (int i = 0; i < sh.batch; ++i) sh.len.push_back(ragged ? below(longest + 1) : longest);
         const long long room = below(3) == 0 ? below(4 * sh.batch) : 1ll << 40;
         for (int kind = 0; kind < 3; ++kind) {

@@ -116,3 +116,44 @@ def test_heads_of_64_need_no_scratch():
     a = dd.verify_attn(*args, None)
     b = dd.verify_attn(*args, dd.Workspace(1, 4, 100, T - 1, Hq, Hkv, D, L))
     assert (a.float() - b.float()).abs().max().item() < 1e-2
+
+
+class _Scratch:
+    """A workspace of exactly nbytes."""
+
+    def __init__(self, nbytes):
+        self.nbytes = nbytes
+        self.buf = torch.empty(nbytes + 256, dtype=torch.uint8, device="cuda")
+        self.ptr = self.buf.data_ptr() + (-self.buf.data_ptr()) % 256
+
+
+@pytest.mark.parametrize("T,Ls,Hq,Hkv,D", [
+    (17, [600], 32, 8, 128), (17, [1000], 8, 8, 128), (65, [2048], 32, 8, 128), (257, [8192], 32, 8, 128),
+    (1025, [900], 8, 2, 128), (33, [900, 0, 31, 2500], 12, 4, 128), (17, [600, 10, 10, 10], 32, 8, 128), (65, [2047], 16, 4, 64)])
+def test_a_workspace_of_the_size_that_a_call_uses(T, Ls, Hq, Hkv, D):
+    """The scratch of ddtree_verify_attn_workspace_bytes is enough, and gives the result of a larger one bit for bit."""
+    batch, rng = len(Ls), np.random.default_rng(T)
+    parts = [di.attn_tensors(40 + b, T, Ls[b], Hq, Hkv, D, "bf16") for b in range(batch)]
+    q, kc, vc, kt, vt = (gu.bf16_dev(np.concatenate([p[i] for p in parts])) for i in range(5))
+    mask = gu.to_dev(np.stack([_tree_mask(rng, T) for _ in Ls]).view(np.int64))
+    off = np.concatenate([[0], np.cumsum(Ls)]).astype(np.int32)
+    args = (q, kc, vc, kt, vt, mask, off, batch, T, Hq, Hkv, D, 1.0 / np.sqrt(D), dd.DTYPE_BF16)
+    need = dd.binding.verify_attn_workspace_bytes(batch, T, Hq, Hkv, D, dd.DTYPE_BF16, int(off[-1]))
+    a = dd.verify_attn(*args, _Scratch(need) if need else None)
+    b = dd.verify_attn(*args, dd.Workspace(batch, 4, 2000, T - 1, Hq, Hkv, D, int(off[-1])))
+    assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+
+
+@pytest.mark.parametrize("T,Ls,Hq,Hkv", [(17, [600, 10, 10, 10], 32, 8), (17, [300], 32, 8), (161, [700] * 16, 32, 8)])
+def test_short_calls_need_no_workspace(T, Ls, Hq, Hkv):
+    """Fewer than eight key tiles a sequence on average, or enough workgroups without a cut."""
+    batch, rng = len(Ls), np.random.default_rng(T)
+    parts = [di.attn_tensors(60 + b, T, Ls[b], Hq, Hkv, 128, "bf16") for b in range(batch)]
+    q, kc, vc, kt, vt = (gu.bf16_dev(np.concatenate([p[i] for p in parts])) for i in range(5))
+    masks = [_tree_mask(rng, T) for _ in Ls]
+    off = np.concatenate([[0], np.cumsum(Ls)]).astype(np.int32)
+    got = dd.verify_attn(q, kc, vc, kt, vt, gu.to_dev(np.stack(masks).view(np.int64)), off, batch, T, Hq, Hkv, 128,
+                         1.0 / np.sqrt(128), dd.DTYPE_BF16, None).float().cpu().numpy().reshape(batch, T, Hq, 128)
+    for b in range(batch):
+        pairs = np.stack([rng.integers(0, T, 24), rng.integers(0, Hq, 24)], axis=1).astype(np.int32)
+        assert gu.attn_err(got[b][pairs[:, 0], pairs[:, 1]], oracle.verify_attn(*parts[b], masks[b], pairs=pairs)) < 1e-2
