@@ -84,9 +84,10 @@ constexpr float kSumLimit = 0x1p72f;
 struct AttnTailArgs {
     const uint16_t *q, *k_cache, *v_cache, *k_tree, *v_tree;
     const uint64_t *mask;
-    uint16_t *out, *part;
+    uint16_t *out;
+    void *part;
     float2 *lse;
-    int32_t T, Hq, Hkv, group_size;
+    int32_t T, Hq, Hkv, wide, group_size;
     uint32_t g_magic;
     float scale_log2e;
 };
@@ -98,7 +99,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
                       const uint16_t *__restrict__ v_cache, const uint16_t *__restrict__ k_tree,
                       const uint16_t *__restrict__ v_tree, const uint64_t *__restrict__ mask,
                       AttnMainArgs args, int T, int Hq, int Hkv, float scale_log2e,
-                      uint16_t *__restrict__ out, uint16_t *__restrict__ part, float2 *__restrict__ lse)
+                      uint16_t *__restrict__ out, void *__restrict__ part, float2 *__restrict__ lse)
 {
     // LDS: kAttnStages stages of {K tile, V tile}, filled by direct global->LDS loads.  One wave
     // instruction writes 64 x 16 B contiguously, but every lane may fetch any 16-byte chunk, so
@@ -132,7 +133,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     if (!attn_main_item(args, (int)blockIdx.x, T, item)) return;
     if (item.tail) {
         const AttnTailArgs tail{q, k_cache, v_cache, k_tree, v_tree, mask, out, part, lse, T, Hq, Hkv,
-                                args.group_size, args.g_magic, scale_log2e};
+                                args.wide, args.group_size, args.g_magic, scale_log2e};
         const AttnWaveItem rows{item.seq, item.hk, 0, item.split, item.splits, item.ranges, item.first_slot, item.kv_start,
                                 item.kv_len, item.m0, item.m_end, item.n_cache, item.t_begin, item.t_end};
         attn_wave_rows<kHD, 1>(tail, rows);
@@ -592,11 +593,11 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
         const float l_tot = row_sum();
         const bool real_ = (own_word >> (e_node & 31)) & 1u;
         const float inv = (e_valid && real_ && l_tot > 0.0f) ? 1.0f / l_tot : 0.0f;
-        // The partial of a key range is stored as fp16 relative to the largest magnitude of its
-        // row (so that it fits whatever the values are: bf16 inputs reach 3e38, fp16 65504), with
-        // that magnitude kept beside the log2-sum-exp.
+        // The partial of a key range is stored as fp32, straight from the registers, or as fp16 relative to the
+        // largest magnitude of its row (so that it fits whatever the values are: bf16 inputs reach 3e38,
+        // fp16 65504), with that magnitude kept beside the log2-sum-exp.
         float rs = 1.0f;
-        if (part_splits != 0) {
+        if (part_splits != 0 && !args.wide) {
             float amax = 0.0f;
 #pragma unroll
             for (int db = 0; db < 4; ++db)
@@ -606,6 +607,17 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
             rs = (amax > 0.0f && amax < INFINITY) ? amax : 1.0f;
         }
         const float mul = part_splits == 0 ? inv : inv / rs;
+        if (part_splits != 0 && args.wide) {
+            float *const dst = static_cast<float *>(part) +
+                               ((size_t)(first_slot + split) * rows_seq + (size_t)(e_node * Hq + hk * G + (e_row - e_node * G))) * kHD;
+            if (e_valid)
+#pragma unroll
+                for (int db = 0; db < 4; ++db)
+#pragma unroll
+                    for (int g4 = 0; g4 < 4; ++g4)
+                        *reinterpret_cast<float4 *>(dst + db * 32 + g4 * 8 + e_half * 4) =
+                            make_float4(o[db][4 * g4] * mul, o[db][4 * g4 + 1] * mul, o[db][4 * g4 + 2] * mul, o[db][4 * g4 + 3] * mul);
+        } else
 #pragma unroll
         for (int db = 0; db < 4; ++db)
 #pragma unroll
@@ -629,8 +641,9 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
                 for (int sx = splits; sx < part_splits; ++sx) lse[ridx + (size_t)sx * rows_seq] = make_float2(-INFINITY, 1.0f);
         }
     }
+    if (part_splits != 0 && args.wide) return;
     uint16_t *dst_base = part_splits == 0 ? out + seq * rows_seq * kHD
-                                          : part + (size_t)(first_slot + split) * rows_seq * kHD;
+                                          : static_cast<uint16_t *>(part) + (size_t)(first_slot + split) * rows_seq * kHD;
     const int chunk = e_lane & 15;
     int r = m0 + e_wave * 32 + (e_lane >> 4);  // rows lane >> 4, + 4, + 8, ... of the block
     int node = div_by(r, G, args.g_magic), g = r - node * G;
@@ -651,17 +664,15 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
 }
 
 // Merge of the split-KV partials: out = sum_s 2^(lse_s - max) O_s / sum_s 2^(lse_s - max).
-// Partials are normalised per split and stored as fp16 relative to the largest magnitude of the
-// row, which travels beside the row's log2-sum-exp (eps 2^-11 is below the bf16 rounding of the
+// Partials are normalised per split and stored as fp32, or as fp16 relative to the largest magnitude of
+// the row, which travels beside the row's log2-sum-exp (eps 2^-11 is below the bf16 rounding of the
 // result).  One thread per (row, 8 dims); the loads of kMergeBatch splits are in flight
 // together: 8 for up to 8 key ranges, 16 beyond (small budgets on long caches).
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-
 struct AttnMergeArgs {
     int32_t range[DDTREE_MAX_BATCH][2];  // first slot and key ranges of each sequence
 };
-template <int D, int kMergeBatch>
-__global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t *__restrict__ part_all,
+template <int D, int kMergeBatch, class Part>
+__global__ __launch_bounds__(256) void attn_merge_kernel(const Part *__restrict__ part_all,
                                                          const float2 *__restrict__ lse_all, AttnMergeArgs args,
                                                          int rows_seq, uint16_t *__restrict__ out)
 {
@@ -671,7 +682,8 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t *__restr
     const int row = gid / CH, dg = gid % CH;
     if (row >= rows_seq || splits == 1) return;  // (an uncut key range is already in `out`)
     const size_t first = (size_t)args.range[seq][0] * rows_seq + row;
-    const uint16_t *part = part_all + first * D + dg * 8;
+    const Part *part = part_all + first * D + dg * 8;
+    typedef Part part8 __attribute__((ext_vector_type(8)));
     const float2 *lse = lse_all + first;
     const size_t n_rows = rows_seq, pstride = n_rows * D;
     out += ((size_t)seq * rows_seq + row) * D + dg * 8;
@@ -682,7 +694,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t *__restr
     float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     float wsum = 0.0f;
     for (int s0 = 0; s0 < splits; s0 += kMergeBatch) {
-        f16x8 v[kMergeBatch];
+        part8 v[kMergeBatch];
         float l[kMergeBatch], sc[kMergeBatch];
 #pragma unroll
         for (int j = 0; j < kMergeBatch; ++j) {
@@ -690,7 +702,7 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(const uint16_t *__restr
             const float2 ls = on ? lse[(size_t)(s0 + j) * n_rows] : make_float2(-INFINITY, 1.0f);
             l[j] = ls.x;
             sc[j] = ls.y;
-            v[j] = on ? *reinterpret_cast<const f16x8 *>(part + (size_t)(s0 + j) * pstride) : f16x8(0);
+            v[j] = on ? *reinterpret_cast<const part8 *>(part + (size_t)(s0 + j) * pstride) : part8(0);
         }
         float bm = l[0];
 #pragma unroll
@@ -901,12 +913,12 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
 
     if (attn_mfma_shape(dtype, D, Hkv)) {
         const bool ws_usable = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
-        const long long room = ws_usable ? attn_slot_room(T, Hq, D, workspace_bytes) : 0;
-        if (attn_lacks_scratch(batch, T, Hq, Hkv, D, kv_len, sum_L, room)) return DDTREE_ERR_WORKSPACE;
-        const AttnPlan p = attn_plan(batch, T, Hq, Hkv, D, kv_len, room);
+        const size_t scratch = ws_usable ? workspace_bytes : 0;
+        if (attn_lacks_scratch(batch, T, Hq, Hkv, D, kv_len, scratch)) return DDTREE_ERR_WORKSPACE;
+        const AttnPlan p = attn_plan(batch, T, Hq, Hkv, D, kv_len, scratch);
         if (!ws_ok(workspace, workspace_bytes, p.bytes)) return DDTREE_ERR_WORKSPACE;
         char *wsb = static_cast<char *>(workspace);
-        uint16_t *part = reinterpret_cast<uint16_t *>(wsb + p.part_off);
+        void *part = wsb + p.part_off;
         float2 *lse = reinterpret_cast<float2 *>(wsb + p.lse_off);
         AttnMergeArgs merge;
         int most = 1;
@@ -947,10 +959,16 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
         if (most > 1) {
             const int rows_seq = T * Hq;
             const dim3 grid((unsigned)((rows_seq * (D / 8) + 255) / 256), (unsigned)batch);
-            auto *kernel = D == kHD ? (most <= 8 ? attn_merge_kernel<kHD, 8> : attn_merge_kernel<kHD, 16>)
-                                    : (most <= 8 ? attn_merge_kernel<64, 8> : attn_merge_kernel<64, 16>);
-            DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, kernel, grid, dim3(256), 0, st, part, lse, merge, rows_seq,
-                       static_cast<uint16_t *>(out));
+            if (p.wide) {
+                auto *kernel = D == kHD ? (most <= 8 ? attn_merge_kernel<kHD, 8, float> : attn_merge_kernel<kHD, 16, float>)
+                                        : (most <= 8 ? attn_merge_kernel<64, 8, float> : attn_merge_kernel<64, 16, float>);
+                DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, kernel, grid, dim3(256), 0, st, static_cast<const float *>(part), lse,
+                           merge, rows_seq, static_cast<uint16_t *>(out));
+            } else {
+                auto *kernel = most <= 8 ? attn_merge_kernel<kHD, 8, _Float16> : attn_merge_kernel<kHD, 16, _Float16>;
+                DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, kernel, grid, dim3(256), 0, st, static_cast<const _Float16 *>(part), lse,
+                           merge, rows_seq, static_cast<uint16_t *>(out));
+            }
         }
         return launch_status();
     }

@@ -39,6 +39,7 @@ struct AttnPlan {
     // partial results: `slots` times the T * Hq rows of a sequence
     long long slots;
     size_t part_off, lse_off, bytes;
+    bool wide;            // they are fp32 rows, otherwise fp16 relative to their row's largest magnitude
     AttnSeqPlan seq[DDTREE_MAX_BATCH];
     long long items;      // workgroups with work
     // attn_wave_kernel (row_blocks > 0): `groups` row groups of rows_per_group <= 32 * row_blocks rows
@@ -50,10 +51,9 @@ struct AttnPlan {
     bool uneven;
 };
 bool attn_mfma_shape(int dtype, int D, int Hkv);
-// slot_room: partial results that the scratch at hand has room for.
-AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long slot_room);
-long long attn_slot_room(int T, int Hq, int D, size_t bytes);
-bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long sum_L, long long slot_room);
+// scratch: bytes at hand.
+AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, size_t scratch);
+bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, size_t scratch);
 
 // ---- attn_wave_kernel ----
 struct AttnWaveSeq {
@@ -64,9 +64,10 @@ struct AttnWaveSeq {
 struct AttnWaveArgs {
     const uint16_t *q, *k_cache, *v_cache, *k_tree, *v_tree;
     const uint64_t *mask;
-    uint16_t *out, *part;
+    uint16_t *out;
+    void *part;
     float2 *lse;
-    int32_t T, Hq, Hkv;
+    int32_t T, Hq, Hkv, wide;
     int32_t batch, items, run;           // work items; consecutive ones that an XCD takes at a time
     int32_t groups, rows_per_group;
     int32_t group_size;                  // G = Hq / Hkv
@@ -126,7 +127,7 @@ struct AttnMainArgs {
     // XCD x executes the whole tiles' work items xcd_start[x] .. xcd_start[x + 1] - 1, then the tail
     // blocks' tail_start[x] .. tail_start[x + 1] - 1
     int32_t xcd_start[9], tail_start[9];
-    int32_t batch, n_tiles, blk_base, blk_extra, uneven;
+    int32_t batch, n_tiles, blk_base, blk_extra, uneven, wide;
     int32_t group_size;                  // G = Hq / Hkv
     uint32_t g_magic, tiles_magic, extra_magic;  // reciprocals of G, n_tiles and blk_extra
     int32_t grid;

@@ -15,23 +15,39 @@ bool attn_mfma_shape(int dtype, int D, int Hkv)
     return dtype == DDTREE_DTYPE_BF16 && (D == kHD || D == 64) && Hkv <= 32768;
 }
 
-// Scratch of `slots` partial results: fp16 rows, then (log2-sum-exp, scale) per row.
-static void plan_scratch(AttnPlan &p, int T, int Hq, int D, long long slots)
+// Whether the partial results of a call are fp32 rows.  They are, except where few workgroups share long caches:
+// there, row tiles of the same height walked uncut leave compute units idle or a last round nearly empty, the key
+// ranges have to be cut for any speed at all, and fp16 relative to the row's largest magnitude (2^-11, the
+// result's own rounding is 2^-9) halves the bytes of many partials (a merge of 7 x 257 x 32 rows: 5.3 us).  A call
+// that does not have to be cut loses no bits where it is cut all the same.  Heads of 64: always fp32.
+static bool wide_partials(int batch, int T, int Hq, int Hkv, int D, long long sum_L)
+{
+    if (D != kHD) return true;
+    const long long tiles = (sum_L / batch + T) / kKT;
+    const long long items = (long long)batch * Hkv * (((long long)T * (Hq / Hkv) + 255) / 256), rounds = (items + 255) / 256;
+    for (long long s = 2; s <= 32 && s * 4 <= tiles; ++s)
+        if ((double)((items * s + 255) / 256) * (1.0 + 0.02 * (double)(s - 1)) < (double)(s * rounds)) return false;
+    return true;
+}
+
+// Scratch of `slots` partial results: their rows, then (log2-sum-exp, scale) per row.
+static void plan_scratch(AttnPlan &p, int T, int Hq, int D, bool wide, long long slots)
 {
     p.slots = slots;
+    p.wide = wide;
     p.part_off = p.lse_off = p.bytes = 0;
     if (slots == 0) return;
     const size_t rows = (size_t)slots * T * Hq;
-    p.lse_off = align_up(rows * D * 2, 256);
+    p.lse_off = align_up(rows * D * (wide ? 4 : 2), 256);
     p.bytes = align_up(p.lse_off + rows * 8, 256);
 }
 
 // Partial results that `bytes` of scratch have room for: the most that plan_scratch lays out in them.
-long long attn_slot_room(int T, int Hq, int D, size_t bytes)
+static long long slot_room(int T, int Hq, int D, bool wide, size_t bytes)
 {
-    long long slots = (long long)(bytes / ((size_t)T * Hq * (D * 2 + 8)));
+    const long long slots = (long long)(bytes / ((size_t)T * Hq * (D * (wide ? 4 : 2) + 8)));
     AttnPlan p{};
-    plan_scratch(p, T, Hq, D, slots);
+    plan_scratch(p, T, Hq, D, wide, slots);
     return p.bytes <= bytes ? slots : slots - 1;  // (each array is padded to 256 bytes)
 }
 
@@ -49,9 +65,15 @@ static long long main_slot_cap(int batch, int T, int Hq, int Hkv)
     return batch + 640 / (Hkv * ((M + 255) / 256));
 }
 
-// Time (us) of the merge of `slots` partial results: a launch, and reading them.  (Measured: 4.0 us for
+static long long slot_cap(int batch, int T, int Hq, int Hkv, int D)
+{
+    const long long wave = std::max(wave_slot_cap(batch, T, Hq, Hkv, 1), wave_slot_cap(batch, T, Hq, Hkv, 2));
+    return D == kHD ? std::max(wave, main_slot_cap(batch, T, Hq, Hkv)) : wave;
+}
+
+// Time (us) of the merge of `slots` partial results: a launch, and reading them.  (Measured, fp16: 4.0 us for
 // 3 x 65 x 32 rows of 128, 4.7 for 7 x 257 x 32, 22 for 32 x 129 x 64.)
-static double merge_us(long long slots, int T, int Hq, int D) { return 4.0 + (double)slots * T * Hq * D * 2 / 6.0e6; }
+static double merge_us(long long slots, int T, int Hq, int D, bool wide) { return 4.0 + (double)slots * T * Hq * D * (wide ? 4 : 2) / 6.0e6; }
 
 // Workgroups of a few sizes, longest first: `count` of `cost` us each.
 struct Sized {
@@ -80,14 +102,14 @@ static void longest_first(int32_t *order, const int32_t *kv_len, int batch)
 
 // attn_wave_kernel: every sequence's key range in pieces of about the same length, so that the pieces
 // of a ragged batch end together.
-static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, int row_blocks, long long slot_room)
+static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, int row_blocks, bool wide, long long room)
 {
     AttnPlan p{};
     const int M = T * (Hq / Hkv);
     p.row_blocks = row_blocks;
     p.groups = up(M, 32 * row_blocks);
     p.rows_per_group = up(M, p.groups);
-    const long long cap = std::min(slot_room, wave_slot_cap(batch, T, Hq, Hkv, row_blocks));
+    const long long cap = std::min(room, wave_slot_cap(batch, T, Hq, Hkv, row_blocks));
     const int tree = up(T, kSK);
     int32_t order[DDTREE_MAX_BATCH];
     longest_first(order, kv_len, batch);
@@ -112,7 +134,7 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
         }
         if (s > 1 && slots > cap) break;
         double cost = rounds_us(sized, batch);
-        cost = std::max(cost, 5.0 + std::max(l2_us, hbm_us)) + (s > 1 ? merge_us(slots, T, Hq, D) : 0.0);
+        cost = std::max(cost, 5.0 + std::max(l2_us, hbm_us)) + (s > 1 ? merge_us(slots, T, Hq, D, wide) : 0.0);
         if (cost < p.cost) p.cost = cost, best_c = c;
     }
     int first = 0;
@@ -124,14 +146,14 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
         cut = cut || si > 1;
     }
     p.items = (long long)first * Hkv * p.groups;
-    plan_scratch(p, T, Hq, D, cut ? first : 0);
+    plan_scratch(p, T, Hq, D, wide, cut ? first : 0);
     return p;
 }
 
 // attn_mfma_kernel.  Even form: row tiles of the same height.  Uneven form, where the blocks of 32 rows are
 // a few more than whole tiles of 8 (T = 257 with four heads per KV head: 33 blocks): whole tiles, and each
 // block left as a work item of its own with key ranges of its own (attn_wave_rows).
-static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_len, long long slot_room)
+static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_len, bool wide, long long room)
 {
     const int nblk = up(T * (Hq / Hkv), 32), full = nblk / 8, rem = nblk % 8;
     const int tree = up(T, kKT);
@@ -151,7 +173,7 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
     // Workgroups of one or two blocks (few rows over long caches) spend less on a tile.
     const bool low = nblk <= 2;
     const double fix = 11.0, tile_few = low ? 0.95 : 1.52, tile_all = low ? 0.95 : 1.9, tail_fix = 7.0, tail_step = 2.4;
-    const long long cap = std::min(slot_room, main_slot_cap(batch, T, Hq, Hkv));
+    const long long cap = std::min(room, main_slot_cap(batch, T, Hq, Hkv));
     AttnPlan best{};
     best.cost = 1e30;
     int best_c = nt_max, best_ct = 0;
@@ -196,7 +218,7 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
                     work += tails > 0 ? 1.5 * tail_longest * up((int)tails, 256) : 0.0;
                 else
                     work = std::max(work, sum / 256 + 0.5 * tail_longest);
-                const double cost = std::max(work, fix + hbm_us) + (cut ? merge_us(slots, T, Hq, kHD) : 0.0);
+                const double cost = std::max(work, fix + hbm_us) + (cut ? merge_us(slots, T, Hq, kHD, wide) : 0.0);
                 if (cost < best.cost) {
                     best.cost = cost;
                     best.uneven = uneven != 0;
@@ -219,7 +241,7 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
         first += best.seq[i].ranges;
         cut = cut || best.seq[i].ranges > 1;
     }
-    plan_scratch(best, T, Hq, kHD, cut ? first : 0);
+    plan_scratch(best, T, Hq, kHD, wide, cut ? first : 0);
     return best;
 }
 
@@ -228,31 +250,40 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
 // 401 x 600 21.8 / 25.7, 257 x 8192 102 / 51, 17 x 8192 17.5 / 20.7; 16 sequences of 10 nodes over up to 26246 keys, 16 and
 // 4 heads, 145 / 103, four of 19 over up to 8468 31 / 36.  Heads of 64: 32-row groups against 64-row
 // groups at 257 x 4096 36.9 / 28.5 (two rounds of workgroups against one), at 65 x 2047 11.5 / 13.0.
-AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long slot_room)
+AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, size_t scratch)
 {
-    const AttnPlan w = plan_wave(batch, T, Hq, Hkv, D, kv_len, 1, slot_room);
-    const AttnPlan m = D == kHD ? plan_main(batch, T, Hq, Hkv, kv_len, slot_room)
-                                : plan_wave(batch, T, Hq, Hkv, D, kv_len, 2, slot_room);
+    long long sum_L = 0;
+    for (int i = 0; i < batch; ++i) sum_L += kv_len[i];
+    const bool wide = wide_partials(batch, T, Hq, Hkv, D, sum_L);
+    const long long room = slot_room(T, Hq, D, wide, scratch);
+    const AttnPlan w = plan_wave(batch, T, Hq, Hkv, D, kv_len, 1, wide, room);
+    const AttnPlan m = D == kHD ? plan_main(batch, T, Hq, Hkv, kv_len, wide, room)
+                                : plan_wave(batch, T, Hq, Hkv, D, kv_len, 2, wide, room);
     return w.cost <= m.cost ? w : m;
 }
 
 // A long key range that few workgroups share is not walked uncut because a workspace is missing: such a call
 // is refused, unless its plan takes no scratch in any case.
-bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, long long sum_L, long long slot_room)
+bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, size_t scratch)
 {
     const long long tiles = (long long)batch * Hkv * (((long long)T * (Hq / Hkv) + 255) / 256);
-    if (D != kHD || slot_room >= 2LL * batch || tiles > 128 || (sum_L / batch + T) / kKT < 8) return false;
-    return attn_plan(batch, T, Hq, Hkv, D, kv_len, 1ll << 40).slots > slot_room;
+    if (D != kHD || tiles > 128) return false;
+    long long sum_L = 0;
+    for (int i = 0; i < batch; ++i) sum_L += kv_len[i];
+    if ((sum_L / batch + T) / kKT < 8 || slot_room(T, Hq, D, false, scratch) >= 2LL * batch) return false;
+    return attn_plan(batch, T, Hq, Hkv, D, kv_len, SIZE_MAX).bytes > scratch;
 }
 
 size_t attn_scratch_upper(int batch, int T, int Hq, int Hkv, int D)
 {
     if (!attn_mfma_shape(DDTREE_DTYPE_BF16, D, Hkv)) return 0;
-    long long slots = std::max(wave_slot_cap(batch, T, Hq, Hkv, 1), wave_slot_cap(batch, T, Hq, Hkv, 2));
-    if (D == kHD) slots = std::max(slots, main_slot_cap(batch, T, Hq, Hkv));
-    AttnPlan p{};
-    plan_scratch(p, T, Hq, D, slots);
-    return p.bytes;
+    const long long slots = slot_cap(batch, T, Hq, Hkv, D);
+    const long long tiles = (long long)batch * Hkv * (((long long)T * (Hq / Hkv) + 255) / 256);
+    // (fp32 partials of at most 128 row tiles: fewer than eight key tiles a sequence, no range shorter than two)
+    AttnPlan narrow{}, wide{};
+    plan_scratch(narrow, T, Hq, D, false, slots);
+    plan_scratch(wide, T, Hq, D, true, D == kHD && tiles <= 128 ? std::min(slots, 6LL * batch) : slots);
+    return std::max(D == kHD ? narrow.bytes : 0, wide.bytes);
 }
 
 // The lengths of the sequences are not known here: no key range is shorter than two key tiles, and a
@@ -262,13 +293,11 @@ size_t attn_scratch_bytes(int batch, int T, int Hq, int Hkv, int D, int dtype, l
     if (!attn_mfma_shape(dtype, D, Hkv)) return 0;
     if (batch == 1 && sum_L <= 0x7FFFFFFF) {
         const int32_t len = (int32_t)sum_L;
-        return attn_plan(1, T, Hq, Hkv, D, &len, 1ll << 40).bytes;
+        return attn_plan(1, T, Hq, Hkv, D, &len, SIZE_MAX).bytes;
     }
-    long long slots = std::max(wave_slot_cap(batch, T, Hq, Hkv, 1), wave_slot_cap(batch, T, Hq, Hkv, 2));
-    if (D == kHD) slots = std::max(slots, main_slot_cap(batch, T, Hq, Hkv));
-    slots = std::min(slots, batch + (sum_L + (T + 128LL) * batch) / (2 * kKT));
+    const long long slots = std::min(slot_cap(batch, T, Hq, Hkv, D), batch + (sum_L + (T + 128LL) * batch) / (2 * kKT));
     AttnPlan p{};
-    plan_scratch(p, T, Hq, D, slots);
+    plan_scratch(p, T, Hq, D, wide_partials(batch, T, Hq, Hkv, D, sum_L), slots);
     return p.bytes;
 }
 
@@ -278,7 +307,7 @@ bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_sta
 {
     if (p.items > (1ll << 28)) return false;
     const int G = Hq / Hkv;
-    args.T = T, args.Hq = Hq, args.Hkv = Hkv, args.batch = batch;
+    args.T = T, args.Hq = Hq, args.Hkv = Hkv, args.wide = p.wide ? 1 : 0, args.batch = batch;
     args.items = (int32_t)p.items;
     args.groups = p.groups;
     args.rows_per_group = p.rows_per_group;
@@ -312,6 +341,7 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
     const int G = Hq / Hkv, tails = p.uneven ? p.blk_extra : 0;
     args.batch = batch, args.n_tiles = p.n_tiles, args.blk_base = p.blk_base, args.blk_extra = p.blk_extra;
     args.uneven = p.uneven ? 1 : 0;
+    args.wide = p.wide ? 1 : 0;
     args.group_size = G;
     args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
     int32_t order[DDTREE_MAX_BATCH];
@@ -460,16 +490,16 @@ static int check_plan(const Shape &sh, int kind, long long room)
     }
     // the scratch that the library says a call uses is enough for the plan that unlimited scratch gives
     {
-        const AttnPlan free = attn_plan(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), 1ll << 40);
+        const AttnPlan free = attn_plan(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), SIZE_MAX);
         const size_t said = attn_scratch_bytes(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, DDTREE_DTYPE_BF16, sum);
-        const long long has = attn_slot_room(sh.T, sh.Hq, sh.D, said);
-        if (free.bytes > said || has < free.slots || (sh.batch == 1 && (free.bytes != said || has != free.slots))) return 12;
-        const AttnPlan again = attn_plan(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), has);
+        if (free.bytes > said || (sh.batch == 1 && free.bytes != said)) return 12;
+        const AttnPlan again = attn_plan(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), said);
         if (again.bytes != free.bytes || again.items != free.items || again.cost != free.cost) return 13;
-        if (attn_lacks_scratch(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), sum, has)) return 14;
+        if (attn_lacks_scratch(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), said)) return 14;
     }
-    const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len.data(), room)
-                                 : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), kind + 1, room);
+    const bool wide = wide_partials(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sum);
+    const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len.data(), wide, room)
+                                 : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), kind + 1, wide, room);
     if (p.slots > room || p.bytes > attn_scratch_upper(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D)) return 1;
     std::vector<Item> items;
     if (kind == 2) {

@@ -35,6 +35,11 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
 {
     using S = WaveShape<D, RB>;
     constexpr int KS = D / 16, DB = D / 32, NI = S::dma, NW = S::waves, NS = S::stages;
+    // Heads of 64: a weight is the sum of two bf16 numbers (2^-17 off), each with a product of its own, and the
+    // reference of a row its true maximum so far, so that weights stay within 1: what fp32 weights give on the
+    // vector ALUs, where these heads ran before.  The second product is hidden behind the waits for the keys.
+    constexpr bool TWO = D == 64;
+    constexpr float kSlack = TWO ? 0.0f : 16.0f;
     const int T = args.T, Hq = args.Hq, Hkv = args.Hkv;
     const float scale_log2e = args.scale_log2e;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -183,7 +188,7 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
     const bf16x8 sel = __builtin_bit_cast(bf16x8, (u32x4){sel_bits, sel_bits, sel_bits, sel_bits});
 
     floatx16 s[RB];
-    uint32_t p[RB][8];
+    uint32_t p[RB][8], p_low[RB][TWO ? 8 : 1];
     float m_use[RB];
     auto mfma_s = [&](int rb, auto I) __attribute__((always_inline)) {
         constexpr int i = decltype(I)::value;
@@ -204,8 +209,14 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
         const bf16x8 b = __builtin_bit_cast(bf16x8, (u32x4){p[rb][4 * t2], p[rb][4 * t2 + 1], p[rb][4 * t2 + 2], p[rb][4 * t2 + 3]});
         o[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, o[rb][db], 0, 0, 0);
         if constexpr (db == DB - 1) l_acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, b, l_acc[rb], 0, 0, 0);
+        if constexpr (TWO) {
+            const bf16x8 low = __builtin_bit_cast(
+                bf16x8, (u32x4){p_low[rb][4 * t2], p_low[rb][4 * t2 + 1], p_low[rb][4 * t2 + 2], p_low[rb][4 * t2 + 3]});
+            o[rb][db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, low, o[rb][db], 0, 0, 0);
+            if constexpr (db == DB - 1) l_acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(sel, low, l_acc[rb], 0, 0, 0);
+        }
     };
-    // mask of the block's scores, then its reference: the accumulators are rescaled only where a score
+    // mask of the block's scores, then its reference: heads of 128 rescale their accumulators only where a score
     // outgrows the reference by more than 2^16 (bf16 weights and fp32 sums carry that as well as 1)
     auto prepare = [&](int rb, bool masked, uint32_t w32) __attribute__((always_inline)) {
         if (masked) {
@@ -220,7 +231,7 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
 #pragma unroll
         for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[rb][v]);
         tmax *= scale_log2e;
-        if (__builtin_amdgcn_ballot_w64(tmax > m_ref[rb] + 16.0f) != 0ull) {
+        if (__builtin_amdgcn_ballot_w64(tmax > m_ref[rb] + kSlack) != 0ull) {
             const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(tmax), __float_as_uint(tmax), false, false);
             tmax = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
             const float m_new = fmaxf(m_ref[rb], tmax);
@@ -240,6 +251,10 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
         const float e0 = __builtin_amdgcn_exp2f(fmaf(s[rb][2 * i], scale_log2e, -m_use[rb]));
         const float e1 = __builtin_amdgcn_exp2f(fmaf(s[rb][2 * i + 1], scale_log2e, -m_use[rb]));
         p[rb][i] = f2bf_pair(e0, e1);
+        if constexpr (TWO) {
+            p_low[rb][i] = f2bf_pair(e0 - __uint_as_float(p[rb][i] << 16), e1 - __uint_as_float(p[rb][i] & 0xFFFF0000u));
+            asm volatile("" : "+v"(p_low[rb][i]));
+        }
         asm volatile("" : "+v"(p[rb][i]));
     };
 
@@ -359,7 +374,22 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
             }
             continue;
         }
-        // a partial is fp16 relative to its row's largest magnitude (see attn.hip)
+        const size_t slot_row = (size_t)(item.first_slot + item.split) * rows_seq + rs;
+        float2 *const lse = args.lse + (size_t)item.first_slot * rows_seq + rs;
+        const float lse2 = inv > 0.0f ? m + __builtin_amdgcn_logf(l) : -INFINITY;
+        // key ranges that this row does not have (rows of attn_mfma_kernel's whole tiles have more): empty
+        if (r < r1 && c8 == 0 && item.split == 0)
+            for (int sx = item.splits; sx < item.ranges; ++sx) lse[(size_t)sx * rows_seq] = make_float2(-INFINITY, 1.0f);
+        if (TWO || args.wide) {
+            if (r < r1) {
+                float4 *const dst = reinterpret_cast<float4 *>(static_cast<float *>(args.part) + slot_row * D + c8);
+                dst[0] = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
+                dst[1] = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
+                if (c8 == 0) lse[(size_t)item.split * rows_seq] = make_float2(lse2, 1.0f);
+            }
+            continue;
+        }
+        // an fp16 partial is relative to its row's largest magnitude (see attn.hip)
         float amax = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(acc[e]));
@@ -372,14 +402,8 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
             uint4 val;
             val.x = f2h_pair(acc[0] * mul, acc[1] * mul), val.y = f2h_pair(acc[2] * mul, acc[3] * mul);
             val.z = f2h_pair(acc[4] * mul, acc[5] * mul), val.w = f2h_pair(acc[6] * mul, acc[7] * mul);
-            *reinterpret_cast<uint4 *>(args.part + ((size_t)(item.first_slot + item.split) * rows_seq + rs) * D + c8) = val;
-            if (c8 == 0) {
-                float2 *const lse = args.lse + (size_t)item.first_slot * rows_seq + rs;
-                lse[(size_t)item.split * rows_seq] = make_float2(inv > 0.0f ? m + __builtin_amdgcn_logf(l) : -INFINITY, scale);
-                // key ranges that this row does not have (rows of attn_mfma_kernel's whole tiles have more): empty
-                if (item.split == 0)
-                    for (int sx = item.splits; sx < item.ranges; ++sx) lse[(size_t)sx * rows_seq] = make_float2(-INFINITY, 1.0f);
-            }
+            *reinterpret_cast<uint4 *>(static_cast<uint16_t *>(args.part) + slot_row * D + c8) = val;
+            if (c8 == 0) lse[(size_t)item.split * rows_seq] = make_float2(lse2, scale);
         }
     }
 }

@@ -118,6 +118,32 @@ def test_heads_of_64_need_no_scratch():
     assert (a.float() - b.float()).abs().max().item() < 1e-2
 
 
+@pytest.mark.parametrize("scale", [1.0, 2.0 ** 116])
+@pytest.mark.parametrize("T,Ls,Hq,Hkv,scratch", [(65, [2047], 16, 4, True), (257, [4096], 32, 8, True), (33, [900, 31, 2500], 12, 4, True),
+                                                 (65, [3000], 8, 2, False), (200, [31], 4, 1, True), (257, [4096], 8, 1, True)])
+def test_heads_of_64_are_as_exact_as_their_result_type(T, Ls, Hq, Hkv, scratch, scale):
+    """fp32 weights, sums and partial results: what is left is the rounding of the result to bf16 (weights of 8 bits
+    or partials of 11 add a fifth to a half of it).  With values of 2^116 too: weights above 1 would overflow."""
+    batch, rng = len(Ls), np.random.default_rng(T)
+    parts = [di.attn_tensors(80 + b, T, Ls[b], Hq, Hkv, 64, "bf16") for b in range(batch)]
+    masks = [_tree_mask(rng, T) for _ in Ls]
+    off = np.concatenate([[0], np.cumsum(Ls)]).astype(np.int32)
+    q, kc, vc, kt, vt = (np.concatenate([p[i] for p in parts]) for i in range(5))
+    q = 3.0 * q  # (scores of a few units: references move)
+    q, s = di.round_to_bf16(q.astype(np.float32)), np.float32(scale)
+    got = dd.verify_attn(*(gu.bf16_dev(a) for a in (q, kc, vc * s, kt, vt * s)), gu.to_dev(np.stack(masks).view(np.int64)), off,
+                         batch, T, Hq, Hkv, 64, 0.125, dd.DTYPE_BF16,
+                         dd.Workspace(batch, 1, 8, T - 1, Hq, Hkv, 64, int(off[-1])) if scratch else None)
+    got = got.double().cpu().numpy().reshape(batch, T, Hq, 64) / scale
+    err, rounding = 0.0, 0.0
+    for b in range(batch):
+        pairs = np.stack([rng.integers(0, T, 200), rng.integers(0, Hq, 200)], axis=1).astype(np.int32)
+        ref = np.asarray(oracle.verify_attn(q[b * T:(b + 1) * T], *parts[b][1:], masks[b], pairs=pairs), np.float64)
+        err += ((got[b][pairs[:, 0], pairs[:, 1]] - ref) ** 2).sum()
+        rounding += ((di.round_to_bf16(ref.astype(np.float32)).astype(np.float64) - ref) ** 2).sum()
+    assert np.sqrt(err) < 1.03 * np.sqrt(rounding), (np.sqrt(err), np.sqrt(rounding))
+
+
 class _Scratch:
     """A workspace of exactly nbytes."""
 
