@@ -62,7 +62,8 @@ int ddtree_version(void);
 const char *ddtree_error_string(int code);
 
 /*
- * Scratch size, in bytes, that covers every entry point for the given problem:
+ * Scratch size, in bytes, that covers every entry point for the given problem and for every smaller one
+ * (fewer sequences, draft positions, tokens or nodes with the same heads):
  * max_sum_L is an upper bound on the total number of cache rows over the batch.
  * Returns 0 if the shape is not supported.  Pure host arithmetic.
  */

@@ -37,6 +37,13 @@ AcceptPlan accept_plan(int batch, int T, int V)
     return p;
 }
 
+// A bound on accept_plan(...).bytes over every call of at most this many rows and elements.
+size_t accept_scratch_upper(int batch, int T, int V)
+{
+    const long long rows = (long long)batch * T;
+    return align_up((size_t)std::min(rows + 3071, rows * std::max(1, V / 4096)) * 8, 256);
+}
+
 struct ArgPart {
     float val;
     int32_t idx;

@@ -1,5 +1,7 @@
 // Library-level entry points of the C ABI that belong to no single stage: version, error text,
 // scratch sizing, and the event-timing hook used by the benchmark.
+#include <algorithm>
+
 #include "common.hpp"
 
 namespace ddt {
@@ -52,12 +54,10 @@ extern "C" size_t ddtree_workspace_bytes(int batch, int B, int V, int N, int Hq,
         return 0;
     const int K = N < V ? N : V;
     const int T = N + 1;
-    TopkPlan tp = topk_plan(batch, B, V, K);
-    if (!tp.ok) return 0;
-    size_t need = tp.bytes;
+    size_t need = topk_scratch_upper(batch, B, V, K);
     const size_t a = attn_scratch_upper(batch, T, Hq, Hkv, D);
     if (a > need) need = a;
-    const size_t c = accept_plan(batch, T, V).bytes;
+    const size_t c = accept_scratch_upper(batch, T, V);
     if (c > need) need = c;
     return need < 256 ? 256 : need;
 }
@@ -147,7 +147,25 @@ extern "C" int ddtree_selftest_host(void)
                 if (p.stat_off < per * p.maxima * 4 || p.hot_off < p.stat_off + per * 24 || p.bytes < p.hot_off + per * p.hot_cap * 8)
                     return 10010;
                 if ((p.stat_off & 255u) || (p.hot_off & 255u) || (p.bytes & 255u)) return 10011;
+                // a workspace for these sizes serves every smaller call: all K of this shape, fewer rows, shorter rows
+                if (rows <= DDTREE_MAX_B) {
+                    const size_t have = ddtree_workspace_bytes(1, rows, V, K, 1, 1, 96, 0);
+                    for (int k = 1; k <= K; ++k)
+                        if (topk_plan(1, rows, V, k).bytes > have) return 10012;
+                    for (int r = 1; r < rows; ++r)
+                        for (int k : {1, K / 2 + 1, K})
+                            if (topk_plan(1, r, V, k).bytes > have) return 10013;
+                    for (int v : Vs)
+                        if (v < V && topk_plan(1, rows, v, std::min(v, K)).bytes > have) return 10014;
+                }
             }
+    for (int batch : {1, 3, 16, 64})  // many rows, and odd ones
+        for (int B : {1, 5, 16, 17, 32})
+            for (int V : Vs)
+                for (int K : Ks)
+                    for (int b = 1; b <= batch && K <= V; b += 1 + b / 5)
+                        for (int k = K; k >= 1; k -= 1 + k / 7)
+                            if (topk_plan(b, B, V, k).bytes > topk_scratch_upper(batch, B, V, K)) return 10015;
     // accept: segments tile the row in multiples of four, scratch holds one partial per segment
     for (int V : Vs)
         for (int T : {2, 17, 65, 257, 513, 1025})
@@ -156,6 +174,9 @@ extern "C" int ddtree_selftest_host(void)
                 if (p.seg_len % 4 != 0 || p.seg_len < 1 || p.splits < 1) return 10021;
                 if ((long long)(p.splits - 1) * p.seg_len >= V || (long long)p.splits * p.seg_len < V) return 10022;
                 if (p.bytes < (size_t)batch * T * p.splits * 8 || (p.bytes & 255u)) return 10023;
+                for (int b = 1; b <= batch; b += 1 + b / 3)
+                    for (int t = T; t >= 2; t -= 1 + t / 5)
+                        if (accept_plan(b, t, V).bytes > accept_scratch_upper(batch, T, V)) return 10024;
             }
     return 0;
 }

@@ -51,6 +51,7 @@ struct TopkPlan {
 };
 constexpr int kTopkChunkMax = 6144;  // elements held in registers by one chunk workgroup
 TopkPlan topk_plan(int batch, int B, int V, int K);
+size_t topk_scratch_upper(int batch, int B, int V, int K);
 
 // ---- attention scratch (bytes): what ddtree_verify_attn may use for a shape and total cache length,
 //      and for any cache length ----
@@ -64,6 +65,7 @@ struct AcceptPlan {
     size_t part_off, bytes;
 };
 AcceptPlan accept_plan(int batch, int T, int V);
+size_t accept_scratch_upper(int batch, int T, int V);
 
 // ---- optional event timing around kernel launches (see ddtree_profile_enable) ----
 struct Profiler {

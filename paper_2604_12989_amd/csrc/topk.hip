@@ -85,6 +85,20 @@ TopkPlan topk_plan(int batch, int B, int V, int K)
     return p;
 }
 
+// A bound on topk_plan(...).bytes over every call of at most this many rows, elements and ranks: a workspace made
+// for the largest call serves the smaller ones, whose chunks may be more and whose hot lists may be longer (there
+// are none where K is large).  A chunk leaves 64 maxima, statistics and 64 hot places; beyond these, groups of
+// fewer than eight threads leave less than 6 K maxima a row (512 in a row of one chunk), and a hot list of c
+// elements wanted has at most 64 + 3.2 (c - 12) places, c - 12 being 2.2 K / chunks; neither exceeds 512 a chunk.
+size_t topk_scratch_upper(int batch, int B, int V, int K)
+{
+    const long long rows = (long long)batch * B, c_min = (V + kTopkChunkMax - 1) / kTopkChunkMax;
+    const long long chunks = std::max(rows * c_min, std::min({rows + 511, 64 * rows, rows * std::max(1, V / 1024)}));
+    const long long maxima = std::min(64 * chunks + rows * (6 * K + kChunkThreads), (long long)kChunkThreads * chunks);
+    const long long places = std::min(64 * chunks + rows * (7 * K + K / 16), 512 * chunks);
+    return 3 * 256 + (size_t)maxima * sizeof(float) + (size_t)chunks * sizeof(ChunkStat) + (size_t)places * sizeof(uint64_t);
+}
+
 // ------------------------------------------------------------------------------------------
 // Block-wide helpers.  NT = threads per workgroup (multiple of 64).
 // ------------------------------------------------------------------------------------------
