@@ -270,7 +270,8 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
                 const bool this_one = need && h[e] >= limit(xe[e]);
                 if (__builtin_amdgcn_ballot_w64(this_one) == 0ull) continue;
                 const float k = sample_key(xe[e], h[e], sa);
-                if (this_one && k > bv) {
+                // (the single elements behind the 16-byte loads came first: of equal keys the lower id)
+                if (this_one && (k > bv || (k == bv && ia + e < bi))) {
                     bv = k;
                     bi = ia + e;
                 }
