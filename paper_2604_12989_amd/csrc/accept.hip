@@ -218,9 +218,10 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
     if (tid == 0) s_best = 0u;
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
-    // the scalar elements in front of and behind the 16-byte loads
+    // the scalar elements in front of the 16-byte loads, and those behind them, which are looked at last: elements are
+    // taken in the order of their ids, so that of equal keys the lowest stays
     if (tid < head) arg_update(bv, bi, sample_key(p[tid], hash(start + tid), sa), start + tid);
-    if (tid < n - tail0) arg_update(bv, bi, sample_key(p[tail0 + tid], hash(start + tail0 + tid), sa), start + tail0 + tid);
+    const float behind = tid < n - tail0 ? p[tail0 + tid] : 0.0f;
     __syncthreads();
     {
         // for u >= 1/2, -ln u <= 2 ln 2 (1 - u), so g >= -ln(1.387 (1 - u))
@@ -270,8 +271,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
                 const bool this_one = need && h[e] >= limit(xe[e]);
                 if (__builtin_amdgcn_ballot_w64(this_one) == 0ull) continue;
                 const float k = sample_key(xe[e], h[e], sa);
-                // (the single elements behind the 16-byte loads came first: of equal keys the lower id)
-                if (this_one && (k > bv || (k == bv && ia + e < bi))) {
+                if (this_one && k > bv) {
                     bv = k;
                     bi = ia + e;
                 }
@@ -282,6 +282,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
             }
         }
     }
+    if (tid < n - tail0) arg_update(bv, bi, sample_key(behind, hash(start + tail0 + tid), sa), start + tail0 + tid);
     workgroup_best(bv, bi, s_v, s_i);
     if (tid == 0) part[rowi * splits + seg] = ArgPart{bv, bi};
 }
