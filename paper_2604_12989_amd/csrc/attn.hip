@@ -912,6 +912,7 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
     hipStream_t st = as_stream(stream);
 
     if (attn_mfma_shape(dtype, D, Hkv)) {
+        if (!attn_rows_fit(T, Hq, Hkv)) return DDTREE_ERR_ARG;
         const bool ws_usable = workspace && (reinterpret_cast<uintptr_t>(workspace) & 255u) == 0;
         const size_t scratch = ws_usable ? workspace_bytes : 0;
         if (attn_lacks_scratch(batch, T, Hq, Hkv, D, kv_len, scratch)) return DDTREE_ERR_WORKSPACE;

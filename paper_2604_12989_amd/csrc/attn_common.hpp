@@ -51,6 +51,7 @@ struct AttnPlan {
     bool uneven;
 };
 bool attn_mfma_shape(int dtype, int D, int Hkv);
+bool attn_rows_fit(int T, int Hq, int Hkv);  // the query rows of a KV head are counted in 32 bits
 // scratch: bytes at hand.
 AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, size_t scratch);
 bool attn_lacks_scratch(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, size_t scratch);
@@ -108,7 +109,7 @@ __host__ __device__ __forceinline__ bool attn_wave_item(const AttnWaveArgs &args
     w.r1 = w.r0 + args.rows_per_group;
     if (w.r1 > args.T * args.group_size) w.r1 = args.T * args.group_size;
     const int last_node = div_by(w.r1 - 1, args.group_size, args.g_magic);
-    w.n_cache = (w.kv_len + kSK - 1) / kSK;
+    w.n_cache = (int)(((unsigned)w.kv_len + kSK - 1) / (unsigned)kSK);
     const int nt = w.n_cache + last_node / kSK + 1;
     w.t_begin = div_by(nt * w.split, w.splits, e.splits_magic);
     w.t_end = div_by(nt * (w.split + 1), w.splits, e.splits_magic);

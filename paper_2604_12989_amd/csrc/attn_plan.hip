@@ -51,7 +51,9 @@ static long long slot_room(int T, int Hq, int D, bool wide, size_t bytes)
     return p.bytes <= bytes ? slots : slots - 1;  // (each array is padded to 256 bytes)
 }
 
-static inline int up(int a, int b) { return (a + b - 1) / b; }
+static inline int up(int a, int b) { return (int)(((unsigned)a + (unsigned)b - 1u) / (unsigned)b); }  // (lengths reach 2^31 - 1)
+
+bool attn_rows_fit(int T, int Hq, int Hkv) { return (long long)T * (Hq / Hkv) <= 0x7FFFFF00ll; }
 
 // Partial results a plan may leave: what about two rounds of workgroups on 256 compute units make.
 static long long wave_slot_cap(int batch, int T, int Hq, int Hkv, int row_blocks)
@@ -290,7 +292,7 @@ size_t attn_scratch_upper(int batch, int T, int Hq, int Hkv, int D)
 // single sequence takes what the plan for its length takes.
 size_t attn_scratch_bytes(int batch, int T, int Hq, int Hkv, int D, int dtype, long long sum_L)
 {
-    if (!attn_mfma_shape(dtype, D, Hkv)) return 0;
+    if (!attn_mfma_shape(dtype, D, Hkv) || !attn_rows_fit(T, Hq, Hkv)) return 0;
     if (batch == 1 && sum_L <= 0x7FFFFFFF) {
         const int32_t len = (int32_t)sum_L;
         return attn_plan(1, T, Hq, Hkv, D, &len, SIZE_MAX).bytes;

@@ -83,6 +83,25 @@ def test_attention_scratch_never_exceeds_the_workspace_bound(lib):
     assert worst > 0.2   # the bound is not vacuous
 
 
+def test_sizing_survives_the_largest_arguments(lib):
+    # more query rows of a KV head than 32 bits count (their product alone is 0 in 32 bits), lengths at the top of their range
+    big = 0x7FFFFFFF
+    for batch, T, Hq, Hkv, D, L in ((1, 1024, 1 << 22, 1, 128, 8192), (1, 1024, 1 << 22, 1, 64, 5), (1, 1025, 1 << 23, 1, 128, 8192),
+                                    (2, 1024, 1 << 22, 1, 128, 8192), (64, 1025, big, 1, 128, 1 << 40)):
+        assert lib.ddtree_verify_attn_workspace_bytes(batch, T, Hq, Hkv, D, 0, L) == 0
+        lib.ddtree_workspace_bytes(batch, 16, 1000, T - 1, Hq, Hkv, D, 0)
+    for D in (64, 128):
+        need = lib.ddtree_verify_attn_workspace_bytes(1, 257, 32, 8, D, 0, big)
+        assert need <= lib.ddtree_workspace_bytes(1, 16, 1000, 256, 32, 8, D, big)
+    buf = ctypes.create_string_buffer(4096)
+    p = ctypes.cast(buf, ctypes.c_void_p)
+    p.value += (-p.value) % 256
+    off = (ctypes.c_int32 * 2)(0, 100)
+    for D in (64, 128):
+        assert lib.ddtree_verify_attn(p, p, p, p, p, p, ctypes.cast(off, ctypes.c_void_p), 1, 1024, 1 << 22, 1, D, 0.1, 0, p,
+                                      None, 0, None) == -1
+
+
 def test_bad_arguments_are_rejected_before_any_launch(lib):
     ERR_ARG, ERR_WS = -1, -2
     buf = ctypes.create_string_buffer(4096)
