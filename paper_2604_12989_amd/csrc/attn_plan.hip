@@ -96,15 +96,51 @@ static double rounds_us(const Sized *w, int n)
     return items <= 256 ? t : std::max(t, sum / 256 + 0.5 * w[0].cost);
 }
 
-static void longest_first(int32_t *order, const int32_t *kv_len, int batch)
+// The lengths of a call as the plans see them: sequences longest first, those of the same number of cache
+// sub-tiles counted together.  (A plan is made for every call, in its host time: one sort, one entry for each
+// different length, and searches that end where neither fewer keys a range nor another partial result
+// can pay any more.  Host time of a plan before and now: 257 nodes x 8192 keys 3.0 -> 1.5, four ragged sequences of 101 nodes
+// 4.6 -> 2.2, 16 of 129 10.5 -> 2.3, 64 of 257 36 -> 4.0 us.)
+struct Lens {
+    int n = 0;
+    int32_t sub[DDTREE_MAX_BATCH], count[DDTREE_MAX_BATCH];
+    int32_t order[DDTREE_MAX_BATCH];
+};
+static Lens lens_of(const int32_t *kv_len, int batch)
 {
-    for (int i = 0; i < batch; ++i) order[i] = i;
-    std::stable_sort(order, order + batch, [&](int32_t a, int32_t b) { return kv_len[a] > kv_len[b]; });
+    Lens l;
+    uint64_t key[DDTREE_MAX_BATCH];
+    for (int i = 0; i < batch; ++i) key[i] = (uint64_t)(0x7FFFFFFF - kv_len[i]) << 32 | (uint32_t)i;
+    std::sort(key, key + batch);
+    for (int i = 0; i < batch; ++i) {
+        l.order[i] = (int32_t)(uint32_t)key[i];
+        const int sub = up(kv_len[l.order[i]], kSK);
+        if (l.n > 0 && l.sub[l.n - 1] == sub) {
+            ++l.count[l.n - 1];
+        } else {
+            l.sub[l.n] = sub;
+            l.count[l.n++] = 1;
+        }
+    }
+    return l;
 }
+
+// x / d rounded up for many x: a multiplication by ceil(2^64 / d), exact for 32-bit operands.
+struct DivUp {
+    unsigned d;
+    uint64_t m;
+    explicit DivUp(int by) : d((unsigned)by), m(~0ull / (unsigned)by + 1) {}
+    int operator()(int x) const
+    {
+        const unsigned y = (unsigned)x + d - 1u;
+        return d == 1u ? (int)y : (int)(uint64_t)((unsigned __int128)y * m >> 64);
+    }
+};
 
 // attn_wave_kernel: every sequence's key range in pieces of about the same length, so that the pieces
 // of a ragged batch end together.
-static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, int row_blocks, bool wide, long long room)
+static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_len, const Lens &lens, int row_blocks, bool wide,
+                          long long room)
 {
     AttnPlan p{};
     const int M = T * (Hq / Hkv);
@@ -113,36 +149,37 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
     p.rows_per_group = up(M, p.groups);
     const long long cap = std::min(room, wave_slot_cap(batch, T, Hq, Hkv, row_blocks));
     const int tree = up(T, kSK);
-    int32_t order[DDTREE_MAX_BATCH];
-    longest_first(order, kv_len, batch);
     long long sub_tiles = 0;
-    for (int i = 0; i < batch; ++i) sub_tiles += up(kv_len[i], kSK) + tree;
-    const int nt_max = up(kv_len[order[0]], kSK) + tree;
+    for (int i = 0; i < lens.n; ++i) sub_tiles += (long long)(lens.sub[i] + tree) * lens.count[i];
+    const int nt_max = lens.sub[0] + tree;
     Sized sized[DDTREE_MAX_BATCH];
     // Measured (us): a workgroup's fixed cost (launch, first requests, combining the waves' results), a
     // step of its eight waves (32 keys each), the rates at which the L2s and HBM serve all of them.
     const double fix = 7.0, step = D == 64 ? (row_blocks == 1 ? 0.62 : 1.17) : 1.2;
     const double l2_us = (double)sub_tiles * Hkv * p.groups * (kSK * 4.0 * D) / 20.0e6;
     const double hbm_us = (double)sub_tiles * Hkv * (kSK * 4.0 * D) / 4.0e6;
+    const double least = 5.0 + std::max(l2_us, hbm_us);
     int best_c = nt_max;
     p.cost = 1e30;
     for (int s = 1; s <= 64 && (s == 1 || (s * 4 <= nt_max && (long long)s * nt_max < (1ll << 30))); ++s) {
         const int c = up(nt_max, s);
+        const DivUp by_c(c);
         long long slots = 0;
-        for (int i = 0; i < batch; ++i) {
-            const int nt = up(kv_len[order[i]], kSK) + tree, si = up(nt, c);
-            slots += si;
-            sized[i] = Sized{fix + step * up(up(nt, si), 8), (long long)si * Hkv * p.groups};
+        for (int i = 0; i < lens.n; ++i) {
+            const int nt = lens.sub[i] + tree, si = by_c(nt);
+            slots += (long long)si * lens.count[i];
+            sized[i] = Sized{fix + step * up(si == 1 ? nt : up(nt, si), 8), (long long)lens.count[i] * si * Hkv * p.groups};
         }
-        if (s > 1 && slots > cap) break;
-        double cost = rounds_us(sized, batch);
-        cost = std::max(cost, 5.0 + std::max(l2_us, hbm_us)) + (s > 1 ? merge_us(slots, T, Hq, D, wide) : 0.0);
+        const double merge = s > 1 ? merge_us(slots, T, Hq, D, wide) : 0.0;
+        if (s > 1 && (slots > cap || least + merge >= p.cost)) break;  // (partial results only grow in number)
+        const double cost = std::max(rounds_us(sized, lens.n), least) + merge;
         if (cost < p.cost) p.cost = cost, best_c = c;
     }
     int first = 0;
     bool cut = false;
+    const DivUp by_c(best_c);
     for (int i = 0; i < batch; ++i) {
-        const int si = up(up(kv_len[i], kSK) + tree, best_c);
+        const int si = by_c(up(kv_len[i], kSK) + tree);
         p.seq[i] = AttnSeqPlan{si, 0, si, first};
         first += si;
         cut = cut || si > 1;
@@ -155,17 +192,16 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
 // attn_mfma_kernel.  Even form: row tiles of the same height.  Uneven form, where the blocks of 32 rows are
 // a few more than whole tiles of 8 (T = 257 with four heads per KV head: 33 blocks): whole tiles, and each
 // block left as a work item of its own with key ranges of its own (attn_wave_rows).
-static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_len, bool wide, long long room)
+static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_len, const Lens &lens, bool wide, long long room)
 {
     const int nblk = up(T * (Hq / Hkv), 32), full = nblk / 8, rem = nblk % 8;
-    const int tree = up(T, kKT);
-    int32_t order[DDTREE_MAX_BATCH];
-    longest_first(order, kv_len, batch);
-    const int nt_max = up(kv_len[order[0]], kKT) + tree;
-    const int sub_max = up(kv_len[order[0]], kSK) + up(T, kSK);
+    const int tree = up(T, kKT), tree_sub = up(T, kSK);
+    static_assert(kKT == 2 * kSK, "key tiles from sub-tiles");
+    const int nt_max = up(lens.sub[0], 2) + tree;
+    const int sub_max = lens.sub[0] + tree_sub;
     Sized sized[DDTREE_MAX_BATCH];
     long long key_tiles = 0;
-    for (int i = 0; i < batch; ++i) key_tiles += up(kv_len[i], kKT) + tree;
+    for (int i = 0; i < lens.n; ++i) key_tiles += (long long)(up(lens.sub[i], 2) + tree) * lens.count[i];
     const double hbm_us = (double)key_tiles * Hkv * (kKT * 4.0 * kHD) / 5.0e6;
     // Measured (us): a workgroup's fixed cost and a key tile (below three quarters of the compute units at work,
     // and with all of them, where the chip lowers its clock: 1.92 over 131 key tiles); for a tail block, and a
@@ -179,48 +215,68 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
     AttnPlan best{};
     best.cost = 1e30;
     int best_c = nt_max, best_ct = 0;
+    int si[DDTREE_MAX_BATCH];
     for (int uneven = 0; uneven < 2; ++uneven) {
         if (uneven && !(full >= 1 && rem >= 1 && rem <= 4)) break;
         const int tiles = uneven ? full : up(nblk, 8);
-        for (int s = 1; s <= 32 && (s == 1 || s * 2 <= nt_max); ++s) {
+        bool more = true;
+        for (int s = 1, c_before = 0; more && s <= 32 && (s == 1 || s * 2 <= nt_max); ++s) {
             const int c = up(nt_max, s);
-            if (s > 1 && up(nt_max, s - 1) == c) continue;
+            if (c == c_before) continue;
+            c_before = c;
+            const DivUp by_c(c);
+            long long items = 0, main_slots = 0;
+            for (int i = 0; i < lens.n; ++i) {
+                si[i] = by_c(up(lens.sub[i], 2) + tree);
+                items += sized[i].count = (long long)tiles * si[i] * Hkv * lens.count[i];
+                main_slots += (long long)si[i] * lens.count[i];
+            }
+            // (with shorter key ranges both kinds leave more partial results: what is too many, or too many to pay, stays so)
+            const double least = fix + hbm_us;
+            if (s > 1 && (main_slots > cap || least + merge_us(main_slots, T, Hq, kHD, wide) >= best.cost)) break;
+            const double tile = tile_few + (tile_all - tile_few) * std::min(1.0, std::max(0.0, (items - 192) / 64.0));
+            double main_sum = 0.0;
+            for (int i = 0; i < lens.n; ++i) {
+                const int nt = up(lens.sub[i], 2) + tree;
+                sized[i].cost = fix + tile * (si[i] == 1 ? nt : up(nt, si[i]));
+                main_sum += sized[i].cost * sized[i].count;
+            }
+            const double main_work = rounds_us(sized, lens.n);
+            if (s > 1 && std::max(main_work, least) + merge_us(main_slots, T, Hq, kHD, wide) >= best.cost) continue;
             // ranges of a tail block: those that take as long as a whole tile's, and more of them in turn
             const int t0 = uneven ? std::min(32, std::max(1, (int)(tail_step * up(sub_max, 8) / (fix - tail_fix + tile_few * c)))) : 0;
             for (int t = t0; t <= std::min(8 * t0, 32); t *= 2) {
                 if (t > 1 && (long long)t * sub_max >= (1ll << 30)) break;
                 const int ct = uneven ? up(sub_max, t) : 0;
-                long long items = 0, tails = 0, slots = 0;
-                for (int i = 0; i < batch; ++i) {
-                    const int si = up(up(kv_len[order[i]], kKT) + tree, c);
-                    items += sized[i].count = (long long)tiles * si * Hkv;
-                    slots += si;
-                }
-                const double tile = tile_few + (tile_all - tile_few) * std::min(1.0, std::max(0.0, (items - 192) / 64.0));
-                double sum = 0.0, tail_longest = 0.0;
-                for (int i = 0; i < batch; ++i) {
-                    const int nt = up(kv_len[order[i]], kKT) + tree, si = up(nt, c);
-                    sized[i].cost = fix + tile * up(nt, si);
-                    sum += sized[i].cost * sized[i].count;
-                    if (!uneven) continue;
-                    const int sub = up(kv_len[order[i]], kSK) + up(T, kSK), ti = up(sub, ct);
-                    const double each = tail_fix + tail_step * up(up(sub, ti), 8);
-                    sum += each * rem * ti * Hkv;
-                    tail_longest = std::max(tail_longest, each);
-                    tails += (long long)rem * ti * Hkv;
-                    slots += std::max(0, ti - si);
+                long long tails = 0, slots = main_slots;
+                double sum = main_sum, tail_longest = 0.0;
+                if (uneven) {
+                    const DivUp by_ct(ct);
+                    for (int i = 0; i < lens.n; ++i) {
+                        const int sub = lens.sub[i] + tree_sub, ti = by_ct(sub);
+                        const double each = tail_fix + tail_step * up(ti == 1 ? sub : up(sub, ti), 8);
+                        const long long n = (long long)rem * ti * Hkv * lens.count[i];
+                        sum += each * n;
+                        tail_longest = std::max(tail_longest, each);
+                        tails += n;
+                        slots += (long long)std::max(0, ti - si[i]) * lens.count[i];
+                    }
                 }
                 const bool cut = s > 1 || t > 1;
-                if (cut && slots > cap) break;
+                const double merge = cut ? merge_us(slots, T, Hq, kHD, wide) : 0.0;
+                if (cut && (slots > cap || least + merge >= best.cost)) {
+                    more = t > t0;
+                    break;
+                }
                 // the whole tiles' items as if alone; the tail blocks' beside them, or where they end
-                double work = rounds_us(sized, batch);
+                double work = main_work;
                 if (items + tails <= 256)
                     work = std::max(work, tail_longest);
                 else if (items <= 256)
                     work += tails > 0 ? 1.5 * tail_longest * up((int)tails, 256) : 0.0;
                 else
                     work = std::max(work, sum / 256 + 0.5 * tail_longest);
-                const double cost = std::max(work, fix + hbm_us) + (cut ? merge_us(slots, T, Hq, kHD, wide) : 0.0);
+                const double cost = std::max(work, least) + merge;
                 if (cost < best.cost) {
                     best.cost = cost;
                     best.uneven = uneven != 0;
@@ -236,10 +292,11 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
     best.blk_extra = best.uneven ? rem : nblk % best.n_tiles;
     int first = 0;
     bool cut = false;
+    const DivUp by_c(best_c), by_ct(std::max(1, best_ct));
     for (int i = 0; i < batch; ++i) {
-        const int si = up(up(kv_len[i], kKT) + tree, best_c);
-        const int ti = best.uneven ? up(up(kv_len[i], kSK) + up(T, kSK), best_ct) : 0;
-        best.seq[i] = AttnSeqPlan{si, ti, std::max(si, ti), first};
+        const int cuts = by_c(up(kv_len[i], kKT) + tree);
+        const int ti = best.uneven ? by_ct(up(kv_len[i], kSK) + tree_sub) : 0;
+        best.seq[i] = AttnSeqPlan{cuts, ti, std::max(cuts, ti), first};
         first += best.seq[i].ranges;
         cut = cut || best.seq[i].ranges > 1;
     }
@@ -258,9 +315,10 @@ AttnPlan attn_plan(int batch, int T, int Hq, int Hkv, int D, const int32_t *kv_l
     for (int i = 0; i < batch; ++i) sum_L += kv_len[i];
     const bool wide = wide_partials(batch, T, Hq, Hkv, D, sum_L);
     const long long room = slot_room(T, Hq, D, wide, scratch);
-    const AttnPlan w = plan_wave(batch, T, Hq, Hkv, D, kv_len, 1, wide, room);
-    const AttnPlan m = D == kHD ? plan_main(batch, T, Hq, Hkv, kv_len, wide, room)
-                                : plan_wave(batch, T, Hq, Hkv, D, kv_len, 2, wide, room);
+    const Lens lens = lens_of(kv_len, batch);
+    const AttnPlan w = plan_wave(batch, T, Hq, Hkv, D, kv_len, lens, 1, wide, room);
+    const AttnPlan m = D == kHD ? plan_main(batch, T, Hq, Hkv, kv_len, lens, wide, room)
+                                : plan_wave(batch, T, Hq, Hkv, D, kv_len, lens, 2, wide, room);
     return w.cost <= m.cost ? w : m;
 }
 
@@ -324,8 +382,8 @@ bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_sta
     args.groups_magic = magic_of((uint64_t)p.groups, (uint64_t)p.items);
     args.hkv_magic = magic_of((uint64_t)Hkv, (uint64_t)p.items);
     args.run_magic = magic_of((uint64_t)args.run, (uint64_t)args.grid);
-    int32_t order[DDTREE_MAX_BATCH];
-    longest_first(order, kv_len, batch);
+    const Lens lens = lens_of(kv_len, batch);
+    const int32_t *const order = lens.order;
     int unit = 0;
     for (int i = 0; i < batch; ++i) {
         const int s = order[i];
@@ -346,8 +404,8 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
     args.wide = p.wide ? 1 : 0;
     args.group_size = G;
     args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
-    int32_t order[DDTREE_MAX_BATCH];
-    longest_first(order, kv_len, batch);
+    const Lens lens = lens_of(kv_len, batch);
+    const int32_t *const order = lens.order;
     long long total = 0, tail_total = 0, per_head_max = 1;
     for (int i = 0; i < batch; ++i) {
         const int s = order[i];
@@ -500,8 +558,9 @@ static int check_plan(const Shape &sh, int kind, long long room)
         if (attn_lacks_scratch(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), said)) return 14;
     }
     const bool wide = wide_partials(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sum);
-    const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len.data(), wide, room)
-                                 : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), kind + 1, wide, room);
+    const Lens lens = lens_of(sh.len.data(), sh.batch);
+    const AttnPlan p = kind == 2 ? plan_main(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.len.data(), lens, wide, room)
+                                 : plan_wave(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D, sh.len.data(), lens, kind + 1, wide, room);
     if (p.slots > room || p.bytes > attn_scratch_upper(sh.batch, sh.T, sh.Hq, sh.Hkv, sh.D)) return 1;
     std::vector<Item> items;
     if (kind == 2) {
