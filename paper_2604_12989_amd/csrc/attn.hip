@@ -87,13 +87,16 @@ struct AttnTailArgs {
     uint16_t *out;
     void *part;
     float2 *lse;
-    int32_t T, Hq, Hkv, wide, group_size;
+    int32_t T, Hq, Hkv, group_size;
     uint32_t g_magic;
     float scale_log2e;
 };
 static_assert(WaveShape<kHD, 1>::threads == kAttnThreads && WaveShape<kHD, 1>::lds_bytes <= kAttnLdsBytes,
               "a tail block runs in a workgroup of this kernel");
 
+// WIDE: partial results are fp32 rows.  (A variant of its own: as a branch of the epilogue it cost the calls with
+// fp16 partials 0.45 us, 47.15 -> 47.6 at 257 nodes x 8192 keys.)
+template <bool WIDE>
 __global__ __launch_bounds__(kAttnThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict__ k_cache,
                       const uint16_t *__restrict__ v_cache, const uint16_t *__restrict__ k_tree,
@@ -133,10 +136,10 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
     if (!attn_main_item(args, (int)blockIdx.x, T, item)) return;
     if (item.tail) {
         const AttnTailArgs tail{q, k_cache, v_cache, k_tree, v_tree, mask, out, part, lse, T, Hq, Hkv,
-                                args.wide, args.group_size, args.g_magic, scale_log2e};
+                                args.group_size, args.g_magic, scale_log2e};
         const AttnWaveItem rows{item.seq, item.hk, 0, item.split, item.splits, item.ranges, item.first_slot, item.kv_start,
                                 item.kv_len, item.m0, item.m_end, item.n_cache, item.t_begin, item.t_end};
-        attn_wave_rows<kHD, 1>(tail, rows);
+        attn_wave_rows<kHD, 1, WIDE>(tail, rows);
         return;
     }
     const int seq = item.seq, hk = item.hk, split = item.split, splits = item.splits;
@@ -597,7 +600,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
         // largest magnitude of its row (so that it fits whatever the values are: bf16 inputs reach 3e38,
         // fp16 65504), with that magnitude kept beside the log2-sum-exp.
         float rs = 1.0f;
-        if (part_splits != 0 && !args.wide) {
+        if (!WIDE && part_splits != 0) {
             float amax = 0.0f;
 #pragma unroll
             for (int db = 0; db < 4; ++db)
@@ -607,7 +610,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
             rs = (amax > 0.0f && amax < INFINITY) ? amax : 1.0f;
         }
         const float mul = part_splits == 0 ? inv : inv / rs;
-        if (part_splits != 0 && args.wide) {
+        if (WIDE && part_splits != 0) {
             float *const dst = static_cast<float *>(part) +
                                ((size_t)(first_slot + split) * rows_seq + (size_t)(e_node * Hq + hk * G + (e_row - e_node * G))) * kHD;
             if (e_valid)
@@ -641,7 +644,7 @@ void attn_mfma_kernel(const uint16_t *__restrict__ q, const uint16_t *__restrict
                 for (int sx = splits; sx < part_splits; ++sx) lse[ridx + (size_t)sx * rows_seq] = make_float2(-INFINITY, 1.0f);
         }
     }
-    if (part_splits != 0 && args.wide) return;
+    if (WIDE && part_splits != 0) return;
     uint16_t *dst_base = part_splits == 0 ? out + seq * rows_seq * kHD
                                           : static_cast<uint16_t *>(part) + (size_t)(first_slot + split) * rows_seq * kHD;
     const int chunk = e_lane & 15;
@@ -944,14 +947,15 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
             args.Hq = Hq;
             args.Hkv = Hkv;
             args.scale_log2e = softmax_scale * kLog2e;
-            if (!attn_wave_launch(args, D, p.row_blocks, st)) return DDTREE_ERR_HIP;
+            if (!attn_wave_launch(args, D, p.row_blocks, p.wide, st)) return DDTREE_ERR_HIP;
         } else {
             AttnMainArgs args;
             if (!attn_main_args(args, p, kv_start, kv_len, batch, T, Hq, Hkv)) return DDTREE_ERR_ARG;
-            static std::atomic<bool> lds_allowed{false};
-            if (!allow_dynamic_lds(reinterpret_cast<const void *>(attn_mfma_kernel), kAttnLdsBytes, lds_allowed))
+            static std::atomic<bool> lds_allowed[2];
+            auto *kernel = p.wide ? attn_mfma_kernel<true> : attn_mfma_kernel<false>;
+            if (!allow_dynamic_lds(reinterpret_cast<const void *>(kernel), kAttnLdsBytes, lds_allowed[p.wide ? 1 : 0]))
                 return DDTREE_ERR_HIP;
-            DDT_LAUNCH(DDTREE_KERNEL_ATTN, st, attn_mfma_kernel, dim3((unsigned)args.grid), dim3(kAttnThreads),
+            DDT_LAUNCH(DDTREE_KERNEL_ATTN, st, kernel, dim3((unsigned)args.grid), dim3(kAttnThreads),
                        kAttnLdsBytes, st, static_cast<const uint16_t *>(q), static_cast<const uint16_t *>(k_cache),
                        static_cast<const uint16_t *>(v_cache), static_cast<const uint16_t *>(k_tree),
                        static_cast<const uint16_t *>(v_tree), ancestor_mask, args, T, Hq, Hkv,

@@ -68,7 +68,7 @@ struct AttnWaveArgs {
     uint16_t *out;
     void *part;
     float2 *lse;
-    int32_t T, Hq, Hkv, wide;
+    int32_t T, Hq, Hkv;
     int32_t batch, items, run;           // work items; consecutive ones that an XCD takes at a time
     int32_t groups, rows_per_group;
     int32_t group_size;                  // G = Hq / Hkv
@@ -79,7 +79,7 @@ struct AttnWaveArgs {
 };
 bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_start, const int32_t *kv_len, int batch,
                     int T, int Hq, int Hkv);
-bool attn_wave_launch(const AttnWaveArgs &args, int D, int row_blocks, hipStream_t st);
+bool attn_wave_launch(const AttnWaveArgs &args, int D, int row_blocks, bool wide, hipStream_t st);
 
 struct AttnWaveItem {
     int seq, hk, grp, split, splits, ranges, first_slot, kv_start, kv_len;
@@ -128,7 +128,7 @@ struct AttnMainArgs {
     // XCD x executes the whole tiles' work items xcd_start[x] .. xcd_start[x + 1] - 1, then the tail
     // blocks' tail_start[x] .. tail_start[x + 1] - 1
     int32_t xcd_start[9], tail_start[9];
-    int32_t batch, n_tiles, blk_base, blk_extra, uneven, wide;
+    int32_t batch, n_tiles, blk_base, blk_extra, uneven;
     int32_t group_size;                  // G = Hq / Hkv
     uint32_t g_magic, tiles_magic, extra_magic;  // reciprocals of G, n_tiles and blk_extra
     int32_t grid;

@@ -367,7 +367,7 @@ bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_sta
 {
     if (p.items > (1ll << 28)) return false;
     const int G = Hq / Hkv;
-    args.T = T, args.Hq = Hq, args.Hkv = Hkv, args.wide = p.wide ? 1 : 0, args.batch = batch;
+    args.T = T, args.Hq = Hq, args.Hkv = Hkv, args.batch = batch;
     args.items = (int32_t)p.items;
     args.groups = p.groups;
     args.rows_per_group = p.rows_per_group;
@@ -401,7 +401,6 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
     const int G = Hq / Hkv, tails = p.uneven ? p.blk_extra : 0;
     args.batch = batch, args.n_tiles = p.n_tiles, args.blk_base = p.blk_base, args.blk_extra = p.blk_extra;
     args.uneven = p.uneven ? 1 : 0;
-    args.wide = p.wide ? 1 : 0;
     args.group_size = G;
     args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
     const Lens lens = lens_of(kv_len, batch);

@@ -20,31 +20,32 @@
 
 namespace ddt {
 
-template <int D, int RB>
+template <int D, int RB, bool WIDE>
 __global__ __launch_bounds__((WaveShape<D, RB>::threads))
 __attribute__((amdgpu_waves_per_eu(WaveShape<D, RB>::waves / 4, WaveShape<D, RB>::waves / 4)))
 void attn_wave_kernel(const AttnWaveArgs args)
 {
     AttnWaveItem item;
     if (!attn_wave_item(args, (int)blockIdx.x, item)) return;
-    attn_wave_rows<D, RB>(args, item);
+    attn_wave_rows<D, RB, WIDE>(args, item);
 }
 
-template <int D, int RB>
+template <int D, int RB, bool WIDE>
 static bool launch_one(const AttnWaveArgs &args, hipStream_t st)
 {
     using S = WaveShape<D, RB>;
     static std::atomic<bool> allowed{false};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(attn_wave_kernel<D, RB>), S::lds_bytes, allowed)) return false;
-    DDT_LAUNCH(DDTREE_KERNEL_ATTN, st, (attn_wave_kernel<D, RB>), dim3((unsigned)args.grid), dim3(S::threads),
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(attn_wave_kernel<D, RB, WIDE>), S::lds_bytes, allowed)) return false;
+    DDT_LAUNCH(DDTREE_KERNEL_ATTN, st, (attn_wave_kernel<D, RB, WIDE>), dim3((unsigned)args.grid), dim3(S::threads),
                S::lds_bytes, st, args);
     return true;
 }
 
-bool attn_wave_launch(const AttnWaveArgs &args, int D, int row_blocks, hipStream_t st)
+// (heads of 64 leave fp32 partials only)
+bool attn_wave_launch(const AttnWaveArgs &args, int D, int row_blocks, bool wide, hipStream_t st)
 {
-    if (D == 128) return row_blocks == 2 ? launch_one<128, 2>(args, st) : launch_one<128, 1>(args, st);
-    return row_blocks == 2 ? launch_one<64, 2>(args, st) : launch_one<64, 1>(args, st);
+    if (D == 128) return wide ? launch_one<128, 1, true>(args, st) : launch_one<128, 1, false>(args, st);
+    return row_blocks == 2 ? launch_one<64, 2, true>(args, st) : launch_one<64, 1, true>(args, st);
 }
 
 }  // namespace ddt

@@ -29,8 +29,9 @@ struct WaveShape {
     static_assert(lds_bytes <= 160 * 1024, "fits the LDS of a compute unit");
 };
 
-// What a workgroup does with its row group and key range.  Args: AttnWaveArgs, or what attn_mfma_kernel has.
-template <int D, int RB, class Args>
+// What a workgroup does with its row group and key range.  Args: AttnWaveArgs, or what attn_mfma_kernel has; WIDE:
+// partial results are fp32 rows.
+template <int D, int RB, bool WIDE, class Args>
 __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveItem &item)
 {
     using S = WaveShape<D, RB>;
@@ -380,30 +381,30 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
         // key ranges that this row does not have (rows of attn_mfma_kernel's whole tiles have more): empty
         if (r < r1 && c8 == 0 && item.split == 0)
             for (int sx = item.splits; sx < item.ranges; ++sx) lse[(size_t)sx * rows_seq] = make_float2(-INFINITY, 1.0f);
-        if (TWO || args.wide) {
+        if constexpr (WIDE) {
             if (r < r1) {
                 float4 *const dst = reinterpret_cast<float4 *>(static_cast<float *>(args.part) + slot_row * D + c8);
                 dst[0] = make_float4(acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv);
                 dst[1] = make_float4(acc[4] * inv, acc[5] * inv, acc[6] * inv, acc[7] * inv);
                 if (c8 == 0) lse[(size_t)item.split * rows_seq] = make_float2(lse2, 1.0f);
             }
-            continue;
-        }
-        // an fp16 partial is relative to its row's largest magnitude (see attn.hip)
-        float amax = 0.0f;
+        } else {
+            // an fp16 partial is relative to its row's largest magnitude (see attn.hip)
+            float amax = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(acc[e]));
+            for (int e = 0; e < 8; ++e) amax = fmaxf(amax, fabsf(acc[e]));
 #pragma unroll
-        for (int d = CH / 2; d >= 1; d >>= 1) amax = fmaxf(amax, __shfl_xor(amax, d, 64));
-        amax *= inv;
-        const float scale = (amax > 0.0f && amax < INFINITY) ? amax : 1.0f;
-        const float mul = inv / scale;
-        if (r < r1) {
-            uint4 val;
-            val.x = f2h_pair(acc[0] * mul, acc[1] * mul), val.y = f2h_pair(acc[2] * mul, acc[3] * mul);
-            val.z = f2h_pair(acc[4] * mul, acc[5] * mul), val.w = f2h_pair(acc[6] * mul, acc[7] * mul);
-            *reinterpret_cast<uint4 *>(static_cast<uint16_t *>(args.part) + slot_row * D + c8) = val;
-            if (c8 == 0) lse[(size_t)item.split * rows_seq] = make_float2(lse2, scale);
+            for (int d = CH / 2; d >= 1; d >>= 1) amax = fmaxf(amax, __shfl_xor(amax, d, 64));
+            amax *= inv;
+            const float scale = (amax > 0.0f && amax < INFINITY) ? amax : 1.0f;
+            const float mul = inv / scale;
+            if (r < r1) {
+                uint4 val;
+                val.x = f2h_pair(acc[0] * mul, acc[1] * mul), val.y = f2h_pair(acc[2] * mul, acc[3] * mul);
+                val.z = f2h_pair(acc[4] * mul, acc[5] * mul), val.w = f2h_pair(acc[6] * mul, acc[7] * mul);
+                *reinterpret_cast<uint4 *>(static_cast<uint16_t *>(args.part) + slot_row * D + c8) = val;
+                if (c8 == 0) lse[(size_t)item.split * rows_seq] = make_float2(lse2, scale);
+            }
         }
     }
 }

@@ -118,6 +118,16 @@ def test_heads_of_64_need_no_scratch():
     assert (a.float() - b.float()).abs().max().item() < 1e-2
 
 
+@pytest.mark.parametrize("T,Ls,Hq,Hkv", [
+    (297, [45, 636, 808, 238], 32, 8),                                                # row tiles of the same height
+    (94, [366, 13, 40, 442, 104, 275, 5, 142, 304, 99, 220], 15, 5),                  # with blocks left beside them
+    (102, [119, 56, 145, 212, 113, 958, 845, 427, 769, 302, 148], 2, 2), (9, [39, 522, 1006, 47, 15, 751, 816], 18, 6)])  # waves
+@pytest.mark.parametrize("nodes", [None, 7])
+def test_ragged_batches_of_short_caches(T, Ls, Hq, Hkv, nodes):
+    """Key ranges are cut for the sake of the longest sequences alone: partial results in fp32."""
+    _check(1100 + T, T, Ls, Hq, Hkv, 128, n_pairs=24, n_nodes=nodes)
+
+
 @pytest.mark.parametrize("scale", [1.0, 2.0 ** 116])
 @pytest.mark.parametrize("T,Ls,Hq,Hkv,scratch", [(65, [2047], 16, 4, True), (257, [4096], 32, 8, True), (33, [900, 31, 2500], 12, 4, True),
                                                  (65, [3000], 8, 2, False), (200, [31], 4, 1, True), (257, [4096], 8, 1, True)])
