@@ -113,9 +113,11 @@ def _keepalive(fn, *objs):
 
 # A call's host time is the marshalling here plus the launches (2-3 us each).  A decoding round that does
 # not defer its calls makes one per stage and layer, and the GPU waits for the host where a call takes
-# longer than its kernels.  Hence plain integers for pointers (the argtypes convert them), one
-# allocation for results of a kind, and the raw stream handle (0.4 us; a torch.cuda.Stream object takes
-# 3.3).  Per call, before and after: build 21.6 -> 15.0 us, attention 15.8 -> 12.5, walk 18.3 -> 15.4.
+# longer than its kernels.  Hence plain integers for pointers (the argtypes convert them), results made from
+# an input (new_empty), and the raw stream handle (0.4 us; a torch.cuda.Stream object takes 3.3).  Each
+# result has memory of its own: views of one allocation would be 2.9 us a round cheaper, but keeping one
+# would keep all.  Per call, with a stream object, pointer objects and torch.empty, and now: build 21.6 -> 17.4 us,
+# attention 15.8 -> 12.5, walk 18.3 -> 15.7.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
@@ -194,11 +196,10 @@ def build(topk_tok, topk_lp, N, root_token, ws=None, out=None, defer=False):
     batch, B, K = topk_tok.shape
     T, W = N + 1, (N + 1 + 63) // 64
     if out is None:
-        tokens, parent, depth, rank = topk_tok.new_empty((4, batch, T)).unbind(0)
-        out = dict(tokens=tokens, parent=parent, depth=depth, rank=rank,
-                   node_score=topk_lp.new_empty((batch, T)),
-                   ancestor_mask=topk_tok.new_empty((batch, T, W), dtype=torch.int64),
-                   n_nodes=topk_tok.new_empty((batch,)))
+        out = {key: topk_tok.new_empty((batch, T)) for key in ("tokens", "parent", "depth", "rank")}
+        out["node_score"] = topk_lp.new_empty((batch, T))
+        out["ancestor_mask"] = topk_tok.new_empty((batch, T, W), dtype=torch.int64)
+        out["n_nodes"] = topk_tok.new_empty((batch,))
     p, n = _ws(ws)
     args = (_ptr(topk_tok), _ptr(topk_lp), batch, B, K, N, _ptr(root_token), _ptr(out["tokens"]),
             _ptr(out["parent"]), _ptr(out["depth"]), _ptr(out.get("rank")),
@@ -259,9 +260,8 @@ def accept(target_logits, tokens, parent, depth, n_nodes, B, ws, out=None, want_
     batch, T, V = target_logits.shape
     if out is None:
         i32 = dict(dtype=torch.int32)
-        n_accepted, bonus_token = target_logits.new_empty((2, batch), **i32).unbind(0)
-        out = dict(path=target_logits.new_empty((batch, B + 1), **i32), n_accepted=n_accepted,
-                   bonus_token=bonus_token,
+        out = dict(path=target_logits.new_empty((batch, B + 1), **i32), n_accepted=target_logits.new_empty((batch,), **i32),
+                   bonus_token=target_logits.new_empty((batch,), **i32),
                    posterior=target_logits.new_empty((batch, T), **i32) if want_posterior else None)
     p, n = _ws(ws)
     if temperature is not None:
