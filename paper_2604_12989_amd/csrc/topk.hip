@@ -12,7 +12,7 @@
 //                  turns out to lie above it: that chunk is read again.  They are ranked exactly (key
 //                  descending, token id ascending) and written with their log-probabilities.
 // A row of one chunk is finished by its chunk workgroup; rows whose candidates do not fit on chip (heavy
-// ties) take a radix select over the row.
+// ties, fewer maxima than ranks) take a radix select over the row.
 //
 // Every candidate is the 64-bit composite (key << 32) | ~token_id, so all composites of a row
 // are distinct and "larger composite" is exactly "larger logit, or equal logit and smaller id".
@@ -24,6 +24,10 @@
 // threads that fill a compute unit alone, and 128 rows or more took one workgroup per row.
 // Measured (both kernels back to back, V = 151936, before -> now): 16 rows K = 256 16.4 -> 14.0 us, K = 1024
 // 20.0 -> 16.2; 32 rows K = 128 23.8 -> 17.6; 112 rows 53.9 -> 29.6; 256 rows 66 -> 54; 8 rows of 1024 12.0 -> 7.3.
+// Rows whose maxima say little about their top K (masked tokens, an outlier, ties), by the ranking chunks, with one
+// range of buckets and a select over the row in six passes, and now: 16 rows K = 256 half masked with -1e9 203 / 181 / 17
+// us, equal logits 111 / 721 / 126; K = 1024 one token 1000 above the others 73 / 117 / 35, half masked with -inf 135 / 206 / 128;
+// 256 rows K = 128 half masked with -1e9 56 / 296 / 57.  Their code costs the other rows 0.1 to 0.3 us a call.
 #include <algorithm>
 #include <cmath>
 
@@ -31,8 +35,6 @@
 
 namespace ddt {
 
-constexpr int kListCap = 1024;  // a radix bin this small is finished by rank counting
-constexpr int kHistBins = 4096;
 constexpr int kChunkThreads = 512;
 constexpr int kChunkWaves = kChunkThreads / 64;
 constexpr int kVecPerThread = kTopkChunkMax / 4 / kChunkThreads;
@@ -40,6 +42,7 @@ constexpr int kSlots = 4 * kVecPerThread + 2;  // float4 body + one head and one
 static_assert(kVecPerThread * 4 * kChunkThreads == kTopkChunkMax, "chunk must tile the workgroup");
 constexpr int kRankCap = 4096;   // candidates of a row held on chip
 constexpr int kBuckets = 1024;
+constexpr int kCrowded = 384;    // members of a bucket beyond which ranking by pairs is slower than a sort
 
 struct ChunkStat {
     double sum;        // sum of exp(x - max) over everything but one instance of the maximum
@@ -99,135 +102,6 @@ size_t topk_scratch_upper(int batch, int B, int V, int K)
     return 3 * 256 + (size_t)maxima * sizeof(float) + (size_t)chunks * sizeof(ChunkStat) + (size_t)places * sizeof(uint64_t);
 }
 
-// ------------------------------------------------------------------------------------------
-// Block-wide helpers.  NT = threads per workgroup (multiple of 64).
-// ------------------------------------------------------------------------------------------
-
-// Exclusive prefix sum of v over the workgroup's threads; *total receives the sum.
-template <int NT>
-__device__ int block_exclusive_scan(int v, int *s_wave /*[NT/64 + 1]*/, int *total)
-{
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int incl = v;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        int t = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += t;
-    }
-    if (lane == 63) s_wave[wave] = incl;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int acc = 0;
-        for (int w = 0; w < NT / 64; ++w) {
-            int t = s_wave[w];
-            s_wave[w] = acc;
-            acc += t;
-        }
-        s_wave[NT / 64] = acc;
-    }
-    __syncthreads();
-    int res = s_wave[wave] + incl - v;
-    *total = s_wave[NT / 64];
-    __syncthreads();
-    return res;
-}
-
-struct SelectScratch {
-    uint32_t *hist;    // [kHistBins]
-    uint64_t *list;    // [kListCap]
-    int *s_wave;       // [NT/64 + 1]
-    int *s_misc;       // [8]
-    uint64_t *s_thr;   // [1]
-};
-
-// Returns thr such that exactly k of the n distinct composites get(i) are >= thr (1 <= k <= n).
-// Radix select from the most significant bits down: 12, 12, 8 bits of the key, then 12, 12, 8
-// bits of the inverted id.  A level ends the search when its threshold bin holds exactly the
-// number still wanted, or few enough elements to rank them directly.
-template <int NT, class Get>
-__device__ uint64_t block_select_threshold(Get get, int n, int k, SelectScratch s)
-{
-    const int tid = threadIdx.x;
-    uint64_t pmask = 0, pval = 0;
-    const int shifts[6] = {52, 40, 32, 20, 8, 0};
-    const int widths[6] = {12, 12, 8, 12, 12, 8};
-    for (int level = 0; level < 6; ++level) {
-        const int shift = shifts[level];
-        const int nb = 1 << widths[level];
-        for (int i = tid; i < nb; i += NT) s.hist[i] = 0;
-        __syncthreads();
-        for (int i = tid; i < n; i += NT) {
-            uint64_t c = get(i);
-            if ((c & pmask) == pval) atomicAdd(&s.hist[(uint32_t)(c >> shift) & (nb - 1)], 1u);
-        }
-        __syncthreads();
-        // locate the bin holding the k-th largest.  Thread t owns the `per` bins that end at
-        // ahi = nb-1 - t*per, so thread 0 owns the highest bins and an exclusive scan over the
-        // threads counts the elements in all higher bins.
-        const int per = nb >= NT ? nb / NT : 1;
-        const int ahi = nb - 1 - tid * per;
-        int mine = 0;
-        if (ahi >= 0)
-            for (int j = 0; j < per; ++j) mine += (int)s.hist[ahi - j];
-        int total;
-        int above = block_exclusive_scan<NT>(mine, s.s_wave, &total);
-        if (ahi >= 0 && above < k && k <= above + mine) {
-            int acc = above;
-            for (int j = 0; j < per; ++j) {
-                int h = (int)s.hist[ahi - j];
-                if (acc + h >= k) {
-                    s.s_misc[1] = ahi - j;  // bin
-                    s.s_misc[2] = acc;      // elements in higher bins
-                    s.s_misc[3] = h;        // elements in the bin
-                    break;
-                }
-                acc += h;
-            }
-        }
-        __syncthreads();
-        const int bin = s.s_misc[1], above_cnt = s.s_misc[2], in_bin = s.s_misc[3];
-        __syncthreads();
-        k -= above_cnt;
-        pval |= (uint64_t)bin << shift;
-        pmask |= (uint64_t)(nb - 1) << shift;
-        if (in_bin == k) return pval;  // the whole bin is wanted: pval's low bits are zero
-        if (in_bin <= kListCap) {
-            if (tid == 0) s.s_misc[4] = 0;
-            __syncthreads();
-            for (int i = tid; i < n; i += NT) {
-                uint64_t c = get(i);
-                if ((c & pmask) == pval) s.list[atomicAdd(&s.s_misc[4], 1)] = c;
-            }
-            __syncthreads();
-            for (int e = tid; e < in_bin; e += NT) {
-                const uint64_t c = s.list[e];
-                int greater = 0;
-                for (int j = 0; j < in_bin; ++j) greater += s.list[j] > c ? 1 : 0;
-                if (greater == k - 1) *s.s_thr = c;
-            }
-            __syncthreads();
-            uint64_t thr = *s.s_thr;
-            __syncthreads();
-            return thr;
-        }
-    }
-    return pval;  // all 64 bits fixed: a single element
-}
-
-// Ranks the m distinct composites in list[] (descending; m <= kCandCap) and calls
-// emit(rank, composite) once per element: all-pairs counting, used on the rare tie-heavy path.
-template <int NT, class Emit>
-__device__ void block_rank_emit(const uint64_t *list, int m, Emit emit)
-{
-    for (int e = threadIdx.x; e < m; e += NT) {
-        const uint64_t c = list[e];
-        int g = 0;
-        for (int j = 0; j < m; ++j) g += list[j] > c ? 1 : 0;
-        emit(g, c);
-    }
-}
-
-
 // exp(y) for y <= 0 in fp64 to a relative error below 4e-11: y = (64 n + j) ln2/64 + r with
 // |r| <= ln2/128, so exp(y) = 2^n * 2^(j/64) * exp(r); 2^(j/64) comes from a 64-entry table and
 // exp(r) from its Taylor polynomial of degree 3 (remainder r^4/24 < 3.6e-11; the reduction by one
@@ -273,10 +147,10 @@ struct FinishLds {
     uint32_t cnt[kBuckets];
     int start[kBuckets + 1];
     int wave[17];
-    int misc[8];
-    uint64_t thr;
+    int found[3];               // the bucket that holds the rank looked for, what the buckets above it hold, what it holds
+    uint32_t low, high;         // range of the maxima in a crowded bucket
     double exc;                 // log1p(sum over everything but the first maximum), i.e. lse - max
-    int n_list;
+    int n_list, crowded;
 };
 struct FinishArgs {
     int V, K, chunks, chunk_len, maxima, hot_cap;
@@ -306,9 +180,10 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
     for (int u = 0; u < PRE; ++u) h[u] = tid + u * NT < n_hot ? hot[tid + u * NT] : 0ull;
     for (int i = tid; i < kBuckets; i += NT) L.cnt[i] = 0u;
     if (tid == 0) {
-        L.n_list = 0;
-        L.misc[0] = kBuckets;
-        L.misc[7] = 0;
+        L.n_list = L.crowded = 0;
+        L.found[0] = kBuckets;
+        L.low = ~0u;
+        L.high = 0u;
     }
     __syncthreads();
     // ---- the K-th largest group maximum, to the resolution of kBuckets equal buckets over the range of
@@ -322,16 +197,19 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
     }
     const float hi = wave_max_f32(vmax);
     vlow = wave_min_u32(vlow);
-    const float lo = vlow == ~0u ? hi : key_float(vlow);
-    const float inv = (float)kBuckets / fmaxf(hi - lo, 1e-30f);
-    auto bucket_of = [&](float v) { return (int)fminf((hi - v) * inv, (float)(kBuckets - 1)); };
+    float top = hi, low = vlow == ~0u ? hi : key_float(vlow);  // the range of the buckets
+    float inv = (float)kBuckets / fmaxf(top - low, 1e-30f);
+    auto bucket_of = [&](float v) { return (int)fminf((top - v) * inv, (float)(kBuckets - 1)); };  // (above the range: negative)
+    auto each_maximum = [&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
-    for (int u = 0; u < PRE; ++u)
-        if (g[u] > -INFINITY) atomicAdd(&L.cnt[bucket_of(g[u])], 1u);
-    for (int i = tid + PRE * NT; i < n_max; i += NT) {
-        const float v = maxima[i];
-        if (v > -INFINITY) atomicAdd(&L.cnt[bucket_of(v)], 1u);
-    }
+        for (int u = 0; u < PRE; ++u)
+            if (g[u] > -INFINITY) f(g[u]);
+        for (int i = tid + PRE * NT; i < n_max; i += NT) {
+            const float v = maxima[i];
+            if (v > -INFINITY) f(v);
+        }
+    };
+    each_maximum([&](float v) { atomicAdd(&L.cnt[bucket_of(v)], 1u); });
     __syncthreads();
     const double mx = (double)hi;
     // log-sum-exp from the chunk statistics (fp64, fixed order), by one whole wave.  The chunk sums leave one
@@ -369,26 +247,47 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
         for (int j = 0; j < PB; ++j) {
             if (starts) L.start[tid * PB + j] = before;
             else L.cnt[tid * PB + j] = 0u;
-            if (before < want && before + c[j] >= want) L.misc[0] = tid * PB + j;
+            if (before < want && before + c[j] >= want) L.found[0] = tid * PB + j, L.found[1] = before, L.found[2] = c[j];
             before += c[j];
         }
         __syncthreads();
     };
     scan(K, false);
-    const bool whole = a.hot_cap == 0 || L.misc[0] == kBuckets;  // the row is read again, all of it
-    if (L.misc[0] == kBuckets) {  // fewer maxima than ranks: the same over all elements
-        for (int i0 = 0; i0 < a.V; i0 += PRE * NT) {
-            float x[PRE];
-#pragma unroll
-            for (int u = 0; u < PRE; ++u) x[u] = i0 + u * NT + tid < a.V ? p[i0 + u * NT + tid] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < PRE; ++u)
-                if (i0 + u * NT + tid < a.V) atomicAdd(&L.cnt[bucket_of(x[u])], 1u);
+    const bool bounded = L.found[0] != kBuckets;  // otherwise there are fewer maxima than ranks
+    int want = K;
+    // A bucket that holds many maxima at once (an outlier or masked tokens stretch the range, most of it empty):
+    // the same again over the maxima of that bucket alone.
+    for (int round = 0; bounded && __builtin_expect(L.found[2] > 64 + 3 * K / 8, 0) && round < 8; ++round) {  // (uniform)
+        const int crowded = L.found[0];
+        want -= L.found[1];
+        uint32_t kl = ~0u, kh = 0u;
+        each_maximum([&](float v) {
+            if (v <= top && v >= low && bucket_of(v) == crowded) kl = min(kl, float_key(v)), kh = max(kh, float_key(v));
+        });
+        kl = wave_min_u32(kl);
+        kh = ~wave_min_u32(~kh);
+        if (lane == 63 && kl <= kh) {
+            atomicMin(&L.low, kl);
+            atomicMax(&L.high, kh);
         }
         __syncthreads();
-        scan(K, false);
+        kl = L.low;
+        kh = L.high;
+        top = key_float(kh);
+        low = key_float(kl);
+        inv = kl == kh ? 1e38f : (float)kBuckets / fmaxf(top - low, 1e-30f);  // (one value: what lies below it is far away)
+        if (kl != kh) each_maximum([&](float v) { if (v <= top && v >= low) atomicAdd(&L.cnt[bucket_of(v)], 1u); });
+        __syncthreads();
+        if (tid == 0) {
+            L.low = ~0u;
+            L.high = 0u;
+            if (kl == kh) L.found[0] = L.found[1] = L.found[2] = 0;
+        }
+        if (kl != kh) scan(want, false);
+        else __syncthreads();
     }
-    const int last = L.misc[0];  // elements of buckets 0 .. last are candidates, at least K of them
+    const int last = bounded ? L.found[0] : -1;  // elements of buckets 0 .. last are candidates, at least K of them
+    const bool whole = a.hot_cap == 0;           // the row is read again, all of it
     auto composite = [&](float x, int i) -> uint64_t {
         return ((uint64_t)float_key(x) << 32) | (uint64_t)(uint32_t)(~(uint32_t)i);
     };
@@ -396,9 +295,10 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
         tok[rank] = (int32_t)(~(uint32_t)cc);
         lp[rank] = (float)(((double)key_float((uint32_t)(cc >> 32)) - mx) - L.exc);
     };
-    // a chunk whose hot list may lack candidates: its bound falls among their buckets
-    auto lacks = [&](float bound) { return !(bucket_of(bound) > last) || bound == INFINITY; };
-    const uint64_t lacking = __builtin_amdgcn_ballot_w64(lane < a.chunks && lacks(st.hot));  // of the first 64
+    // a chunk whose hot list may lack candidates: it has some, and its bound falls among their buckets
+    auto lacks = [&](float max, float bound) { return (bound == INFINITY || bucket_of(bound) <= last) && bucket_of(max) <= last; };
+    uint64_t lacking = __builtin_amdgcn_ballot_w64(lane < a.chunks && (st.hot == INFINITY || bucket_of(st.hot) <= last));  // of the first 64
+    if (lacking != 0ull) lacking &= __builtin_amdgcn_ballot_w64(bucket_of(st.max) <= last);
     auto reserve = [&](int n) -> int {  // n list places for this thread (one atomic per wave)
         const int incl = wave_scan_inclusive_i32(n);
         const int total = __builtin_amdgcn_readlane(incl, 63);
@@ -407,7 +307,7 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
         if (lane == 63) base = atomicAdd(&L.n_list, total);
         return __builtin_amdgcn_readlane(base, 63) + incl - n;
     };
-    if (!whole)
+    if (!whole && bounded)
         for (int b0 = 0; b0 < n_hot; b0 += PRE * NT) {  // (uniform)
             if (b0 > 0) {
 #pragma unroll
@@ -419,7 +319,7 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
             for (int u = 0; u < PRE; ++u) {
                 const int i = b0 + tid + u * NT, c = i >> cap_shift;
                 take[u] = h[u] != 0ull && bucket_of(key_float((uint32_t)(h[u] >> 32))) <= last &&
-                          !(c < 64 ? (bool)((lacking >> c) & 1ull) : lacks(stat[c].hot));
+                          !(c < 64 ? (bool)((lacking >> c) & 1ull) : lacks(stat[c].max, stat[c].hot));
                 n += take[u] ? 1 : 0;
             }
             int at = reserve(n);
@@ -430,6 +330,12 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
                     ++at;
                 }
         }
+    auto put = [&](float x, int id, bool take, int &at) {
+        if (take) {
+            if (at < kRankCap) L.list[at] = composite(x, id);
+            ++at;
+        }
+    };
     auto rescan = [&](int begin, int end) {  // (uniform over the workgroup)
         for (int i0 = begin; i0 < end; i0 += PRE * NT) {
             float x[PRE];
@@ -444,91 +350,183 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
             }
             int at = reserve(n);
 #pragma unroll
-            for (int u = 0; u < PRE; ++u)
-                if (take[u]) {
-                    if (at < kRankCap) L.list[at] = composite(x[u], i0 + u * NT + tid);
-                    ++at;
-                }
+            for (int u = 0; u < PRE; ++u) put(x[u], i0 + u * NT + tid, take[u], at);
         }
     };
-    if (whole) rescan(0, a.V);
-    for (int c0 = 0; c0 < a.chunks && !whole; c0 += 64) {
-        uint64_t todo = c0 == 0 ? lacking : __builtin_amdgcn_ballot_w64(c0 + lane < a.chunks && lacks(stat[min(c0 + lane, a.chunks - 1)].hot));
+    if (whole && bounded) rescan(0, a.V);
+    for (int c0 = 0; c0 < a.chunks && !whole && bounded; c0 += 64) {
+        uint64_t todo = lacking;
+        if (c0 > 0) {
+            const ChunkStat t = stat[min(c0 + lane, a.chunks - 1)];
+            todo = __builtin_amdgcn_ballot_w64(c0 + lane < a.chunks && lacks(t.max, t.hot));
+        }
         for (; todo != 0ull; todo &= todo - 1ull) {
             const int begin = (c0 + __builtin_ctzll(todo)) * a.chunk_len;
             rescan(begin, min(begin + a.chunk_len, a.V));
         }
     }
     __syncthreads();
-    const int m = L.n_list;
-    if (m > kRankCap) {
-        // heavy ties: exact radix select over the row
-        if (wave == NW - 1) log_sum_exp();
-        SelectScratch sc{reinterpret_cast<uint32_t *>(L.sorted), L.sorted + kHistBins / 2, L.wave, L.misc, &L.thr};
-        auto get = [&](int i) -> uint64_t { return composite(p[i], i); };
-        const uint64_t thr = block_select_threshold<NT>(get, a.V, K, sc);
-        for (int i = tid; i < a.V; i += NT) {
-            const uint64_t cc = get(i);
-            if (cc >= thr) {
-                const int at = atomicAdd(&L.misc[7], 1);  // exactly K
-                if (at < kRankCap) L.list[at] = cc;
+    int m = L.n_list;
+    if (wave == NW - 1) log_sum_exp();  // (this wave has the fewest candidates)
+    if (__builtin_expect(bounded && m <= kRankCap, 1)) {
+        if (m <= NT / 8) {
+            // all pairs: the threads of a wave share the element they compare with (a broadcast read), and
+            // each element's comparisons are dealt to NT / E threads
+            int E = 64;
+            while (E < m) E <<= 1;
+            const int parts = NT / E, e = tid & (E - 1), part_no = tid / E;
+            const uint64_t mine = e < m ? L.list[e] : 0ull;
+            const int j1 = min(m, (part_no + 1) * ((m + parts - 1) / parts));
+            int above = 0;
+            for (int j = part_no * ((m + parts - 1) / parts); j < j1; ++j) above += L.list[j] > mine ? 1 : 0;
+            if (e < m && above) atomicAdd(&L.cnt[e], (uint32_t)above);
+            __syncthreads();
+            if (tid < m && (int)L.cnt[tid] < K) emit((int)L.cnt[tid], mine);
+            return;
+        }
+        // by buckets over the candidates' own range: a candidate's rank is the population of the buckets above
+        // its own plus the larger members of its bucket
+        const float least = top - (float)(last + 1) / inv;  // (about the smallest candidate)
+        const float inv2 = (float)kBuckets / fmaxf(top - least, 1e-30f);
+        auto bucket2 = [&](uint64_t cc) { return (int)fminf(fmaxf((top - key_float((uint32_t)(cc >> 32))) * inv2, 0.0f), (float)(kBuckets - 1)); };
+        constexpr int PER = kRankCap / NT;
+        uint64_t mine[PER];
+        int bkt[PER], pos[PER];
+#pragma unroll
+        for (int u = 0; u < PER; ++u) {
+            const int i = tid + u * NT;
+            bkt[u] = pos[u] = 0;
+            mine[u] = 0ull;
+            if (i < m) {
+                mine[u] = L.list[i];
+                bkt[u] = bucket2(mine[u]);
+                pos[u] = (int)atomicAdd(&L.cnt[bkt[u]], 1u);
+                if (pos[u] == kCrowded) L.crowded = 1;
             }
         }
         __syncthreads();
-        block_rank_emit<NT>(L.list, K, emit);
-        return;
-    }
-    if (m <= NT / 8) {
-        // all pairs: the threads of a wave share the element they compare with (a broadcast read), and
-        // each element's comparisons are dealt to NT / E threads
-        int E = 64;
-        while (E < m) E <<= 1;
-        const int parts = NT / E, e = tid & (E - 1), part_no = tid / E;
-        const uint64_t mine = e < m ? L.list[e] : 0ull;
-        const int j1 = min(m, (part_no + 1) * ((m + parts - 1) / parts));
-        int above = 0;
-        for (int j = part_no * ((m + parts - 1) / parts); j < j1; ++j) above += L.list[j] > mine ? 1 : 0;
-        if (e < m && above) atomicAdd(&L.cnt[e], (uint32_t)above);
-        if (wave == NW - 1) log_sum_exp();  // (this wave has the fewest candidates)
-        __syncthreads();
-        if (tid < m && (int)L.cnt[tid] < K) emit((int)L.cnt[tid], mine);
-        return;
-    }
-    // by buckets over the candidates' own range: a candidate's rank is the population of the buckets above
-    // its own plus the larger members of its bucket
-    const float span = (float)(last + 1) / inv;
-    const float inv2 = (float)kBuckets / fmaxf(span, 1e-30f);
-    auto bucket2 = [&](uint64_t cc) { return (int)fminf((hi - key_float((uint32_t)(cc >> 32))) * inv2, (float)(kBuckets - 1)); };
-    constexpr int PER = kRankCap / NT;
-    uint64_t mine[PER];
-    int bkt[PER], pos[PER];
+        if (__builtin_expect(!L.crowded, 1)) {
+            scan(0, true);
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        const int i = tid + u * NT;
-        bkt[u] = pos[u] = 0;
-        mine[u] = 0ull;
-        if (i < m) {
-            mine[u] = L.list[i];
-            bkt[u] = bucket2(mine[u]);
-            pos[u] = (int)atomicAdd(&L.cnt[bkt[u]], 1u);
+            for (int u = 0; u < PER; ++u)
+                if (tid + u * NT < m) L.sorted[L.start[bkt[u]] + pos[u]] = mine[u];
+            __syncthreads();
+#pragma unroll
+            for (int u = 0; u < PER; ++u) {
+                if (tid + u * NT >= m) break;
+                const int bs = L.start[bkt[u]], nb = (int)L.cnt[bkt[u]];
+                if (bs >= K) continue;
+                int above = bs;
+#pragma unroll 4
+                for (int j = 0; j < nb; ++j) above += L.sorted[bs + j] > mine[u] ? 1 : 0;
+                if (above < K) emit(above, mine[u]);
+            }
+            return;
         }
-    }
-    if (wave == NW - 1) log_sum_exp();
-    __syncthreads();
-    scan(0, true);
+    } else {
+        // Too few maxima, or too many elements that reach the bound (ties among them): the K-th largest element of
+        // the row itself, ten bits of its distance d from the maximum (as order-preserving integers) at a time, until
+        // what lies at or above its bucket fits on chip.  Where one value has too many elements for that, those
+        // above it are ranked and the first of its own follow in the order of their ids.
+        const uint32_t key_hi = float_key(hi), range = key_hi - (bounded ? float_key(low) : 0x007FFFFFu);  // (-inf)
+        auto distance = [&](float v) { return key_hi - float_key(v); };
+        int shift = max(0, 22 - __builtin_clz(range | 1u)), chosen;
+        uint32_t base = 0u, buckets = (range >> shift) + 1u;
+        want = K;
+        for (;;) {
+            for (int i0 = 0; i0 < a.V; i0 += 8 * NT) {
+                float x[8];
 #pragma unroll
-    for (int u = 0; u < PER; ++u)
-        if (tid + u * NT < m) L.sorted[L.start[bkt[u]] + pos[u]] = mine[u];
-    __syncthreads();
+                for (int u = 0; u < 8; ++u) x[u] = i0 + u * NT + tid < a.V ? p[i0 + u * NT + tid] : 0.0f;
 #pragma unroll
-    for (int u = 0; u < PER; ++u) {
-        if (tid + u * NT >= m) break;
-        const int bs = L.start[bkt[u]], nb = (int)L.cnt[bkt[u]];
-        if (bs >= K) continue;
-        int above = bs;
-        for (int j = 0; j < nb; ++j) above += L.sorted[bs + j] > mine[u] ? 1 : 0;
-        if (above < K) emit(above, mine[u]);
+                for (int u = 0; u < 8; ++u) {
+                    // the first lane's bucket takes all its lanes at once (a masked row has most of them in one)
+                    const uint32_t d = distance(x[u]), bk = (d - base) >> shift;
+                    const bool on = i0 + u * NT + tid < a.V && d >= base && bk < buckets;
+                    const uint64_t any = __builtin_amdgcn_ballot_w64(on);
+                    if (any == 0ull) continue;
+                    const int first = __builtin_ctzll(any);
+                    const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)bk, first);
+                    const uint64_t same = __builtin_amdgcn_ballot_w64(on && bk == b0);
+                    if (lane == first) atomicAdd(&L.cnt[b0], (uint32_t)__builtin_popcountll(same));
+                    else if (on && bk != b0) atomicAdd(&L.cnt[bk], 1u);
+                }
+            }
+            __syncthreads();
+            scan(want, false);
+            const uint32_t bk = (uint32_t)L.found[0];
+            want -= L.found[1];
+            chosen = K - want + L.found[2];
+            base += bk << shift;
+            if (chosen <= kRankCap || shift == 0) break;
+            const int finer = max(0, shift - 10);
+            buckets = 1u << (shift - finer);
+            shift = finer;
+        }
+        const bool tied = chosen > kRankCap;
+        const uint32_t limit = base + ((1u << shift) - 1u);  // the largest distance chosen
+        if (tid == 0) L.n_list = 0;
+        __syncthreads();
+        for (int i0 = 0; i0 < a.V; i0 += 8 * NT) {
+            float x[8];
+            uint32_t take = 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = i0 + u * NT + tid < a.V ? p[i0 + u * NT + tid] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const uint32_t d = distance(x[u]);
+                take |= i0 + u * NT + tid < a.V && (tied ? d < base : d <= limit) ? 1u << u : 0u;
+            }
+            int at = reserve(__builtin_popcount(take));
+#pragma unroll
+            for (int u = 0; u < 8; ++u) put(x[u], i0 + u * NT + tid, (take >> u) & 1u, at);
+        }
+        for (int i0 = 0, have = 0; tied && i0 < a.V && have < want; i0 += 8 * NT) {  // (uniform)
+            const int i = i0 + tid * 8;
+            uint32_t bits = 0u;
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i + u < a.V && distance(p[i + u]) == base) bits |= 1u << u;
+            const int n = __builtin_popcount(bits), incl = wave_scan_inclusive_i32(n);
+            if (lane == 63) L.wave[wave] = incl;
+            __syncthreads();
+            int at = have + incl - n, total = 0;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                at += w < wave ? L.wave[w] : 0;
+                total += L.wave[w];
+            }
+            for (; bits != 0u && at < want; bits &= bits - 1u, ++at) {
+                const int id = i + __builtin_ctz(bits);
+                emit(K - want + at, composite(p[id], id));
+            }
+            have += total;
+            __syncthreads();
+        }
+        __syncthreads();
+        m = L.n_list;
+        if (m == 0) return;
     }
+    // a bucket of many (equal values, clusters far apart): a bitonic sort of all candidates, descending.  A wave has
+    // 128 consecutive places of its own, so only steps of 128 places and more wait for the others.
+    int n = 128;
+    while (n < m) n <<= 1;
+    for (int i = m + tid; i < n; i += NT) L.list[i] = 0ull;
+    __syncthreads();
+    for (int k = 2; k <= n; k <<= 1)
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int e = tid; e < n / 2; e += NT) {
+                const int at = ((e & ~(j - 1)) << 1) | (e & (j - 1));
+                const uint64_t x = L.list[at], y = L.list[at + j];
+                const bool descending = (at & k) == 0;
+                if ((x < y) == descending) L.list[at] = y, L.list[at + j] = x;
+            }
+            const int next = j > 1 ? j >> 1 : k;  // the next step's distance
+            if (j >= 128 || next >= 128) __syncthreads();
+            else __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+    __syncthreads();
+    for (int i = tid; i < min(m, K); i += NT) emit(i, L.list[i]);
 }
 
 // ------------------------------------------------------------------------------------------

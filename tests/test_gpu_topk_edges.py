@@ -54,6 +54,65 @@ def test_top_k_in_one_place(K):
     _check(x, K)
 
 
+def _row(kind, rng, V, K):
+    x = (rng.standard_normal(V) * 3.0).astype(np.float32)
+    lowest = np.finfo(np.float32).min
+    kept = np.zeros(V, bool)
+    if kind == "outlier":                      # the range of the group maxima is nearly empty
+        x[V // 3] = 1000.0
+    elif kind == "two clusters":
+        x[rng.permutation(V)[:K // 2]] += 5000.0
+    elif kind == "masked half, lowest":        # scattered
+        x[rng.random(V) < 0.5] = lowest
+    elif kind == "masked half, -1e9":          # whole chunks
+        x[V // 2:] = -1e9
+    elif kind == "masked half, -inf":
+        x[V // 2:] = -np.inf
+    elif kind == "few kept, -1e4":             # fewer than K at the smaller sizes: masked tokens in the order of ids
+        kept[rng.permutation(V)[:min(V, 150)]] = True
+        x[~kept] = -1e4
+    elif kind == "few kept, -inf":
+        kept[rng.permutation(V)[:min(V, 150)]] = True
+        x[~kept] = -np.inf
+    elif kind == "equal":
+        x[:] = 0.25
+    elif kind == "steps":
+        x = np.round(x * 2) / 2
+    elif kind == "zeros of both signs":
+        x = np.where(rng.random(V) < 0.5, -0.0, 0.0).astype(np.float32)
+        x[rng.permutation(V)[:K // 2]] = 1.0
+    elif kind == "powers":                     # a range that no linear scale resolves
+        x = np.ldexp(1.0, -rng.integers(0, 120, V)).astype(np.float32) * np.where(rng.random(V) < 0.5, 1, -1)
+    elif kind == "whole range":
+        x = (x / 16.0 * 3e38).astype(np.float32)
+    return x.astype(np.float32)
+
+
+KINDS = ["outlier", "two clusters", "masked half, lowest", "masked half, -1e9", "masked half, -inf", "few kept, -1e4",
+         "few kept, -inf", "equal", "steps", "zeros of both signs", "powers", "whole range"]
+
+
+@pytest.mark.parametrize("V,K", [(700, 64), (1000, 512), (6144, 200), (6144, 1024), (20011, 100), (50003, 300), (151936, 1024)])
+@pytest.mark.parametrize("kind", KINDS)
+def test_masks_ties_and_ranges(kind, V, K):
+    rng = np.random.default_rng(V + K + len(kind))
+    _check(np.stack([_row(kind, rng, V, K) for _ in range(3)]), K)
+
+
+@pytest.mark.parametrize("V,K", [(400003, 256), (700001, 200), (700001, 1024)])
+def test_rows_of_more_than_64_chunks(V, K):
+    rng = np.random.default_rng(V)
+    x = (rng.standard_normal((7, V)) * 3.0).astype(np.float32)
+    x[0, V - 5000:V - 5000 + K] += 30.0               # the top K behind chunk 64, more than its hot list takes
+    x[1, [100, V - 7]] = 40.0                         # the maximum on both sides of it
+    x[2, V - 6000:] = 20.0                            # equal values: a hot list that overflows there, ties at the K-th
+    x[3, :V - 9000] = -np.inf
+    x[4] = _row("masked half, -1e9", rng, V, K)
+    x[5] = _row("equal", rng, V, K)
+    x[6, rng.permutation(V)[:K // 2]] = 7.5
+    _check(x, K)
+
+
 def test_many_rows():
     rng = np.random.default_rng(5)
     x = (rng.standard_normal((7, 19, 20011)) * 2.0).astype(np.float32)
