@@ -188,7 +188,6 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
     const float *__restrict__ logits, int T, int V, int seg_len, int splits,
     const int32_t *__restrict__ n_nodes, ArgPart *__restrict__ part, SampleArgs sa)
 {
-    constexpr int kInFlight = 1;
     __shared__ float s_v[kArgmaxThreads / 64];
     __shared__ int s_i[kArgmaxThreads / 64];
     __shared__ uint32_t s_best;  // a lower bound on the row's best key, order-preserving
@@ -206,15 +205,8 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
     const float4 *pv = reinterpret_cast<const float4 *>(p + head);
     auto hash = [&](int id) { return sample_mix(sample_mix((uint32_t)id ^ sa.seed_lo) + row_term); };
 
-    float4 x[kInFlight];
-    auto load = [&](int j0) {
-#pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-            const int j = j0 + u * kArgmaxThreads;
-            x[u] = j < nvec ? load_streamed(pv + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-        }
-    };
-    load(tid);
+    auto load = [&](int j) { return j < nvec ? load_streamed(pv + j) : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY); };
+    float4 x = load(tid);
     if (tid == 0) s_best = 0u;
     float bv = -INFINITY;
     int bi = 0x7FFFFFFF;
@@ -225,7 +217,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
     __syncthreads();
     {
         // for u >= 1/2, -ln u <= 2 ln 2 (1 - u), so g >= -ln(1.387 (1 - u))
-        const float xe[4] = {x[0].x, x[0].y, x[0].z, x[0].w};
+        const float xe[4] = {x.x, x.y, x.z, x.w};
         float low = -INFINITY;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -240,12 +232,10 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
     __syncthreads();
     const float scale = sa.inv_tau * 1.44269504f;
     // (the loop is uniform over a wave: the wave maximum below wants all its lanes in every round)
-    for (int jb = tid & ~63; jb < nvec; jb += kInFlight * kArgmaxThreads) {
-        const int j0 = jb + (tid & 63);
-        float4 c[kInFlight];
-#pragma unroll
-        for (int u = 0; u < kInFlight; ++u) c[u] = x[u];
-        load(j0 + kInFlight * kArgmaxThreads);
+    for (int jb = tid & ~63; jb < nvec; jb += kArgmaxThreads) {
+        const int j = jb + (tid & 63);
+        const float4 c = x;
+        x = load(j + kArgmaxThreads);
         // (another wave's key may or may not be there yet: any of them will do)
         const uint32_t best = __hip_atomic_load(&s_best, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         // With k = h >> 8, 2^32 (1 - u) = 2^32 - 256 k - 128 >= ~h - 127: only an element with
@@ -255,31 +245,28 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
             const float t = __builtin_amdgcn_exp2f(fminf(fmaf(v, scale, bias), 32.0f));
             return t < 4294960000.0f ? ~(uint32_t)(t + 129.0f) : 0u;
         };
+        const int ia = start + head + 4 * j;
+        uint32_t h[4];
 #pragma unroll
-        for (int u = 0; u < kInFlight; ++u) {
-            const int j = j0 + u * kArgmaxThreads, ia = start + head + 4 * j;
-            uint32_t h[4];
+        for (int e = 0; e < 4; ++e) h[e] = hash(ia + e);
+        const bool need = j < nvec && max(max(h[0], h[1]), max(h[2], h[3])) >=
+                                          limit(fmaxf(fmaxf(c.x, c.y), fmaxf(c.z, c.w)));
+        if (__builtin_amdgcn_ballot_w64(need) == 0ull) continue;
+        const float xe[4] = {c.x, c.y, c.z, c.w};
+        const float before = bv;
 #pragma unroll
-            for (int e = 0; e < 4; ++e) h[e] = hash(ia + e);
-            const bool need = j < nvec && max(max(h[0], h[1]), max(h[2], h[3])) >=
-                                              limit(fmaxf(fmaxf(c[u].x, c[u].y), fmaxf(c[u].z, c[u].w)));
-            if (__builtin_amdgcn_ballot_w64(need) == 0ull) continue;
-            const float xe[4] = {c[u].x, c[u].y, c[u].z, c[u].w};
-            const float before = bv;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const bool this_one = need && h[e] >= limit(xe[e]);
-                if (__builtin_amdgcn_ballot_w64(this_one) == 0ull) continue;
-                const float k = sample_key(xe[e], h[e], sa);
-                if (this_one && k > bv) {
-                    bv = k;
-                    bi = ia + e;
-                }
+        for (int e = 0; e < 4; ++e) {
+            const bool this_one = need && h[e] >= limit(xe[e]);
+            if (__builtin_amdgcn_ballot_w64(this_one) == 0ull) continue;
+            const float k = sample_key(xe[e], h[e], sa);
+            if (this_one && k > bv) {
+                bv = k;
+                bi = ia + e;
             }
-            if (__builtin_amdgcn_ballot_w64(bv > before) != 0ull) {
-                const float wmax = wave_max_f32(bv);
-                if ((tid & 63) == 0) atomicMax(&s_best, float_key(wmax));
-            }
+        }
+        if (__builtin_amdgcn_ballot_w64(bv > before) != 0ull) {
+            const float wmax = wave_max_f32(bv);
+            if ((tid & 63) == 0) atomicMax(&s_best, float_key(wmax));
         }
     }
     if (tid < n - tail0) arg_update(bv, bi, sample_key(behind, hash(start + tail0 + tid), sa), start + tail0 + tid);

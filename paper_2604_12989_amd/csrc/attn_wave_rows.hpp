@@ -9,11 +9,10 @@ namespace ddt {
 // Sizes that follow from the head dim D and the row blocks per wave RB.
 template <int D, int RB>
 struct WaveShape {
-    // 64 rows of 128 dims take 128 registers for the results and 64 for the queries: one wave per SIMD.
-    // Everything else runs with two.
-    static constexpr int waves = D == 128 && RB == 2 ? 4 : 8;
+    static_assert(D == 64 || RB == 1, "64 rows of 128 dims would take 192 registers a lane for results and queries alone");
+    static constexpr int waves = 8;
     static constexpr int threads = 64 * waves;
-    static constexpr int stages = D == 128 && RB == 1 ? 1 : 2;  // sub-tiles of a wave in LDS
+    static constexpr int stages = D == 128 ? 1 : 2;  // sub-tiles of a wave in LDS
     static constexpr int row_bytes = D * 2;                  // one key or value row in LDS
     static constexpr int tile_bytes = kSK * row_bytes;       // K or V sub-tile
     static constexpr int mask_bytes = 256;                   // a mask word per row of the sub-tile's row blocks
@@ -294,7 +293,7 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
         prepare(0, masked, (tree ? w[0] : ~0u) & vbits);
         if constexpr (RB == 2) {
             static_for<0, 8>([&](auto I) {
-                if constexpr (KS == 8 || decltype(I)::value % 2 == 0) mfma_s(1, IC<KS == 8 ? decltype(I)::value : decltype(I)::value / 2>{});
+                if constexpr (decltype(I)::value % 2 == 0) mfma_s(1, IC<decltype(I)::value / 2>{});
                 weights(0, I);
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -310,7 +309,7 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
         if constexpr (RB == 2) {
             prepare(1, masked, (tree ? w[1] : ~0u) & vbits);
             static_for<0, 8>([&](auto I) {
-                if constexpr (DB == 4 || decltype(I)::value % 2 == 0) mfma_o(0, IC<DB == 4 ? decltype(I)::value : decltype(I)::value / 2>{});
+                if constexpr (decltype(I)::value % 2 == 0) mfma_o(0, IC<decltype(I)::value / 2>{});
                 weights(1, I);
                 __builtin_amdgcn_sched_barrier(0);
             });
@@ -321,7 +320,7 @@ __device__ __forceinline__ void attn_wave_rows(const Args &args, const AttnWaveI
     };
     for (int i = 0; i < n; ++i) step(i);
 
-    // ---- the four waves' results are combined in LDS (the rings are idle: every request of a wave
+    // ---- the eight waves' results are combined in LDS (the rings are idle: every request of a wave
     //      has landed before its last sub-tile was worked on) ----
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
