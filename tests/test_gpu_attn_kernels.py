@@ -99,11 +99,16 @@ def test_scores_that_keep_outgrowing_the_reference(T, L, Hq, Hkv, D):
 
 
 def test_padding_rows_are_zero_in_every_kernel():
+    """... and every head of every real row is what the oracle says."""
     for T, L, Hq, Hkv, D in ((80, 50, 4, 2, 64), (80, 50, 4, 2, 128), (300, 6000, 32, 8, 128), (257, 4096, 32, 8, 64)):
         rng = np.random.default_rng(T)
-        q, kc, vc, kt, vt = di.attn_tensors(T, T, L, Hq, Hkv, D, "bf16")
-        got = gu.gpu_attn(q, kc, vc, kt, vt, _tree_mask(rng, T, 40)[None], [0, L], 1, T, "bf16")[0]
-        assert not got[41:].any() and np.isfinite(got).all() and np.abs(got[:41]).min(axis=(1, 2)).max() > 0.0
+        parts = di.attn_tensors(T, T, L, Hq, Hkv, D, "bf16")
+        mask = _tree_mask(rng, T, 40)
+        got = gu.gpu_attn(*parts, mask[None], [0, L], 1, T, "bf16")[0]
+        assert not got[41:].any() and np.isfinite(got).all()
+        assert np.abs(got[:41]).max(axis=2).min() > 0.0
+        pairs = np.stack(np.meshgrid(np.arange(41), np.arange(Hq), indexing="ij"), axis=-1).reshape(-1, 2).astype(np.int32)
+        assert gu.attn_err(got[pairs[:, 0], pairs[:, 1]], oracle.verify_attn(*parts, mask, pairs=pairs)) < 1e-2
 
 
 def test_heads_of_64_need_no_scratch():
