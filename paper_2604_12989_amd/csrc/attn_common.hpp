@@ -73,6 +73,8 @@ struct AttnWaveArgs {
     int32_t groups, rows_per_group;
     int32_t group_size;                  // G = Hq / Hkv
     uint32_t g_magic, groups_magic, hkv_magic, run_magic;  // reciprocals of G, groups, Hkv, run
+    int32_t per_seq;                     // (key range, kv head) pairs of every sequence, 0 where they differ
+    uint32_t per_seq_magic;
     int32_t grid;
     float scale_log2e;
     AttnWaveSeq seq[DDTREE_MAX_BATCH];   // (behind what every workgroup reads first)
@@ -96,9 +98,13 @@ __host__ __device__ __forceinline__ bool attn_wave_item(const AttnWaveArgs &args
     const int unit = div_by(wid, args.groups, args.groups_magic);
     w.grp = wid - unit * args.groups;
     int pos = 0;  // the last sequence whose first unit is not behind this one
+    if (args.per_seq > 0) {
+        pos = div_by(unit, args.per_seq, args.per_seq_magic);
+    } else {
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1)
-        if (pos + s < args.batch && args.seq[pos + s].first_unit <= unit) pos += s;
+        for (int s = 32; s >= 1; s >>= 1)
+            if (pos + s < args.batch && args.seq[pos + s].first_unit <= unit) pos += s;
+    }
     const AttnWaveSeq &e = args.seq[pos];
     const int local = unit - e.first_unit;
     w.split = div_by(local, args.Hkv, args.hkv_magic);
@@ -131,6 +137,10 @@ struct AttnMainArgs {
     int32_t batch, n_tiles, blk_base, blk_extra, uneven;
     int32_t group_size;                  // G = Hq / Hkv
     uint32_t g_magic, tiles_magic, extra_magic;  // reciprocals of G, n_tiles and blk_extra
+    // work items of every sequence, whole tiles' and tail blocks', 0 where they differ (the search for the sequence
+    // is a chain of six loads: 0.7 us of 14 for 16 sequences of 36 nodes x 127 keys)
+    int32_t per_seq, tail_per_seq;
+    uint32_t per_seq_magic, tail_per_seq_magic;
     int32_t grid;
     AttnMainSeq seq[DDTREE_MAX_BATCH];
 };
@@ -153,9 +163,14 @@ __host__ __device__ __forceinline__ bool attn_main_item(const AttnMainArgs &args
     wid += w.tail ? args.tail_start[x] - n_main : args.xcd_start[x];
     if (w.tail && wid >= args.tail_start[x + 1]) return false;
     int pos = 0;
+    const int per_seq = w.tail ? args.tail_per_seq : args.per_seq;
+    if (per_seq > 0) {
+        pos = div_by(wid, per_seq, w.tail ? args.tail_per_seq_magic : args.per_seq_magic);
+    } else {
 #pragma unroll
-    for (int s = 32; s >= 1; s >>= 1)
-        if (pos + s < args.batch && (w.tail ? args.seq[pos + s].first_tail : args.seq[pos + s].first_item) <= wid) pos += s;
+        for (int s = 32; s >= 1; s >>= 1)
+            if (pos + s < args.batch && (w.tail ? args.seq[pos + s].first_tail : args.seq[pos + s].first_item) <= wid) pos += s;
+    }
     const AttnMainSeq &e = args.seq[pos];
     const int local = wid - (w.tail ? e.first_tail : e.first_item);
     const int tiles = w.tail ? args.blk_extra : args.n_tiles;

@@ -82,9 +82,9 @@ struct Sized {
     double cost;
     long long count;
 };
-// Their time on 256 compute units, one at a time on each: what all of them make together and half of
-// the longest, and no less than k times the k-th round's longest.
-static double rounds_us(const Sized *w, int n)
+// Their time on 256 compute units, one at a time on each: k times the k-th round's longest, and, where others run
+// beside them (`beside`) or their sizes differ, no less than what all of them make together and a third of the longest.
+static double rounds_us(const Sized *w, int n, bool beside, double tail)
 {
     long long items = 0;
     double sum = 0.0, t = 0.0;
@@ -93,7 +93,7 @@ static double rounds_us(const Sized *w, int n)
         items += w[i].count;
         sum += w[i].cost * w[i].count;
     }
-    return items <= 256 ? t : std::max(t, sum / 256 + 0.5 * w[0].cost);
+    return items <= 256 || (n == 1 && !beside) ? t : std::max(t, sum / 256 + tail * w[0].cost);
 }
 
 // The lengths of a call as the plans see them: sequences longest first, those of the same number of cache
@@ -155,7 +155,12 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
     Sized sized[DDTREE_MAX_BATCH];
     // Measured (us): a workgroup's fixed cost (launch, first requests, combining the waves' results), a
     // step of its eight waves (32 keys each), the rates at which the L2s and HBM serve all of them.
-    const double fix = 7.0, step = D == 64 ? (row_blocks == 1 ? 0.62 : 1.17) : 1.2;
+    // A step whose keys no L2 holds waits for HBM, in one workgroup's row group at least (48 workgroups of one row
+    // group over 85 MB: 2.7 us; 192 to 512 of four over 79 to 363 MB: 2.3 to 2.5, of ten and more 1.3 to 1.8).
+    const double far = D == 64 ? 0.0 : std::min(1.0, std::max(0.0, ((double)sub_tiles * Hkv * (kSK * 4.0 * D) * 1e-6 - 24.0) / 48.0)) *
+                                           (p.groups <= 6 ? 1.0 : p.groups <= 9 ? 0.7 : 0.3);
+    const double fix = 7.0, step = D == 64 ? (row_blocks == 1 ? 0.62 : 1.17) : 1.2 + 1.2 * far;
+    const double masked = D == 64 ? 0.0 : 0.19;  // more for each sub-tile of a large tree (997 nodes over 230 keys: 2.7 us a step)
     const double l2_us = (double)sub_tiles * Hkv * p.groups * (kSK * 4.0 * D) / 20.0e6;
     const double hbm_us = (double)sub_tiles * Hkv * (kSK * 4.0 * D) / 4.0e6;
     const double least = 5.0 + std::max(l2_us, hbm_us);
@@ -168,11 +173,13 @@ static AttnPlan plan_wave(int batch, int T, int Hq, int Hkv, int D, const int32_
         for (int i = 0; i < lens.n; ++i) {
             const int nt = lens.sub[i] + tree, si = by_c(nt);
             slots += (long long)si * lens.count[i];
-            sized[i] = Sized{fix + step * up(si == 1 ? nt : up(nt, si), 8), (long long)lens.count[i] * si * Hkv * p.groups};
+            const int range = si == 1 ? nt : up(nt, si);
+            sized[i] = Sized{fix + step * up(range, 8) + masked * std::max(0, std::min(tree, range) - 8),
+                             (long long)lens.count[i] * si * Hkv * p.groups};
         }
         const double merge = s > 1 ? merge_us(slots, T, Hq, D, wide) : 0.0;
         if (s > 1 && (slots > cap || least + merge >= p.cost)) break;  // (partial results only grow in number)
-        const double cost = std::max(rounds_us(sized, lens.n), least) + merge;
+        const double cost = std::max(rounds_us(sized, lens.n, false, 0.0), least) + merge;
         if (cost < p.cost) p.cost = cost, best_c = c;
     }
     int first = 0;
@@ -202,23 +209,26 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
     Sized sized[DDTREE_MAX_BATCH];
     long long key_tiles = 0;
     for (int i = 0; i < lens.n; ++i) key_tiles += (long long)(up(lens.sub[i], 2) + tree) * lens.count[i];
-    const double hbm_us = (double)key_tiles * Hkv * (kKT * 4.0 * kHD) / 5.0e6;
+    const double hbm_us = (double)key_tiles * Hkv * (kKT * 4.0 * kHD) / 5.8e6;
     // Measured (us): a workgroup's fixed cost and a key tile (below three quarters of the compute units at work,
     // and with all of them, where the chip lowers its clock: 1.92 over 131 key tiles); for a tail block, and a
     // step of eight sub-tiles beside them (1.2 alone, keys from the L2).  With 513 nodes x 32768 keys, four key
     // ranges and the tail blocks in a second round (the sum of times says 246 us) took 340 where three and
     // everything in one round take 307: the few workgroups of that second round wait for HBM.
-    // Workgroups of one or two blocks (few rows over long caches) spend less on a tile.
-    const bool low = nblk <= 2;
-    const double fix = 11.0, tile_few = low ? 0.95 : 1.52, tile_all = low ? 0.95 : 1.9, tail_fix = 7.0, tail_step = 2.4;
+    // Workgroups of fewer blocks (few rows over long caches) spend less on a tile: of one or two 0.9, of three or four
+    // 1.05 and with all compute units at work 1.15, of five or six 1.45 and 1.55; up to four, less on the rest too.
+    const double tail_fix = 7.0, tail_step = 2.4;
     const long long cap = std::min(room, main_slot_cap(batch, T, Hq, Hkv));
     AttnPlan best{};
     best.cost = 1e30;
     int best_c = nt_max, best_ct = 0;
-    int si[DDTREE_MAX_BATCH];
+    int si[DDTREE_MAX_BATCH], range[DDTREE_MAX_BATCH];
     for (int uneven = 0; uneven < 2; ++uneven) {
         if (uneven && !(full >= 1 && rem >= 1 && rem <= 4)) break;
-        const int tiles = uneven ? full : up(nblk, 8);
+        const int tiles = uneven ? full : up(nblk, 8), blocks = uneven ? 8 : up(nblk, tiles);
+        const double tile_few = blocks <= 2 ? 0.95 : blocks <= 4 ? 1.05 : blocks <= 6 ? 1.45 : 1.52;
+        const double tile_all = blocks <= 2 ? 0.95 : blocks <= 4 ? 1.15 : blocks <= 6 ? 1.55 : 1.9;
+        const double fix = blocks <= 4 ? 9.0 : 11.0;
         bool more = true;
         for (int s = 1, c_before = 0; more && s <= 32 && (s == 1 || s * 2 <= nt_max); ++s) {
             const int c = up(nt_max, s);
@@ -234,14 +244,22 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
             // (with shorter key ranges both kinds leave more partial results: what is too many, or too many to pay, stays so)
             const double least = fix + hbm_us;
             if (s > 1 && (main_slots > cap || least + merge_us(main_slots, T, Hq, kHD, wide) >= best.cost)) break;
-            const double tile = tile_few + (tile_all - tile_few) * std::min(1.0, std::max(0.0, (items - 192) / 64.0));
-            double main_sum = 0.0;
+            // compute units at work while the longest range is walked, on average (those of short sequences end early)
+            int longest = 1;
+            double walked = 0.0;
             for (int i = 0; i < lens.n; ++i) {
                 const int nt = up(lens.sub[i], 2) + tree;
-                sized[i].cost = fix + tile * (si[i] == 1 ? nt : up(nt, si[i]));
+                range[i] = si[i] == 1 ? nt : up(nt, si[i]);
+                longest = std::max(longest, range[i]);
+                walked += (double)range[i] * sized[i].count;
+            }
+            const double tile = tile_few + (tile_all - tile_few) * std::min(1.0, std::max(0.0, (walked / longest - 192) / 64.0));
+            double main_sum = 0.0;
+            for (int i = 0; i < lens.n; ++i) {
+                sized[i].cost = fix + tile * range[i];
                 main_sum += sized[i].cost * sized[i].count;
             }
-            const double main_work = rounds_us(sized, lens.n);
+            const double main_work = rounds_us(sized, lens.n, uneven != 0, 0.5);
             if (s > 1 && std::max(main_work, least) + merge_us(main_slots, T, Hq, kHD, wide) >= best.cost) continue;
             // ranges of a tail block: those that take as long as a whole tile's, and more of them in turn
             const int t0 = uneven ? std::min(32, std::max(1, (int)(tail_step * up(sub_max, 8) / (fix - tail_fix + tile_few * c)))) : 0;
@@ -273,7 +291,7 @@ static AttnPlan plan_main(int batch, int T, int Hq, int Hkv, const int32_t *kv_l
                 if (items + tails <= 256)
                     work = std::max(work, tail_longest);
                 else if (items <= 256)
-                    work += tails > 0 ? 1.5 * tail_longest * up((int)tails, 256) : 0.0;
+                    work += tails > 0 ? std::max(1.5 * tail_longest * up((int)tails, 256), 1.2 * hbm_us) : 0.0;  // (they read the keys again)
                 else
                     work = std::max(work, sum / 256 + 0.5 * tail_longest);
                 const double cost = std::max(work, least) + merge;
@@ -361,6 +379,13 @@ size_t attn_scratch_bytes(int batch, int T, int Hq, int Hkv, int D, int dtype, l
     return p.bytes;
 }
 
+static bool same_of_all(const AttnPlan &p, int batch, int32_t AttnSeqPlan::*of)
+{
+    for (int i = 1; i < batch; ++i)
+        if (p.seq[i].*of != p.seq[0].*of) return false;
+    return true;
+}
+
 // False if the launch would exceed 2^28 work items.
 bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_start, const int32_t *kv_len, int batch,
                     int T, int Hq, int Hkv)
@@ -391,6 +416,8 @@ bool attn_wave_args(AttnWaveArgs &args, const AttnPlan &p, const int32_t *kv_sta
                                   magic_of((uint64_t)p.seq[s].splits, (uint64_t)(up(kv_len[s], kSK) + up(T, kSK)) * p.seq[s].splits)};
         unit += p.seq[s].splits * Hkv;
     }
+    args.per_seq = batch > 1 && same_of_all(p, batch, &AttnSeqPlan::splits) ? p.seq[0].splits * Hkv : 0;
+    args.per_seq_magic = magic_of((uint64_t)args.per_seq, (uint64_t)unit);
     return true;
 }
 
@@ -404,7 +431,17 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
     args.group_size = G;
     args.g_magic = magic_of((uint64_t)G, (uint64_t)T * G);
     const Lens lens = lens_of(kv_len, batch);
-    const int32_t *const order = lens.order;
+    int32_t order[DDTREE_MAX_BATCH];
+    // In one round, where the XCDs take equal numbers of items, each gets long and short sequences alike: the 8 k-th
+    // longest are dealt to the XCDs in turn, forth and back.
+    if (p.items <= 256 && batch >= 16)
+        for (int x = 0, n = 0; x < 8; ++x)
+            for (int i = 0; i < batch; i += 8) {
+                const int from = i + ((i & 8) ? 7 - x : x);
+                if (from < batch) order[n++] = lens.order[from];
+            }
+    else
+        std::copy(lens.order, lens.order + batch, order);
     long long total = 0, tail_total = 0, per_head_max = 1;
     for (int i = 0; i < batch; ++i) {
         const int s = order[i];
@@ -422,6 +459,10 @@ bool attn_main_args(AttnMainArgs &args, const AttnPlan &p, const int32_t *kv_sta
         if (total + tail_total > (1ll << 28)) return false;
         per_head_max = std::max(per_head_max, std::max(per_head, per_tail));
     }
+    args.per_seq = batch > 1 && same_of_all(p, batch, &AttnSeqPlan::splits) ? (int32_t)(total / batch) : 0;
+    args.tail_per_seq = batch > 1 && same_of_all(p, batch, &AttnSeqPlan::tail_splits) ? (int32_t)(tail_total / batch) : 0;
+    args.per_seq_magic = magic_of((uint64_t)args.per_seq, (uint64_t)total);
+    args.tail_per_seq_magic = magic_of((uint64_t)args.tail_per_seq, (uint64_t)tail_total);
     args.tiles_magic = magic_of((uint64_t)p.n_tiles, (uint64_t)per_head_max);
     args.extra_magic = tails ? magic_of((uint64_t)tails, (uint64_t)per_head_max) : 0u;
     // Consecutive work items run on the same XCD: the row tiles that read the same K and V rows share an
