@@ -26,8 +26,8 @@
 // 20.0 -> 16.2; 32 rows K = 128 23.8 -> 17.6; 112 rows 53.9 -> 29.6; 256 rows 66 -> 54; 8 rows of 1024 12.0 -> 7.3.
 // Rows whose maxima say little about their top K (masked tokens, an outlier, ties), by the ranking chunks, with one
 // range of buckets and a select over the row in six passes, and now: 16 rows K = 256 half masked with -1e9 203 / 181 / 17
-// us, equal logits 111 / 721 / 126; K = 1024 one token 1000 above the others 73 / 117 / 35, half masked with -inf 135 / 206 / 128;
-// 256 rows K = 128 half masked with -1e9 56 / 296 / 57.  Their code costs the other rows 0.1 to 0.3 us a call.
+// us, equal logits 111 / 721 / 128; K = 1024 one token 1000 above the others 73 / 117 / 16, half masked with -inf 135 / 206 / 130;
+// 256 rows K = 128 half masked with -1e9 56 / 296 / 58.  Their code costs the other rows 0.1 to 0.4 us a call.
 #include <algorithm>
 #include <cmath>
 
@@ -197,9 +197,14 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
     }
     const float hi = wave_max_f32(vmax);
     vlow = wave_min_u32(vlow);
-    float top = hi, low = vlow == ~0u ? hi : key_float(vlow);  // the range of the buckets
+    // The range of the buckets ends at the second largest chunk maximum: one token far above the others (a confident
+    // row) does not stretch it.  What lies above is in bucket 0.
+    const uint64_t tops = __builtin_amdgcn_ballot_w64(vmax == hi);
+    float top = wave_max_f32(lane == __builtin_ctzll(tops) ? -INFINITY : vmax), low = vlow == ~0u ? hi : key_float(vlow);
+    if (!(top > low)) top = hi;
+    float ceiling = INFINITY;  // (of the maxima still counted: at first, bucket 0 holds those above the range too)
     float inv = (float)kBuckets / fmaxf(top - low, 1e-30f);
-    auto bucket_of = [&](float v) { return (int)fminf((top - v) * inv, (float)(kBuckets - 1)); };  // (above the range: negative)
+    auto bucket_of = [&](float v) { return (int)fminf(fmaxf((top - v) * inv, 0.0f), (float)(kBuckets - 1)); };
     auto each_maximum = [&](auto &&f) __attribute__((always_inline)) {
 #pragma unroll
         for (int u = 0; u < PRE; ++u)
@@ -253,16 +258,18 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
         __syncthreads();
     };
     scan(K, false);
-    const bool bounded = L.found[0] != kBuckets;  // otherwise there are fewer maxima than ranks
+    // (Fewer maxima than ranks: no bound.  All elements of a short row are candidates then.)
+    const bool all = L.found[0] == kBuckets && a.V <= kRankCap;
+    const bool bounded = L.found[0] != kBuckets || all;
     int want = K;
     // A bucket that holds many maxima at once (an outlier or masked tokens stretch the range, most of it empty):
     // the same again over the maxima of that bucket alone.
-    for (int round = 0; bounded && __builtin_expect(L.found[2] > 64 + 3 * K / 8, 0) && round < 8; ++round) {  // (uniform)
+    for (int round = 0; bounded && !all && __builtin_expect(L.found[2] > 64 + 3 * K / 8, 0) && round < 8; ++round) {  // (uniform)
         const int crowded = L.found[0];
         want -= L.found[1];
         uint32_t kl = ~0u, kh = 0u;
         each_maximum([&](float v) {
-            if (v <= top && v >= low && bucket_of(v) == crowded) kl = min(kl, float_key(v)), kh = max(kh, float_key(v));
+            if (v <= ceiling && v >= low && bucket_of(v) == crowded) kl = min(kl, float_key(v)), kh = max(kh, float_key(v));
         });
         kl = wave_min_u32(kl);
         kh = ~wave_min_u32(~kh);
@@ -273,7 +280,7 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
         __syncthreads();
         kl = L.low;
         kh = L.high;
-        top = key_float(kh);
+        top = ceiling = key_float(kh);
         low = key_float(kl);
         inv = kl == kh ? 1e38f : (float)kBuckets / fmaxf(top - low, 1e-30f);  // (one value: what lies below it is far away)
         if (kl != kh) each_maximum([&](float v) { if (v <= top && v >= low) atomicAdd(&L.cnt[bucket_of(v)], 1u); });
@@ -286,7 +293,7 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
         if (kl != kh) scan(want, false);
         else __syncthreads();
     }
-    const int last = bounded ? L.found[0] : -1;  // elements of buckets 0 .. last are candidates, at least K of them
+    const int last = all ? kBuckets - 1 : bounded ? L.found[0] : -1;  // elements of buckets 0 .. last are candidates, at least K of them
     const bool whole = a.hot_cap == 0;           // the row is read again, all of it
     auto composite = [&](float x, int i) -> uint64_t {
         return ((uint64_t)float_key(x) << 32) | (uint64_t)(uint32_t)(~(uint32_t)i);
@@ -401,7 +408,7 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
                 mine[u] = L.list[i];
                 bkt[u] = bucket2(mine[u]);
                 pos[u] = (int)atomicAdd(&L.cnt[bkt[u]], 1u);
-                if (pos[u] == kCrowded) L.crowded = 1;
+                if (pos[u] == kCrowded && !(all && bkt[u] == kBuckets - 1)) L.crowded = 1;
             }
         }
         __syncthreads();

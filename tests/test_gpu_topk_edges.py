@@ -113,6 +113,20 @@ def test_rows_of_more_than_64_chunks(V, K):
     _check(x, K)
 
 
+@pytest.mark.parametrize("K", [86, 150, 300])
+def test_one_chunk_above_all_others(K):
+    # rows of two chunks, every group maximum of one above the other chunk's maximum: the K-th maximum lies above the
+    # range that the second largest chunk maximum ends
+    rng = np.random.default_rng(K)
+    x = rng.standard_normal((16, 16, 12000)).astype(np.float32)
+    x[0::2, :, :6000] += 50.0
+    x[1::2, :, 6000:] += 50.0 * (1 + np.arange(16))[None, :, None]
+    tok_g, lp_g = gu.gpu_topk(x, K)
+    for b in (0, 1, 14, 15):
+        tok_o, lp_o = oracle.topk(x[b], K)
+        assert np.array_equal(tok_g[b], tok_o) and ulp_diff(lp_g[b], lp_o).max() <= 2
+
+
 def test_many_rows():
     rng = np.random.default_rng(5)
     x = (rng.standard_normal((7, 19, 20011)) * 2.0).astype(np.float32)
