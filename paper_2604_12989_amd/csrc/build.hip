@@ -1,8 +1,9 @@
 // Best-first draft-tree construction (paper Algorithm 1) and the tensors compiled from the
 // tree for the verifier (Section 4.4: token ids, depth as position id, ancestor-only mask).
 //
-// One workgroup per sequence; the pops are inherently serial (pop i+1 depends on the pushes of
-// pop i), so a single wavefront runs them and the others wait at a barrier, then all
+// One workgroup per sequence.  Three constructions of the same tree: by deviations and by levels, which find it as a
+// set (see there), and Algorithm 1's pops.  The pops are inherently serial (pop i+1 depends on the pushes of
+// pop i), so a single wavefront runs them and the others wait at a barrier.  Then all
 // threads write the outputs and the ancestor bitmask.
 //
 // Frontier layout.  Algorithm 1's heap holds, at any time, exactly one candidate per node that
@@ -22,9 +23,13 @@
 // smaller rank tuple first, a prefix before its extensions.  They are rare and take a slow
 // path that walks parent links in LDS.
 #include "common.hpp"
+#include <algorithm>
 #include <atomic>
 
 namespace ddt {
+
+// Floats from one row of the log-probability table in LDS to the next: K and three or four of padding.
+__host__ __device__ constexpr int table_stride(int K) { return K % 4 == 0 ? K + 4 : K + 3; }
 
 __device__ __forceinline__ uint32_t pack_node(int parent, int rank, int depth)
 {
@@ -88,9 +93,8 @@ __device__ bool tuple_before(const uint32_t *s_node, int pa, int ra, int pb, int
 //   * levels with at most 64 parents are run by one wave without barriers (see wave_levels); a
 //     level whose candidates do not fit their arrays is counted by bucket first, the cut moves,
 //     and its children are counted again.
-//   * where the prefixes entered up front already give a cut (peaked rows), the members are not
-//     found depth by depth at all but by generations: by the number of their non-zero ranks, of
-//     which there are at most log2(N + 1) + 1 (see by_generations).
+// It serves what the construction by deviations below does not: fewer ranks than budget, and more members
+// than that one has room for.
 // Giving up (a cut that cannot be proven, or a capacity that heavy ties exceed) returns -1 and
 // the caller runs the sequential pops instead.
 // ------------------------------------------------------------------------------------------
@@ -206,14 +210,14 @@ __device__ __forceinline__ void build_block_scan2(int *a, int *b, int (*s_w2)[NT
 
 // Returns the number of nodes written to s_node / s_score (ids 1..n), or -1 after giving up.
 template <int NT>
-__device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, LevelMem L,
+__device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, LevelMem L, int *s_bucket,
                            uint32_t *s_node, float *s_score)
 {
     static_assert(NT >= kLvBuckets, "one bucket per thread");
-    __shared__ __align__(16) int s_hist[kLvBuckets + 4];    // every prefix known so far, by bucket
-    __shared__ __align__(16) int s_histc[kLvBuckets + 4];   // the candidates of the level; at the end: cursors
-    __shared__ __align__(16) int s_histv[kLvBuckets + 4];   // the prefixes the level makes known
-    __shared__ __align__(16) int s_pref[kLvBuckets + 4];    // exclusive prefix of s_histc, later of s_hist
+    int *const s_hist = s_bucket;                           // every prefix known so far, by bucket
+    int *const s_histc = s_hist + kLvBuckets + 4;           // the candidates of the level; at the end: cursors
+    int *const s_histv = s_histc + kLvBuckets + 4;          // the prefixes the level makes known
+    int *const s_pref = s_histv + kLvBuckets + 4;           // exclusive prefix of s_histc, later of s_hist
     __shared__ int s_state[8];                // what the single-wave levels hand back to the workgroup
     __shared__ float s_cc[DDTREE_MAX_B + 1];  // scores of the top-1 chain's nodes
     __shared__ __align__(16) int s_w[NT / 64];
@@ -440,135 +444,6 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
     }
     __syncthreads();
     bstar = s_state[5];
-
-    // By generations.  Where the up-front entries already give a cut (peaked rows), the members --
-    // every prefix at or above it -- are enumerated by the number of their non-zero ranks instead
-    // of by depth: generation g + 1 is found from generation g in one step of the whole workgroup,
-    // and there are at most log2(N + 1) + 1 generations (a prefix with g non-zero ranks has 2^g - 1
-    // better ones: itself with any subset of them set to rank 0), two or three on a tree from a
-    // confident drafter, against B levels.  One step: (A) every head of the generation (a member
-    // that ends in a non-zero rank; the root for generation 0) walks its top-1 continuation while
-    // it stays at or above the cut, and those nodes become members; (B) every head and every
-    // continuation node counts its children of rank >= 1 at or above the cut (a prefix of its
-    // sorted row): they are the heads of the next generation.  The cut is left where it is
-    // (allowed: see the settled levels below), so nothing is bucketed and no histogram is kept;
-    // if that lets in far more members than a tight cut would (beyond 3.5 N + 64), the
-    // construction starts over level by level; a smaller surplus is shed when the members are
-    // ranked.  Returns the number of members, or -1.
-    auto by_generations = [&]() -> int {
-        const int limit = min(L.capm, 3 * N + N / 2 + 64);
-        const int cap = min(K, N);
-        auto alive = [&](float v) { return v > kLvNeg && bucket_of(v) <= bstar; };
-        int hs = 0, he = 1, Mg = 1;
-        if (tid == 0) s_nbig = 0;  // (the scan below has barriers before the first use)
-        for (;;) {
-            // A. the continuations of the heads [hs, he)
-            const int n_heads = he - hs;
-            const int chain_base = Mg;
-            int Cn = 0;
-            for (int i0 = 0; i0 < n_heads; i0 += NT) {
-                const int i = i0 + tid, h = hs + i;
-                float S = 0.0f;
-                int dh = 0, len = 0;
-                if (i < n_heads) {
-                    S = L.m_score[h];
-                    dh = member_depth(L.m_info[h]);
-                    float v = S;
-                    bool live = true;
-                    for (int t0 = dh; t0 < B && live; t0 += 8) {
-                        float inc[8];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) inc[k] = s_lp[min(t0 + k, B - 1) * Kp];
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) asm volatile("" : "+v"(inc[k]));
-#pragma unroll
-                        for (int k = 0; k < 8; ++k) {
-                            v += inc[k];
-                            live = live && t0 + k < B && alive(v);
-                            len += live ? 1 : 0;
-                        }
-                    }
-                }
-                int total;
-                const int off = Cn + build_block_scan<NT>(len, s_w, &total);
-                if (chain_base + Cn + total > limit) return -1;  // (before anything of it is written)
-                if (len > 0) {
-                    float v = S;
-                    for (int j = 0; j < len; ++j) {
-                        v += s_lp[(dh + j) * Kp];
-                        const int id = chain_base + off + j;
-                        L.m_score[id] = v;
-                        L.m_info[id] = pack_member(j == 0 ? h : id - 1, 0, dh + 1 + j);
-                        L.m_jlo[id] = 0;
-                    }
-                }
-                Cn += total;
-            }
-            Mg = chain_base + Cn;
-            __syncthreads();
-            // B. the children of rank >= 1 of the heads and of their continuation nodes
-            const int n_par = n_heads + Cn;
-            const int head_base = Mg;
-            int H = 0;
-            for (int p0 = 0; p0 < n_par; p0 += NT) {
-                const int p = p0 + tid;
-                const int pm = p < n_heads ? hs + p : chain_base + (p - n_heads);
-                float S = 0.0f;
-                int dp = 0, c = 0;
-                if (p < n_par) {
-                    S = L.m_score[pm];
-                    dp = member_depth(L.m_info[pm]);
-                    if (dp < B) c = max(0, count_children(s_lp + dp * Kp, S, cap, bstar) - 1);
-                }
-                int total;
-                const int off = H + build_block_scan<NT>(c, s_w, &total);
-                if (head_base + H + total > limit) return -1;
-                // small families are written by their parent's thread, large ones are queued and
-                // written by the whole workgroup (s_nbig is 0 here: see the end of the round)
-                bool own = c > 0;
-                if (c > kLvSmall) {
-                    const int slot = atomicAdd(&s_nbig, 1);
-                    if (slot < kLvBigCap) {
-                        s_big[slot] = (uint16_t)pm;
-                        L.p_c[slot] = (uint16_t)c;
-                        L.p_off[slot] = (uint16_t)off;  // (below limit <= capm <= 8192)
-                        own = false;
-                    }
-                }
-                if (own) {
-                    const float *row = s_lp + dp * Kp;
-                    for (int r = 1; r <= c; ++r) {
-                        const int id = head_base + off + r - 1;
-                        L.m_score[id] = S + row[r];
-                        L.m_info[id] = pack_member(pm, r, dp + 1);
-                        L.m_jlo[id] = 0;
-                    }
-                }
-                __syncthreads();
-                const int nbig = min(s_nbig, kLvBigCap);
-                for (int qb = 0; qb < nbig; ++qb) {
-                    const int bpm = s_big[qb], bc = L.p_c[qb], boff = L.p_off[qb];
-                    const float bS = L.m_score[bpm];
-                    const int bdp = member_depth(L.m_info[bpm]);
-                    const float *row = s_lp + bdp * Kp;
-                    for (int r = 1 + tid; r <= bc; r += NT) {
-                        const int id = head_base + boff + r - 1;
-                        L.m_score[id] = bS + row[r];
-                        L.m_info[id] = pack_member(bpm, r, bdp + 1);
-                        L.m_jlo[id] = 0;
-                    }
-                }
-                __syncthreads();
-                if (tid == 0) s_nbig = 0;
-                H += total;
-            }
-            __syncthreads();
-            hs = head_base;
-            he = head_base + H;
-            Mg = he;
-            if (H == 0) return Mg;
-        }
-    };
 
     // Levels with at most 64 parents are run by wave 0 alone, as many in a row as there are: no
     // barriers, prefix sums and the compaction of survivors by cross-lane operations, the level's
@@ -822,14 +697,6 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
     };
 
     bool by_workgroup = false;  // the single wave has handed this level over
-    if (walks && bstar < kLvBuckets) {
-        const int Mgen = by_generations();
-        if (Mgen >= 0) {
-            M = Mgen;
-            d = B + 1;  // no level is left
-        }
-        __syncthreads();
-    }
     while (d <= B) {
         if (le - ls <= kWave && C_resume < 0 && !by_workgroup) {
             if (tid < kWave) wave_levels();
@@ -1142,6 +1009,428 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
     return min(N, total_alive);
 }
 
+// ------------------------------------------------------------------------------------------
+// Construction by deviations: what every tree beyond a star is built with.
+//
+// A prefix is the top-1 chain with some of its ranks replaced by non-zero ones, its deviations.  The members --
+// every prefix whose score reaches a cut that at least N prefixes reach -- are enumerated by the number of their
+// deviations, of which a prefix of the tree has at most log2(N + 1) (one with g of them has 2^g - 1 better ones:
+// itself with any subset of them set to rank 0), two or three from a confident drafter.  A member that ends in a
+// deviation is a head; its continuation is the same prefix followed by ranks 0.
+//   * A first bound.  The chain's first l nodes and their single deviations of ranks 1 .. R are l + R l (l + 1) / 2
+//     prefixes, and the worst of them is the chain's l-th node with the largest loss of a rank R: the best bound
+//     over sixteen l (l = 1: the N-th rank of row 0) is where the histogram's range ends.
+//   * The cut.  A histogram of 256 equal score buckets counts every prefix known so far, once; the bucket in which
+//     the count reaches N holds the cut.  It starts with the chain and the heads off it of ranks 1 .. 64 (off the
+//     root: all), takes their continuations when those are first walked, and every member found later, so that
+//     the cut only rises.  A prefix below it is not in the tree, and neither is anything that continues it
+//     (scores only fall along a path).
+//   * Enumeration, in turns of the whole workgroup.  A queue holds nodes with children of rank >= 1 at or above the
+//     cut: they are expanded, 16 lanes a node, 64 ranks at once, which gives heads.  Heads whose continuation
+//     reaches the cut are listed and walked, a lane a head, 16 nodes of each in registers.  Both put what has
+//     further children into the queue.  Places are handed out by one atomic per wave; their order does not
+//     matter, the members are ranked in the end.
+//   * The members that reach the final cut are ranked exactly: 1024 buckets of about equal population, by the
+//     histogram, then all pairs inside a bucket with the full comparison.  The first N become nodes 1 .. N.
+// What bounds it: a chain of dependent instructions of a workgroup that has the chip to itself.  Measured on a wave alone
+// on its SIMD, cycles: a dependent addition 7, through DPP 23, a ballot that scalar code looks at 45, a branch
+// under a lane mask 55, an LDS read 62, a barrier of eight waves 15.  256 nodes at p = 0.9: table 5.2 thousand, first
+// bound and histogram 4.5, turns 19, ranking 6.5, arrays and masks 4.5.
+// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 11.8; 256 nodes p = 0
+// (flat) 17.1 -> 12.4, 0.4 29.5 -> 13.1, 0.9 20.7 -> 13.3; 512 nodes 0.4 34.2 -> 16.5, 0.9 25.4 -> 14.6; 1024 nodes 0 35.3 -> 19.4, 0.5 59.3 -> 22.2,
+// 0.9 43.7 -> 21.3.
+// Returns N, or -1 (uniform): no bound (fewer ranks than budget), or more members than there is room for (heavy ties).
+// ------------------------------------------------------------------------------------------
+constexpr int kRankBuckets = 1024;
+constexpr int kHistInts = kLvBuckets + 64;  // (and a word for each lane with nothing to count)
+// histogram, its prefix sums, ranking buckets, four 64-bit counters and one for each lane but the first
+constexpr int kBucketInts = 2 * kHistInts + kRankBuckets + 2 * (4 + 64);
+static_assert(kBucketInts >= 4 * (kLvBuckets + 4), "the level construction's histograms lie in the same place");
+
+__device__ __forceinline__ float lane_value(float v, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
+}
+
+template <int NT>
+__device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, LevelMem L, int *s_bucket,
+                               uint32_t *s_node, float *s_score)
+{
+    constexpr int NW = NT / 64;
+    static_assert(kRankBuckets % NT == 0, "ranking buckets are dealt evenly");
+    // (all zero on entry)
+    int *const s_hist = s_bucket, *const s_pref = s_hist + kHistInts, *const s_cnt = s_pref + kHistInts;
+    unsigned long long *const s_alloc = reinterpret_cast<unsigned long long *>(s_cnt + kRankBuckets);
+    __shared__ int s_wave[NW];
+    uint32_t *const queue = reinterpret_cast<uint32_t *>(L.c_score);  // node | children's row << 13 | first rank << 19
+    uint16_t *const list = L.p_c;                                     // heads to walk
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cap = min(K, N);  // ranks that can matter
+    // Nothing is written or counted under a branch (a wave alone on its SIMD pays some 55 cycles for one, a select 7):
+    // each array has 64 places behind its room for the lanes that have nothing, and for what does not fit.
+    const int room = L.capm - 64, queue_room = L.capc - 64, list_room = 2 * L.capp - 64;
+
+    // Every wave for itself: lane d holds the first rank of row d and the score of the chain's node at depth d + 1.
+    const float lp0 = lane < B ? s_lp[lane * Kp] : -INFINITY;
+    float chain = 0.0f + lp0;
+    // (wave_shr:1, lane 0: 0; after k steps lanes 0 .. k are right, and stay so)
+#pragma unroll
+    for (int k = 1; k < 16; ++k) chain = __int_as_float(dpp_or_zero<0x138>(__float_as_int(chain))) + lp0;
+    for (int k = 16; k < B; ++k) chain = __int_as_float(dpp_or_zero<0x138>(__float_as_int(chain))) + lp0;
+    const float hi = lane_value(chain, 0);
+    const float at_depth = __int_as_float(dpp_or_zero<0x138>(__float_as_int(chain)));  // lane i: the node at depth i
+    // The first bound: four lanes for each l.  (The scores are formed here in another order than along a path: at
+    // most 32 roundings of 2^-24 each way, well below the margin.)
+    float lo;
+    {
+        const int l = B > 16 ? max(1, 2 * (lane >> 2)) : (lane >> 2) + 1;
+        const float at_l = __shfl(chain, l - 1, 64);
+        const int R = (int)((float)(N - l) * __builtin_amdgcn_rcpf(0.5f * (float)(l * (l + 1))) * 1.0001f) + 1;
+        const int r = l == 1 ? min(N - 1, K) : min(max(R, 0), K);  // (rank K: -inf)
+        float worst = 0.0f;
+        for (int i0 = lane & 3; i0 < B; i0 += 16) {
+            float x[4], y[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float *const p = s_lp + min(i0 + 4 * k, B - 1) * Kp;
+                x[k] = p[r];
+                y[k] = p[0];
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) worst = fminf(worst, i0 + 4 * k < min(l, B) ? x[k] - y[k] : 0.0f);
+        }
+        worst = fminf(worst, dpp_f<0xB1>(worst, worst));
+        worst = fminf(worst, dpp_f<0x4E>(worst, worst));
+        const float at = at_l + worst;
+        const float exact = s_lp[min(N - 1, K)];
+        lo = l == 1 && r == N - 1 ? exact : at - 1e-5f * fabsf(at);
+        lo = wave_max_f32(l <= B && at_l > kLvNeg && worst > kLvNeg ? lo : -INFINITY);
+    }
+    if (!(lo > kLvNeg)) return -1;
+    const float width = (hi - lo) * (1.0f / ((float)kLvBuckets - 0.5f)), inv = ((float)kLvBuckets - 0.5f) / fmaxf(hi - lo, 1e-30f);
+    auto scaled = [&](float v) { return fmaxf((hi - v) * inv, 0.0f); };
+    auto count = [&](float v, bool on) { atomicAdd(&s_hist[on ? min((int)scaled(v), kLvBuckets - 1) : kLvBuckets + lane], 1); };
+    auto below = [&](unsigned long long mask) {  // lanes of the mask before this one
+        return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
+    };
+    auto put_entry = [&](bool on, int at, int id, int row, int first) {
+        queue[on ? min(at, queue_room) : queue_room + lane] = (uint32_t)id | ((uint32_t)row << 13) | ((uint32_t)first << 19);
+    };
+
+    // The chain is members 0 .. B, its nodes with children at or above the bound are the first queue: rank 1, and
+    // every 64th after it.  (All waves count the entries, the last one writes them.)
+    int Q = 0;
+    for (int first = 1; first < cap; first += 64) {
+        const bool on = lane < B && at_depth + s_lp[min(lane, B - 1) * Kp + first] >= lo;
+        const unsigned long long any = __builtin_amdgcn_ballot_w64(on);
+        if (any == 0ull) break;
+        if (wave == NW - 1) put_entry(on, Q + below(any), lane, lane, first);
+        Q += __builtin_popcountll(any);
+    }
+    if (wave == NW - 1) {
+        count(at_depth, lane > 0 && lane <= B && at_depth >= lo);
+        const int m = lane <= B ? lane : room + lane;
+        L.m_score[m] = at_depth;
+        L.m_info[m] = pack_member(max(lane - 1, 0), 0, lane & 63);
+    }
+    // heads off the chain, 16 lanes a row
+    for (int i0 = 4 * wave; i0 < B; i0 += 4 * NW) {
+        const int i = min(i0 + (lane >> 4), B - 1);
+        const float S = __shfl(at_depth, i, 64);
+        float v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int r = 1 + (lane & 15) + 16 * u;
+            const float x = s_lp[i * Kp + min(r, K)];
+            v[u] = i0 + (lane >> 4) < B && r < cap ? S + x : -INFINITY;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (__builtin_amdgcn_ballot_w64(v[u] >= lo) == 0ull) break;
+            count(v[u], v[u] >= lo);
+        }
+    }
+    for (int r0 = 65; r0 < cap; r0 += NT) {
+        const int r = r0 + tid;
+        const float v = s_lp[min(r, K)];
+        count(v, r < cap && v >= lo);
+    }
+
+    // The cut that the histogram gives: a value that everything in the buckets up to the one where the count reaches
+    // N is at or above (a value of a later bucket is), or the first bound.  A wave may read counts that others are
+    // adding to: any part of what is known gives a cut.
+    int4 known;
+    int known_before;
+    auto cut = [&]() -> float {
+        known = *reinterpret_cast<const int4 *>(&s_hist[4 * lane]);
+        const int sum = known.x + known.y + known.z + known.w, incl = wave_scan_inclusive_i32(sum);
+        const int c0 = incl - sum + known.x, c1 = c0 + known.y, c2 = c1 + known.z;
+        known_before = incl - sum;
+        const unsigned long long reached = __builtin_amdgcn_ballot_w64(incl >= N);
+        if (reached == 0ull) return lo;
+        const int mine = 4 * lane + (c0 >= N ? 0 : c1 >= N ? 1 : c2 >= N ? 2 : 3);
+        const int b = __builtin_amdgcn_readlane(mine, __builtin_ctzll(reached));
+        const float at = hi - ((float)b + 1.02f) * width;
+        return at > lo && (int)fminf((hi - at) * inv, (float)kLvBuckets) > b ? at : lo;
+    };
+    // Places for members, queue entries and listed heads: phase p counts in cell p % 4 (three fields of 21 bits);
+    // what a phase handed out is read at the start of the next, and the cell is cleared in the one after it.
+    int phase = 0, M = B + 1, W = 0;
+    auto take = [&](int members, int entries, int heads) -> unsigned long long {  // (uniform over a wave)
+        const unsigned long long want = (unsigned long long)(unsigned)members | ((unsigned long long)(unsigned)entries << 21) |
+                                        ((unsigned long long)(unsigned)heads << 42);
+        const unsigned long long old = atomicAdd(&s_alloc[lane == 0 ? phase & 3 : 3 + lane], lane == 0 ? want : 0ull);
+        const uint32_t a = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)old);
+        const uint32_t b = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(old >> 32));
+        return (unsigned long long)a | ((unsigned long long)b << 32);
+    };
+    auto field = [](unsigned long long x, int f) { return (int)((x >> (21 * f)) & 0x1FFFFFull); };
+    auto next_phase = [&]() -> bool {  // false: out of room
+        if (tid == 0) s_alloc[(phase + 2) & 3] = 0ull;
+        __syncthreads();
+        const unsigned long long cell = s_alloc[phase & 3];
+        const unsigned long long got = (unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)cell) |
+                                       ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(cell >> 32)) << 32);
+        M += field(got, 0);
+        Q += field(got, 1);
+        W += field(got, 2);
+        ++phase;
+        return M <= room && Q <= queue_room && W <= list_room;
+    };
+
+    float s = lo;
+    if (!next_phase()) return -1;
+    for (int q_done = 0; q_done < Q;) {  // (uniform, like everything that M, Q and W decide)
+        // ---- the nodes of the queue: their children of ranks first .. first + 63 ----
+        const bool first_turn = q_done == 0;
+        const int q_end = Q;
+        s = cut();
+        for (int q0 = q_done + 4 * wave; q0 < q_end; q0 += 4 * NW) {
+            const int at = q0 + (lane >> 4);
+            const uint32_t entry = queue[min(at, q_end - 1)];
+            const int id = (int)(entry & 0x1FFFu), row = (int)((entry >> 13) & 63u), first = (int)(entry >> 19);
+            const float S = L.m_score[id];
+            const float *const rowp = s_lp + row * Kp;
+            const float *const next = s_lp + (row + 1) * Kp;  // (row B: -inf)
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = rowp[min(first + (lane & 15) + 16 * u, K)];
+            const float next0 = next[0], next1 = next[1];
+            const int ranks = at < q_end ? cap - first - (lane & 15) : 0;  // (left from this lane's first rank on)
+            unsigned long long on[4];
+            int n_on = 0, n_kid = 0, n_walk = 0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                v[u] = 16 * u < ranks ? S + v[u] : -INFINITY;
+                on[u] = __builtin_amdgcn_ballot_w64(v[u] >= s);
+                n_on += __builtin_popcountll(on[u]);
+                n_walk += __builtin_popcountll(__builtin_amdgcn_ballot_w64(v[u] + next0 >= s));
+                n_kid += __builtin_popcountll(__builtin_amdgcn_ballot_w64(v[u] + next1 >= s));
+            }
+            if (n_on == 0) continue;
+            // (all 64: the rest of the row is another entry; a node of the chain has those already)
+            const bool more = (lane & 15) == 15 && v[3] >= s && first + 64 < cap && id > B;
+            const unsigned long long rest = __builtin_amdgcn_ballot_w64(more);
+            const unsigned long long got = take(n_on, n_kid + __builtin_popcountll(rest), n_walk);
+            int m_at = M + field(got, 0), q_at = Q + field(got, 1), w_at = W + field(got, 2);
+            if (rest != 0ull) {
+                put_entry(more, q_at + below(rest), id, row, first + 64);
+                q_at += __builtin_popcountll(rest);
+            }
+            const uint32_t info = pack_member(id, first + (lane & 15), row + 1);
+            // (counted before the first turn: heads off the chain of ranks up to 64, and all of the root's)
+            const bool fresh = !first_turn || (first > 64 && id > 0);
+            const bool any_fresh = __builtin_amdgcn_ballot_w64(fresh) != 0ull;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (on[u] == 0ull) break;
+                const int m = m_at + below(on[u]), place = v[u] >= s ? min(m, room) : room + lane;
+                L.m_score[place] = v[u];
+                L.m_info[place] = info + ((uint32_t)(16 * u) << 13);
+                if (any_fresh) count(v[u], fresh && v[u] >= s);
+                const unsigned long long walk = __builtin_amdgcn_ballot_w64(v[u] + next0 >= s);
+                if (walk != 0ull) {
+                    list[v[u] + next0 >= s ? min(w_at + below(walk), list_room) : list_room + lane] = (uint16_t)m;
+                    w_at += __builtin_popcountll(walk);
+                    const unsigned long long kid = __builtin_amdgcn_ballot_w64(v[u] + next1 >= s);  // (these have a continuation too)
+                    if (kid != 0ull) {
+                        put_entry(v[u] + next1 >= s, q_at + below(kid), m, row + 1, 1);
+                        q_at += __builtin_popcountll(kid);
+                    }
+                }
+                m_at += __builtin_popcountll(on[u]);
+            }
+        }
+        q_done = q_end;
+        const int w_first = W;
+        if (!next_phase()) return -1;
+        const int w_end = W;
+        if (w_first == w_end) continue;
+        // ---- the listed heads, a lane each: their continuations, up to 16 nodes at a time in registers; in the first
+        //      turn they are counted before any is kept ----
+        for (int keep = first_turn ? 0 : 1; keep < 2; ++keep) {
+            s = cut();
+            for (int w0 = w_first + 64 * wave; w0 < w_end; w0 += NT) {
+                int id = list[min(w0 + lane, w_end - 1)];
+                float S = L.m_score[id];
+                int depth = member_depth(L.m_info[id]);  // (of the node in front)
+                S = w0 + lane < w_end ? S : -INFINITY;
+                for (;;) {
+                    // rows depth .. depth + 16: the step to the next node, and that node's first child of rank >= 1
+                    // is in the row after
+                    float v[16], kid[17];
+#pragma unroll
+                    for (int k = 0; k < 17; ++k) {
+                        const float *const p = s_lp + __mul24(min(depth + k, B), Kp);  // (row B: -inf)
+                        if (k < 16) v[k] = p[0];
+                        kid[k] = p[1];
+                    }
+                    v[0] += S;
+#pragma unroll
+                    for (int k = 1; k < 16; ++k) v[k] += v[k - 1];
+                    if (keep == 0) {
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) {
+                            if (k % 4 == 0 && __builtin_amdgcn_ballot_w64(v[k] >= s) == 0ull) break;
+                            count(v[k], v[k] >= s);
+                        }
+                    } else {
+                        int len = 0;
+                        uint32_t kids = 0u;  // bit k: the k-th node has a child of rank >= 1
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) {
+                            len += v[k] >= s ? 1 : 0;
+                            kids |= v[k] + kid[k + 1] >= s ? 1u << k : 0u;
+                        }
+                        const int both = len | (__builtin_popcount(kids) << 16), incl = wave_scan_inclusive_i32(both);
+                        const int total = __builtin_amdgcn_readlane(incl, 63);
+                        if (total == 0) break;
+                        const unsigned long long got = take(total & 0xFFFF, total >> 16, 0);
+                        const int m_at = M + field(got, 0) + ((incl - both) & 0xFFFF);
+                        int q_at = Q + field(got, 1) + ((incl - both) >> 16);
+                        uint32_t info = pack_member(id, 0, depth + 1);
+#pragma unroll
+                        for (int k = 0; k < 16; ++k) {
+                            if (k % 4 == 0 && __builtin_amdgcn_ballot_w64(k < len) == 0ull) break;
+                            const int place = k < len ? min(m_at + k, room) : room + lane;
+                            L.m_score[place] = v[k];
+                            L.m_info[place] = info;
+                            info = pack_member(m_at + k, 0, depth + k + 2);
+                            if (!first_turn) count(v[k], k < len);
+                        }
+                        while (__builtin_amdgcn_ballot_w64(kids != 0u) != 0ull) {
+                            const int k = __builtin_ctz(kids | 0x10000u);
+                            put_entry(kids != 0u, q_at, m_at + k, depth + k + 1, 1);
+                            q_at += 1;
+                            kids &= kids - 1u;
+                        }
+                        id = m_at + 15;
+                    }
+                    // more than 16 nodes: from the last one on
+                    S = v[15] >= s ? v[15] : -INFINITY;
+                    depth += 16;
+                    if (__builtin_amdgcn_ballot_w64(S >= s && depth < B) == 0ull) break;
+                }
+            }
+            if (!next_phase()) return -1;
+        }
+    }
+
+    // ---- exact order of the members that reach the cut ----
+    s = cut();
+    if (wave == 0) {
+        const int k1 = known_before + known.x, k2 = k1 + known.y, k3 = k2 + known.z;
+        auto packed = [](int before, int n) { return min(before, 0x7FFF) << 16 | min(n, 0xFFFF); };
+        *reinterpret_cast<int4 *>(&s_pref[4 * lane]) =
+            make_int4(packed(known_before, known.x), packed(k1, known.y), packed(k2, known.z), packed(k3, known.w));
+    }
+    __syncthreads();
+    // a ranking bucket per known prefix: its place among them, estimated within its score bucket (monotone)
+    auto place_of = [&](float v) {
+        const float x = fminf(scaled(v), (float)kLvBuckets - 0.25f);
+        const int b = (int)x, p = s_pref[b];
+        return fminf((float)(p >> 16) + (x - (float)b) * (float)(p & 0xFFFF), 32767.0f);
+    };
+    const float shrink = fminf(1.0f, (float)kRankBuckets / fmaxf(place_of(s), 1.0f));
+    auto fine = [&](float v) { return min((int)(place_of(v) * shrink), kRankBuckets - 1); };
+    unsigned long long *const sorted = reinterpret_cast<unsigned long long *>(  // score << 32 | bucket << 13 | member
+        L.c_score + ((B * Kp) & 1));  // (on 8 bytes: what lies in front of it is even but for the table)
+    const int sorted_room = L.capc - 1;
+    uint16_t *const node_id = L.p_c;
+    for (int m = 1 + tid; m < M; m += NT) {
+        const float v = L.m_score[m];
+        if (v >= s) L.m_jlo[m] = (uint16_t)atomicAdd(&s_cnt[fine(v)], 1);
+    }
+    __syncthreads();
+    int alive = 0;
+    {
+        constexpr int PER = kRankBuckets / NT;
+        int c[PER], mine = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) mine += c[j] = s_cnt[PER * tid + j];
+        const int incl = wave_scan_inclusive_i32(mine);
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        int at = incl - mine;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            at += w < wave ? s_wave[w] : 0;
+            alive += s_wave[w];
+        }
+        alive = __builtin_amdgcn_readfirstlane(alive);
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            s_cnt[PER * tid + j] = (at << 16) | c[j];  // (both below 2^13)
+            at += c[j];
+        }
+    }
+    if (alive > sorted_room) return -1;
+    __syncthreads();
+    for (int m = 1 + tid; m < M; m += NT) {
+        const float v = L.m_score[m];
+        if (v >= s) {
+            const int f = fine(v);
+            sorted[(s_cnt[f] >> 16) + L.m_jlo[m]] =
+                ((unsigned long long)__float_as_uint(v) << 32) | (unsigned long long)(unsigned)(f << 13 | m);
+        }
+    }
+    __syncthreads();
+    for (int e = tid; e < alive; e += NT) {
+        const unsigned long long mine = sorted[e];
+        const float v = __uint_as_float((uint32_t)(mine >> 32));
+        const int m = (int)(mine & 0x1FFFull), bk = s_cnt[((uint32_t)mine >> 13) & (kRankBuckets - 1)], at = bk >> 16, n = bk & 0xFFFF;
+        int place = at;
+        if (n > 1 && at < N) {
+            // (only equal scores, which the rank tuples decide, take the full comparison)
+            for (int j0 = 0; j0 < n; j0 += 4) {
+                unsigned long long o[4];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o[k] = sorted[at + min(j0 + k, n - 1)];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const float so = __uint_as_float((uint32_t)(o[k] >> 32));
+                    const bool other = j0 + k < n && o[k] != mine;
+                    place += other && so > v ? 1 : 0;
+                    if (other && so == v) place += member_before(L.m_score, L.m_info, (int)(o[k] & 0x1FFFull), m) ? 1 : 0;
+                }
+            }
+        }
+        node_id[m] = (uint16_t)(place < N ? place + 1 : 0);
+    }
+    __syncthreads();
+    for (int e = tid; e < alive; e += NT) {
+        const unsigned long long mine = sorted[e];
+        const int m = (int)(mine & 0x1FFFull), id = node_id[m];
+        const uint32_t info = L.m_info[m];
+        const int pm = member_parent(info), up = node_id[pm];
+        if (id == 0) continue;
+        s_node[id] = pack_node(pm == 0 ? 0 : up, member_rank(info), member_depth(info));
+        s_score[id] = __uint_as_float((uint32_t)(mine >> 32));
+    }
+    __syncthreads();
+    return N;
+}
+
 // The pops of a budget of at most 63 nodes, by one wave: entry e of the frontier in lane e, and with it the
 // record and score of node e, which leave for LDS at the end.  A pop is a chain of dependent instructions of a
 // wave that is alone on its SIMD, so what counts is how many there are; the log-probability that a popped
@@ -1222,21 +1511,23 @@ __device__ __forceinline__ int pops_of_one_slot(const float *s_lp, int Kp, int B
     return n;
 }
 
-template <int NSLOT, int NT>
-__global__ __launch_bounds__(NT) void build_kernel(
+constexpr int kBuildThreads = 512;
+template <int NSLOT>
+__global__ __launch_bounds__(kBuildThreads) void build_kernel(
     const int32_t *__restrict__ topk_tok, const float *__restrict__ topk_lp, int B, int K, int N,
     const int32_t *__restrict__ root_token, int32_t *__restrict__ tokens,
     int32_t *__restrict__ parent, int32_t *__restrict__ depth, int32_t *__restrict__ rank,
     float *__restrict__ node_score, uint64_t *__restrict__ ancestor_mask,
-    int32_t *__restrict__ n_nodes, int algo, int capm, int capp, int capc)
+    int32_t *__restrict__ n_nodes, int algo, int capm, int capp, int capc, int mask_off, int mask_rows)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    const int Kp = K + 3;
+    constexpr int NT = kBuildThreads;
+    const int Kp = table_stride(K);
     const int T = N + 1;
     float *s_lp = reinterpret_cast<float *>(smem);                     // [B][Kp], -inf padded
-    uint32_t *s_node = reinterpret_cast<uint32_t *>(s_lp + B * Kp);     // [T]
+    uint32_t *s_node = reinterpret_cast<uint32_t *>(s_lp + B * Kp + 4);  // [T]  (row B of the table: four times -inf)
     float *s_score = reinterpret_cast<float *>(s_node + T);             // [T]
-    // the level-synchronous construction's arrays follow
+    // the arrays of the constructions that find the tree as a set follow
     LevelMem lv;
     lv.capm = capm;
     lv.capp = capp;
@@ -1249,23 +1540,28 @@ __global__ __launch_bounds__(NT) void build_kernel(
     lv.p_c = lv.m_jlo + capm;
     lv.p_off = lv.p_c + capp;
     __shared__ int s_built;
+    __shared__ __align__(16) int s_bucket[kBucketInts];
 
     const int tid = threadIdx.x;
     const int seq = blockIdx.x;
+    const bool may_use_set = capm > 0 && algo != DDTREE_BUILD_POPS && (algo != DDTREE_BUILD_AUTO || N >= 28);
     const float *lp = topk_lp + (size_t)seq * B * K;
     const int32_t *tk = topk_tok + (size_t)seq * B * K;
 
     // log-probabilities into LDS, rows padded with -inf.  The [B][K] table is contiguous: thread
     // t takes the 16-byte pieces t, t + NT, ..., sixteen loads in flight at a time (one round trip
-    // to memory up to B K = 16384), and keeps (row, column) of its first element by stepping both.
+    // to memory up to B K = 64 NT), and keeps (row, column) of its first element by stepping both.  Rows of
+    // whole pieces start on 16 bytes in LDS too.
     {
         const int n_el = B * K;
         // whole pieces of four, if this sequence's table starts on a 16-byte boundary (else, and
         // for the last one to three elements, the plain loop below)
         const int n_q = (reinterpret_cast<uintptr_t>(lp) & 15) == 0 ? n_el >> 2 : 0;
-        const int dq = (4 * NT) / K, dr = (4 * NT) % K;  // one step of 4 NT elements
-        int d = (4 * tid) / K, k = (4 * tid) % K;
         const float4 *lp4 = reinterpret_cast<const float4 *>(lp);
+        int d = 0, k = 0, dq = 0, dr = 0;
+        // (the tokens are wanted at the very end, a few of each line: one touch brings the line nearer)
+        int touched = 0;
+        if (32 * tid < n_el) touched = tk[32 * tid];
         for (int q0 = tid; q0 < n_q; q0 += 16 * NT) {
             float4 v[16];
 #pragma unroll
@@ -1273,17 +1569,27 @@ __global__ __launch_bounds__(NT) void build_kernel(
                 const int q = q0 + u * NT;
                 v[u] = q < n_q ? lp4[q] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
             }
+            if (q0 == tid) {
+                if (may_use_set)
+                    for (int i = tid; i < kBucketInts; i += NT) s_bucket[i] = 0;
+                d = (4 * tid) / K, k = (4 * tid) % K;
+                dq = (4 * NT) / K, dr = (4 * NT) % K;  // one step of 4 NT elements
+            }
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
                 if (q0 + u * NT < n_q) {
-                    const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-                    int dd = d, kk = k;
+                    if ((K & 3) == 0) {
+                        *reinterpret_cast<float4 *>(&s_lp[d * Kp + k]) = v[u];
+                    } else {
+                        const float x[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                        int dd = d, kk = k;
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) {
-                        s_lp[dd * Kp + kk] = x[c];
-                        if (++kk == K) {
-                            kk = 0;
-                            ++dd;
+                        for (int c = 0; c < 4; ++c) {
+                            s_lp[dd * Kp + kk] = x[c];
+                            if (++kk == K) {
+                                kk = 0;
+                                ++dd;
+                            }
                         }
                     }
                 }
@@ -1295,8 +1601,13 @@ __global__ __launch_bounds__(NT) void build_kernel(
                 }
             }
         }
+        if (may_use_set && tid >= n_q)
+            for (int i = tid; i < kBucketInts; i += NT) s_bucket[i] = 0;
         for (int e = 4 * n_q + tid; e < n_el; e += NT) s_lp[(e / K) * Kp + e % K] = lp[e];
-        for (int i = tid; i < 3 * B; i += NT) s_lp[(i / 3) * Kp + K + i % 3] = -INFINITY;
+        for (int i = tid; i < 4 * B; i += NT)
+            if (K + (i & 3) < Kp) s_lp[(i >> 2) * Kp + K + (i & 3)] = -INFINITY;
+        if (tid < 4) s_lp[B * Kp + tid] = -INFINITY;
+        asm volatile("" ::"v"(touched));
     }
     if (tid == 0) {
         s_node[0] = pack_node(0, 0, 0);
@@ -1304,28 +1615,42 @@ __global__ __launch_bounds__(NT) void build_kernel(
     }
     __syncthreads();
 
-    // Which construction: the sequential pops win on small budgets and on stars (nearly all nodes
-    // at depth 1: their sibling runs pop in batches); the level-synchronous construction wins on
-    // large budgets and wherever pops alternate between parents, each a step of its own.  A star
-    // is recognised by the top-1 chain falling below the worst useful rank of row 0 within two
-    // steps and by the best depth-1 node having fewer than four children above that rank.
-    // Both constructions give the same tree; algo 1 / 2 force one of them.
-    // (Measured, rows peaked at 0.7, pops / levels: 32 nodes 13.4 / 14.5 us, 40 nodes 15.8 / 14.7, 64 nodes 32.6 / 15.3;
-    // flat rows 4.0 / 8.8 up to 63 nodes.)
-    bool use_levels = capm > 0 && algo != DDTREE_BUILD_POPS;
+    // Which construction.  A pop that alternates between parents is a step of its own (0.3 us, and it ends a run), a run
+    // of siblings pops as one: flat rows, whose tree is a star or nearly.  The construction by deviations takes about
+    // the same time whatever the rows are.  Below 28 nodes pops always win; up to 256 they do where hardly any node of
+    // depth 2 (of ranks 0 .. 3 counted, an upper bound) reaches the worst useful rank of row 0.
+    // All constructions give the same tree; algo 1 / 2 force pops / the others.
+    // (Launch to launch, pops / deviations, us.  Rows peaked at 0.7: 16 nodes 8.9 / 10.3, 20 10.3 / 10.8, 24 11.5 / 10.9, 32
+    // 14.0 / 11.2, 64 33.7 / 11.5.  Stars: 32 nodes 5.0 / 8.2, 64 5.3 / 8.4, 128 6.0 / 8.7, 256 8.0 / 9.2; with two nodes of depth 2: 40
+    // 6.9 / 8.4, 128 9.2 / 8.7; with four: 32 7.6 / 10.5, 64 11.2 / 8.5, 256 14.9 / 11.5.)
+    bool use_levels = may_use_set;
     if (use_levels && algo == DDTREE_BUILD_AUTO && N <= 256) {
-        use_levels = false;
-        if (N >= 36) {
-            const float worst = s_lp[min(K, N) - 1];
-            // (scores only fall along the chain: its third node speaks for the first two)
-            const bool deep = B >= 3 && (s_lp[0] + s_lp[Kp]) + s_lp[2 * Kp] >= worst;
-            const bool bushy = B >= 2 && s_lp[0] + s_lp[Kp + min(3, K - 1)] >= worst;
-            use_levels = deep || bushy;
+        int below_star = 0, limit = 4;
+        if (B >= 2) {
+            const int lane = tid & 63, last = min(K, N) - 1;
+            const float S = s_lp[min(lane, last)], worst = s_lp[last];
+            float first[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) first[j] = s_lp[Kp + min(j, K)];
+            // (none of rank 0: none at all)
+            below_star = __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane <= last && S + first[0] >= worst));
+            // (one of rank 0: no head has a continuation to walk, which makes the construction by deviations 2.5 us cheaper)
+            if (N >= 48) limit = below_star > 1 && N < 100 ? 3 : 2;
+            if (below_star > 0) {
+#pragma unroll
+                for (int j = 1; j < 4; ++j)
+                    below_star += __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane <= last && S + first[j] >= worst));
+            }
         }
+        use_levels = below_star > limit || K < N;
     }
     int level_n = -1;
     if (use_levels) {
-        level_n = level_build<NT>(s_lp, Kp, B, K, N, lv, s_node, s_score);
+        level_n = deviation_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
+        if (level_n < 0) {
+            __syncthreads();  // (the histograms are reused)
+            level_n = level_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
+        }
         if (level_n < 0 && tid == 0) atomicAdd(&g_level_giveups, 1u);
     }
     if (level_n >= 0) {
@@ -1491,86 +1816,65 @@ __global__ __launch_bounds__(NT) void build_kernel(
     const int W = (T + 63) / 64;
     if (tid == 0) n_nodes[seq] = built;
 
-    // Node ids are dealt so that T = 257 (a budget of 256 and the root) takes one pass: the last
-    // thread also takes the root, whose row is trivial, before its own node.
-    for (int i0 = 1; i0 < T; i0 += NT) {
-        const int i = i0 + tid;
-        if (i0 == 1 && tid == NT - 1) {
-            const size_t o0 = (size_t)seq * T;
-            tokens[o0] = root_token[seq];
-            parent[o0] = -1;
-            depth[o0] = 0;
-            if (rank) rank[o0] = -1;
-            if (node_score) node_score[o0] = 0.0f;
-            uint64_t *m0 = ancestor_mask + o0 * W;
-            m0[0] = 1ull;
-            for (int w = 1; w < W; ++w) m0[w] = 0ull;
-        }
-        if (i >= T) continue;
-        const size_t o = (size_t)seq * T + i;
-        uint64_t *mrow = ancestor_mask + o * W;
-        if (i > built) {
-            tokens[o] = -1;
-            parent[o] = -1;
-            depth[o] = -1;
-            if (rank) rank[o] = -1;
-            if (node_score) node_score[o] = 0.0f;
-            for (int w = 0; w < W; ++w) mrow[w] = 0ull;
-            continue;
-        }
-        const uint32_t nd = s_node[i];
-        // (depth and rank are clamped to the table: whatever the records hold, every read below
-        // stays inside topk_tok and the workgroup's LDS)
-        const int d = min(max(node_depth(nd), 1), B);
-        tokens[o] = tk[(d - 1) * K + min(node_rank(nd), K - 1)];
-        parent[o] = node_parent(nd);
-        depth[o] = d;
-        if (rank) rank[o] = node_rank(nd);
-        if (node_score) node_score[o] = s_score[i];
-        if constexpr (NSLOT <= 5) {
-            // ancestors of i (itself first, the root last), folded into the W <= NSLOT mask words as
-            // the chain is walked: the words stay in registers (compile-time indices), so the only
-            // dependent LDS reads are the d parent look-ups
-            uint64_t word[NSLOT];
+    // The root, then the nodes, a thread each.  A node's ancestor mask is put together in LDS while its parent chain
+    // is walked, and leaves in one piece with its neighbours': a thread that stores its own row of W words
+    // touches a cache line per word and lane (this part of the kernel at 1024 nodes: 19.7 thousand cycles before, 13.5 now).
+    uint64_t *const masks = ancestor_mask + (size_t)seq * T * W;
+    if (tid < W) masks[tid] = tid == 0 ? 1ull : 0ull;
+    if (tid == NT - 1) {
+        const size_t o0 = (size_t)seq * T;
+        tokens[o0] = root_token[seq];
+        parent[o0] = -1;
+        depth[o0] = 0;
+        if (rank) rank[o0] = -1;
+        if (node_score) node_score[o0] = 0.0f;
+    }
+    unsigned long long *const s_mask = reinterpret_cast<unsigned long long *>(smem + mask_off);
+    for (int i0 = 1; i0 < T; i0 += mask_rows) {
+        const int n = min(mask_rows, T - i0), i = i0 + tid;
+        int32_t token = -1, up = -1, dp = -1, rk = -1;
+        float score = 0.0f;
+        if (tid < n) {
+            unsigned long long *const row = s_mask + tid * W;
+            for (int w = 0; w < W; ++w) row[w] = 0ull;
+            if (i <= built) {
+                const uint32_t nd = s_node[i];
+                // (depth, rank and ids are clamped: whatever the records hold, every access stays inside
+                // topk_tok and the workgroup's LDS)
+                dp = min(max(node_depth(nd), 1), B);
+                rk = node_rank(nd);
+                up = node_parent(nd);
+                token = tk[(dp - 1) * K + min(rk, K - 1)];
+                score = s_score[i];
+                int j = i;
+                // (four steps between the tests: the root is its own parent)
+                do {
 #pragma unroll
-            for (int w = 0; w < NSLOT; ++w) word[w] = 0ull;
-            int j = i;
-            for (int t = 0; t <= d; ++t) {
-                const uint64_t bit = 1ull << (j & 63);
-                const int wj = j >> 6;
-#pragma unroll
-                for (int w = 0; w < NSLOT; ++w) word[w] |= wj == w ? bit : 0ull;
-                j = node_parent(s_node[j]);
+                    for (int k = 0; k < 4; ++k) {
+                        atomicOr(&row[j >> 6], 1ull << (j & 63));
+                        j = min(node_parent(s_node[j]), max(j - 1, 0));
+                    }
+                } while (j > 0);
+                atomicOr(&row[0], 1ull);
             }
-#pragma unroll
-            for (int w = 0; w < NSLOT; ++w)
-                if (w < W) mrow[w] = word[w];
-        } else {
-            // many words, few ancestors: the row is cleared, then the chain is walked with one word
-            // in hand (a parent's id is below its child's, so the word index never rises) and
-            // every word that received bits is stored over its zero (stores of one thread to
-            // one address keep their order)
-            for (int w = 0; w < W; ++w) mrow[w] = 0ull;
-            int j = i, cur_w = i >> 6;
-            uint64_t cur = 0ull;
-            for (int t = 0; t <= d; ++t) {
-                const int wj = min(j >> 6, W - 1);  // (clamped like every index taken from a record)
-                if (wj != cur_w) {
-                    mrow[cur_w] = cur;
-                    cur = 0ull;
-                    cur_w = wj;
-                }
-                cur |= 1ull << (j & 63);
-                j = node_parent(s_node[j]);
-            }
-            mrow[cur_w] = cur;
         }
+        __syncthreads();
+        for (int e = tid; e < n * W; e += NT) masks[(size_t)i0 * W + e] = s_mask[e];
+        if (tid < n) {
+            const size_t o = (size_t)seq * T + i;
+            parent[o] = up;
+            depth[o] = dp;
+            if (rank) rank[o] = rk;
+            if (node_score) node_score[o] = score;
+            tokens[o] = token;
+        }
+        if (i0 + mask_rows < T) __syncthreads();
     }
 }
 
 static size_t build_lds_bytes(int B, int K, int N)
 {
-    return (size_t)B * (K + 3) * 4 + (size_t)(N + 1) * 8;
+    return ((size_t)B * table_stride(K) + 4) * 4 + (size_t)(N + 1) * 8;
 }
 
 // Dynamic LDS of the kernel and the capacities of the level-synchronous construction (members,
@@ -1579,12 +1883,12 @@ static size_t build_lds_bytes(int B, int K, int N)
 struct BuildLds {
     size_t bytes;
     int capm, capp, capc;
+    int mask_off, mask_rows;  // where the masks are put together, and how many rows at a time
 };
-static BuildLds build_lds_plan(int B, int K, int N, bool level)
+static BuildLds set_lds_plan(int B, int K, int N)
 {
-    const size_t base = (size_t)B * (K + 3) * 4 + (size_t)(N + 1) * 8;
-    BuildLds r{base, 0, 0, 0};
-    if (!level) return r;
+    const size_t base = build_lds_bytes(B, K, N);
+    BuildLds r{base, 0, 0, 0, 0, 0};
     const size_t limit = 150 * 1024;
     if (base >= limit) return r;
     const size_t avail = limit - base;
@@ -1608,23 +1912,43 @@ static BuildLds build_lds_plan(int B, int K, int N, bool level)
     r.bytes = base + lv;
     return r;
 }
+// Masks take the place of the set constructions' arrays, or else of the table, or a place of their own behind a table
+// that is too small for them.
+static BuildLds build_lds_plan(int B, int K, int N, bool set, int threads)
+{
+    const size_t base = build_lds_bytes(B, K, N), row = (size_t)((N + 1 + 63) / 64) * 8, table = (size_t)B * table_stride(K) * 4;
+    BuildLds r{base, 0, 0, 0, 0, 0};
+    if (set) r = set_lds_plan(B, K, N);
+    const size_t rows = std::min(threads, N), behind = align_up(base, 8);
+    if (r.capm > 0) {
+        r.mask_off = (int)behind;
+        r.mask_rows = (int)std::min(rows, (r.bytes - behind) / row);
+    } else if (table >= rows * row || base > 64 * 1024) {
+        r.mask_rows = (int)std::min(rows, table / row);
+    } else {
+        r.mask_off = (int)behind;
+        r.mask_rows = (int)rows;
+        r.bytes = behind + rows * row;
+    }
+    return r;
+}
 
 static std::atomic<int> g_build_algo{DDTREE_BUILD_AUTO};
 
-template <int NSLOT, int NT>
+template <int NSLOT>
 static int launch_build(const int32_t *topk_tok, const float *topk_lp, int batch, int B, int K, int N,
                         const int32_t *root_token, int32_t *tokens, int32_t *parent, int32_t *depth,
                         int32_t *rank, float *node_score, uint64_t *ancestor_mask, int32_t *n_nodes,
                         hipStream_t st)
 {
     const int algo = g_build_algo.load();
-    const BuildLds lds = build_lds_plan(B, K, N, algo != DDTREE_BUILD_POPS);
+    const BuildLds lds = build_lds_plan(B, K, N, algo != DDTREE_BUILD_POPS, kBuildThreads);
     static std::atomic<bool> lds_allowed{false};
-    if (!allow_dynamic_lds(reinterpret_cast<const void *>(build_kernel<NSLOT, NT>), 150 * 1024, lds_allowed))
+    if (!allow_dynamic_lds(reinterpret_cast<const void *>(build_kernel<NSLOT>), 150 * 1024, lds_allowed))
         return DDTREE_ERR_HIP;
-    DDT_LAUNCH(DDTREE_KERNEL_BUILD, st, (build_kernel<NSLOT, NT>), dim3(batch), dim3(NT), lds.bytes,
+    DDT_LAUNCH(DDTREE_KERNEL_BUILD, st, (build_kernel<NSLOT>), dim3(batch), dim3(kBuildThreads), lds.bytes,
                        st, topk_tok, topk_lp, B, K, N, root_token, tokens, parent, depth, rank,
-                       node_score, ancestor_mask, n_nodes, algo, lds.capm, lds.capp, lds.capc);
+                       node_score, ancestor_mask, n_nodes, algo, lds.capm, lds.capp, lds.capc, lds.mask_off, lds.mask_rows);
     return launch_status();
 }
 
@@ -1664,17 +1988,16 @@ extern "C" int ddtree_build(const int32_t *topk_tok, const float *topk_lp, int b
     if (build_lds_bytes(B, K, N) > 150 * 1024) return DDTREE_ERR_ARG;
     hipStream_t st = as_stream(stream);
     const int slots = (N + 1 + 63) / 64;
-    // Beyond 320 nodes the exact order, the masks and the generations have work for eight waves; below, barriers
-    // among more waves cost what they bring.  (256 / 512 / 1024 threads, us, rows peaked at 0.7: 256 nodes 19.7 / 18.9 /
-    // 21.4, at 0.3 26.4 / 27.6 / 31.0; 512 nodes 27.8 / 24.4 / 25.4; 1024 nodes 54.9 / 43.2 / 40.2, at 0.5 66.8 / 59.3 / 61.4.)
-#define DDT_BUILD(S, NT)                                                                          \
-    return launch_build<S, NT>(topk_tok, topk_lp, batch, B, K, N, root_token, tokens, parent, depth, \
+    // Eight waves: with four the ranking and the masks of a large tree take longer, with sixteen the barriers do (256 /
+    // 512 / 1024 threads, us, rows peaked at 0.9: 64 nodes 12.2 / 12.1 / 13.6, 256 14.7 / 13.4 / 15.4, 1024 29.7 / 21.7 / 21.3).
+#define DDT_BUILD(S)                                                                                  \
+    return launch_build<S>(topk_tok, topk_lp, batch, B, K, N, root_token, tokens, parent, depth, \
                            rank, node_score, ancestor_mask, n_nodes, st)
-    if (slots <= 1) DDT_BUILD(1, 256);
-    if (slots <= 2) DDT_BUILD(2, 256);
-    if (slots <= 3) DDT_BUILD(3, 256);
-    if (slots <= 5) DDT_BUILD(5, 256);
-    if (slots <= 9) DDT_BUILD(9, 512);
-    DDT_BUILD(17, 512);
+    if (slots <= 1) DDT_BUILD(1);
+    if (slots <= 2) DDT_BUILD(2);
+    if (slots <= 3) DDT_BUILD(3);
+    if (slots <= 5) DDT_BUILD(5);
+    if (slots <= 9) DDT_BUILD(9);
+    DDT_BUILD(17);
 #undef DDT_BUILD
 }

@@ -50,3 +50,45 @@ def test_constructions_meet(kind, N, B, K):
             assert np.array_equal(g["ancestor_mask"][0], mask), algo
     finally:
         dd.set_build_algorithm(dd.BUILD_AUTO)
+
+
+def _check(tok, lp, N):
+    o = oracle.build_tree(tok, lp, N, 5)
+    mask = oracle.ancestor_mask(o["parent"], o["n_nodes"], T=N + 1)
+    try:
+        for algo in (dd.BUILD_AUTO, dd.BUILD_LEVELS):
+            dd.set_build_algorithm(algo)
+            g = gu.gpu_build(tok, lp, N, 5)
+            assert int(g["n_nodes"][0]) == o["n_nodes"], algo
+            for key in ("tokens", "parent", "depth", "rank"):
+                assert np.array_equal(g[key][0], o[key]), (algo, key)
+            assert np.array_equal(g["node_score"][0].view(np.uint32), o["score"].view(np.uint32)), algo
+            assert np.array_equal(g["ancestor_mask"][0], mask), algo
+    finally:
+        dd.set_build_algorithm(dd.BUILD_AUTO)
+
+
+# wide: nodes off the chain with more than 64 children in the tree; long: continuations of more than 16 nodes; mixed: one
+# flat row among peaked ones; twins: equal rows, so that many prefixes have equal scores; masked: ranks of -1e9 and -inf
+@pytest.mark.parametrize("kind", ["wide", "long", "mixed", "twins", "masked"])
+@pytest.mark.parametrize("N,B,K", [(23, 16, 23), (24, 16, 24), (63, 32, 63), (64, 32, 64), (65, 2, 65), (66, 16, 66), (129, 17, 129),
+                                   (255, 32, 255), (512, 31, 512), (513, 16, 513), (1023, 24, 1023), (1024, 32, 700)])
+def test_deviations(kind, N, B, K):
+    rng = np.random.default_rng(7 * N + B)
+    r = np.arange(K)
+    if kind == "wide":
+        lp = np.where(r == 0, -0.3, -4.0 - 1e-3 * r - 1e-4 * rng.random((B, K)))
+        lp[0] = np.where(r < 3, -1.0 - 0.1 * r, -30.0 - 0.01 * r)
+    elif kind == "long":
+        lp = np.where(r == 0, -0.01, -3.0 - 0.3 * r) - 0.005 * rng.random((B, K))
+    elif kind == "mixed":
+        lp = np.where(r == 0, -0.1, -3.5 - 0.02 * r) - 0.01 * rng.random((B, K))
+        lp[B // 2] = -5.0 - 1e-3 * rng.random(K)
+    elif kind == "twins":
+        lp = np.repeat((np.where(r == 0, -0.25, -2.0 - 0.125 * (r // 2)))[None], B, 0)
+    else:
+        lp = np.where(r == 0, -0.2, -3.0 - 0.1 * r) - 0.01 * rng.random((B, K))
+        lp[:, K // 2:] = -1e9
+        lp[1::2, 3 * K // 4:] = -np.inf
+    lp = -np.sort(-lp.astype(np.float32), axis=1)
+    _check(rng.integers(0, 5000, (B, K)).astype(np.int32), lp, N)
