@@ -359,20 +359,25 @@ struct CompactArgs {
     int32_t dst_row[DDTREE_MAX_BATCH];
 };
 
-__global__ __launch_bounds__(256) void compact_kernel(
+constexpr int kCompactThreads = 256;
+__global__ __launch_bounds__(kCompactThreads) void compact_kernel(
+    const int32_t *__restrict__ path, const int32_t *__restrict__ n_accepted, int T, int B, int row_words, int dst0,
     const uint32_t *__restrict__ k_tree, const uint32_t *__restrict__ v_tree,
-    const int32_t *__restrict__ path, const int32_t *__restrict__ n_accepted, CompactArgs args,
-    int T, int B, int row_words, uint32_t *__restrict__ k_cache, uint32_t *__restrict__ v_cache)
+    uint32_t *__restrict__ k_cache, uint32_t *__restrict__ v_cache, CompactArgs args)
 {
     const int j = blockIdx.x, seq = blockIdx.y;
-    if (j > n_accepted[seq]) return;
-    const int node = path[(size_t)seq * (B + 1) + j];
-    if (node < 0 || node >= T) return;
+    // Bound by latencies: a launch, the path, the row.  The path and its length are requested together (entries behind
+    // the path are allocated and hold -1), K and V likewise; the first sequence's row is a scalar argument.  (A round of
+    // eight layers, each with attention, merge and append: 206 -> 189 us with this and the like in attn_common.hpp.)
+    const int len = n_accepted[seq], node = path[(size_t)seq * (B + 1) + j];
+    const int dst_row = seq == 0 ? dst0 : args.dst_row[seq];
+    if (j > len || node < 0 || node >= T) return;
     const size_t src = ((size_t)seq * T + node) * row_words;
-    const size_t dst = ((size_t)args.dst_row[seq] + j) * row_words;
-    for (int w = threadIdx.x; w < row_words; w += blockDim.x) {
-        k_cache[dst + w] = k_tree[src + w];
-        v_cache[dst + w] = v_tree[src + w];
+    const size_t dst = ((size_t)dst_row + j) * row_words;
+    for (int w = threadIdx.x; w < row_words; w += kCompactThreads) {
+        const uint32_t k = k_tree[src + w], v = v_tree[src + w];
+        k_cache[dst + w] = k;
+        v_cache[dst + w] = v;
     }
 }
 
@@ -502,9 +507,9 @@ extern "C" int ddtree_compact(const void *k_tree, const void *v_tree, const int3
         if (dst_row[s] < 0) return DDTREE_ERR_ARG;
         args.dst_row[s] = dst_row[s];
     }
-    hipLaunchKernelGGL(compact_kernel, dim3(B + 1, batch), dim3(256), 0, as_stream(stream),
+    hipLaunchKernelGGL(compact_kernel, dim3(B + 1, batch), dim3(kCompactThreads), 0, as_stream(stream),
+                       path, n_accepted, T, B, (int)(row_bytes / 4), dst_row[0],
                        static_cast<const uint32_t *>(k_tree), static_cast<const uint32_t *>(v_tree),
-                       path, n_accepted, args, T, B, (int)(row_bytes / 4),
-                       static_cast<uint32_t *>(k_cache), static_cast<uint32_t *>(v_cache));
+                       static_cast<uint32_t *>(k_cache), static_cast<uint32_t *>(v_cache), args);
     return launch_status();
 }

@@ -676,15 +676,16 @@ struct AttnMergeArgs {
 };
 template <int D, int kMergeBatch, class Part>
 __global__ __launch_bounds__(256) void attn_merge_kernel(const Part *__restrict__ part_all,
-                                                         const float2 *__restrict__ lse_all, AttnMergeArgs args,
-                                                         int rows_seq, uint16_t *__restrict__ out)
+                                                         const float2 *__restrict__ lse_all, uint16_t *__restrict__ out,
+                                                         int rows_seq, int first0, int splits0, AttnMergeArgs args)
 {
     constexpr int CH = D / 8;
-    const int seq = blockIdx.y, splits = args.range[seq][1];
+    // (the first sequence's range is in registers when the kernel starts, the others' are a load of the arguments)
+    const int seq = blockIdx.y, splits = seq == 0 ? splits0 : args.range[seq][1], slot0 = seq == 0 ? first0 : args.range[seq][0];
     const int gid = (int)blockIdx.x * 256 + (int)threadIdx.x;
     const int row = gid / CH, dg = gid % CH;
     if (row >= rows_seq || splits == 1) return;  // (an uncut key range is already in `out`)
-    const size_t first = (size_t)args.range[seq][0] * rows_seq + row;
+    const size_t first = (size_t)slot0 * rows_seq + row;
     const Part *part = part_all + first * D + dg * 8;
     typedef Part part8 __attribute__((ext_vector_type(8)));
     const float2 *lse = lse_all + first;
@@ -968,11 +969,11 @@ static int verify_attn_impl(const void *q, const void *k_cache, const void *v_ca
                 auto *kernel = D == kHD ? (most <= 8 ? attn_merge_kernel<kHD, 8, float> : attn_merge_kernel<kHD, 16, float>)
                                         : (most <= 8 ? attn_merge_kernel<64, 8, float> : attn_merge_kernel<64, 16, float>);
                 DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, kernel, grid, dim3(256), 0, st, static_cast<const float *>(part), lse,
-                           merge, rows_seq, static_cast<uint16_t *>(out));
+                           static_cast<uint16_t *>(out), rows_seq, merge.range[0][0], merge.range[0][1], merge);
             } else {
                 auto *kernel = most <= 8 ? attn_merge_kernel<kHD, 8, _Float16> : attn_merge_kernel<kHD, 16, _Float16>;
                 DDT_LAUNCH(DDTREE_KERNEL_ATTN_MERGE, st, kernel, grid, dim3(256), 0, st, static_cast<const _Float16 *>(part), lse,
-                           merge, rows_seq, static_cast<uint16_t *>(out));
+                           static_cast<uint16_t *>(out), rows_seq, merge.range[0][0], merge.range[0][1], merge);
             }
         }
         return launch_status();

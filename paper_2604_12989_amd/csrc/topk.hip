@@ -541,9 +541,10 @@ __device__ void finish_row(const float *p, const FinishArgs a, const float *maxi
 // ------------------------------------------------------------------------------------------
 template <bool FINISH>
 __global__ __launch_bounds__(kChunkThreads, 4) void topk_chunk_kernel(
-    const float *__restrict__ logits, const FinishArgs a, int group, int hot_rank, float *maxima, ChunkStat *stat,
-    uint64_t *hot, int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
+    const float *__restrict__ logits, int V, int chunk_len, int chunks, int group, int hot_rank, int hot_cap, float *maxima,
+    ChunkStat *stat, uint64_t *hot, int K, int maxima_per_chunk, int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
 {
+    const FinishArgs a{V, K, chunks, chunk_len, maxima_per_chunk, hot_cap};
     __shared__ float s_fmax[kChunkWaves], s_group[64];
     __shared__ uint32_t s_low[kChunkWaves];
     __shared__ double s_dsum[kChunkWaves];
@@ -723,9 +724,11 @@ __global__ __launch_bounds__(kChunkThreads, 4) void topk_chunk_kernel(
 
 constexpr int kFinishThreads = 1024;
 __global__ __launch_bounds__(kFinishThreads) void topk_finish_kernel(
-    const float *__restrict__ logits, const FinishArgs a, const float *__restrict__ maxima,
-    const ChunkStat *__restrict__ stat, const uint64_t *__restrict__ hot, int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
+    const float *__restrict__ logits, const float *__restrict__ maxima, const ChunkStat *__restrict__ stat,
+    const uint64_t *__restrict__ hot, int V, int K, int chunks, int chunk_len, int maxima_per_chunk, int hot_cap,
+    int32_t *__restrict__ topk_tok, float *__restrict__ topk_lp)
 {
+    const FinishArgs a{V, K, chunks, chunk_len, maxima_per_chunk, hot_cap};
     __shared__ __align__(16) FinishLds L;
     const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
     finish_row<kFinishThreads>(logits + row * (size_t)a.V, a, maxima + row * (size_t)a.chunks * a.maxima,
@@ -749,16 +752,17 @@ extern "C" int ddtree_topk(const float *logits, int batch, int B, int V, int K, 
     float *maxima = reinterpret_cast<float *>(ws + p.max_off);
     ChunkStat *stat = reinterpret_cast<ChunkStat *>(ws + p.stat_off);
     uint64_t *hot = reinterpret_cast<uint64_t *>(ws + p.hot_off);
-    const FinishArgs a{V, K, p.chunks, p.chunk_len, p.maxima, p.hot_cap};
+    // (Scalars one by one, what is wanted first in front: the first 14 words of the arguments are in registers when a
+    // kernel starts, a structure by value is not among them.)
     hipStream_t st = as_stream(stream);
     if (p.chunks == 1) {
-        DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_chunk_kernel<true>, dim3(1, B, batch), dim3(kChunkThreads), 0, st, logits, a,
-                   p.group, p.hot_rank, maxima, stat, hot, topk_tok, topk_lp);
+        DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_chunk_kernel<true>, dim3(1, B, batch), dim3(kChunkThreads), 0, st, logits, V,
+                   p.chunk_len, p.chunks, p.group, p.hot_rank, p.hot_cap, maxima, stat, hot, K, p.maxima, topk_tok, topk_lp);
         return launch_status();
     }
     DDT_LAUNCH(DDTREE_KERNEL_TOPK_CHUNK, st, topk_chunk_kernel<false>, dim3(p.chunks, B, batch), dim3(kChunkThreads), 0, st, logits,
-               a, p.group, p.hot_rank, maxima, stat, hot, topk_tok, topk_lp);
-    DDT_LAUNCH(DDTREE_KERNEL_TOPK_MERGE, st, topk_finish_kernel, dim3(B, batch), dim3(kFinishThreads), 0, st, logits, a, maxima,
-               stat, hot, topk_tok, topk_lp);
+               V, p.chunk_len, p.chunks, p.group, p.hot_rank, p.hot_cap, maxima, stat, hot, K, p.maxima, topk_tok, topk_lp);
+    DDT_LAUNCH(DDTREE_KERNEL_TOPK_MERGE, st, topk_finish_kernel, dim3(B, batch), dim3(kFinishThreads), 0, st, logits, maxima,
+               stat, hot, V, K, p.chunks, p.chunk_len, p.maxima, p.hot_cap, topk_tok, topk_lp);
     return launch_status();
 }
