@@ -87,9 +87,11 @@ def _check(code: int, what: str):
 def _call(name, args, result, defer):
     """Run the C entry point now, or (defer=True) return a zero-argument callable that runs it
     with the arguments marshalled once: tight loops then pay one ctypes call per stage."""
-    fn = getattr(load(), name)
+    fn = getattr(_lib or load(), name)
     if not defer:
-        _check(fn(*args), name)
+        rc = fn(*args)
+        if rc != 0:
+            _check(rc, name)
         return result
 
     # the callable holds raw pointers: the caller keeps the tensors alive while it is in use
@@ -111,20 +113,24 @@ def _keepalive(fn, *objs):
     return run
 
 
-# A call's host time is the marshalling here plus the launches (2-3 us each).  A decoding round that does
+# A call's host time is the marshalling here plus the launches (1.5-2 us each).  A decoding round that does
 # not defer its calls makes one per stage and layer, and the GPU waits for the host where a call takes
 # longer than its kernels.  Hence plain integers for pointers (the argtypes convert them), results made from
-# an input (new_empty), and the raw stream handle (0.4 us; a torch.cuda.Stream object takes 3.3).  Each
+# an input or from one another (empty_like 1.1 us, new_empty 1.7), the raw stream handle (a torch.cuda.Stream
+# object takes 3.3 us) of the device that the C level of torch names (current_device() checks more: 0.4), and the
+# address of a host array through its buffer (0.3 us; its ctypes object 1.1).  Each
 # result has memory of its own: views of one allocation would be 2.9 us a round cheaper, but keeping one
-# would keep all.  Per call, with a stream object, pointer objects and torch.empty, and now: build 21.6 -> 17.4 us,
-# attention 15.8 -> 12.5, walk 18.3 -> 15.7.
+# would keep all.  Per call, before and now, on one
+# box: top-K 13.0 -> 12.3 us, build 18.2 -> 16.2, attention 16.6 -> 15.4, walk 16.4 -> 15.4, append 7.5 -> 6.4.
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
-if hasattr(torch._C, "_cuda_getCurrentRawStream"):
+if hasattr(torch._C, "_cuda_getCurrentRawStream") and hasattr(torch._C, "_cuda_getDevice"):
+    _raw_stream, _device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+
     def _stream():
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+        return _raw_stream(_device())
 else:
     def _stream():
         return torch.cuda.current_stream().cuda_stream
@@ -143,6 +149,8 @@ def _host_i32(values, n, what):
         values = np.ascontiguousarray(np.asarray(values, dtype=np.int32))
     if values.shape != (n,):
         raise DDTreeError(what)
+    if n > 0 and values.flags.writeable:
+        return values, ctypes.addressof(ctypes.c_char.from_buffer(values))
     return values, values.ctypes.data
 
 
@@ -196,10 +204,10 @@ def build(topk_tok, topk_lp, N, root_token, ws=None, out=None, defer=False):
     batch, B, K = topk_tok.shape
     T, W = N + 1, (N + 1 + 63) // 64
     if out is None:
-        out = {key: topk_tok.new_empty((batch, T)) for key in ("tokens", "parent", "depth", "rank")}
-        out["node_score"] = topk_lp.new_empty((batch, T))
-        out["ancestor_mask"] = topk_tok.new_empty((batch, T, W), dtype=torch.int64)
-        out["n_nodes"] = topk_tok.new_empty((batch,))
+        like, tokens = torch.empty_like, topk_tok.new_empty((batch, T))
+        out = dict(tokens=tokens, parent=like(tokens), depth=like(tokens), rank=like(tokens),
+                   node_score=topk_lp.new_empty((batch, T)),
+                   ancestor_mask=topk_tok.new_empty((batch, T, W), dtype=torch.int64), n_nodes=topk_tok.new_empty((batch,)))
     p, n = _ws(ws)
     args = (_ptr(topk_tok), _ptr(topk_lp), batch, B, K, N, _ptr(root_token), _ptr(out["tokens"]),
             _ptr(out["parent"]), _ptr(out["depth"]), _ptr(out.get("rank")),
@@ -259,10 +267,11 @@ def accept(target_logits, tokens, parent, depth, n_nodes, B, ws, out=None, want_
     _dev(target_logits, torch.float32, "target_logits")
     batch, T, V = target_logits.shape
     if out is None:
-        i32 = dict(dtype=torch.int32)
-        out = dict(path=target_logits.new_empty((batch, B + 1), **i32), n_accepted=target_logits.new_empty((batch,), **i32),
-                   bonus_token=target_logits.new_empty((batch,), **i32),
-                   posterior=target_logits.new_empty((batch, T), **i32) if want_posterior else None)
+        i32 = torch.int32
+        n_accepted = target_logits.new_empty((batch,), dtype=i32)
+        out = dict(path=target_logits.new_empty((batch, B + 1), dtype=i32), n_accepted=n_accepted,
+                   bonus_token=torch.empty_like(n_accepted),
+                   posterior=target_logits.new_empty((batch, T), dtype=i32) if want_posterior else None)
     p, n = _ws(ws)
     if temperature is not None:
         args = (_ptr(target_logits), batch, T, V, _ptr(tokens), _ptr(parent), _ptr(depth),
