@@ -44,10 +44,20 @@ size_t accept_scratch_upper(int batch, int T, int V)
     return align_up((size_t)std::min(rows + 3071, rows * std::max(1, V / 4096)) * 8, 256);
 }
 
-struct ArgPart {
-    float val;
-    int32_t idx;
-};
+// A segment's best: the value's order-preserving key, and below it the complement of the token id, so that the larger
+// of two is the larger value or, of equal ones, the lower id.
+typedef unsigned long long ArgPart;
+constexpr ArgPart kNoPart = 0ull;  // (below everything)
+__device__ __forceinline__ ArgPart arg_part(float v, int i) { return (ArgPart)float_key(v) << 32 | (uint32_t)~i; }
+__device__ __forceinline__ int arg_token(ArgPart p) { return (int)~(uint32_t)p; }
+// Against the lane that CTRL names.  (On two registers through DPP a step costs some 50 cycles, value and id exchanged
+// through LDS 190: scan and walk, launch to launch, of 17 rows of 151936 8.1 -> 6.8 us, 65 of 32003 7.7 -> 6.5, 257 of 151936 28.2 -> 27.6.)
+template <int CTRL, int ROW_MASK = 0xF>
+__device__ __forceinline__ ArgPart arg_max_dpp(ArgPart p)
+{
+    const ArgPart o = (ArgPart)dpp_u<CTRL, ROW_MASK>((uint32_t)(p >> 32)) << 32 | dpp_u<CTRL, ROW_MASK>((uint32_t)p);
+    return o > p ? o : p;
+}
 
 __device__ __forceinline__ void arg_update(float &bv, int &bi, float v, int i)
 {
@@ -93,25 +103,22 @@ __device__ __forceinline__ float sample_key(float logit, uint32_t h, const Sampl
     return fmaf(logit, sa.inv_tau, g);
 }
 
-// The workgroup's best (value, id), valid in thread 0.
-__device__ __forceinline__ void workgroup_best(float &bv, int &bi, float *s_v, int *s_i)
+// The workgroup's best, valid in thread 0.
+__device__ __forceinline__ ArgPart workgroup_best(float bv, int bi, ArgPart *s_best)
 {
-    const int tid = threadIdx.x;
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const float ov = __shfl_xor(bv, d, 64);
-        const int oi = __shfl_xor(bi, d, 64);
-        arg_update(bv, bi, ov, oi);
-    }
-    if ((tid & 63) == 0) {
-        s_v[tid >> 6] = bv;
-        s_i[tid >> 6] = bi;
-    }
+    ArgPart p = arg_part(bv, bi);
+    p = arg_max_dpp<0xB1>(p);
+    p = arg_max_dpp<0x4E>(p);
+    p = arg_max_dpp<0x141>(p);
+    p = arg_max_dpp<0x140>(p);
+    p = arg_max_dpp<0x142, 0xA>(p);
+    p = arg_max_dpp<0x143, 0xC>(p);
+    if ((threadIdx.x & 63) == 63) s_best[threadIdx.x >> 6] = p;
     __syncthreads();
-    if (tid == 0) {
+    p = s_best[0];
 #pragma unroll
-        for (int w = 1; w < kArgmaxThreads / 64; ++w) arg_update(bv, bi, s_v[w], s_i[w]);
-    }
+    for (int w = 1; w < kArgmaxThreads / 64; ++w) p = s_best[w] > p ? s_best[w] : p;
+    return p;
 }
 
 __device__ __forceinline__ float4 load_streamed(const float4 *p)  // (read once: marked non-temporal)
@@ -125,8 +132,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_argmax_kernel(
     const float *__restrict__ logits, int T, int V, int seg_len, int splits,
     const int32_t *__restrict__ n_nodes, ArgPart *__restrict__ part)
 {
-    __shared__ float s_v[kArgmaxThreads / 64];
-    __shared__ int s_i[kArgmaxThreads / 64];
+    __shared__ ArgPart s_parts[kArgmaxThreads / 64];
     const int tid = threadIdx.x;
     const int seg = blockIdx.x, i = blockIdx.y, seq = blockIdx.z;
     if (i > n_nodes[seq]) return;  // padding row: never read, the walk ignores its partial
@@ -140,8 +146,8 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_argmax_kernel(
     int head = (int)((4 - ((reinterpret_cast<uintptr_t>(p) >> 2) & 3)) & 3);
     if (head > n) head = n;
     if (tid < head) {
-        bv = p[tid];
-        bi = start + tid;
+        const float x = p[tid];
+        if (x >= bv) { bv = x; bi = start + tid; }
     }
     const int nvec = (n - head) >> 2;
     const float4 *pv = reinterpret_cast<const float4 *>(p + head);
@@ -169,8 +175,8 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_argmax_kernel(
         const float x = p[tail0 + tid];
         if (x > bv) { bv = x; bi = start + tail0 + tid; }
     }
-    workgroup_best(bv, bi, s_v, s_i);
-    if (tid == 0) part[rowi * splits + seg] = ArgPart{bv, bi};
+    const ArgPart best_part = workgroup_best(bv, bi, s_parts);
+    if (tid == 0) part[rowi * splits + seg] = best_part;
 }
 
 // The sampled scan, bound by the vector ALUs: the hash of an element is four 32-bit multiplies, a
@@ -188,8 +194,7 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
     const float *__restrict__ logits, int T, int V, int seg_len, int splits,
     const int32_t *__restrict__ n_nodes, ArgPart *__restrict__ part, SampleArgs sa)
 {
-    __shared__ float s_v[kArgmaxThreads / 64];
-    __shared__ int s_i[kArgmaxThreads / 64];
+    __shared__ ArgPart s_parts[kArgmaxThreads / 64];
     __shared__ uint32_t s_best;  // a lower bound on the row's best key, order-preserving
     const int tid = threadIdx.x;
     const int seg = blockIdx.x, i = blockIdx.y, seq = blockIdx.z;
@@ -275,8 +280,8 @@ __global__ __launch_bounds__(kArgmaxThreads) void accept_sample_kernel(
         }
     }
     if (tid < n - tail0) arg_update(bv, bi, sample_key(behind, hash(start + tail0 + tid), sa), start + tail0 + tid);
-    workgroup_best(bv, bi, s_v, s_i);
-    if (tid == 0) part[rowi * splits + seg] = ArgPart{bv, bi};
+    const ArgPart best_part = workgroup_best(bv, bi, s_parts);
+    if (tid == 0) part[rowi * splits + seg] = best_part;
 }
 
 // One workgroup per sequence, `lanes` (a power of two) per row.
@@ -306,17 +311,24 @@ __global__ __launch_bounds__(kWalkMaxThreads) void accept_walk_kernel(
         // read there is never used), its token, parent and depth.
         const bool on = i < T;
         const ArgPart *pp = part + (base + (on ? i : 0)) * splits;
-        float bv = -INFINITY;
-        int bi = 0x7FFFFFFF;
-        ArgPart a[kPer];
+        ArgPart a[kPer], best = kNoPart;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) a[u] = sub + u * lanes < splits ? pp[sub + u * lanes] : ArgPart{-INFINITY, 0x7FFFFFFF};
+        for (int u = 0; u < kPer; ++u) a[u] = sub + u * lanes < splits ? pp[sub + u * lanes] : kNoPart;
         int tk = -1, pr = -1, dp = 0;
         if (on && sub == 0) tk = tokens[base + i], pr = parent[base + i], dp = depth[base + i];
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) arg_update(bv, bi, a[u].val, a[u].idx);
-        for (int q = sub + kPer * lanes; q < splits; q += lanes) arg_update(bv, bi, pp[q].val, pp[q].idx);
-        for (int d = lanes >> 1; d >= 1; d >>= 1) arg_update(bv, bi, __shfl_xor(bv, d, 64), __shfl_xor(bi, d, 64));
+        for (int u = 0; u < kPer; ++u) best = a[u] > best ? a[u] : best;
+        for (int q = sub + kPer * lanes; q < splits; q += lanes) best = pp[q] > best ? pp[q] : best;
+        // (the lanes of a row are neighbours; each step leaves the larger in both of a pair, so that mirrored lanes will do)
+        if (lanes >= 2) best = arg_max_dpp<0xB1>(best);
+        if (lanes >= 4) best = arg_max_dpp<0x4E>(best);
+        if (lanes >= 8) best = arg_max_dpp<0x141>(best);
+        if (lanes >= 16) best = arg_max_dpp<0x140>(best);
+        for (int d = 16; d < lanes; d *= 2) {
+            const ArgPart o = __shfl_xor(best, d, 64);
+            best = o > best ? o : best;
+        }
+        const int bi = arg_token(best);
         if (on && sub == 0) {
             const bool in_tree = i <= n;
             const int post = in_tree ? bi : -1;
