@@ -1036,8 +1036,8 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 // on its SIMD, cycles: a dependent addition 7, through DPP 23, a ballot that scalar code looks at 45, a branch
 // under a lane mask 55, an LDS read 62, a barrier of eight waves 15.  256 nodes at p = 0.9: table 5.2 thousand, first
 // bound and histogram 4.5, turns 19, ranking 6.5, arrays and masks 4.5.
-// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 11.8; 256 nodes p = 0
-// (flat) 17.1 -> 12.4, 0.4 29.5 -> 13.1, 0.9 20.7 -> 13.3; 512 nodes 0.4 34.2 -> 16.5, 0.9 25.4 -> 14.6; 1024 nodes 0 35.3 -> 19.4, 0.5 59.3 -> 22.2,
+// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 11.2; 256 nodes p = 0
+// (flat) 17.1 -> 11.9, 0.4 29.5 -> 13.1, 0.9 20.7 -> 13.3; 512 nodes 0.4 34.2 -> 16.5, 0.9 25.4 -> 14.6; 1024 nodes 0 35.3 -> 19.4, 0.5 59.3 -> 22.2,
 // 0.9 43.7 -> 21.3.
 // Returns N, or -1 (uniform): no bound (fewer ranks than budget), or more members than there is room for (heavy ties).
 // ------------------------------------------------------------------------------------------
@@ -1266,9 +1266,12 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
         if (!next_phase()) return -1;
         const int w_end = W;
         if (w_first == w_end) continue;
-        // ---- the listed heads, a lane each: their continuations, up to 16 nodes at a time in registers; in the first
-        //      turn they are counted before any is kept ----
-        for (int keep = first_turn ? 0 : 1; keep < 2; ++keep) {
+        // ---- the listed heads, a lane each: their continuations, up to 16 nodes at a time in registers.  In the first
+        //      turn, whose cut is the loosest, they are counted before any is kept, unless there is room for all of
+        //      them whatever the cut (rows peaked at 0.9, launch to launch: 64 nodes 12.1 us with the count, 11.2 without, 128
+        //      12.8 and 12.1; hence the room that budgets up to 128 have) ----
+        const bool count_first = first_turn && M + (w_end - w_first) * (B - 1) > room;
+        for (int keep = count_first ? 0 : 1; keep < 2; ++keep) {
             s = cut();
             for (int w0 = w_first + 64 * wave; w0 < w_end; w0 += NT) {
                 int id = list[min(w0 + lane, w_end - 1)];
@@ -1316,7 +1319,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
                             L.m_score[place] = v[k];
                             L.m_info[place] = info;
                             info = pack_member(m_at + k, 0, depth + k + 2);
-                            if (!first_turn) count(v[k], k < len);
+                            if (!count_first) count(v[k], k < len);
                         }
                         while (__builtin_amdgcn_ballot_w64(kids != 0u) != 0ull) {
                             const int k = __builtin_ctz(kids | 0x10000u);
@@ -1892,7 +1895,7 @@ static BuildLds set_lds_plan(int B, int K, int N)
     const size_t limit = 150 * 1024;
     if (base >= limit) return r;
     const size_t avail = limit - base;
-    const int capp = 2 * N + 256;       // members of one depth that can be parents
+    const int capp = N <= 128 ? 4 * N + 512 : 2 * N + 256;  // members of one depth that can be parents
     const int min_m = 2 * N + 64;
     int capc = 4 * N + 512;             // candidates of one level
     // large budgets leave little room beside the log-probability table: favour the members
@@ -1901,7 +1904,8 @@ static BuildLds set_lds_plan(int B, int K, int N)
     const size_t fixed = 4 * (size_t)capp + 8 * (size_t)capc;
     if (fixed + 10 * (size_t)min_m > avail) return r;
     size_t capm = (avail - fixed) / 10 / 2 * 2;
-    if (capm > (size_t)8 * N + 256) capm = (size_t)8 * N + 256;
+    const size_t most = (size_t)(N <= 128 ? 16 : 8) * N + 256;
+    if (capm > most) capm = most;
     if (capm > 8192) capm = 8192;       // member ids are 13 bits wide
     if (capm > 2 * (size_t)capc) capm = 2 * (size_t)capc;
     if (capm > 2 * (size_t)capp) capm = 2 * (size_t)capp;
