@@ -250,10 +250,10 @@ int ddtree_compact(const void *k_tree, const void *v_tree, const int32_t *path,
                    int Hkv, int D, int elem_bytes, void *k_cache, void *v_cache, void *stream);
 
 /*
- * Construction used by ddtree_build (Algorithm 1 defines the result; both constructions produce
+ * Construction used by ddtree_build (Algorithm 1 defines the result; all constructions produce
  * it bit for bit).  DDTREE_BUILD_POPS runs the best-first pops one after the other on one
- * wavefront; DDTREE_BUILD_LEVELS finds the same N best prefixes (Proposition 2) as a set, depth
- * by depth or, on peaked rows, by the number of non-zero ranks in a prefix, orders them, and
+ * wavefront; DDTREE_BUILD_LEVELS finds the same N best prefixes (Proposition 2) as a set, by the
+ * number of non-zero ranks in a prefix or, where that does not do, depth by depth, orders them, and
  * falls back to the pops when heavy score ties defeat its bounds;
  * DDTREE_BUILD_AUTO (the default) picks per sequence from the budget and the shape of the
  * log-probabilities.  Process-wide, takes effect at the next ddtree_build call; meant for
@@ -277,8 +277,8 @@ int ddtree_set_build_algorithm(int algo);
  * are numbered from 10000 on), 10000 + (number of the failed check) for the plans. */
 int ddtree_selftest_host(void);
 /*
- * Number of sequences, since the library was loaded, for which the level-synchronous
- * construction gave up and the pops built the tree instead.  count is a host pointer; the call
+ * Number of sequences, since the library was loaded, for which the set
+ * constructions gave up and the pops built the tree instead.  count is a host pointer; the call
  * waits for the device.  Meant for tests.
  */
 int ddtree_build_giveups(unsigned int *count);

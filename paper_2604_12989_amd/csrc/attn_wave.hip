@@ -14,7 +14,8 @@
 // all keys: 16 KB per wave and step), which is why attn_mfma_kernel takes over where there are many
 // rows per key (attn_plan.hip weighs the two).
 // Measured, attention and merge together: D = 128, 17 nodes x 300 keys 14.7 -> 8.6 us, 65 x 2048 20.1 -> 15.2,
-// 61 x 3001 21.9 -> 15.7 (32 query and 8 KV heads); D = 64, 65 x 2047, 16 and 4 heads 147 (one workgroup
+// 61 x 3001 21.9 -> 15.7, and launch to launch 14.9 -> 14.2 since a single sequence's entry is requested with the other
+// arguments (32 query and 8 KV heads); D = 64, 65 x 2047, 16 and 4 heads 147 (one workgroup
 // per node and head on the vector ALUs) -> 11 us.
 #include "attn_wave_rows.hpp"
 
