@@ -313,7 +313,10 @@ __global__ __launch_bounds__(kWalkMaxThreads) void accept_walk_kernel(
         const ArgPart *pp = part + (base + (on ? i : 0)) * splits;
         ArgPart a[kPer], best = kNoPart;
 #pragma unroll
-        for (int u = 0; u < kPer; ++u) a[u] = sub + u * lanes < splits ? pp[sub + u * lanes] : kNoPart;
+        for (int u = 0; u < kPer; ++u) {  // (past the end: the last one once more, which changes nothing)
+            a[u] = kNoPart;
+            if (u * lanes < splits) a[u] = pp[min(sub + u * lanes, splits - 1)];
+        }
         int tk = -1, pr = -1, dp = 0;
         if (on && sub == 0) tk = tokens[base + i], pr = parent[base + i], dp = depth[base + i];
 #pragma unroll
