@@ -1034,10 +1034,10 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 //     histogram, then all pairs inside a bucket with the full comparison.  The first N become nodes 1 .. N.
 // What bounds it: a chain of dependent instructions of a workgroup that has the chip to itself.  Measured on a wave alone
 // on its SIMD, cycles: a dependent addition 7, through DPP 23, a ballot that scalar code looks at 45, a branch
-// under a lane mask 55, an LDS read 62, a barrier of eight waves 15.  256 nodes at p = 0.9: table 5.2 thousand, first
-// bound and histogram 4.5, turns 19, ranking 6.5, arrays and masks 4.5.
-// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 11.2; 256 nodes p = 0
-// (flat) 17.1 -> 11.9, 0.4 29.5 -> 13.1, 0.9 20.7 -> 13.3; 512 nodes 0.4 34.2 -> 16.5, 0.9 25.4 -> 14.6; 1024 nodes 0 35.3 -> 19.4, 0.5 59.3 -> 22.2,
+// under a lane mask 55, an LDS read 62, a barrier of eight waves 15.  256 nodes at p = 0.9: table 5.2 thousand (with a
+// lane mask for each load; 1 us less without), first bound and histogram 4.5, turns 19, ranking 6.5, arrays and masks 4.5 (time stamps included).
+// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 10.2; 256 nodes p = 0
+// (flat) 17.1 -> 10.9, 0.4 29.5 -> 12.3, 0.9 20.7 -> 12.4; 512 nodes 0.4 34.2 -> 15.9, 0.9 25.4 -> 14.0; 1024 nodes 0 35.3 -> 18.4, 0.5 59.3 -> 22.4,
 // 0.9 43.7 -> 21.3.
 // Returns N, or -1 (uniform): no bound (fewer ranks than budget), or more members than there is room for (heavy ties).
 // ------------------------------------------------------------------------------------------
