@@ -252,11 +252,11 @@ int ddtree_compact(const void *k_tree, const void *v_tree, const int32_t *path,
 /*
  * Construction used by ddtree_build (Algorithm 1 defines the result; all constructions produce
  * it bit for bit).  DDTREE_BUILD_POPS runs the best-first pops one after the other on one
- * wavefront; DDTREE_BUILD_LEVELS finds the same N best prefixes (Proposition 2) as a set, by the
- * number of non-zero ranks in a prefix or, where that does not do, depth by depth, orders them, and
- * falls back to the pops when heavy score ties defeat its bounds;
+ * wavefront; DDTREE_BUILD_LEVELS finds the same N best prefixes (Proposition 2) as a set, depth by
+ * depth, orders them, and falls back to the pops when heavy score ties defeat its bounds;
  * DDTREE_BUILD_AUTO (the default) picks per sequence from the budget and the shape of the
- * log-probabilities.  Process-wide, takes effect at the next ddtree_build call; meant for
+ * log-probabilities: the pops, or the same set found by the number of non-zero ranks in a prefix,
+ * and where that has no bound or no room the levels.  Process-wide, takes effect at the next ddtree_build call; meant for
  * tests and tuning.  Returns DDTREE_ERR_ARG for any other value.
  */
 #define DDTREE_BUILD_AUTO 0
@@ -277,11 +277,14 @@ int ddtree_set_build_algorithm(int algo);
  * are numbered from 10000 on), 10000 + (number of the failed check) for the plans. */
 int ddtree_selftest_host(void);
 /*
- * Number of sequences, since the library was loaded, for which the set
- * constructions gave up and the pops built the tree instead.  count is a host pointer; the call
+ * Number of sequences, since the library was loaded, for which the level
+ * construction gave up and the pops built the tree instead.  count is a host pointer; the call
  * waits for the device.  Meant for tests.
  */
 int ddtree_build_giveups(unsigned int *count);
+/* The same for sequences whose prefixes the construction by the number of non-zero ranks
+ * (DDTREE_BUILD_AUTO) had no room for, so that the levels built the tree. */
+int ddtree_build_handovers(unsigned int *count);
 
 /*
  * Kernel timing hook for benchmarks (no passage of the paper: measurement only).  While a

@@ -37,6 +37,7 @@ _SIGNATURES = {
     "ddtree_set_build_algorithm": (_i, [_i]),
     "ddtree_selftest_host": (_i, []),
     "ddtree_build_giveups": (_i, [ctypes.POINTER(ctypes.c_uint)]),
+    "ddtree_build_handovers": (_i, [ctypes.POINTER(ctypes.c_uint)]),
     "ddtree_profile_enable": (_i, [ctypes.c_uint, _i]),
     "ddtree_profile_enable_every": (_i, [ctypes.c_uint, _i, _i]),
     "ddtree_profile_reset": (_i, []),
@@ -322,6 +323,13 @@ def build_giveups():
     """Sequences (since load) that the level-synchronous construction handed back to the pops."""
     n = ctypes.c_uint(0)
     _check(load().ddtree_build_giveups(ctypes.byref(n)), "ddtree_build_giveups")
+    return int(n.value)
+
+
+def build_handovers():
+    """Sequences (since load) that the construction by deviations handed to the levels for lack of room."""
+    n = ctypes.c_uint(0)
+    _check(load().ddtree_build_handovers(ctypes.byref(n)), "ddtree_build_handovers")
     return int(n.value)
 
 

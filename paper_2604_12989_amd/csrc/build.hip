@@ -99,6 +99,7 @@ __device__ bool tuple_before(const uint32_t *s_node, int pa, int ra, int pb, int
 // the caller runs the sequential pops instead.
 // ------------------------------------------------------------------------------------------
 __device__ unsigned int g_level_giveups;  // sequences the level construction handed to the pops
+__device__ unsigned int g_handovers;      // sequences the construction by deviations had no room for
 
 constexpr int kLvBuckets = 256;
 constexpr float kLvNeg = -3.0e38f;   // scores at or below count as -inf: never part of a tree
@@ -1039,8 +1040,9 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 // Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 10.2; 256 nodes p = 0
 // (flat) 17.1 -> 10.9, 0.4 29.5 -> 12.3, 0.9 20.7 -> 12.4; 512 nodes 0.4 34.2 -> 15.9, 0.9 25.4 -> 14.0; 1024 nodes 0 35.3 -> 18.4, 0.5 59.3 -> 22.4,
 // 0.9 43.7 -> 21.3.
-// Returns N, or -1 (uniform): no bound (fewer ranks than budget), or more members than there is room for (heavy ties).
+// Returns N, or (uniform) -1: no bound (fewer ranks than budget), or kNoRoom: more members than there is room for.
 // ------------------------------------------------------------------------------------------
+constexpr int kNoRoom = -2;
 constexpr int kRankBuckets = 1024;
 constexpr int kHistInts = kLvBuckets + 64;  // (and a word for each lane with nothing to count)
 // histogram, its prefix sums, ranking buckets, four 64-bit counters and one for each lane but the first
@@ -1200,7 +1202,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     };
 
     float s = lo;
-    if (!next_phase()) return -1;
+    if (!next_phase()) return kNoRoom;
     for (int q_done = 0; q_done < Q;) {  // (uniform, like everything that M, Q and W decide)
         // ---- the nodes of the queue: their children of ranks first .. first + 63 ----
         const bool first_turn = q_done == 0;
@@ -1264,7 +1266,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
         }
         q_done = q_end;
         const int w_first = W;
-        if (!next_phase()) return -1;
+        if (!next_phase()) return kNoRoom;
         const int w_end = W;
         if (w_first == w_end) continue;
         // ---- the listed heads, a lane each: their continuations, up to 16 nodes at a time in registers.  In the first
@@ -1336,7 +1338,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
                     if (__builtin_amdgcn_ballot_w64(S >= s && depth < B) == 0ull) break;
                 }
             }
-            if (!next_phase()) return -1;
+            if (!next_phase()) return kNoRoom;
         }
     }
 
@@ -1388,7 +1390,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
             at += c[j];
         }
     }
-    if (alive > sorted_room) return -1;
+    if (alive > sorted_room) return kNoRoom;
     __syncthreads();
     for (int m = 1 + tid; m < M; m += NT) {
         const float v = L.m_score[m];
@@ -1627,7 +1629,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
     // of siblings pops as one: flat rows, whose tree is a star or nearly.  The construction by deviations takes about
     // the same time whatever the rows are.  Below 28 nodes pops always win; up to 256 they do where hardly any node of
     // depth 2 (of ranks 0 .. 3 counted, an upper bound) reaches the worst useful rank of row 0.
-    // All constructions give the same tree; algo 1 / 2 force pops / the others.
+    // All constructions give the same tree; algo 1 / 2 force the pops / the levels.
     // (Launch to launch, pops / deviations, us.  Rows peaked at 0.7: 16 nodes 8.9 / 10.3, 20 10.3 / 10.8, 24 11.5 / 10.9, 32
     // 14.0 / 11.2, 64 33.7 / 11.5.  Stars: 32 nodes 5.0 / 8.2, 64 5.3 / 8.4, 128 6.0 / 8.7, 256 8.0 / 9.2; with two nodes of depth 2: 40
     // 6.9 / 8.4, 128 9.2 / 8.7; with four: 32 7.6 / 10.5, 64 11.2 / 8.5, 256 14.9 / 11.5.)
@@ -1654,9 +1656,14 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
     }
     int level_n = -1;
     if (use_levels) {
-        level_n = deviation_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
+        if (algo == DDTREE_BUILD_AUTO) {
+            level_n = deviation_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
+            if (level_n < 0) {
+                if (level_n == kNoRoom && tid == 0) atomicAdd(&g_handovers, 1u);
+                __syncthreads();  // (the histograms are reused)
+            }
+        }
         if (level_n < 0) {
-            __syncthreads();  // (the histograms are reused)
             level_n = level_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
         }
         if (level_n < 0 && tid == 0) atomicAdd(&g_level_giveups, 1u);
@@ -1975,6 +1982,14 @@ extern "C" int ddtree_build_giveups(unsigned int *count)
 {
     if (!count) return DDTREE_ERR_ARG;
     if (hipMemcpyFromSymbol(count, HIP_SYMBOL(ddt::g_level_giveups), sizeof(unsigned int)) != hipSuccess)
+        return DDTREE_ERR_HIP;
+    return DDTREE_OK;
+}
+
+extern "C" int ddtree_build_handovers(unsigned int *count)
+{
+    if (!count) return DDTREE_ERR_ARG;
+    if (hipMemcpyFromSymbol(count, HIP_SYMBOL(ddt::g_handovers), sizeof(unsigned int)) != hipSuccess)
         return DDTREE_ERR_HIP;
     return DDTREE_OK;
 }

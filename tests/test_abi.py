@@ -168,6 +168,7 @@ def test_bad_arguments_are_rejected_before_any_launch(lib):
     for algo in (2, 1, 0):
         assert lib.ddtree_set_build_algorithm(algo) == 0
     assert lib.ddtree_build_giveups(None) == ERR_ARG
+    assert lib.ddtree_build_handovers(None) == ERR_ARG
 
 
 def test_product_path_does_not_import_the_oracle():

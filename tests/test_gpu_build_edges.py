@@ -92,3 +92,21 @@ def test_deviations(kind, N, B, K):
         lp[1::2, 3 * K // 4:] = -np.inf
     lp = -np.sort(-lp.astype(np.float32), axis=1)
     _check(rng.integers(0, 5000, (B, K)).astype(np.int32), lp, N)
+
+
+def test_forced_levels_run_alone():
+    """Rows of equal values: more prefixes share the last score of the tree than the construction by deviations has room
+    for, so that it hands the sequence over.  Forced levels do not try it first."""
+    B, K, N = 8, 50, 64
+    lp = np.full((B, K), np.float32(-np.log(K)))
+    tok = np.tile(np.arange(K, dtype=np.int32), (B, 1))
+    o = oracle.build_tree(tok, lp, N, 5)
+    try:
+        for algo, more in ((dd.BUILD_AUTO, 1), (dd.BUILD_LEVELS, 0), (dd.BUILD_POPS, 0)):
+            dd.set_build_algorithm(algo)
+            before = dd.build_handovers()
+            g = gu.gpu_build(tok, lp, N, 5)
+            assert dd.build_handovers() - before == more, algo
+            assert np.array_equal(g["parent"][0], o["parent"]) and np.array_equal(g["rank"][0], o["rank"]), algo
+    finally:
+        dd.set_build_algorithm(dd.BUILD_AUTO)
