@@ -1019,8 +1019,10 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 // itself with any subset of them set to rank 0), two or three from a confident drafter.  A member that ends in a
 // deviation is a head; its continuation is the same prefix followed by ranks 0.
 //   * A first bound.  The chain's first l nodes and their single deviations of ranks 1 .. R are l + R l (l + 1) / 2
-//     prefixes, and the worst of them is the chain's l-th node with the largest loss of a rank R: the best bound
-//     over sixteen l (l = 1: the N-th rank of row 0) is where the histogram's range ends.
+//     prefixes, and the worst of them is the chain's l-th node with the largest loss of a rank R; the prefixes of l tokens of
+//     ranks 0 .. R are (R + 1)^l, and the worst of them is rank R throughout.  The best of both over sixteen l (l = 1: the
+//     N-th rank of row 0) is where the histogram's range ends.  The second is what serves rows with several plausible
+//     tokens each and rows with fewer ranks than the budget.
 //   * The cut.  A histogram of 256 equal score buckets counts every prefix known so far, once; the bucket in which
 //     the count reaches N holds the cut.  It starts with the chain and the heads off it of ranks 1 .. 64 (off the
 //     root: all), takes their continuations when those are first walked, and every member found later, so that
@@ -1031,6 +1033,10 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 //     reaches the cut are listed and walked, a lane a head, 16 nodes of each in registers.  Both put what has
 //     further children into the queue.  Places are handed out by one atomic per wave; their order does not
 //     matter, the members are ranked in the end.
+//   * Room.  A turn keeps what reaches the cut that it began with, on bushy rows several times what the final cut leaves.
+//     Continuations that may not fit are counted before any is kept.  Where members or queue entries run out of places all the
+//     same, what was found has been counted, without a place too, and the enumeration starts over with the cut that this
+//     gives; a phase that has been counted is not counted again.  Equal scores, which no cut tells apart, may still not fit.
 //   * The members that reach the final cut are ranked exactly: 1024 buckets of about equal population, by the
 //     histogram, then all pairs inside a bucket with the full comparison.  The first N become nodes 1 .. N.
 // What bounds it: a chain of dependent instructions of a workgroup that has the chip to itself.  Measured on a wave alone
@@ -1039,8 +1045,10 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 // lane mask for each load; 1 us less without), first bound and histogram 4.5, turns 19, ranking 6.5, arrays and masks 4.5 (time stamps included).
 // Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 10.2; 256 nodes p = 0
 // (flat) 17.1 -> 10.9, 0.4 29.5 -> 12.3, 0.9 20.7 -> 12.4; 512 nodes 0.4 34.2 -> 15.9, 0.9 25.4 -> 14.0; 1024 nodes 0 35.3 -> 18.4, 0.5 59.3 -> 22.4,
-// 0.9 43.7 -> 21.3.
-// Returns N, or (uniform) -1: no bound (fewer ranks than budget), or kNoRoom: more members than there is room for.
+// 0.9 43.7 -> 21.3.  Bushy rows, by levels, by deviations that handed over for lack of room, and now: 256 nodes 16 plausible
+// tokens a row 84 / 87 / 20, 40 tokens 53 / 54 / 14; 512 nodes 5 tokens 58 / 74 / 33; 1024 nodes 16 tokens 83 / 95 / 38, Gumbel noise of scale 3 118 /
+// 108 / 62, rows that fall by half a rank 1270 / 1210 / 94; 1000 nodes in 24 rows, 4 tokens 75 / 97 / 76; 1024 nodes of 50 ranks 40 tokens 102 / 115 / 31.
+// Returns N, or (uniform) -1: no bound (fewer finite prefixes among those above than the budget), or kNoRoom.
 // ------------------------------------------------------------------------------------------
 constexpr int kNoRoom = -2;
 constexpr int kRankBuckets = 1024;
@@ -1056,7 +1064,7 @@ __device__ __forceinline__ float lane_value(float v, int lane)
 }
 
 template <int NT>
-__device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, LevelMem L, int *s_bucket,
+__device__ __forceinline__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, unsigned char *mem, int bytes, int *s_bucket,
                                uint32_t *s_node, float *s_score)
 {
     constexpr int NW = NT / 64;
@@ -1065,13 +1073,20 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     int *const s_hist = s_bucket, *const s_pref = s_hist + kHistInts, *const s_cnt = s_pref + kHistInts;
     unsigned long long *const s_alloc = reinterpret_cast<unsigned long long *>(s_cnt + kRankBuckets);
     __shared__ int s_wave[NW];
-    uint32_t *const queue = reinterpret_cast<uint32_t *>(L.c_score);  // node | children's row << 13 | first rank << 19
-    uint16_t *const list = L.p_c;                                     // heads to walk
+    __shared__ __align__(16) float s_bound[NW];
+    // As many places as the bytes give: ten a member and four an entry of the queue, in which the members are put in order in
+    // the end.  (The queue of bushy trees takes half as many entries as there are members.)
+    const int places = min(bytes / 14 & ~1, 8192), queue_places = (bytes - 10 * places) / 4;
+    float *const m_score = reinterpret_cast<float *>(mem);
+    uint32_t *const m_info = reinterpret_cast<uint32_t *>(m_score + places);  // (parent member, rank, depth)
+    uint32_t *const queue = m_info + places;                                  // node | children's row << 13 | first rank << 19
+    uint16_t *const list = reinterpret_cast<uint16_t *>(queue + queue_places);  // heads to walk; in the end places, then node ids
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int cap = min(K, N);  // ranks that can matter
     // Nothing is written or counted under a branch (a wave alone on its SIMD pays some 55 cycles for one, a select 7):
     // each array has 64 places behind its room for the lanes that have nothing, and for what does not fit.
-    const int room = L.capm - 64, queue_room = L.capc - 64, list_room = 2 * L.capp - 64;
+    const int room = places - 64, queue_room = queue_places - 64;
+    const int ample = min(room, N <= 128 ? 8 * N + 960 : 4 * N + 448);
 
     // Every wave for itself: lane d holds the first rank of row d and the score of the chain's node at depth d + 1.
     const float lp0 = lane < B ? s_lp[lane * Kp] : -INFINITY;
@@ -1082,32 +1097,40 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     for (int k = 16; k < B; ++k) chain = __int_as_float(dpp_or_zero<0x138>(__float_as_int(chain))) + lp0;
     const float hi = lane_value(chain, 0);
     const float at_depth = __int_as_float(dpp_or_zero<0x138>(__float_as_int(chain)));  // lane i: the node at depth i
-    // The first bound: four lanes for each l.  (The scores are formed here in another order than along a path: at
-    // most 32 roundings of 2^-24 each way, well below the margin.)
+    // The first bound: a wave has two of the sixteen l, half a wave each, a lane a row.  (The scores are formed here in another
+    // order than along a path: at most 32 roundings of 2^-24 each way, well below the margin.)
     float lo;
     {
-        const int l = B > 16 ? max(1, 2 * (lane >> 2)) : (lane >> 2) + 1;
+        const int idx = 2 * wave + (lane >> 5), l = B > 16 ? max(1, 2 * idx) : idx + 1, i = lane & 31;
         const float at_l = __shfl(chain, l - 1, 64);
         const int R = (int)((float)(N - l) * __builtin_amdgcn_rcpf(0.5f * (float)(l * (l + 1))) * 1.0001f) + 1;
         const int r = l == 1 ? min(N - 1, K) : min(max(R, 0), K);  // (rank K: -inf)
-        float worst = 0.0f;
-        for (int i0 = lane & 3; i0 < B; i0 += 16) {
-            float x[4], y[4];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const float *const p = s_lp + min(i0 + 4 * k, B - 1) * Kp;
-                x[k] = p[r];
-                y[k] = p[0];
-            }
-#pragma unroll
-            for (int k = 0; k < 4; ++k) worst = fminf(worst, i0 + 4 * k < min(l, B) ? x[k] - y[k] : 0.0f);
-        }
+        const int r_all = min((int)(__builtin_amdgcn_exp2f(__builtin_amdgcn_logf((float)N) * __builtin_amdgcn_rcpf((float)l)) * 1.0001f), K);
+        const float *const p = s_lp + min(i, B - 1) * Kp;
+        const float x = p[r], y = p[0], z = p[r_all];
+        const bool in = i < min(l, B);
+        float worst = in ? x - y : 0.0f, all = in ? z : 0.0f;
         worst = fminf(worst, dpp_f<0xB1>(worst, worst));
+        all += dpp_f<0xB1>(all, all);
         worst = fminf(worst, dpp_f<0x4E>(worst, worst));
+        all += dpp_f<0x4E>(all, all);
+        worst = fminf(worst, dpp_f<0x141>(worst, worst));
+        all += dpp_f<0x141>(all, all);
+        worst = fminf(worst, dpp_f<0x140>(worst, worst));
+        all += dpp_f<0x140>(all, all);
+        worst = fminf(worst, dpp_f<0x142, 0xA>(worst, worst));
+        all += __int_as_float(dpp_or_zero<0x142, 0xA>(__float_as_int(all)));  // (valid in the last lane of each half)
         const float at = at_l + worst;
-        const float exact = s_lp[min(N - 1, K)];
-        lo = l == 1 && r == N - 1 ? exact : at - 1e-5f * fabsf(at);
-        lo = wave_max_f32(l <= B && at_l > kLvNeg && worst > kLvNeg ? lo : -INFINITY);
+        float b = l == 1 && r == N - 1 ? s_lp[min(N - 1, K)] : at - 1e-5f * fabsf(at);
+        b = at_l > kLvNeg && worst > kLvNeg ? b : -INFINITY;
+        b = fmaxf(b, all - 1e-5f * fabsf(all));
+        b = l <= B ? b : -INFINITY;
+        const float best = fmaxf(lane_value(b, 31), lane_value(b, 63));
+        if (lane == 0) s_bound[wave] = best;
+        __syncthreads();
+        lo = s_bound[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) lo = fmaxf(lo, s_bound[w]);
     }
     if (!(lo > kLvNeg)) return -1;
     const float width = (hi - lo) * (1.0f / ((float)kLvBuckets - 0.5f)), inv = ((float)kLvBuckets - 0.5f) / fmaxf(hi - lo, 1e-30f);
@@ -1133,8 +1156,8 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     if (wave == NW - 1) {
         count(at_depth, lane > 0 && lane <= B && at_depth >= lo);
         const int m = lane <= B ? lane : room + lane;
-        L.m_score[m] = at_depth;
-        L.m_info[m] = pack_member(max(lane - 1, 0), 0, lane & 63);
+        m_score[m] = at_depth;
+        m_info[m] = pack_member(max(lane - 1, 0), 0, lane & 63);
     }
     // heads off the chain, 16 lanes a row
     for (int i0 = 4 * wave; i0 < B; i0 += 4 * NW) {
@@ -1198,21 +1221,23 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
         Q += field(got, 1);
         W += field(got, 2);
         ++phase;
-        return M <= room && Q <= queue_room && W <= list_room;
+        return M <= room && Q <= queue_room;  // (W <= M)
     };
 
     float s = lo;
     if (!next_phase()) return kNoRoom;
-    for (int q_done = 0; q_done < Q;) {  // (uniform, like everything that M, Q and W decide)
+    const int chain_entries = Q;
+    int counted = 0;  // phases (two a turn) whose finds the histogram holds
+    for (int turn = 0, q_done = 0; q_done < Q; ++turn) {  // (uniform, like everything that M, Q and W decide)
         // ---- the nodes of the queue: their children of ranks first .. first + 63 ----
-        const bool first_turn = q_done == 0;
         const int q_end = Q;
+        W = 0;
         s = cut();
         for (int q0 = q_done + 4 * wave; q0 < q_end; q0 += 4 * NW) {
             const int at = q0 + (lane >> 4);
             const uint32_t entry = queue[min(at, q_end - 1)];
             const int id = (int)(entry & 0x1FFFu), row = (int)((entry >> 13) & 63u), first = (int)(entry >> 19);
-            const float S = L.m_score[id];
+            const float S = m_score[id];
             const float *const rowp = s_lp + row * Kp;
             const float *const next = s_lp + (row + 1) * Kp;  // (row B: -inf)
             float v[4];
@@ -1242,18 +1267,18 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
             }
             const uint32_t info = pack_member(id, first + (lane & 15), row + 1);
             // (counted before the first turn: heads off the chain of ranks up to 64, and all of the root's)
-            const bool fresh = !first_turn || (first > 64 && id > 0);
+            const bool fresh = 2 * turn >= counted && (turn > 0 || (first > 64 && id > 0));
             const bool any_fresh = __builtin_amdgcn_ballot_w64(fresh) != 0ull;
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 if (on[u] == 0ull) break;
                 const int m = m_at + below(on[u]), place = v[u] >= s ? min(m, room) : room + lane;
-                L.m_score[place] = v[u];
-                L.m_info[place] = info + ((uint32_t)(16 * u) << 13);
+                m_score[place] = v[u];
+                m_info[place] = info + ((uint32_t)(16 * u) << 13);
                 if (any_fresh) count(v[u], fresh && v[u] >= s);
                 const unsigned long long walk = __builtin_amdgcn_ballot_w64(v[u] + next0 >= s);
                 if (walk != 0ull) {
-                    list[v[u] + next0 >= s ? min(w_at + below(walk), list_room) : list_room + lane] = (uint16_t)m;
+                    list[v[u] + next0 >= s ? min(w_at + below(walk), room) : room + lane] = (uint16_t)m;
                     w_at += __builtin_popcountll(walk);
                     const unsigned long long kid = __builtin_amdgcn_ballot_w64(v[u] + next1 >= s);  // (these have a continuation too)
                     if (kid != 0ull) {
@@ -1264,82 +1289,95 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
                 m_at += __builtin_popcountll(on[u]);
             }
         }
-        q_done = q_end;
-        const int w_first = W;
-        if (!next_phase()) return kNoRoom;
-        const int w_end = W;
-        if (w_first == w_end) continue;
-        // ---- the listed heads, a lane each: their continuations, up to 16 nodes at a time in registers.  In the first
-        //      turn, whose cut is the loosest, they are counted before any is kept, unless there is room for all of
-        //      them whatever the cut (rows peaked at 0.9, launch to launch: 64 nodes 12.1 us with the count, 11.2 without, 128
-        //      12.8 and 12.1; hence the room that budgets up to 128 have) ----
-        const bool count_first = first_turn && M + (w_end - w_first) * (B - 1) > room;
-        for (int keep = count_first ? 0 : 1; keep < 2; ++keep) {
-            s = cut();
-            for (int w0 = w_first + 64 * wave; w0 < w_end; w0 += NT) {
-                int id = list[min(w0 + lane, w_end - 1)];
-                float S = L.m_score[id];
-                int depth = member_depth(L.m_info[id]);  // (of the node in front)
-                S = w0 + lane < w_end ? S : -INFINITY;
-                for (;;) {
-                    // rows depth .. depth + 16: the step to the next node, and that node's first child of rank >= 1
-                    // is in the row after
-                    float v[16], kid[17];
+        bool fits = next_phase();
+        int found = 2 * turn + 1;
+        if (fits && W > 0) {
+            // ---- the listed heads, a lane each: their continuations, up to 16 nodes at a time in registers.  Where there may
+            //      be no room for all of them they are counted before any is kept, which raises the cut ----
+            const bool count_first = found >= counted && M + W * (B - 1) > (turn == 0 ? ample : room), count_now = found >= counted && !count_first;
+            for (int keep = count_first ? 0 : 1; keep < 2; ++keep) {
+                s = cut();
+                for (int w0 = 64 * wave; w0 < W; w0 += NT) {
+                    int id = list[min(w0 + lane, W - 1)];
+                    float S = m_score[id];
+                    int depth = member_depth(m_info[id]);  // (of the node in front)
+                    S = w0 + lane < W ? S : -INFINITY;
+                    for (;;) {
+                        // rows depth .. depth + 16: the step to the next node, and that node's first child of rank >= 1
+                        // is in the row after
+                        float v[16], kid[17];
 #pragma unroll
-                    for (int k = 0; k < 17; ++k) {
-                        const float *const p = s_lp + __mul24(min(depth + k, B), Kp);  // (row B: -inf)
-                        if (k < 16) v[k] = p[0];
-                        kid[k] = p[1];
+                        for (int k = 0; k < 17; ++k) {
+                            const float *const p = s_lp + __mul24(min(depth + k, B), Kp);  // (row B: -inf)
+                            if (k < 16) v[k] = p[0];
+                            kid[k] = p[1];
+                        }
+                        v[0] += S;
+#pragma unroll
+                        for (int k = 1; k < 16; ++k) v[k] += v[k - 1];
+                        if (keep == 0) {
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) {
+                                if (k % 4 == 0 && __builtin_amdgcn_ballot_w64(v[k] >= s) == 0ull) break;
+                                count(v[k], v[k] >= s);
+                            }
+                        } else {
+                            int len = 0;
+                            uint32_t kids = 0u;  // bit k: the k-th node has a child of rank >= 1
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) {
+                                len += v[k] >= s ? 1 : 0;
+                                kids |= v[k] + kid[k + 1] >= s ? 1u << k : 0u;
+                            }
+                            const int both = len | (__builtin_popcount(kids) << 16), incl = wave_scan_inclusive_i32(both);
+                            const int total = __builtin_amdgcn_readlane(incl, 63);
+                            if (total == 0) break;
+                            const unsigned long long got = take(total & 0xFFFF, total >> 16, 0);
+                            const int m_at = M + field(got, 0) + ((incl - both) & 0xFFFF);
+                            int q_at = Q + field(got, 1) + ((incl - both) >> 16);
+                            uint32_t info = pack_member(id, 0, depth + 1);
+#pragma unroll
+                            for (int k = 0; k < 16; ++k) {
+                                if (k % 4 == 0 && __builtin_amdgcn_ballot_w64(k < len) == 0ull) break;
+                                const int place = k < len ? min(m_at + k, room) : room + lane;
+                                m_score[place] = v[k];
+                                m_info[place] = info;
+                                info = pack_member(m_at + k, 0, depth + k + 2);
+                                if (count_now) count(v[k], k < len);
+                            }
+                            while (__builtin_amdgcn_ballot_w64(kids != 0u) != 0ull) {
+                                const int k = __builtin_ctz(kids | 0x10000u);
+                                put_entry(kids != 0u, q_at, m_at + k, depth + k + 1, 1);
+                                q_at += 1;
+                                kids &= kids - 1u;
+                            }
+                            id = m_at + 15;
+                        }
+                        // more than 16 nodes: from the last one on
+                        S = v[15] >= s ? v[15] : -INFINITY;
+                        depth += 16;
+                        if (__builtin_amdgcn_ballot_w64(S >= s && depth < B) == 0ull) break;
                     }
-                    v[0] += S;
-#pragma unroll
-                    for (int k = 1; k < 16; ++k) v[k] += v[k - 1];
-                    if (keep == 0) {
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) {
-                            if (k % 4 == 0 && __builtin_amdgcn_ballot_w64(v[k] >= s) == 0ull) break;
-                            count(v[k], v[k] >= s);
-                        }
-                    } else {
-                        int len = 0;
-                        uint32_t kids = 0u;  // bit k: the k-th node has a child of rank >= 1
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) {
-                            len += v[k] >= s ? 1 : 0;
-                            kids |= v[k] + kid[k + 1] >= s ? 1u << k : 0u;
-                        }
-                        const int both = len | (__builtin_popcount(kids) << 16), incl = wave_scan_inclusive_i32(both);
-                        const int total = __builtin_amdgcn_readlane(incl, 63);
-                        if (total == 0) break;
-                        const unsigned long long got = take(total & 0xFFFF, total >> 16, 0);
-                        const int m_at = M + field(got, 0) + ((incl - both) & 0xFFFF);
-                        int q_at = Q + field(got, 1) + ((incl - both) >> 16);
-                        uint32_t info = pack_member(id, 0, depth + 1);
-#pragma unroll
-                        for (int k = 0; k < 16; ++k) {
-                            if (k % 4 == 0 && __builtin_amdgcn_ballot_w64(k < len) == 0ull) break;
-                            const int place = k < len ? min(m_at + k, room) : room + lane;
-                            L.m_score[place] = v[k];
-                            L.m_info[place] = info;
-                            info = pack_member(m_at + k, 0, depth + k + 2);
-                            if (!count_first) count(v[k], k < len);
-                        }
-                        while (__builtin_amdgcn_ballot_w64(kids != 0u) != 0ull) {
-                            const int k = __builtin_ctz(kids | 0x10000u);
-                            put_entry(kids != 0u, q_at, m_at + k, depth + k + 1, 1);
-                            q_at += 1;
-                            kids &= kids - 1u;
-                        }
-                        id = m_at + 15;
-                    }
-                    // more than 16 nodes: from the last one on
-                    S = v[15] >= s ? v[15] : -INFINITY;
-                    depth += 16;
-                    if (__builtin_amdgcn_ballot_w64(S >= s && depth < B) == 0ull) break;
                 }
+                fits = next_phase();
             }
-            if (!next_phase()) return kNoRoom;
+            found += 1;
         }
+        if (fits) {
+            q_done = q_end;
+            continue;
+        }
+        // Out of room: the histogram now holds what was found, and everything starts over with the higher cut that this
+        // gives.  (Not where the phase has been counted before, or where the prefixes known up to the cut's
+        // bucket, many equal ones, are more than there are places.)
+        if (found <= counted) return kNoRoom;
+        counted = found;
+        s = cut();
+        const int k0 = known_before + known.x, k1 = k0 + known.y, k2 = k1 + known.z, k3 = k2 + known.w;
+        const unsigned long long reached = __builtin_amdgcn_ballot_w64(k3 >= N);
+        const int up_to = k0 >= N ? k0 : k1 >= N ? k1 : k2 >= N ? k2 : k3;
+        if (reached != 0ull && __builtin_amdgcn_readlane(up_to, __builtin_ctzll(reached)) > room) return kNoRoom;
+        turn = -1, q_done = 0, M = B + 1, Q = chain_entries;
     }
 
     // ---- exact order of the members that reach the cut ----
@@ -1360,12 +1398,12 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     const float shrink = fminf(1.0f, (float)kRankBuckets / fmaxf(place_of(s), 1.0f));
     auto fine = [&](float v) { return min((int)(place_of(v) * shrink), kRankBuckets - 1); };
     unsigned long long *const sorted = reinterpret_cast<unsigned long long *>(  // score << 32 | bucket << 13 | member
-        L.c_score + ((B * Kp) & 1));  // (on 8 bytes: what lies in front of it is even but for the table)
-    const int sorted_room = L.capc - 1;
-    uint16_t *const node_id = L.p_c;
+        queue + ((B * Kp) & 1));  // (on 8 bytes: what lies in front of it is even but for the table)
+    const int sorted_room = queue_places / 2 - 1;
+    uint16_t *const node_id = list;
     for (int m = 1 + tid; m < M; m += NT) {
-        const float v = L.m_score[m];
-        if (v >= s) L.m_jlo[m] = (uint16_t)atomicAdd(&s_cnt[fine(v)], 1);
+        const float v = m_score[m];
+        if (v >= s) list[m] = (uint16_t)atomicAdd(&s_cnt[fine(v)], 1);
     }
     __syncthreads();
     int alive = 0;
@@ -1393,10 +1431,10 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     if (alive > sorted_room) return kNoRoom;
     __syncthreads();
     for (int m = 1 + tid; m < M; m += NT) {
-        const float v = L.m_score[m];
+        const float v = m_score[m];
         if (v >= s) {
             const int f = fine(v);
-            sorted[(s_cnt[f] >> 16) + L.m_jlo[m]] =
+            sorted[(s_cnt[f] >> 16) + list[m]] =
                 ((unsigned long long)__float_as_uint(v) << 32) | (unsigned long long)(unsigned)(f << 13 | m);
         }
     }
@@ -1417,7 +1455,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
                     const float so = __uint_as_float((uint32_t)(o[k] >> 32));
                     const bool other = j0 + k < n && o[k] != mine;
                     place += other && so > v ? 1 : 0;
-                    if (other && so == v) place += member_before(L.m_score, L.m_info, (int)(o[k] & 0x1FFFull), m) ? 1 : 0;
+                    if (other && so == v) place += member_before(m_score, m_info, (int)(o[k] & 0x1FFFull), m) ? 1 : 0;
                 }
             }
         }
@@ -1427,7 +1465,7 @@ __device__ int deviation_build(const float *s_lp, int Kp, int B, int K, int N, L
     for (int e = tid; e < alive; e += NT) {
         const unsigned long long mine = sorted[e];
         const int m = (int)(mine & 0x1FFFull), id = node_id[m];
-        const uint32_t info = L.m_info[m];
+        const uint32_t info = m_info[m];
         const int pm = member_parent(info), up = node_id[pm];
         if (id == 0) continue;
         s_node[id] = pack_node(pm == 0 ? 0 : up, member_rank(info), member_depth(info));
@@ -1518,13 +1556,14 @@ __device__ __forceinline__ int pops_of_one_slot(const float *s_lp, int Kp, int B
 }
 
 constexpr int kBuildThreads = 512;
+// (Arguments in the order in which they are wanted: the first 14 words are in registers when the kernel starts, the others
+// are a load.)
 template <int NSLOT>
 __global__ __launch_bounds__(kBuildThreads) void build_kernel(
-    const int32_t *__restrict__ topk_tok, const float *__restrict__ topk_lp, int B, int K, int N,
-    const int32_t *__restrict__ root_token, int32_t *__restrict__ tokens,
-    int32_t *__restrict__ parent, int32_t *__restrict__ depth, int32_t *__restrict__ rank,
-    float *__restrict__ node_score, uint64_t *__restrict__ ancestor_mask,
-    int32_t *__restrict__ n_nodes, int algo, int capm, int capp, int capc, int mask_off, int mask_rows)
+    const float *__restrict__ topk_lp, int B, int K, int N, int algo, int capm, int capp, int capc, int mask_off, int mask_rows,
+    const int32_t *__restrict__ topk_tok, const int32_t *__restrict__ root_token, int32_t *__restrict__ tokens,
+    int32_t *__restrict__ parent, int32_t *__restrict__ depth, int32_t *__restrict__ rank, float *__restrict__ node_score,
+    uint64_t *__restrict__ ancestor_mask, int32_t *__restrict__ n_nodes)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int NT = kBuildThreads;
@@ -1657,7 +1696,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
     int level_n = -1;
     if (use_levels) {
         if (algo == DDTREE_BUILD_AUTO) {
-            level_n = deviation_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
+            level_n = deviation_build<NT>(s_lp, Kp, B, K, N, reinterpret_cast<unsigned char *>(lv.m_score), 10 * capm + 4 * capp + 8 * capc, s_bucket, s_node, s_score);
             if (level_n < 0) {
                 if (level_n == kNoRoom && tid == 0) atomicAdd(&g_handovers, 1u);
                 __syncthreads();  // (the histograms are reused)
@@ -1893,8 +1932,8 @@ static size_t build_lds_bytes(int B, int K, int N)
 }
 
 // Dynamic LDS of the kernel and the capacities of the level-synchronous construction (members,
-// candidates per level).  capm = 0: no room,
-// sequential pops only.
+// candidates per level); the construction by deviations lays its own arrays over the same bytes.
+// capm = 0: no room, sequential pops only.
 struct BuildLds {
     size_t bytes;
     int capm, capp, capc;
@@ -1963,8 +2002,8 @@ static int launch_build(const int32_t *topk_tok, const float *topk_lp, int batch
     if (!allow_dynamic_lds(reinterpret_cast<const void *>(build_kernel<NSLOT>), 150 * 1024, lds_allowed))
         return DDTREE_ERR_HIP;
     DDT_LAUNCH(DDTREE_KERNEL_BUILD, st, (build_kernel<NSLOT>), dim3(batch), dim3(kBuildThreads), lds.bytes,
-                       st, topk_tok, topk_lp, B, K, N, root_token, tokens, parent, depth, rank,
-                       node_score, ancestor_mask, n_nodes, algo, lds.capm, lds.capp, lds.capc, lds.mask_off, lds.mask_rows);
+                       st, topk_lp, B, K, N, algo, lds.capm, lds.capp, lds.capc, lds.mask_off, lds.mask_rows,
+                       topk_tok, root_token, tokens, parent, depth, rank, node_score, ancestor_mask, n_nodes);
     return launch_status();
 }
 

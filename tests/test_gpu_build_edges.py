@@ -110,3 +110,36 @@ def test_forced_levels_run_alone():
             assert np.array_equal(g["parent"][0], o["parent"]) and np.array_equal(g["rank"][0], o["rank"]), algo
     finally:
         dd.set_build_algorithm(dd.BUILD_AUTO)
+
+
+# Rows without equal scores whose trees are bushy: a few plausible tokens a row (few), none that stands out (gumbel, normal),
+# falling by a factor (geometric, zipf), all but some masked.  The construction by deviations finds several
+# times as many prefixes as the tree has nodes on the way, and has to have room for them.
+@pytest.mark.parametrize("kind", ["few5", "few16", "few40", "gumbel3", "normal6", "geometric", "zipf2", "masked4", "masked16"])
+@pytest.mark.parametrize("N,B,K", [(256, 8, 256), (256, 16, 256), (512, 16, 512), (512, 32, 512), (1024, 8, 1024), (1024, 16, 1024),
+                                   (700, 24, 700), (1000, 24, 1000), (256, 16, 50), (1024, 16, 200)])
+def test_bushy_trees_fit(kind, N, B, K):
+    rng = np.random.default_rng(N + B + K)
+    V, number = 8192, float("".join(c for c in kind if c.isdigit()) or 0)
+    x = rng.standard_normal((B, V))
+    if kind.startswith("few"):
+        x[:, :int(number)] += 14.0
+    elif kind.startswith("gumbel"):
+        x = number * rng.gumbel(size=(B, V))
+    elif kind.startswith("normal"):
+        x *= number
+    elif kind == "geometric":
+        x = np.log(0.6) * np.arange(V) + 0.05 * x
+    elif kind.startswith("zipf"):
+        x = 0.3 * x - number * np.log(1.0 + np.arange(V))
+    else:
+        x[:, int(number):] -= 100.0
+    tok, lp = oracle.topk(x.astype(np.float32), K)
+    o = oracle.build_tree(tok, lp, N, 5)
+    before, given_up = dd.build_handovers(), dd.build_giveups()
+    g = gu.gpu_build(tok, lp, N, 5)
+    assert dd.build_handovers() == before and dd.build_giveups() == given_up
+    for key in ("tokens", "parent", "depth", "rank"):
+        assert np.array_equal(g[key][0], o[key]), key
+    assert np.array_equal(g["node_score"][0].view(np.uint32), o["score"].view(np.uint32))
+    assert np.array_equal(g["ancestor_mask"][0], oracle.ancestor_mask(o["parent"], o["n_nodes"], T=N + 1))
