@@ -1051,6 +1051,11 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 // Returns N, or (uniform) -1: no bound (fewer finite prefixes among those above than the budget), or kNoRoom.
 // ------------------------------------------------------------------------------------------
 constexpr int kNoRoom = -2;
+// Up to so many nodes a table whose members do not fit goes to the pops at once: with ten times as many places as nodes
+// only equal scores get there, among which the pops choose in a time that goes with the nodes squared, the others with
+// their own number squared.  (64 nodes, 8 rows of 50 ranks of one value: pops 180 us, levels and then pops 207; of two values: pops
+// 117, deviations or levels 545.  128 nodes, two values: pops 268, deviations 76; hence six members a node.)
+constexpr int kTiedPops = 128;
 constexpr int kRankBuckets = 1024;
 constexpr int kHistInts = kLvBuckets + 64;  // (and a word for each lane with nothing to count)
 // histogram, its prefix sums, ranking buckets, four 64-bit counters and one for each lane but the first
@@ -1399,7 +1404,7 @@ __device__ __forceinline__ int deviation_build(const float *s_lp, int Kp, int B,
     auto fine = [&](float v) { return min((int)(place_of(v) * shrink), kRankBuckets - 1); };
     unsigned long long *const sorted = reinterpret_cast<unsigned long long *>(  // score << 32 | bucket << 13 | member
         queue + ((B * Kp) & 1));  // (on 8 bytes: what lies in front of it is even but for the table)
-    const int sorted_room = queue_places / 2 - 1;
+    const int sorted_room = min(queue_places / 2 - 1, N <= kTiedPops ? 6 * N : 8192);
     uint16_t *const node_id = list;
     for (int m = 1 + tid; m < M; m += NT) {
         const float v = m_score[m];
@@ -1696,16 +1701,15 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
     int level_n = -1;
     if (use_levels) {
         if (algo == DDTREE_BUILD_AUTO) {
-            level_n = deviation_build<NT>(s_lp, Kp, B, K, N, reinterpret_cast<unsigned char *>(lv.m_score), 10 * capm + 4 * capp + 8 * capc, s_bucket, s_node, s_score);
-            if (level_n < 0) {
-                if (level_n == kNoRoom && tid == 0) atomicAdd(&g_handovers, 1u);
-                __syncthreads();  // (the histograms are reused)
-            }
+            level_n = deviation_build<NT>(s_lp, Kp, B, K, N, reinterpret_cast<unsigned char *>(lv.m_score),
+                                          10 * capm + 4 * capp + 8 * capc, s_bucket, s_node, s_score);
+            if (level_n < 0) __syncthreads();  // (the histograms are reused)
         }
-        if (level_n < 0) {
+        if (level_n < 0 && (level_n != kNoRoom || N > kTiedPops)) {
+            if (level_n == kNoRoom && tid == 0) atomicAdd(&g_handovers, 1u);
             level_n = level_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
+            if (level_n < 0 && tid == 0) atomicAdd(&g_level_giveups, 1u);
         }
-        if (level_n < 0 && tid == 0) atomicAdd(&g_level_giveups, 1u);
     }
     if (level_n >= 0) {
         if (tid == 0) s_built = level_n;

@@ -97,7 +97,7 @@ def test_deviations(kind, N, B, K):
 def test_forced_levels_run_alone():
     """Rows of equal values: more prefixes share the last score of the tree than the construction by deviations has room
     for, so that it hands the sequence over.  Forced levels do not try it first."""
-    B, K, N = 8, 50, 64
+    B, K, N = 8, 50, 256
     lp = np.full((B, K), np.float32(-np.log(K)))
     tok = np.tile(np.arange(K, dtype=np.int32), (B, 1))
     o = oracle.build_tree(tok, lp, N, 5)
@@ -143,3 +143,16 @@ def test_bushy_trees_fit(kind, N, B, K):
         assert np.array_equal(g[key][0], o[key]), key
     assert np.array_equal(g["node_score"][0].view(np.uint32), o["score"].view(np.uint32))
     assert np.array_equal(g["ancestor_mask"][0], oracle.ancestor_mask(o["parent"], o["n_nodes"], T=N + 1))
+
+
+# equal values: 1 to 4 distinct ones a row, budgets whose members do not fit (they go to the pops, not to the levels and then the
+# pops) and others
+@pytest.mark.parametrize("values", [1, 2, 4])
+@pytest.mark.parametrize("N,B,K", [(28, 4, 20), (64, 8, 50), (64, 8, 7), (100, 16, 60), (128, 5, 40)])
+def test_small_budgets_of_equal_scores(values, N, B, K):
+    rng = np.random.default_rng(N + K + values)
+    lp = -np.sort(rng.integers(0, values, (B, K)), axis=1).astype(np.float32) / 4 - 1
+    tok = rng.integers(0, 5000, (B, K)).astype(np.int32)
+    before = dd.build_handovers()
+    _check(tok, lp, N)
+    assert dd.build_handovers() == before
