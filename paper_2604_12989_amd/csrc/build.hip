@@ -1671,12 +1671,14 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
 
     // Which construction.  A pop that alternates between parents is a step of its own (0.3 us, and it ends a run), a run
     // of siblings pops as one: flat rows, whose tree is a star or nearly.  The construction by deviations takes about
-    // the same time whatever the rows are.  Below 28 nodes pops always win; up to 256 they do where hardly any node of
-    // depth 2 (of ranks 0 .. 3 counted, an upper bound) reaches the worst useful rank of row 0.
+    // the same time whatever the rows are.  Pops up to 256 nodes where hardly any node of depth 2 (of ranks 0 .. 3 counted, an
+    // upper bound) reaches the worst useful rank of row 0; below 48 also where the top-1 chain's third node (below 36, where
+    // a pop costs less of the whole, its fourth) does not; below 28 always: what either way gains there depends on the rows.
     // All constructions give the same tree; algo 1 / 2 force the pops / the levels.
-    // (Launch to launch, pops / deviations, us.  Rows peaked at 0.7: 16 nodes 8.9 / 10.3, 20 10.3 / 10.8, 24 11.5 / 10.9, 32
-    // 14.0 / 11.2, 64 33.7 / 11.5.  Stars: 32 nodes 5.0 / 8.2, 64 5.3 / 8.4, 128 6.0 / 8.7, 256 8.0 / 9.2; with two nodes of depth 2: 40
-    // 6.9 / 8.4, 128 9.2 / 8.7; with four: 32 7.6 / 10.5, 64 11.2 / 8.5, 256 14.9 / 11.5.)
+    // (Launch to launch, pops / deviations, us.  Over 29 kinds of rows near a star: 24 nodes 6.4 / 8.1, with this rule 6.3, 28
+    // 7.2 / 8.5, 6.9, 36 8.4 / 8.9, 7.4, 47 10.4 / 9.1, 8.0.  Rows peaked at 0.7: 24 nodes 11.5 / 9.2, 32 14.0 / 9.2, 64 33.7 / 9.9;
+    // rows falling by 0.9 a rank: 28 nodes 6.1 / 9.9, 40 8.2 / 9.9, 47 11.6 / 10.0.  Stars: 32 nodes 4.5 / 7.3, 64 4.4 / 7.5, 128 5.2 / 8, 256
+    // 7.2 / 8.5; with two nodes of depth 2: 40 5.9 / 8.8, 100 7.8 / 9.3; with four: 32 7.0 / 8.8, 64 9.1 / 9.1.)
     bool use_levels = may_use_set;
     if (use_levels && algo == DDTREE_BUILD_AUTO && N <= 256) {
         int below_star = 0, limit = 4;
@@ -1694,6 +1696,14 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
 #pragma unroll
                 for (int j = 1; j < 4; ++j)
                     below_star += __builtin_popcountll(__builtin_amdgcn_ballot_w64(lane <= last && S + first[j] >= worst));
+            }
+            // (below 48 nodes runs of siblings at depth 2 are few steps too: pops unless the top-1 chain goes deeper)
+            if (N < 48) {
+                const float third = s_lp[min(2, B) * Kp], fourth = s_lp[min(3, B) * Kp];
+                float chain = s_lp[0] + s_lp[Kp];
+                chain += B > 2 ? third : 0.0f;
+                chain += B > 3 && N < 36 ? fourth : 0.0f;
+                if (chain < worst) below_star = 0;
             }
         }
         use_levels = below_star > limit || K < N;

@@ -1,6 +1,6 @@
-"""Tree construction where its variants meet: budgets whose frontier just fits one wave (63 nodes), the budgets at
-which pops give way to levels (36) and 256 threads to 512 (320), with tied scores, sibling runs, fewer
-ranks than budget and the most rows.  Bit for bit against the oracle, under every construction."""
+"""Tree construction where its variants meet: budgets whose frontier just fits one wave (63 nodes), the budgets and the
+near-stars at which pops give way to the construction by deviations (28 to 257 nodes), with tied scores, sibling runs, fewer
+ranks than budget and the most rows.  Bit for bit against the oracle, by the automatic choice, the pops and the levels."""
 import numpy as np
 import pytest
 
@@ -156,3 +156,20 @@ def test_small_budgets_of_equal_scores(values, N, B, K):
     before = dd.build_handovers()
     _check(tok, lp, N)
     assert dd.build_handovers() == before
+
+
+# exactly `below` prefixes of depth 2 reach the worst useful rank of row 0, where the choice between pops and deviations lies;
+# the top-1 chain reaches it to its second node, or to its last
+@pytest.mark.parametrize("chain", ["short", "long"])
+@pytest.mark.parametrize("below", [0, 2, 3, 4, 5])
+@pytest.mark.parametrize("N", [27, 28, 35, 36, 47, 48, 99, 100, 128, 129, 256, 257])
+def test_choice_between_pops_and_deviations(N, below, chain):
+    B, K, rng = 5, N, np.random.default_rng(N + below)
+    r = np.arange(K)
+    lp = np.empty((B, K))
+    lp[0] = -1.0 - 0.01 * r
+    lp[1] = -0.01 * (N - below) + 0.004 - 9.0 * (r > 0) - 0.001 * r
+    lp[2:] = (-1e-4 if chain == "long" else -9.0) - 9.0 * (r > 0) - 0.001 * r - 1e-5 * rng.random((B - 2, K))
+    lp = lp.astype(np.float32)
+    assert ((lp[0][:, None] + lp[1][None, :4]) >= lp[0][-1]).sum() == below
+    _check(rng.integers(0, 5000, (B, K)).astype(np.int32), lp, N)
