@@ -118,7 +118,7 @@ int ddtree_topk(const float *logits, int batch, int B, int V, int K, int32_t *to
  * A prefix of score -inf (it contains a token of probability zero; the paper assumes
  * probabilities in (0,1)) never becomes a node: n_nodes counts prefixes of finite score only.
  * Requires 1 <= N <= DDTREE_MAX_N, 1 <= K <= DDTREE_MAX_N, 1 <= B <= DDTREE_MAX_B (the
- * log-probability table and the node records, 4 B (K + 3) + 8 (N + 1) bytes, then fit the
+ * log-probability table and the node records, at most 4 B (K + 4) + 16 + 8 (N + 1) bytes, then fit the
  * workgroup's LDS); anything else returns DDTREE_ERR_ARG.
  */
 int ddtree_build(const int32_t *topk_tok, const float *topk_lp, int batch, int B, int K, int N,
@@ -253,11 +253,13 @@ int ddtree_compact(const void *k_tree, const void *v_tree, const int32_t *path,
  * Construction used by ddtree_build (Algorithm 1 defines the result; all constructions produce
  * it bit for bit).  DDTREE_BUILD_POPS runs the best-first pops one after the other on one
  * wavefront; DDTREE_BUILD_LEVELS finds the same N best prefixes (Proposition 2) as a set, depth by
- * depth, orders them, and falls back to the pops when heavy score ties defeat its bounds;
+ * depth, orders them, and falls back to the pops where its bounds or its room do not do (heavy
+ * score ties, rows with many plausible tokens at the largest budgets);
  * DDTREE_BUILD_AUTO (the default) picks per sequence from the budget and the shape of the
  * log-probabilities: the pops, or the same set found by the number of non-zero ranks in a prefix,
- * and where that has no bound or no room the levels.  Process-wide, takes effect at the next ddtree_build call; meant for
- * tests and tuning.  Returns DDTREE_ERR_ARG for any other value.
+ * and where heavy ties leave that no room the levels (up to 128 nodes the pops).  Process-wide,
+ * takes effect at the next ddtree_build call; meant for tests and tuning.  Returns DDTREE_ERR_ARG
+ * for any other value.
  */
 #define DDTREE_BUILD_AUTO 0
 #define DDTREE_BUILD_POPS 1
@@ -283,7 +285,7 @@ int ddtree_selftest_host(void);
  */
 int ddtree_build_giveups(unsigned int *count);
 /* The same for sequences whose prefixes the construction by the number of non-zero ranks
- * (DDTREE_BUILD_AUTO) had no room for, so that the levels built the tree. */
+ * (DDTREE_BUILD_AUTO) had no room for, so that the levels were run. */
 int ddtree_build_handovers(unsigned int *count);
 
 /*

@@ -320,7 +320,7 @@ def selftest_host():
 
 
 def build_giveups():
-    """Sequences (since load) that the level-synchronous construction handed back to the pops."""
+    """Sequences (since load) that the levels handed to the pops."""
     n = ctypes.c_uint(0)
     _check(load().ddtree_build_giveups(ctypes.byref(n)), "ddtree_build_giveups")
     return int(n.value)

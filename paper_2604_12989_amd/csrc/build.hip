@@ -93,10 +93,10 @@ __device__ bool tuple_before(const uint32_t *s_node, int pa, int ra, int pb, int
 //   * levels with at most 64 parents are run by one wave without barriers (see wave_levels); a
 //     level whose candidates do not fit their arrays is counted by bucket first, the cut moves,
 //     and its children are counted again.
-// It serves what the construction by deviations below does not: fewer ranks than budget, and more members
-// than that one has room for.
-// Giving up (a cut that cannot be proven, or a capacity that heavy ties exceed) returns -1 and
-// the caller runs the sequential pops instead.
+// It serves what the construction by deviations below does not: more than 128 nodes among so many equal scores that its
+// members do not fit, and tables that give it no bound.
+// Giving up (a cut that cannot be proven, or a capacity that heavy ties, or bushy rows at budgets near 1024, exceed)
+// returns -1 and the caller runs the sequential pops instead.
 // ------------------------------------------------------------------------------------------
 __device__ unsigned int g_level_giveups;  // sequences the level construction handed to the pops
 __device__ unsigned int g_handovers;      // sequences the construction by deviations had no room for
@@ -291,7 +291,7 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
     // candidate counts when it is found, rank 0 included, and no continuation is walked.
     const float chain3 = B >= 3 ? (s_lp[0] + s_lp[Kp]) + s_lp[2 * Kp] : -INFINITY;
     const bool walks = chain3 > kLvNeg && bucket_of(chain3) < kLvBuckets;
-    // ranks 1 .. seed_ranks off the chain are entered: 16 up to N = 256, N/16 beyond (at most 64)
+    // ranks 1 .. seed_ranks off the chain are entered: 32 up to N = 256, N/8 beyond (at most 64)
     const int seed_ranks = min(kLvSeedRanksMax, max(32, N >> 3));
     if (walks) {
         // scores of the chain's nodes, summed in path order by one thread (the row maxima fetched

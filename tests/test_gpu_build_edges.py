@@ -69,10 +69,12 @@ def _check(tok, lp, N):
 
 
 # wide: nodes off the chain with more than 64 children in the tree; long: continuations of more than 16 nodes; mixed: one
-# flat row among peaked ones; twins: equal rows, so that many prefixes have equal scores; masked: ranks of -1e9 and -inf
+# flat row among peaked ones; twins: equal rows, so that many prefixes have equal scores; masked: ranks of -1e9 and -inf.
+# From 28 nodes on the automatic choice builds them by deviations and hands none over, but for 1023 x 24 x 1023, whose table
+# leaves no room for anything but pops, and near-stars.
 @pytest.mark.parametrize("kind", ["wide", "long", "mixed", "twins", "masked"])
 @pytest.mark.parametrize("N,B,K", [(23, 16, 23), (24, 16, 24), (63, 32, 63), (64, 32, 64), (65, 2, 65), (66, 16, 66), (129, 17, 129),
-                                   (255, 32, 255), (512, 31, 512), (513, 16, 513), (1023, 24, 1023), (1024, 32, 700)])
+                                   (255, 32, 255), (512, 31, 512), (513, 16, 513), (1000, 24, 1000), (1023, 24, 1023), (1024, 32, 700)])
 def test_deviations(kind, N, B, K):
     rng = np.random.default_rng(7 * N + B)
     r = np.arange(K)
@@ -91,7 +93,9 @@ def test_deviations(kind, N, B, K):
         lp[:, K // 2:] = -1e9
         lp[1::2, 3 * K // 4:] = -np.inf
     lp = -np.sort(-lp.astype(np.float32), axis=1)
+    before = dd.build_handovers()
     _check(rng.integers(0, 5000, (B, K)).astype(np.int32), lp, N)
+    assert dd.build_handovers() == before
 
 
 def test_forced_levels_run_alone():
@@ -114,7 +118,8 @@ def test_forced_levels_run_alone():
 
 # Rows without equal scores whose trees are bushy: a few plausible tokens a row (few), none that stands out (gumbel, normal),
 # falling by a factor (geometric, zipf), all but some masked.  The construction by deviations finds several
-# times as many prefixes as the tree has nodes on the way, and has to have room for them.
+# times as many prefixes as the tree has nodes on the way, and has to have room for them.  The levels are wide here, count
+# levels whose candidates do not fit before they write them (few16, masked16), and give up on some (geometric).
 @pytest.mark.parametrize("kind", ["few5", "few16", "few40", "gumbel3", "normal6", "geometric", "zipf2", "masked4", "masked16"])
 @pytest.mark.parametrize("N,B,K", [(256, 8, 256), (256, 16, 256), (512, 16, 512), (512, 32, 512), (1024, 8, 1024), (1024, 16, 1024),
                                    (700, 24, 700), (1000, 24, 1000), (256, 16, 50), (1024, 16, 200)])
@@ -136,13 +141,20 @@ def test_bushy_trees_fit(kind, N, B, K):
         x[:, int(number):] -= 100.0
     tok, lp = oracle.topk(x.astype(np.float32), K)
     o = oracle.build_tree(tok, lp, N, 5)
-    before, given_up = dd.build_handovers(), dd.build_giveups()
-    g = gu.gpu_build(tok, lp, N, 5)
-    assert dd.build_handovers() == before and dd.build_giveups() == given_up
-    for key in ("tokens", "parent", "depth", "rank"):
-        assert np.array_equal(g[key][0], o[key]), key
-    assert np.array_equal(g["node_score"][0].view(np.uint32), o["score"].view(np.uint32))
-    assert np.array_equal(g["ancestor_mask"][0], oracle.ancestor_mask(o["parent"], o["n_nodes"], T=N + 1))
+    mask = oracle.ancestor_mask(o["parent"], o["n_nodes"], T=N + 1)
+    try:
+        for algo in (dd.BUILD_AUTO, dd.BUILD_LEVELS):
+            dd.set_build_algorithm(algo)
+            before, given_up = dd.build_handovers(), dd.build_giveups()
+            g = gu.gpu_build(tok, lp, N, 5)
+            if algo == dd.BUILD_AUTO:
+                assert dd.build_handovers() == before and dd.build_giveups() == given_up
+            for key in ("tokens", "parent", "depth", "rank"):
+                assert np.array_equal(g[key][0], o[key]), (algo, key)
+            assert np.array_equal(g["node_score"][0].view(np.uint32), o["score"].view(np.uint32)), algo
+            assert np.array_equal(g["ancestor_mask"][0], mask), algo
+    finally:
+        dd.set_build_algorithm(dd.BUILD_AUTO)
 
 
 # equal values: 1 to 4 distinct ones a row, budgets whose members do not fit (they go to the pops, not to the levels and then the

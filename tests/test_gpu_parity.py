@@ -246,14 +246,14 @@ def test_build_deep_trees(spike, N, build_algo):
     tok, lp = oracle.topk(x, min(N, 8192))
     before = dd.build_giveups()
     o = _check_build(tok, lp, N)
-    # tie-free logits: the level construction must carry these through on its own
+    # tie-free logits: no construction hands these to the pops (levels: the forced levels alone)
     assert dd.build_giveups() == before
     print(f"spike {spike}: max depth {o['depth'].max()}")
 
 
 @pytest.mark.parametrize("spike,N", [(16.0, 1024), (24.0, 1024), (18.0, 768)])
 def test_build_large_budget_on_peaked_rows(spike, N, build_algo):
-    # deep trees at large budgets: the level construction has to squeeze dead members out
+    # deep trees at large budgets: up to fourteen levels of more than 64 parents for the forced levels
     import paper_2604_12989_amd as dd
     x = _peaked_logits(23, 16, 8192, spike)
     tok, lp = oracle.topk(x, N)
@@ -265,8 +265,8 @@ def test_build_large_budget_on_peaked_rows(spike, N, build_algo):
 
 @pytest.mark.parametrize("B,spike,N,K", [(24, 13.0, 256, 256), (32, 12.0, 300, 200), (32, 14.0, 512, 512), (17, 13.0, 128, 64)])
 def test_build_more_than_sixteen_positions(B, spike, N, K, build_algo):
-    # block sizes beyond 16: deep chains that run past row 16 (the level construction enters the
-    # low ranks off the top-1 chain two rows per thread there) and fewer ranks than budget
+    # block sizes beyond 16: deep chains that run past row 16, where continuations are walked 16 rows at a time and
+    # the first bound looks at every other length, and fewer ranks than budget
     x = _peaked_logits(29, B, 4096, spike)
     tok, lp = oracle.topk(x, K)
     o = _check_build(tok, lp, N)
@@ -275,9 +275,8 @@ def test_build_more_than_sixteen_positions(B, spike, N, K, build_algo):
 
 @pytest.mark.parametrize("p_top,N", [(0.3, 256), (0.6, 256), (0.6, 512), (0.9, 256), (0.9, 512), (0.9, 1024), (0.97, 128)])
 def test_build_rows_peaked_at_a_given_probability(p_top, N, build_algo):
-    # every draft row with one token at probability p_top: at 0.9 the whole tree comes from the
-    # prefixes entered up front and is enumerated by generations; at 0.6 and N = 512 that attempt
-    # lets in too many members and the levels take over; at 0.3 no cut is known up front
+    # every draft row with one token at probability p_top: at 0.9 nearly the whole tree comes from the
+    # prefixes entered up front; at 0.3 these give no cut
     import paper_2604_12989_amd as dd
     x = di.peaked_draft_logits(31, 16, 30000, p_top)
     tok, lp = oracle.topk(x, min(N, 30000))
@@ -356,8 +355,8 @@ def test_build_randomized_shapes(build_algo):
         tok = rng.permutation(B * K).astype(np.int32).reshape(B, K)
         before = dd.build_giveups()
         _check_build(tok, lp, N, root=3)
-        # rows without exact ties: the level construction carries them through on its own
-        # (candidate arrays that overflow are counted first and searched again)
+        # rows without exact ties: no construction hands these to the pops (the forced levels count candidates
+        # that do not fit and search again in thirty of them, and squeeze dead members out in two)
         if kind in ("flat", "peaked", "mixed"):
             assert dd.build_giveups() == before, (kind, B, K, N)
 
