@@ -1043,11 +1043,12 @@ __device__ int level_build(const float *s_lp, int Kp, int B, int K, int N, Level
 // on its SIMD, cycles: a dependent addition 7, through DPP 23, a ballot that scalar code looks at 45, a branch
 // under a lane mask 55, an LDS read 62, a barrier of eight waves 15.  256 nodes at p = 0.9: table 5.2 thousand (with a
 // lane mask for each load; 1 us less without), first bound and histogram 4.5, turns 19, ranking 6.5, arrays and masks 4.5 (time stamps included).
-// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 16.9 -> 10.2; 256 nodes p = 0
-// (flat) 17.1 -> 10.9, 0.4 29.5 -> 12.3, 0.9 20.7 -> 12.4; 512 nodes 0.4 34.2 -> 15.9, 0.9 25.4 -> 14.0; 1024 nodes 0 35.3 -> 18.4, 0.5 59.3 -> 22.4,
-// 0.9 43.7 -> 21.3.  Bushy rows, by levels, by deviations that handed over for lack of room, and now: 256 nodes 16 plausible
-// tokens a row 84 / 87 / 20, 40 tokens 53 / 54 / 14; 512 nodes 5 tokens 58 / 74 / 33; 1024 nodes 16 tokens 83 / 95 / 38, Gumbel noise of scale 3 118 /
-// 108 / 62, rows that fall by half a rank 1270 / 1210 / 94; 1000 nodes in 24 rows, 4 tokens 75 / 97 / 76; 1024 nodes of 50 ranks 40 tokens 102 / 115 / 31.
+// Kernel, launch to launch, us, by levels (before) and now, rows peaked at p: 64 nodes p = 0.9 17.3 -> 11.2; 256 nodes p = 0
+// (flat) 18.9 -> 11.0, 0.4 30.0 -> 12.7, 0.9 21.6 -> 13.6; 512 nodes 0.4 35.9 -> 16.1, 0.9 26.1 -> 14.9; 1024 nodes 0 37.3 -> 19.0,
+// 0.5 58.8 -> 23.3, 0.9 43.8 -> 21.9.  Bushy rows, by levels, by deviations that handed over for lack of room, and now: 256 nodes
+// 16 plausible tokens a row 85 / 89 / 19, 40 tokens 53 / 54 / 13; 512 nodes 5 tokens 60 / 72 / 32; 1024 nodes 16 tokens 83 / 94 / 36,
+// Gumbel noise of scale 3 120 / 114 / 58, rows that fall by 0.7 a rank 1218 / 1156 / 57; 1000 nodes in 24 rows, 5 tokens 73 / 93 / 71;
+// 1024 nodes of 50 ranks, 40 tokens 102 / 117 / 29.
 // Returns N, or (uniform) -1: no bound (fewer finite prefixes among those above than the budget), or kNoRoom.
 // ------------------------------------------------------------------------------------------
 constexpr int kNoRoom = -2;
