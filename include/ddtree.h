@@ -284,8 +284,8 @@ int ddtree_selftest_host(void);
  * waits for the device.  Meant for tests.
  */
 int ddtree_build_giveups(unsigned int *count);
-/* The same for sequences whose prefixes the construction by the number of non-zero ranks
- * (DDTREE_BUILD_AUTO) had no room for, so that the levels were run. */
+/* The same for sequences that the construction by the number of non-zero ranks (DDTREE_BUILD_AUTO)
+ * handed to the levels: no room for their prefixes, or no bound on the scores of the tree. */
 int ddtree_build_handovers(unsigned int *count);
 
 /*

@@ -327,7 +327,7 @@ def build_giveups():
 
 
 def build_handovers():
-    """Sequences (since load) that the construction by deviations handed to the levels for lack of room."""
+    """Sequences (since load) that the construction by deviations handed to the levels (no room, or no bound)."""
     n = ctypes.c_uint(0)
     _check(load().ddtree_build_handovers(ctypes.byref(n)), "ddtree_build_handovers")
     return int(n.value)

@@ -99,7 +99,7 @@ __device__ bool tuple_before(const uint32_t *s_node, int pa, int ra, int pb, int
 // returns -1 and the caller runs the sequential pops instead.
 // ------------------------------------------------------------------------------------------
 __device__ unsigned int g_level_giveups;  // sequences the level construction handed to the pops
-__device__ unsigned int g_handovers;      // sequences the construction by deviations had no room for
+__device__ unsigned int g_handovers;      // sequences the construction by deviations handed to the levels
 
 constexpr int kLvBuckets = 256;
 constexpr float kLvNeg = -3.0e38f;   // scores at or below count as -inf: never part of a tree
@@ -1717,7 +1717,7 @@ __global__ __launch_bounds__(kBuildThreads) void build_kernel(
             if (level_n < 0) __syncthreads();  // (the histograms are reused)
         }
         if (level_n < 0 && (level_n != kNoRoom || N > kTiedPops)) {
-            if (level_n == kNoRoom && tid == 0) atomicAdd(&g_handovers, 1u);
+            if (algo == DDTREE_BUILD_AUTO && tid == 0) atomicAdd(&g_handovers, 1u);
             level_n = level_build<NT>(s_lp, Kp, B, K, N, lv, s_bucket, s_node, s_score);
             if (level_n < 0 && tid == 0) atomicAdd(&g_level_giveups, 1u);
         }
